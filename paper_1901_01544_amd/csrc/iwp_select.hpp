@@ -65,7 +65,6 @@ __device__ __forceinline__ uint32_t sample_stage_bin(const DevLayer& L, const fl
     const float* rl = rp + L.offset;
     const float* gl = gp ? gp + L.offset : nullptr;
     const float* wl = w + L.offset;
-    const bool vec = is_aligned16(rl) && is_aligned16(wl) && (!gp || is_aligned16(gl));
     const uint32_t runs_total = (uint32_t)(((uint64_t)L.n + SAMPLE_RUN - 1) / SAMPLE_RUN);
     // enough runs for the sample's rank to be about SAMPLE_RANK (a relative error of a few percent in the
     // count, well inside the slack of one bin), at most SAMPLE_RUNS, at least 16
@@ -84,9 +83,9 @@ __device__ __forceinline__ uint32_t sample_stage_bin(const DevLayer& L, const fl
             const uint64_t pos = run * SAMPLE_RUN + lane * VEC;
             e[c] = (i < runs && pos < L.n) ? (uint32_t)pos : 0xFFFFFFFFu;
             if (e[c] != 0xFFFFFFFFu) {
-                load_quad(rl, e[c], L.n, vec, rv[c]);
-                if (gp) load_quad(gl, e[c], L.n, vec, gv[c]);
-                load_quad(wl, e[c], L.n, vec, wv[c], 1.0f);
+                load_quad(rl, e[c], L.n, rv[c]);
+                if (gp) load_quad(gl, e[c], L.n, gv[c]);
+                load_quad(wl, e[c], L.n, wv[c], 1.0f);
             }
         }
 #pragma unroll
@@ -360,12 +359,11 @@ __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __
         if (!prestaged || raw) {                           // uniform: this tile is read again
             const float* rl = R.r[leader_of(leader, j, W)] + L.offset;
             const float* wl = w + L.offset;
-            const bool vec = is_aligned16(rl) && is_aligned16(wl);
             const uint32_t base = lt * TILE;
             uint32_t key[CHUNKS_PER_TILE][4];
             float val[CHUNKS_PER_TILE][4];
             float wgt[CHUNKS_PER_TILE][4];
-            const bool full = vec && base + TILE <= L.n;
+            const bool full = base + TILE <= L.n;
             if (full) {
 #pragma unroll
                 for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
@@ -380,8 +378,8 @@ __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __
                 for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
                     const uint32_t i = base + u * CHUNK + tid * VEC;
                     if (i < L.n) {
-                        load_quad(rl, i, L.n, vec, val[u]);
-                        load_quad(wl, i, L.n, vec, wgt[u], 1.0f);
+                        load_quad(rl, i, L.n, val[u]);
+                        load_quad(wl, i, L.n, wgt[u], 1.0f);
                     } else {
 #pragma unroll
                         for (int q = 0; q < 4; ++q) { val[u][q] = 0.0f; wgt[u][q] = 1.0f; }
@@ -525,15 +523,14 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
         if (raw_tiles) {                                                       // uniform
             const float* rl = R.r[leader_of(leader, j, W)] + L.offset;
             const float* wl = w + L.offset;
-            const bool vec = is_aligned16(rl) && is_aligned16(wl);
             for (uint32_t tl = 0; tl < nt; ++tl) {
                 if (!((raw_tiles >> tl) & 1ull)) continue;
                 for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
                     const uint32_t i = (lt0 + tl) * TILE + u * CHUNK + tid * VEC;
                     if (i >= L.n) break;
                     float rv[4], wv[4];
-                    load_quad(rl, i, L.n, vec, rv);
-                    load_quad(wl, i, L.n, vec, wv, 1.0f);
+                    load_quad(rl, i, L.n, rv);
+                    load_quad(wl, i, L.n, wv, 1.0f);
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const uint32_t key2 = score_key(rv[q], wv[q], eps);
@@ -872,7 +869,6 @@ __global__ __launch_bounds__(BLOCK) void k_write(ResidualPtrs R, const float* __
 
     // RAW tile: every element is scored again, 256 at a time
     const float* wl = w + L.offset;
-    const bool vec = is_aligned16(rl) && is_aligned16(wl);
     uint32_t G = Gt, E = Et;
     for (uint32_t c = 0; c < TILE / (WAVE * VEC); ++c) {
         const uint32_t cbase = tile_first + c * (WAVE * VEC);
@@ -880,8 +876,8 @@ __global__ __launch_bounds__(BLOCK) void k_write(ResidualPtrs R, const float* __
         const uint32_t i = cbase + lane * VEC;
         float rv[4] = {0.f, 0.f, 0.f, 0.f}, wv[4] = {1.f, 1.f, 1.f, 1.f};
         if (i < L.n) {
-            load_quad(rl, i, L.n, vec, rv);
-            load_quad(wl, i, L.n, vec, wv, 1.0f);
+            load_quad(rl, i, L.n, rv);
+            load_quad(wl, i, L.n, wv, 1.0f);
         }
         uint32_t key[4];
         uint32_t packed = 0;

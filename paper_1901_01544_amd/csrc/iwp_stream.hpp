@@ -31,9 +31,9 @@ struct LeadCtx {
 
 // One tile of a plain worker: r <- m * r + g, streaming (non-temporal) accesses.
 __device__ __forceinline__ void stream_tile(const float* __restrict__ gl, float* __restrict__ rl, uint32_t n,
-                                            uint32_t base, bool vec, float m) {
+                                            uint32_t base, float m) {
     const uint32_t tid = threadIdx.x;
-    if (vec && base + TILE <= n) {
+    if (base + TILE <= n) {
         v4f rr[CHUNKS_PER_TILE], gg[CHUNKS_PER_TILE];
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
@@ -47,15 +47,15 @@ __device__ __forceinline__ void stream_tile(const float* __restrict__ gl, float*
             store_v4<true>(rl + i, accum(rr[u], gg[u], m));
         }
     } else {
-        // ragged tail of a layer, or a layer whose base is not 16-byte aligned: the same shape, every load of
+        // ragged tail of a layer: the same shape, every load of
         // the tile that lies inside the layer issued before the first use
         float rv[CHUNKS_PER_TILE][4], gv[CHUNKS_PER_TILE][4];
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
             const uint32_t i = base + u * CHUNK + tid * VEC;
             if (i < n) {
-                load_quad<true>(rl, i, n, vec, rv[u]);
-                load_quad<true>(gl, i, n, vec, gv[u]);
+                load_quad<true>(rl, i, n, rv[u]);
+                load_quad<true>(gl, i, n, gv[u]);
             }
         }
 #pragma unroll
@@ -64,7 +64,7 @@ __device__ __forceinline__ void stream_tile(const float* __restrict__ gl, float*
             if (i < n) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) rv[u][q] = accum(rv[u][q], gv[u][q], m);
-                store_quad<true>(rl, i, n, vec, rv[u]);
+                store_quad<true>(rl, i, n, rv[u]);
             }
         }
     }
@@ -84,13 +84,13 @@ __device__ __forceinline__ void stream_tile(const float* __restrict__ gl, float*
 constexpr int KEEP_NOTHING = 0, KEEP_W = 1, KEEP_W_AND_R = 2;
 template <bool ACC, int KEEP>
 __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* __restrict__ rl,
-                                          const float* __restrict__ wl, uint32_t n, uint32_t lt, bool vec,
+                                          const float* __restrict__ wl, uint32_t n, uint32_t lt,
                                           float eps, float m, const LeadCtx& C) {
     const uint32_t tid = threadIdx.x;
     const uint32_t base = lt * TILE;
     uint32_t key[CHUNKS_PER_TILE][4];
     float val[CHUNKS_PER_TILE][4];
-    if (vec && base + TILE <= n) {
+    if (base + TILE <= n) {
         v4f rr[CHUNKS_PER_TILE], gg[CHUNKS_PER_TILE], ww[CHUNKS_PER_TILE];
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
@@ -113,16 +113,16 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
             key[u][3] = score_key(rr[u].w, ww[u].w, eps);
         }
     } else {
-        // ragged tail of a layer, or a layer whose base is not 16-byte aligned: the same shape, every load of
+        // ragged tail of a layer: the same shape, every load of
         // the tile that lies inside the layer issued before the first use
         float gv[CHUNKS_PER_TILE][4], wv[CHUNKS_PER_TILE][4];
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
             const uint32_t i = base + u * CHUNK + tid * VEC;
             if (i < n) {
-                load_quad<true>(rl, i, n, vec, val[u]);
-                if (ACC) load_quad<true>(gl, i, n, vec, gv[u]);
-                load_quad<true>(wl, i, n, vec, wv[u], 1.0f);
+                load_quad<true>(rl, i, n, val[u]);
+                if (ACC) load_quad<true>(gl, i, n, gv[u]);
+                load_quad<true>(wl, i, n, wv[u], 1.0f);
             }
         }
 #pragma unroll
@@ -131,7 +131,7 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
             if (ACC && i < n) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) val[u][q] = accum(val[u][q], gv[u][q], m);
-                store_quad<true>(rl, i, n, vec, val[u]);
+                store_quad<true>(rl, i, n, val[u]);
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) key[u][q] = (i + q < n) ? score_key(val[u][q], wv[u][q], eps) : NOT_AN_ELEMENT;
@@ -170,12 +170,11 @@ __device__ __forceinline__ void leader_group(const float* gp, float* rp, const f
     float* rl = rp + L.offset;
     const float* gl = gp ? gp + L.offset : nullptr;
     const float* wl = w + L.offset;
-    const bool vec = is_aligned16(rl) && is_aligned16(wl) && (!gp || is_aligned16(gl));
     const uint32_t ntiles = (L.n + TILE - 1) / TILE;
     const uint32_t last = min(first_tile + group_tiles, ntiles);
     for (uint32_t t = first_tile; t < last; ++t) {
-        if (gp) lead_tile<true, KEEP>(gl, rl, wl, L.n, t, vec, eps, m, C);
-        else lead_tile<false, KEEP>(gl, rl, wl, L.n, t, vec, eps, m, C);
+        if (gp) lead_tile<true, KEEP>(gl, rl, wl, L.n, t, eps, m, C);
+        else lead_tile<false, KEEP>(gl, rl, wl, L.n, t, eps, m, C);
     }
     __syncthreads();
     for (uint32_t b = threadIdx.x; b < HIST0; b += BLOCK) {
@@ -211,7 +210,7 @@ __global__ __launch_bounds__(BLOCK) void k_accumulate_rest(WorkerPtrs P, const D
     if (!gp || (L.k > 0 && leader_of(leader, j, W) == p)) return;
     float* rl = P.r[p] + L.offset;
     const float* gl = gp + L.offset;
-    stream_tile(gl, rl, L.n, (t - L.tile_begin) * TILE, is_aligned16(rl) && is_aligned16(gl), P.momentum);
+    stream_tile(gl, rl, L.n, (t - L.tile_begin) * TILE, P.momentum);
 }
 
 // Leaders only: one workgroup per group of LG tiles of every layer with k > 0.  The grid:
@@ -285,8 +284,7 @@ __global__ __launch_bounds__(BLOCK) void k_follow_gather(WorkerPtrs P, WorkerLis
     float* go = gathered + (size_t)p * K + L.out_offset + lo;
     const uint32_t first = (uint32_t)L.offset + base;           // flat position of the tile's first element
     const float* gl = gp + L.offset;
-    const bool vec = is_aligned16(rl) && is_aligned16(gl);
-    const bool full = vec && base + TILE <= L.n;
+    const bool full = base + TILE <= L.n;
     // the tile's loads go out first; the bitmap of sent positions is built while they are in flight
     float rv[CHUNKS_PER_TILE][4], gv[CHUNKS_PER_TILE][4];      // one set of registers for both forms of the tile
     if (full) {
@@ -303,8 +301,8 @@ __global__ __launch_bounds__(BLOCK) void k_follow_gather(WorkerPtrs P, WorkerLis
         for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
             const uint32_t i = base + u * CHUNK + tid * VEC;
             if (i < L.n) {
-                load_quad<true>(rl, i, L.n, vec, rv[u]);
-                load_quad<true>(gl, i, L.n, vec, gv[u]);
+                load_quad<true>(rl, i, L.n, rv[u]);
+                load_quad<true>(gl, i, L.n, gv[u]);
             }
         }
     }
@@ -335,7 +333,7 @@ __global__ __launch_bounds__(BLOCK) void k_follow_gather(WorkerPtrs P, WorkerLis
             store_v4<true>(rl + base + loc, out);
         }
     } else {
-        // ragged tail of a layer, or a layer whose base is not 16-byte aligned (loaded above)
+        // ragged tail of a layer (loaded above)
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
             const uint32_t loc = u * CHUNK + tid * VEC;
@@ -348,7 +346,7 @@ __global__ __launch_bounds__(BLOCK) void k_follow_gather(WorkerPtrs P, WorkerLis
                     rv[u][q] = accum(rv[u][q], gv[u][q], P.momentum);
                     if ((nib >> q) & 1u) { go[rank++] = rv[u][q]; rv[u][q] = 0.0f; }
                 }
-                store_quad<true>(rl, i, L.n, vec, rv[u]);
+                store_quad<true>(rl, i, L.n, rv[u]);
             }
         }
     }

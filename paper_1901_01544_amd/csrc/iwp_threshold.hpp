@@ -71,8 +71,7 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 __device__ __forceinline__ void chosen_tile(const float* gp, float* rl, const float* gl, const float* wl, float m,
                                             uint32_t n, uint32_t base, uint32_t tid, float (&rv)[CHUNKS_PER_TILE][4],
                                             float (&wv)[CHUNKS_PER_TILE][4]) {
-    const bool vec = is_aligned16(rl) && is_aligned16(wl) && (!gp || is_aligned16(gl));
-    if (vec && base + TILE <= n) {
+    if (base + TILE <= n) {
         v4f rr[CHUNKS_PER_TILE], gg[CHUNKS_PER_TILE], ww[CHUNKS_PER_TILE];
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
@@ -92,7 +91,7 @@ __device__ __forceinline__ void chosen_tile(const float* gp, float* rl, const fl
             wv[u][0] = ww[u].x; wv[u][1] = ww[u].y; wv[u][2] = ww[u].z; wv[u][3] = ww[u].w;
         }
     } else {
-        // ragged tail or misaligned base: the same shape, every load inside the layer issued before the first use
+        // ragged tail: the same shape, every load inside the layer issued before the first use
         float gv[CHUNKS_PER_TILE][4];
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
@@ -100,9 +99,9 @@ __device__ __forceinline__ void chosen_tile(const float* gp, float* rl, const fl
 #pragma unroll
             for (int c = 0; c < 4; ++c) { rv[u][c] = 0.0f; wv[u][c] = 1.0f; }
             if (i < n) {
-                load_quad<true>(rl, i, n, vec, rv[u]);
-                if (gp) load_quad<true>(gl, i, n, vec, gv[u]);
-                load_quad<true>(wl, i, n, vec, wv[u], 1.0f);
+                load_quad<true>(rl, i, n, rv[u]);
+                if (gp) load_quad<true>(gl, i, n, gv[u]);
+                load_quad<true>(wl, i, n, wv[u], 1.0f);
             }
         }
         if (gp) {
@@ -112,7 +111,7 @@ __device__ __forceinline__ void chosen_tile(const float* gp, float* rl, const fl
                 if (i < n) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c) rv[u][c] = accum(rv[u][c], gv[u][c], m);
-                    store_quad<true>(rl, i, n, vec, rv[u]);
+                    store_quad<true>(rl, i, n, rv[u]);
                 }
             }
         }
@@ -418,8 +417,7 @@ __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLa
     const uint32_t base = lt * TILE;
     float* rl = P.r[p] + L.offset;
     const float* gl = gp + L.offset;
-    const bool vec = is_aligned16(rl) && is_aligned16(gl);
-    const bool full = vec && base + TILE <= L.n;
+    const bool full = base + TILE <= L.n;
     float rv[CHUNKS_PER_TILE][4], gv[CHUNKS_PER_TILE][4];      // one set of registers for both forms of the tile
     if (full) {
 #pragma unroll
@@ -435,8 +433,8 @@ __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLa
         for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
             const uint32_t i = base + u * CHUNK + tid * VEC;
             if (i < L.n) {
-                load_quad<true>(rl, i, L.n, vec, rv[u]);
-                load_quad<true>(gl, i, L.n, vec, gv[u]);
+                load_quad<true>(rl, i, L.n, rv[u]);
+                load_quad<true>(gl, i, L.n, gv[u]);
             }
         }
     }
@@ -480,7 +478,7 @@ __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLa
                     rv[u][q] = accum(rv[u][q], gv[u][q], P.momentum);
                     if ((nib >> q) & 1u) { if (rank < room) go[rank] = rv[u][q]; ++rank; rv[u][q] = 0.0f; }
                 }
-                store_quad<true>(rl, i, L.n, vec, rv[u]);
+                store_quad<true>(rl, i, L.n, rv[u]);
             }
         }
     }
