@@ -211,14 +211,13 @@ int compress_segmented_static(const iwp_plan* plan, const float* w, const float*
  * w and every r[p] are updated in place.  Workspace: iwp_plan_step_workspace_bytes.
  * thr_hint: NULL, or a device array of n_layers threshold records that are
  * expected to be close to this call's (typically the previous step's thr_out; a
- * different buffer than thr_out).  The hint never changes any output: it lets the
- * first pass over a leader's layer already copy out every element from slightly
- * below the hinted threshold, which makes the second pass over that layer
- * unnecessary whenever the new threshold is not below that mark; otherwise, and
- * for records that are wrong or garbage, the layer just takes the two-pass route.
- * With NULL the library derives the same mark itself from a small sample of each
- * layer (read-only, inside the call's first launch); equally without influence on
- * any output. */
+ * different buffer than thr_out).  The hint never changes any output.  The first
+ * pass over a leader's layer already copies out every element that may be kept,
+ * which makes a second pass unnecessary; from which importance on, the library
+ * takes from a small sample of the layer (read-only, inside the call's first
+ * launch), and from the hint where that lies far below the sample's estimate (a
+ * layer whose sample misleads).  Where the copies turn out incomplete, and for
+ * records that are wrong or garbage, the layer takes the two-pass route. */
 int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, float* const* r, uint32_t W,
                        const uint32_t* leader, const iwp_threshold* thr_hint, float eps, float scale,
                        uint32_t* idx_out, float* val_out, float* sum_out, iwp_threshold* thr_out,

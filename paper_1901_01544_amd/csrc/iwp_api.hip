@@ -61,11 +61,12 @@ struct TimedLaunch {       // records an event pair around the launch made while
 
 // Launch `kernel<<<grid, BLOCK, 0, s>>>(args...)`, timed if asked for, and turn a
 // launch failure into IWP_EHIP.
-#define IWP_LAUNCH(name, kernel, grid, s, ...)                        \
+#define IWP_LAUNCH(name, kernel, grid, s, ...) IWP_LAUNCH_BLOCK(name, kernel, grid, BLOCK, s, __VA_ARGS__)
+#define IWP_LAUNCH_BLOCK(name, kernel, grid, block, s, ...)           \
     do {                                                              \
         {                                                             \
             TimedLaunch tl_(name, s);                                 \
-            kernel<<<(grid), BLOCK, 0, (s)>>>(__VA_ARGS__);           \
+            kernel<<<(grid), (block), 0, (s)>>>(__VA_ARGS__);         \
         }                                                             \
         hipError_t e_ = hipGetLastError();                            \
         if (e_ != hipSuccess) return hip_fail(e_, name);              \
@@ -107,6 +108,22 @@ inline uint32_t slot_cap_of(uint32_t n, uint32_t k) {
     if (k == 0) return 0u;
     const uint64_t per_tile = ((uint64_t)TILE * k + n - 1) / n;
     return (uint32_t)std::min<uint64_t>(TILE, 64 + 3 * per_tile);
+}
+
+// How k_init samples a layer: enough runs for the threshold's rank in the sample to be about SAMPLE_RANK, and the rank
+// of the sample's element from whose key look 1 copies out (see iwp_select.hpp).
+uint32_t sample_of(uint32_t n, uint32_t k) {
+    if (n == 0 || k == 0) return 0u;
+    const uint64_t runs_total = ((uint64_t)n + SAMPLE_RUN - 1) / SAMPLE_RUN;
+    const uint64_t want = ((uint64_t)SAMPLE_RANK * n / k + SAMPLE_RUN - 1) / SAMPLE_RUN;
+    const uint64_t runs = std::min({runs_total, (uint64_t)SAMPLE_RUNS, std::max<uint64_t>(SAMPLE_RUNS_MIN, want)});
+    uint64_t rank = k;                                   // the whole layer
+    if (runs < runs_total) {
+        const uint64_t sampled = runs * SAMPLE_RUN;      // only a layer's last run can be short
+        const uint64_t ks = std::max<uint64_t>(1, ((uint64_t)k * sampled + n - 1) / n);
+        rank = std::min<uint64_t>(sampled, ks + ks / 4 + (uint64_t)(4.0 * std::sqrt((double)ks)) + 2);
+    }
+    return (uint32_t)(runs << 16 | (rank - 1));
 }
 
 // Copies of a layer's first-digit histogram: one per FLUSHES_PER_COPY look-1 workgroups, a power of two.
@@ -187,11 +204,11 @@ SampleSource sample_from(const WorkerPtrs& P, const float* w, const uint32_t* le
 
 int launch_init(const Workspace& ws, uint32_t n_layers, const iwp_threshold* hint, const DevLayer* layers,
                 const DevLayer* row, const DevLayer* sentinel, const SampleSource& S, hipStream_t s) {
-    uint32_t zero_blocks = (uint32_t)std::min<uint64_t>((ws.hist_words + BLOCK - 1) / BLOCK, 4096);
+    uint32_t zero_blocks = (uint32_t)std::min<uint64_t>((ws.hist_words + 4 * INIT_BLOCK - 1) / (4 * INIT_BLOCK), 1024);
     if (zero_blocks == 0) zero_blocks = 1;
     DevLayer zero;
     memset(&zero, 0, sizeof zero);
-    IWP_LAUNCH("k_init", k_init, n_layers + zero_blocks, s, ws.hist, ws.hist_words, ws.state, n_layers, hint, layers,
+    IWP_LAUNCH_BLOCK("k_init", k_init, n_layers + zero_blocks, INIT_BLOCK, s, ws.hist, ws.hist_words, ws.state, zero_blocks, hint, layers,
                row ? ws.single_table : nullptr, row ? *row : zero, sentinel ? *sentinel : zero, S);
     return IWP_OK;
 }
@@ -253,13 +270,12 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
                iwp_threshold* thr_out, hipStream_t s) {
     if (!T.any_k || T.tiles == 0) return IWP_OK;
     IWP_LAUNCH("k_first_pick", k_first_pick, T.n_layers, s, T.layers, ws.hist, ws.state);
-    // Consecutive tiles per workgroup: STAGE_TILES on tables of long layers (most tiles have nothing to do when look 1
-    // staged their layer), one on tables of short layers (a layer that has to be read again wants all the workgroups
-    // it can get), more on tables of very long layers (fewer flushes into a layer's one histogram), at most 64 (their
-    // look-1 counts are fetched one per lane).
+    // Consecutive tiles per look-2 workgroup, by the tiles of the average layer.  Look 1's copies are complete for
+    // nearly every layer, and then only every STAGE_GROUP-th tile has work: few workgroups, few flushes into a layer's
+    // one second-digit histogram.  Tables of short layers keep one tile each: a workgroup pays a chain of loads per layer.
     const uint32_t avg_tiles = T.tiles / std::max<uint32_t>(1u, T.n_layers);
-    const uint32_t per_wg = avg_tiles < STAGE_LONG_LAYER_TILES ? 1u :
-        std::min<uint32_t>(std::max<uint32_t>(avg_tiles / STAGE_TILES_PER_AVG, STAGE_TILES), STAGE_TILES_MAX);
+    const uint32_t per_wg = avg_tiles < STAGE_GROUP ? 1u : avg_tiles < 16u * STAGE_GROUP ? 4u
+        : std::min<uint32_t>(std::max<uint32_t>(avg_tiles / 64u, STAGE_GROUP), STAGE_TILES_MAX);
     const uint32_t stage_grid = std::max<uint32_t>(std::min<uint32_t>((T.tiles + per_wg - 1) / per_wg, STAGE_MAX_GRID),
                                                    (T.tiles + WAVE - 1) / WAVE);
     IWP_LAUNCH("k_stage", k_stage, stage_grid, s, R, w, T.layers, T.n_layers, T.tiles,
@@ -362,6 +378,7 @@ static int single_common(SingleOp op, const float* w, const float* g, float* r, 
     memset(&row, 0, sizeof row);
     memset(&sentinel, 0, sizeof sentinel);
     row.n = n; row.k = k; row.slot_cap = slot_cap_of(n, k);
+    row.sample = sample_of(n, k);
     row.hist_begin = 0; row.h0_copies = h0_copies_of(n, k);
     sentinel.tile_begin = z.tiles; sentinel.stile_begin = z.stiles; sentinel.out_offset = k;
     SampleSource S = sample_from(P, w, nullptr, 1u, eps);
@@ -466,6 +483,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
         D.stile_begin = (uint32_t)stiles;
         D.slot_cap = slot_cap_of(L.n, L.k);
         D.mask_begin = (uint32_t)mask_words;
+        D.sample = sample_of(L.n, L.k);
         D.hist_begin = (uint32_t)hist_words;
         D.h0_copies = h0_copies_of(L.n, L.k);
         hist_words += layer_hist_words(D.h0_copies);

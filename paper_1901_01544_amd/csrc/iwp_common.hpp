@@ -90,7 +90,7 @@ struct DevLayer {
     uint32_t mask_begin;   // first 32-bit word of the layer's encoded mask (threshold mode)
     uint32_t hist_begin;   // first word of the layer's histograms
     uint32_t h0_copies;    // copies of the first-digit histogram (a power of two)
-    uint32_t pad;
+    uint32_t sample;       // how k_init samples the layer: rank - 1 in the low half, runs in the high half
 };
 
 // Where digit `level`'s histogram of a layer starts (level 0: the first copy).
@@ -110,7 +110,8 @@ struct LayerState {        // selection state of one layer, lives in the workspa
     uint32_t k_rem1;       // rank inside that 22-bit group
     uint32_t thr;          // the threshold key (third pick, or given by the caller)
     uint32_t n_eq_take;    // ties to keep
-    uint32_t stage_bin;    // look 1 copies out every element whose top digit is >= this bin (from a threshold hint)
+    uint32_t stage_bin;    // look 1 copies out every element whose top digit is >= this bin (from a sample of the layer)
+    uint32_t shift;        // what is added to every key of the layer before it is split into digits (see shifted())
     uint32_t prestaged;    // set with the first pick: stage_bin <= b1, so look 1's copies are complete
 };
 
@@ -141,6 +142,18 @@ __device__ __forceinline__ uint32_t score_key(float r, float w, float eps) {
     float denom = fabsf(w) + eps;
     float s = fabsf(r) / denom;
     return __float_as_uint(s) & 0x7fffffffu;
+}
+
+// The selection works on keys moved up by a layer's `shift` (less than one top-digit bin), which puts a bin's lower
+// edge exactly at the key from which look 1 copies candidates out.  Keys of NaN (0 / 0 with eps = 0: quiet, from
+// 0x7fc00000 up) stay where they are: a finite or infinite score ends below them shifted too, so the map keeps the
+// order, loses nothing and ends inside 31 bits.
+constexpr uint32_t QUIET_NAN_KEY = 0x7fc00000u;
+__device__ __forceinline__ uint32_t shifted(uint32_t key, uint32_t shift) {
+    return key + (key < QUIET_NAN_KEY ? shift : 0u);
+}
+__device__ __forceinline__ uint32_t unshifted(uint32_t key, uint32_t shift) {
+    return key - (key < QUIET_NAN_KEY ? shift : 0u);
 }
 
 // The worker that leads layer j.  The table lives in device memory, so it cannot
@@ -224,29 +237,33 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* s
 }
 
 // Digit pick over a histogram of NB bins (LDS or global): the bin that holds rank
-// k_rem counted from the top bin down, and the rank inside that bin.  All 256
-// threads call it; the result is broadcast through `sh` (BLOCK + 2 words of LDS).
-// Requires sum(hist) >= k_rem >= 1.
-template <int NB>
+// k_rem counted from the top bin down, and the rank inside that bin.  All THREADS
+// threads call it; the result is broadcast through `sh` (PICK_WORDS words of LDS).
+// Requires sum(hist) >= k_rem >= 1.  Suffix sums inside each wavefront by lane shuffles, then over the
+// wavefronts' totals: three barriers, where a scan over all threads in LDS takes two per doubling.
+constexpr uint32_t PICK_WORDS = 16 + 2;
+template <int NB, int THREADS = BLOCK>
 __device__ __forceinline__ void block_pick(const uint32_t* hist, uint32_t k_rem, uint32_t* sh,
                                            uint32_t* bin_out, uint32_t* k_rem_out) {
-    constexpr int PER = NB / BLOCK;
-    const uint32_t tid = threadIdx.x;
+    constexpr int PER = NB / THREADS, WAVES = THREADS / WAVE;
+    static_assert(WAVES + 2 <= (int)PICK_WORDS, "one word per wavefront, two for the result");
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
     uint32_t h[PER];
     uint32_t local = 0;
 #pragma unroll
     for (int q = 0; q < PER; ++q) { h[q] = hist[tid * PER + q]; local += h[q]; }
-    __syncthreads();                       // sh may still be in use by a previous call
-    sh[tid] = local;
-    if (tid == 0) { sh[BLOCK] = 0u; sh[BLOCK + 1] = 1u; }
-    __syncthreads();
-    for (int d = 1; d < BLOCK; d <<= 1) {  // inclusive suffix sums over the threads
-        const uint32_t v = (tid + d < BLOCK) ? sh[tid + d] : 0u;
-        __syncthreads();
-        sh[tid] += v;
-        __syncthreads();
+    uint32_t incl = local;                 // this lane's bins and those of the lanes above it
+#pragma unroll
+    for (int d = 1; d < WAVE; d <<= 1) {
+        const uint32_t y = __shfl_down(incl, d, WAVE);
+        if (lane + d < WAVE) incl += y;
     }
-    const uint32_t incl = sh[tid];
+    __syncthreads();                       // sh may still be in use by a previous call
+    if (lane == 0) sh[wave] = incl;
+    if (tid == 0) { sh[WAVES] = 0u; sh[WAVES + 1] = 1u; }
+    __syncthreads();
+#pragma unroll
+    for (int v = 1; v < WAVES; ++v) incl += (int)wave < v ? sh[v] : 0u;
     const uint32_t above = incl - local;
     if (above < k_rem && k_rem <= incl) {  // true for exactly one thread
         uint32_t acc = above, bin = tid * PER;
@@ -255,12 +272,12 @@ __device__ __forceinline__ void block_pick(const uint32_t* hist, uint32_t k_rem,
             if (acc + h[q] >= k_rem) { bin = tid * PER + q; break; }
             acc += h[q];
         }
-        sh[BLOCK] = bin;
-        sh[BLOCK + 1] = k_rem - acc;
+        sh[WAVES] = bin;
+        sh[WAVES + 1] = k_rem - acc;
     }
     __syncthreads();
-    *bin_out = sh[BLOCK];
-    *k_rem_out = sh[BLOCK + 1];
+    *bin_out = sh[WAVES];
+    *k_rem_out = sh[WAVES + 1];
 }
 
 // Orders LDS traffic inside one wavefront (the lanes run in lockstep; this makes

@@ -4,15 +4,13 @@
 //
 // The selection is an MSB-first radix select on the 31-bit importance key
 // (digits of 12 + 10 + 9 bits).  Look 1 (iwp_stream.hpp) histograms the top digit
-// of every element.  Look 2 (k_stage) reads the leader's residual and weights once
-// more and copies out, per tile, the only elements that can still matter: those whose
-// top digit is >= b1, the bin that holds rank k (above b1 all of them are kept, the
-// threshold lies among those inside b1), and histograms the second digit of those
-// inside b1.  Every tile owns a fixed slot in the staging arrays, so look 2 needs no
-// cross-workgroup coordination at all.  With a threshold hint (say, last step's
-// thresholds) look 1 already copies out everything from a bin slightly below the
-// hinted one; if the new b1 is not below that bin the copies are complete and look 2
-// only reads the slots, not the layer.  Everything after that works on the staged
+// of every element and copies out, per tile, the elements that can be kept by the estimate of a
+// small sample (k_init).  Every tile owns a fixed slot in the staging arrays, so this needs no
+// cross-workgroup coordination at all.  If b1, the bin that holds rank k, is not below the
+// sample's mark, the copies are complete and look 2 (k_stage) only reads the slots, to histogram the
+// second digit of those inside b1; otherwise it reads the leader's residual and weights once
+// more and copies out the elements whose top digit is >= b1 (above b1 all of them are kept, the
+// threshold lies among those inside).  Everything after that works on the staged
 // copies, a few percent of the layer: k_refine2 histograms the third digit, k_count /
 // k_write place every kept element at its rank in index order.  A tile whose
 // candidates do not fit its slot (heavy ties, e.g. a tile that is all zeros) is marked
@@ -37,13 +35,22 @@ namespace iwp {
 // node, so the call sequence can be graph-captured): histograms to zero, layer
 // states reset; for the single-layer entry points also the one-row layer table.
 //
-// The first n_layers workgroups each reset one layer's state and decide from which bin
-// look 1 copies candidates out (LayerState.stage_bin): from the caller's threshold hint if
-// there is one; otherwise from a sample of the layer -- 16 to 256 evenly spaced runs of 256
-// elements (the whole layer if it has no more), scored exactly as look 1 will score them,
-// histogrammed in LDS, and the bin of the sample's rank k * (sample size / n) taken as the
-// estimate.  Either way the guess only decides whether look 2 has to read the layer again;
-// it never changes a result.  The other workgroups clear the histograms.
+// The first zero_blocks workgroups clear the histograms.  The others each reset one layer's state and
+// decide from which key look 1 copies candidates out, by a sample of the layer: 16 to 64 evenly spaced
+// runs of 256 elements (the whole layer if it has no more), scored exactly as look 1 will score them.  The key
+// is the sample's of rank 1.25 ks + 4 sqrt(ks) + 2, ks = k * (sample size / n): four standard
+// deviations and a quarter on top, so that look 1 copies about 1.5 elements per kept one and
+// practically never misses one (a layer sampled whole: rank k itself).  The guess only decides
+// whether look 2 has to read the layer again; it never changes a result.  A guess in whole
+// top-digit bins (1/16 octave, with one bin of slack) copied 3 to 4 per kept element where
+// the scores lie evenly below the threshold, as after some hundred steps, and overflowed the slots at
+// small keep ratios.  With the sample's key, thresholds of the step before in hand either way: one worker's
+// share of a 25.6 M-element table 207 -> 169 us, a 400 M-element layer at 1/1000 1745 -> 1494 us a step (look 2
+// 652 -> 54 us).
+//
+// Latency bound: a layer's sample is at most two rounds of loads for its workgroup of 16 wavefronts (one
+// for keep ratios from 1/64 up), its keys stay in registers for the second histogram; the numbers of runs and the
+// rank come from the host with the table row.
 // ---------------------------------------------------------------------------
 struct SampleSource {      // what the sample is taken from; on == 0: no sampling
     WorkerPtrs P;
@@ -55,98 +62,121 @@ struct SampleSource {      // what the sample is taken from; on == 0: no samplin
 };
 
 constexpr uint32_t SAMPLE_RUN = WAVE * VEC;        // 256 consecutive elements, one quad per lane
-constexpr uint32_t SAMPLE_RUNS = 256;              // at most 65536 sampled elements per layer
-constexpr uint32_t SAMPLE_RANK = 256;              // rank of the estimated threshold inside the sample, about
+constexpr uint32_t SAMPLE_RUNS = 64;               // at most 16384 sampled elements per layer
+constexpr uint32_t SAMPLE_RUNS_MIN = 16;           // at least 4096 (or the whole layer)
+constexpr uint32_t SAMPLE_RANK = 128;              // rank of the estimated threshold inside the sample, about
+constexpr uint32_t HINT_SLACK = 4u << 19;          // four top-digit bins
+constexpr int INIT_BLOCK = 1024;                   // threads of a k_init workgroup
+constexpr uint32_t SAMPLE_LOW_BITS = 7;            // the key's low bits that the sample does not resolve
 
-__device__ __forceinline__ uint32_t sample_stage_bin(const DevLayer& L, const float* gp, const float* rp,
+// The key from which look 1 should copy out (its low SAMPLE_LOW_BITS bits zero).
+__device__ __forceinline__ uint32_t sample_stage_key(const DevLayer& L, const float* gp, const float* rp,
                                                      const float* __restrict__ w, float eps, float m, uint32_t* lh,
                                                      uint32_t* sh) {
+    constexpr uint32_t WAVES = INIT_BLOCK / WAVE;
+    constexpr uint32_t ROUND = 2, ROUNDS = SAMPLE_RUNS / (WAVES * ROUND);   // runs a wavefront has in flight; rounds
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
     const float* rl = rp + L.offset;
     const float* gl = gp ? gp + L.offset : nullptr;
     const float* wl = w + L.offset;
-    const uint32_t runs_total = (uint32_t)(((uint64_t)L.n + SAMPLE_RUN - 1) / SAMPLE_RUN);
-    // enough runs for the sample's rank to be about SAMPLE_RANK (a relative error of a few percent in the
-    // count, well inside the slack of one bin), at most SAMPLE_RUNS, at least 16
-    const uint64_t want = ((uint64_t)SAMPLE_RANK * L.n / L.k + SAMPLE_RUN - 1) / SAMPLE_RUN;
-    const uint32_t runs = min(runs_total, (uint32_t)min((uint64_t)SAMPLE_RUNS, max((uint64_t)16, want)));
-    for (uint32_t b = tid; b < HIST0; b += BLOCK) lh[b] = 0u;
-    __syncthreads();
-    constexpr uint32_t PER_ROUND = 8;                // runs a wavefront has in flight
-    for (uint32_t i0 = wave; i0 < runs; i0 += (BLOCK / WAVE) * PER_ROUND) {
-        float rv[PER_ROUND][4], gv[PER_ROUND][4], wv[PER_ROUND][4];
-        uint32_t e[PER_ROUND];
+    const uint32_t runs_total = (L.n - 1) / SAMPLE_RUN + 1;
+    const uint32_t runs = L.sample >> 16, rank = (L.sample & 0xffffu) + 1u;
+    for (uint32_t b = tid; b < HIST0; b += INIT_BLOCK) lh[b] = 0u;
+    uint32_t key[ROUNDS][ROUND][4];
 #pragma unroll
-        for (uint32_t c = 0; c < PER_ROUND; ++c) {
-            const uint32_t i = i0 + c * (BLOCK / WAVE);
-            const uint64_t run = (uint64_t)i * runs_total / runs;
-            const uint64_t pos = run * SAMPLE_RUN + lane * VEC;
+    for (uint32_t d = 0; d < ROUNDS; ++d) {
+        float rv[ROUND][4], gv[ROUND][4], wv[ROUND][4];
+        uint32_t e[ROUND];
+        const bool any = d * ROUND * WAVES < runs;       // uniform
+#pragma unroll
+        for (uint32_t c = 0; c < ROUND; ++c) {
+            const uint32_t i = (d * ROUND + c) * WAVES + wave;
+            const uint64_t pos = (uint64_t)(i * runs_total / runs) * SAMPLE_RUN + lane * VEC;   // i * runs_total < 2^30
             e[c] = (i < runs && pos < L.n) ? (uint32_t)pos : 0xFFFFFFFFu;
-            if (e[c] != 0xFFFFFFFFu) {
+            if (any && e[c] != 0xFFFFFFFFu) {
                 load_quad(rl, e[c], L.n, rv[c]);
                 if (gp) load_quad(gl, e[c], L.n, gv[c]);
                 load_quad(wl, e[c], L.n, wv[c], 1.0f);
             }
         }
 #pragma unroll
-        for (uint32_t c = 0; c < PER_ROUND; ++c) {
-            if (e[c] == 0xFFFFFFFFu) continue;
+        for (uint32_t c = 0; c < ROUND; ++c)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                if (e[c] + q >= L.n) break;
-                const float v = gp ? accum(rv[c][q], gv[c][q], m) : rv[c][q];
-                atomicAdd(&lh[score_key(v, wv[c][q], eps) >> digit_shift(0)], 1u);
+                key[d][c][q] = NOT_AN_ELEMENT;
+                if (any && e[c] != 0xFFFFFFFFu && (uint64_t)e[c] + q < L.n)
+                    key[d][c][q] = score_key(gp ? accum(rv[c][q], gv[c][q], m) : rv[c][q], wv[c][q], eps);
             }
-        }
     }
     __syncthreads();
-    // every run but the layer's last is full, and the last is only sampled when all are
-    const uint64_t sampled = runs == runs_total ? (uint64_t)L.n : (uint64_t)runs * SAMPLE_RUN;
-    const uint32_t ks = (uint32_t)max((uint64_t)1, ((uint64_t)L.k * sampled + L.n - 1) / L.n);
-    uint32_t bin, k_rem;
-    block_pick<(int)HIST0>(lh, ks, sh, &bin, &k_rem);
-    return bin;
+#pragma unroll
+    for (uint32_t d = 0; d < ROUNDS; ++d)
+#pragma unroll
+        for (uint32_t c = 0; c < ROUND; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (key[d][c][q] != NOT_AN_ELEMENT) atomicAdd(&lh[key[d][c][q] >> digit_shift(0)], 1u);
+    __syncthreads();
+    uint32_t top, k_rem, mid, k_rem2;
+    block_pick<(int)HIST0, INIT_BLOCK>(lh, rank, sh, &top, &k_rem);
+    for (uint32_t b = tid; b < HIST0; b += INIT_BLOCK) lh[b] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t d = 0; d < ROUNDS; ++d)
+#pragma unroll
+        for (uint32_t c = 0; c < ROUND; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (key[d][c][q] != NOT_AN_ELEMENT && (key[d][c][q] >> digit_shift(0)) == top)
+                    atomicAdd(&lh[(key[d][c][q] >> SAMPLE_LOW_BITS) & (HIST0 - 1)], 1u);
+    __syncthreads();
+    block_pick<(int)HIST0, INIT_BLOCK>(lh, k_rem, sh, &mid, &k_rem2);
+    return (top << digit_shift(0)) | (mid << SAMPLE_LOW_BITS);
 }
 
-__global__ __launch_bounds__(BLOCK) void k_init(uint32_t* __restrict__ words, uint64_t n_words,
-                                                LayerState* __restrict__ state, uint32_t n_layers,
-                                                const iwp_threshold* __restrict__ hint,
-                                                const DevLayer* __restrict__ layers,
-                                                DevLayer* __restrict__ single_table, DevLayer row, DevLayer sentinel,
-                                                SampleSource S) {
+__global__ __launch_bounds__(INIT_BLOCK, 8) void k_init(uint32_t* __restrict__ words, uint64_t n_words,
+                                                     LayerState* __restrict__ state, uint32_t zero_blocks,
+                                                     const iwp_threshold* __restrict__ hint,
+                                                     const DevLayer* __restrict__ layers,
+                                                     DevLayer* __restrict__ single_table, DevLayer row, DevLayer sentinel,
+                                                     SampleSource S) {
     __shared__ uint32_t lh[HIST0];
-    __shared__ uint32_t sh[BLOCK + 2];
-    if (blockIdx.x >= n_layers) {
-        const uint64_t stride = (uint64_t)(gridDim.x - n_layers) * BLOCK;
-        for (uint64_t i = (uint64_t)(blockIdx.x - n_layers) * BLOCK + threadIdx.x; i < n_words; i += stride) words[i] = 0u;
-        if (single_table && blockIdx.x == n_layers && threadIdx.x == 0) {
+    __shared__ uint32_t sh[PICK_WORDS];
+    if (blockIdx.x < zero_blocks) {                          // the workspace's parts are whole 256-byte blocks
+        const uint64_t quads = (n_words + 3) / 4, stride = (uint64_t)zero_blocks * INIT_BLOCK;
+        uint4* w4 = reinterpret_cast<uint4*>(words);
+        for (uint64_t i = (uint64_t)blockIdx.x * INIT_BLOCK + threadIdx.x; i < quads; i += stride) w4[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (single_table && blockIdx.x == 0 && threadIdx.x == 0) {
             single_table[0] = row;
             single_table[1] = sentinel;
         }
         return;
     }
-    const uint32_t j = blockIdx.x;
+    const uint32_t j = blockIdx.x - zero_blocks;
     const DevLayer L = single_table ? row : layers[j];       // the one-row table is only being written by this launch
-    // one bin of slack below the hinted / estimated threshold bin (a bin is 1/16 octave); a threshold in
-    // bin 0 or 1 (among zero scores): look 1 stages nothing
-    uint32_t guess = 0;
-    if (hint) {
-        guess = (hint[j].key & 0x7fffffffu) >> digit_shift(0);
-    } else if (S.on && L.k > 0 && L.n > 0) {                 // uniform over the workgroup
+    uint32_t from = 0;
+    if (S.on && L.k > 0 && L.n > 0) {                        // uniform over the workgroup
         const uint32_t p = leader_of(S.leader, j, S.W);
-        guess = sample_stage_bin(L, S.P.g[p], S.P.r[p], S.w, S.eps, S.P.momentum, lh, sh);
+        from = sample_stage_key(L, S.P.g[p], S.P.r[p], S.w, S.eps, S.P.momentum, lh, sh);
     }
     if (threadIdx.x == 0) {
         LayerState st;
         st.b1 = 0; st.k_rem0 = 0; st.p22 = 0; st.k_rem1 = 0; st.thr = 0; st.n_eq_take = 0; st.prestaged = 0;
-        st.stage_bin = guess >= 2u ? guess - 1u : NO_STAGE_BIN;
+        // a guess in the lowest bin (among zero scores): look 1 stages nothing; among NaN: whole bins
+        constexpr uint32_t BIN = 1u << digit_shift(0);
+        if (hint) {
+            const uint32_t h = hint[j].key & 0x7fffffffu;
+            if (h >= BIN && h + HINT_SLACK < from) from = h;
+        }
+        st.shift = (from >= BIN && from < QUIET_NAN_KEY) ? (0u - from) & (BIN - 1u) : 0u;
+        st.stage_bin = from >= BIN ? shifted(from, st.shift) >> digit_shift(0) : NO_STAGE_BIN;
         state[j] = st;
     }
 }
 
 // ---------------------------------------------------------------------------
 // First digit pick, one workgroup per layer: the bin b1 of the 4096-bin histogram that holds
-// rank k, and whether look 1's copies (staged from a hinted bin) already cover it.  This pick
+// rank k, and whether look 1's copies already cover it.  This pick
 // keeps a launch of its own: its histogram is too large for every tile's workgroup to re-read,
 // and a summary of it would have to be built with atomics on a handful of addresses that all
 // workgroups of look 1 hit (measured: look 1 nearly twice as slow).  A layer whose look 1
@@ -154,7 +184,7 @@ __global__ __launch_bounds__(BLOCK) void k_init(uint32_t* __restrict__ words, ui
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(BLOCK) void k_first_pick(const DevLayer* __restrict__ layers, uint32_t* __restrict__ hist,
                                                       LayerState* __restrict__ state) {
-    __shared__ uint32_t sh[BLOCK + 2];
+    __shared__ uint32_t sh[PICK_WORDS];
     const uint32_t j = blockIdx.x;
     const DevLayer L = layers[j];
     if (L.k == 0) return;
@@ -204,7 +234,7 @@ __global__ __launch_bounds__(BLOCK) void k_first_pick(const DevLayer* __restrict
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(BLOCK) void k_final_pick(const DevLayer* __restrict__ layers, const uint32_t* __restrict__ hist,
                                                       LayerState* __restrict__ state, iwp_threshold* __restrict__ thr_out) {
-    __shared__ uint32_t sh[BLOCK + 2];
+    __shared__ uint32_t sh[PICK_WORDS];
     const uint32_t j = blockIdx.x;
     const DevLayer L = layers[j];
     if (L.k == 0) return;
@@ -216,7 +246,7 @@ __global__ __launch_bounds__(BLOCK) void k_final_pick(const DevLayer* __restrict
         state[j].n_eq_take = k_rem;
         if (thr_out) {
             iwp_threshold th;
-            th.key = (p22 << digit_bits(2)) | bin; th.n_gt = L.k - k_rem; th.n_eq_take = k_rem;
+            th.key = unshifted((p22 << digit_bits(2)) | bin, state[j].shift); th.n_gt = L.k - k_rem; th.n_eq_take = k_rem;
             thr_out[j] = th;
         }
     }
@@ -231,7 +261,7 @@ __global__ __launch_bounds__(BLOCK) void k_load_thresholds(const DevLayer* __res
     LayerState st;
     st.b1 = 0; st.k_rem0 = 0; st.p22 = 0; st.k_rem1 = 0;
     st.thr = thr[j].key; st.n_eq_take = thr[j].n_eq_take;
-    st.stage_bin = NO_STAGE_BIN; st.prestaged = 0;
+    st.stage_bin = NO_STAGE_BIN; st.shift = 0; st.prestaged = 0;
     state[j] = st;
 }
 
@@ -249,7 +279,7 @@ __device__ __forceinline__ void flush_hist(const uint32_t* lh, uint32_t* __restr
 // for the passes that follow.  The unit of work is a tile; a workgroup takes the tiles
 // blockIdx.x, blockIdx.x + gridDim.x, ... (the grid is capped: a launch of hundreds of
 // thousands of workgroups that mostly have nothing to do costs more than their work).
-//  * Look 1 already filled the layer's slots from a bin <= b1 (threshold hint or sample):
+//  * Look 1 already filled the layer's slots from a bin <= b1:
 //    only the slots are read, by the first tile's unit of every STAGE_GROUP tiles, into one
 //    LDS histogram that is flushed once.  In the steady state of a training run the
 //    threshold's bin holds about as many elements as are kept; that many single atomics per
@@ -263,15 +293,7 @@ __device__ __forceinline__ void flush_hist(const uint32_t* lh, uint32_t* __restr
 // ---------------------------------------------------------------------------
 constexpr uint32_t STAGE_GROUP = 16;               // tiles whose slots one unit histograms
 constexpr uint32_t STAGE_MAX_GRID = 32768;         // with at most 2^20 tiles per table: at most 32 tiles per workgroup
-constexpr uint32_t STAGE_TILES_MAX = 64;           // ... and one per STAGE_TILES_PER_AVG tiles of the average layer beyond
-constexpr uint32_t STAGE_TILES_PER_AVG = 4096;     // that, up to the 64 the kernel handles: every workgroup flushes into
-                                                   // its layer's one second-digit histogram, and same-address atomics
-                                                   // queue up (a 2^30-element layer: 15 000 flushes of up to 1024 bins)
-constexpr uint32_t STAGE_TILES = 4;                // tiles per workgroup on tables whose layers average STAGE_LONG_LAYER_TILES
-constexpr uint32_t STAGE_LONG_LAYER_TILES = 256;   // tiles or more: most tiles have nothing to do when look 1 staged the
-                                                   // layer, and a workgroup that only finds that out still costs a launch
-                                                   // slot and two dependent loads (AlexNet-shaped: 3 us per step less; on
-                                                   // the ResNet-50-shaped set, whose hints miss more often, 8 us more)
+constexpr uint32_t STAGE_TILES_MAX = 64;           // tiles per workgroup, at most (their look-1 counts: one per lane)
 
 __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __restrict__ w,
                                                  const DevLayer* __restrict__ layers, uint32_t n_layers,
@@ -288,7 +310,7 @@ __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __
     const uint32_t per = (tiles + gridDim.x - 1) / gridDim.x;
     const uint32_t t0 = blockIdx.x * per, t1 = min(t0 + per, tiles);
     const uint32_t my_cnt = (t0 + lane < t1) ? stage_cnt[t0 + lane] : 0u;
-    uint32_t cur_j = 0xFFFFFFFFu, b1 = 0;
+    uint32_t cur_j = 0xFFFFFFFFu, b1 = 0, shift = 0;
     bool prestaged = false;
     bool filled = false;                                   // lh holds counts of layer cur_j that are not flushed yet:
                                                            // one flush per workgroup and layer, however many tiles
@@ -303,6 +325,7 @@ __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __
             }
             L = layers[j];
             b1 = state[j].b1;
+            shift = state[j].shift;
             prestaged = state[j].prestaged != 0;
             cur_j = j;
         }
@@ -392,7 +415,7 @@ __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     if (full || i + q < L.n) {
-                        key[u][q] = score_key(val[u][q], wgt[u][q], eps);
+                        key[u][q] = shifted(score_key(val[u][q], wgt[u][q], eps), shift);
                     } else {
                         key[u][q] = NOT_AN_ELEMENT;
                     }
@@ -400,7 +423,7 @@ __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __
             }
             // a tile whose keys are all the same (typically a tile of zero residuals in a layer whose threshold is
             // zero, where everything ties) is recorded as such: one entry instead of an overflowing slot
-            const uint32_t k0 = score_key(rl[base], wl[base], eps);            // the tile's first element
+            const uint32_t k0 = shifted(score_key(rl[base], wl[base], eps), shift);   // the tile's first element
             bool same = true;
 #pragma unroll
             for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
@@ -448,7 +471,7 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
                                                    const uint32_t* __restrict__ stage_cnt, StageArrays A,
                                                    uint32_t* __restrict__ hist) {
     __shared__ uint32_t lh[HIST2];
-    __shared__ uint32_t sh[BLOCK + 2];
+    __shared__ uint32_t sh[PICK_WORDS];
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
     const uint32_t per = (stiles + gridDim.x - 1) / gridDim.x;
     const uint32_t s0 = blockIdx.x * per, s1 = min(s0 + per, stiles);
@@ -523,6 +546,7 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
         if (raw_tiles) {                                                       // uniform
             const float* rl = R.r[leader_of(leader, j, W)] + L.offset;
             const float* wl = w + L.offset;
+            const uint32_t shift = state[j].shift;
             for (uint32_t tl = 0; tl < nt; ++tl) {
                 if (!((raw_tiles >> tl) & 1ull)) continue;
                 for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
@@ -533,7 +557,7 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
                     load_quad(wl, i, L.n, wv, 1.0f);
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const uint32_t key2 = score_key(rv[q], wv[q], eps);
+                        const uint32_t key2 = shifted(score_key(rv[q], wv[q], eps), shift);
                         if (i + q < L.n && (key2 >> digit_shift(1)) == prefix) atomicAdd(&lh[key2 & (HIST2 - 1)], 1u);
                     }
                 }
@@ -563,13 +587,13 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
                                                  const uint32_t* __restrict__ stage_cnt, StageArrays A,
                                                  uint2* __restrict__ tile_counts, uint2* __restrict__ stile_counts) {
     __shared__ uint32_t cg[GROUP], ce[GROUP];
-    __shared__ uint32_t sh[BLOCK + 2];
+    __shared__ uint32_t sh[PICK_WORDS];
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = tid & (WAVE - 1), wave = tid >> 6;
     constexpr bool all_raw = FROM_RECORDS;
     const uint32_t per = (stiles + gridDim.x - 1) / gridDim.x;
     const uint32_t s0 = blockIdx.x * per, s1 = min(s0 + per, stiles);
-    uint32_t cur_j = 0xFFFFFFFFu, thr = 0;
+    uint32_t cur_j = 0xFFFFFFFFu, thr = 0, shift = 0;
     DevLayer L;
     for (uint32_t s = s0; s < s1; ++s) {
         const uint32_t j = find_layer<true>(layers, n_layers, s);
@@ -577,6 +601,7 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
             L = layers[j];
             cur_j = j;
             if (L.k == 0) continue;
+            shift = state[j].shift;
             if (FROM_RECORDS) {
                 thr = state[j].thr;
             } else {
@@ -589,7 +614,7 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
                     state[j].n_eq_take = k_rem2;
                     if (thr_out) {
                         iwp_threshold th;
-                        th.key = thr; th.n_gt = L.k - k_rem2; th.n_eq_take = k_rem2;
+                        th.key = unshifted(thr, state[j].shift); th.n_gt = L.k - k_rem2; th.n_eq_take = k_rem2;
                         thr_out[j] = th;
                     }
                 }
@@ -643,7 +668,7 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
                 const uint32_t first = (lt0 + tl) * TILE;
                 const uint32_t end = min(L.n, first + TILE);
                 for (uint32_t i = first + lane; i < end; i += WAVE) {
-                    const uint32_t k2 = score_key(rl[i], wl[i], eps);
+                    const uint32_t k2 = shifted(score_key(rl[i], wl[i], eps), shift);
                     gt += k2 > thr ? 1u : 0u;
                     eq += k2 == thr ? 1u : 0u;
                 }
@@ -883,7 +908,7 @@ __global__ __launch_bounds__(BLOCK) void k_write(ResidualPtrs R, const float* __
         uint32_t packed = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            key[q] = score_key(rv[q], wv[q], eps);
+            key[q] = shifted(score_key(rv[q], wv[q], eps), st.shift);
             const bool valid = i + q < L.n;
             packed += (valid && key[q] > thr) ? 1u : 0u;
             packed += (valid && key[q] == thr) ? 0x10000u : 0u;

@@ -17,12 +17,13 @@
 
 namespace iwp {
 
-// What a leader's workgroup needs besides the data: its LDS histogram, and, when a
-// threshold hint makes look 1 copy candidates out, where they go.
+// What a leader's workgroup needs besides the data: its LDS histogram, and where the
+// candidates go that look 1 copies out.
 struct LeadCtx {
     uint32_t* lh;           // LDS, HIST0 bins
     uint32_t* slot;         // LDS, 2 x 4 words for the scans
     uint32_t stage_bin;     // NO_STAGE_BIN: no staging in look 1
+    uint32_t shift;         // of the layer's keys
     uint32_t cap;           // slot entries per tile
     uint64_t slot_begin;    // the layer's first slot
     uint32_t* stage_cnt;    // the layer's first tile count
@@ -107,10 +108,10 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
                 store_v4<(KEEP < KEEP_W_AND_R)>(rl + i, rr[u]);
             }
             val[u][0] = rr[u].x; val[u][1] = rr[u].y; val[u][2] = rr[u].z; val[u][3] = rr[u].w;
-            key[u][0] = score_key(rr[u].x, ww[u].x, eps);
-            key[u][1] = score_key(rr[u].y, ww[u].y, eps);
-            key[u][2] = score_key(rr[u].z, ww[u].z, eps);
-            key[u][3] = score_key(rr[u].w, ww[u].w, eps);
+            key[u][0] = shifted(score_key(rr[u].x, ww[u].x, eps), C.shift);
+            key[u][1] = shifted(score_key(rr[u].y, ww[u].y, eps), C.shift);
+            key[u][2] = shifted(score_key(rr[u].z, ww[u].z, eps), C.shift);
+            key[u][3] = shifted(score_key(rr[u].w, ww[u].w, eps), C.shift);
         }
     } else {
         // ragged tail of a layer: the same shape, every load of
@@ -134,7 +135,7 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
                 store_quad<true>(rl, i, n, val[u]);
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) key[u][q] = (i + q < n) ? score_key(val[u][q], wv[u][q], eps) : NOT_AN_ELEMENT;
+            for (int q = 0; q < 4; ++q) key[u][q] = (i + q < n) ? shifted(score_key(val[u][q], wv[u][q], eps), C.shift) : NOT_AN_ELEMENT;
         }
     }
     // zero scores (zero residuals: a layer's untouched part) are counted in a register and added once per
@@ -144,7 +145,7 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
     for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            if (key[u][q] == 0u) ++zeros;
+            if (key[u][q] == C.shift) ++zeros;
             else if (key[u][q] != NOT_AN_ELEMENT) atomicAdd(&C.lh[key[u][q] >> digit_shift(0)], 1u);
         }
     if (__any(zeros != 0)) {
@@ -189,6 +190,7 @@ __device__ __forceinline__ LeadCtx lead_ctx(uint32_t* lh, uint32_t* slot, const 
     C.lh = lh;
     C.slot = slot;
     C.stage_bin = state[j].stage_bin;
+    C.shift = state[j].shift;
     C.cap = L.slot_cap;
     C.slot_begin = L.slot_begin;
     C.stage_cnt = stage_cnt + L.tile_begin;
