@@ -280,23 +280,6 @@ __device__ __forceinline__ void block_pick(const uint32_t* hist, uint32_t k_rem,
     *k_rem_out = sh[WAVES + 1];
 }
 
-// Orders LDS traffic inside one wavefront (the lanes run in lockstep; this makes
-// earlier LDS writes and atomics of the wave visible to its later reads).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Wavefront-private version of bitmap_prefix: each lane owns two of the 128 words.
-__device__ __forceinline__ void wave_bitmap_prefix(const uint32_t* map, uint32_t* prefix) {
-    const uint32_t lane = threadIdx.x & (WAVE - 1);
-    const uint32_t c0 = __popc(map[2 * lane]), c1 = __popc(map[2 * lane + 1]);
-    const uint32_t ex = wave_inclusive_scan(c0 + c1) - (c0 + c1);
-    prefix[2 * lane] = ex;
-    prefix[2 * lane + 1] = ex + c0;
-    wave_sync();
-}
-
 // One bit per element of a tile.  prefix[w] = number of set bits in words < w.
 // Called by all 256 threads after the bitmap is complete (and synchronised).
 __device__ __forceinline__ void bitmap_prefix(const uint32_t* map, uint32_t* prefix, uint32_t* slot) {
@@ -315,25 +298,42 @@ __device__ __forceinline__ uint32_t bitmap_rank(const uint32_t* map, const uint3
 }
 
 // Copy the elements of one tile whose top key digit is >= bin into the tile's slot,
-// in index order.  key[u][q] / val[u][q]: the lane's element q of chunk u (the
-// lane's elements are consecutive, chunks follow each other), NOT_AN_ELEMENT past
+// in index order, so that the ordered split can rank a slot's entries by their place in it.  key[u][q] / val[u][q]: the
+// lane's element q of chunk u (the lane's elements are consecutive, chunks follow each other), NOT_AN_ELEMENT past
 // the layer's end.  Returns the number of copies, or RAW_TILE if they exceed the
-// slot (then nothing is written).  All 256 threads call it; `slot`: 4 words of LDS.
+// slot (then nothing is written).  All 256 threads call it; `slot`: STAGE_WORDS words of LDS, not to be used again
+// before the next __syncthreads().
+constexpr uint32_t STAGE_WORDS = 2 * BLOCK / WAVE;
 __device__ __forceinline__ uint32_t stage_tile(const uint32_t (&key)[CHUNKS_PER_TILE][4],
                                                const float (&val)[CHUNKS_PER_TILE][4], uint32_t base, uint32_t bin,
                                                uint32_t cap, uint64_t sb, const StageArrays& A, uint32_t* slot) {
-    uint32_t c = 0;
+    static_assert(CHUNKS_PER_TILE == 4 && CHUNK < 65536, "two chunks' counts in one word");
+    const uint32_t lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
+    uint32_t c[2] = {0u, 0u};                                // counts of chunks 0, 1 and of chunks 2, 3
 #pragma unroll
     for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            c += (key[u][q] != NOT_AN_ELEMENT && (key[u][q] >> digit_shift(0)) >= bin) ? 1u : 0u;
-    uint32_t tot;
-    uint32_t o = block_exclusive_scan(c, slot, &tot);
-    if (tot > cap) return RAW_TILE;
-    if (c) {
+            c[u / 2] += (key[u][q] != NOT_AN_ELEMENT && (key[u][q] >> digit_shift(0)) >= bin) ? 1u << (16 * (u % 2)) : 0u;
+    const uint32_t i0 = wave_inclusive_scan(c[0]), i1 = wave_inclusive_scan(c[1]);
+    if (lane == WAVE - 1) { slot[2 * wave] = i0; slot[2 * wave + 1] = i1; }
+    __syncthreads();
+    uint32_t b0 = i0 - c[0], b1 = i1 - c[1], t0 = 0, t1 = 0;
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+    for (uint32_t v = 0; v < BLOCK / WAVE; ++v) {
+        const uint32_t s0 = slot[2 * v], s1 = slot[2 * v + 1];
+        b0 += v < wave ? s0 : 0u;
+        b1 += v < wave ? s1 : 0u;
+        t0 += s0;
+        t1 += s1;
+    }
+    const uint32_t n0 = t0 & 0xffffu, n01 = n0 + (t0 >> 16), n012 = n01 + (t1 & 0xffffu), tot = n012 + (t1 >> 16);
+    if (tot > cap) return RAW_TILE;
+    const uint32_t first[CHUNKS_PER_TILE] = {b0 & 0xffffu, n0 + (b0 >> 16), n01 + (b1 & 0xffffu), n012 + (b1 >> 16)};
+    if (c[0] | c[1]) {
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+            uint32_t o = first[u];
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 if (key[u][q] != NOT_AN_ELEMENT && (key[u][q] >> digit_shift(0)) >= bin) {
@@ -342,6 +342,7 @@ __device__ __forceinline__ uint32_t stage_tile(const uint32_t (&key)[CHUNKS_PER_
                     A.val[sb + o] = val[u][q];
                     ++o;
                 }
+        }
     }
     return tot;
 }

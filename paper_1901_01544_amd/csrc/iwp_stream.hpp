@@ -21,7 +21,7 @@ namespace iwp {
 // candidates go that look 1 copies out.
 struct LeadCtx {
     uint32_t* lh;           // LDS, HIST0 bins
-    uint32_t* slot;         // LDS, 2 x 4 words for the scans
+    uint32_t* slot;         // LDS, 2 x STAGE_WORDS words for the scans
     uint32_t stage_bin;     // NO_STAGE_BIN: no staging in look 1
     uint32_t shift;         // of the layer's keys
     uint32_t cap;           // slot entries per tile
@@ -155,7 +155,7 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
     }
     if (C.stage_bin != NO_STAGE_BIN) {                      // uniform
         const uint32_t cnt = stage_tile(key, val, base, C.stage_bin, C.cap, C.slot_begin + (uint64_t)lt * C.cap, C.A,
-                                        C.slot + (lt & 1u) * 4u);
+                                        C.slot + (lt & 1u) * STAGE_WORDS);
         if (tid == 0) C.stage_cnt[lt] = cnt;
     }
 }
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(BLOCK) void k_leader_pass(WorkerPtrs P, const float
                                                        const LayerState* __restrict__ state,
                                                        uint32_t* __restrict__ stage_cnt, StageArrays A) {
     __shared__ uint32_t lh[HIST0];
-    __shared__ uint32_t slot[8];
+    __shared__ uint32_t slot[2 * STAGE_WORDS];
     uint32_t j, first;
     if (LG == 1) {
         j = find_layer<false>(layers, n_layers, blockIdx.x);
