@@ -246,17 +246,17 @@ int launch_leader_pass(const Table& T, const Workspace& ws, const WorkerPtrs& P,
 
 template <bool FUSED>
 int launch_write(const Table& T, const Workspace& ws, const ResidualPtrs& R, const float* w, const uint32_t* leader,
-                 uint32_t W, float eps, bool all_raw, uint32_t* idx_out, float* val_out, hipStream_t s) {
+                 uint32_t W, float eps, uint32_t* idx_out, float* val_out, hipStream_t s) {
     const uint32_t grid = T.stiles * (GROUP / (BLOCK / WAVE));
     float* gathered = FUSED ? ws.gathered : nullptr;
     if (T.max_layer_stiles <= FOLD_SCAN_MAX_STILES) {
         IWP_LAUNCH("k_write", (k_write<FUSED, true>), grid, s, R, w, T.layers, T.n_layers, leader, W, eps, ws.state,
-                   ws.stage, ws.A, all_raw, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, gathered,
+                   ws.stage, ws.A, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, gathered,
                    T.pairs);
     } else {
         IWP_LAUNCH("k_scan", k_scan, T.n_layers, s, T.layers, ws.stile_counts, false, nullptr);
         IWP_LAUNCH("k_write", (k_write<FUSED, false>), grid, s, R, w, T.layers, T.n_layers, leader, W, eps, ws.state,
-                   ws.stage, ws.A, all_raw, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, gathered,
+                   ws.stage, ws.A, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, gathered,
                    T.pairs);
     }
     return IWP_OK;
@@ -289,19 +289,19 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
     }
     IWP_LAUNCH("k_count", k_count<false>, stile_grid, s, R, w, T.layers, T.n_layers, T.stiles, leader, W, eps, ws.state,
                ws.hist, thr_out, ws.stage, ws.A, ws.tile_counts, ws.stile_counts);
-    if (fused) return launch_write<true>(T, ws, R, w, leader, W, eps, false, idx_out, val_out, s);
-    return launch_write<false>(T, ws, R, w, leader, W, eps, false, idx_out, val_out, s);
+    if (fused) return launch_write<true>(T, ws, R, w, leader, W, eps, idx_out, val_out, s);
+    return launch_write<false>(T, ws, R, w, leader, W, eps, idx_out, val_out, s);
 }
 
-// Ordered split from threshold records given by the caller (nothing is staged: every tile is re-read).
+// Ordered split from threshold records given by the caller.
 int run_compact_from(const Table& T, const Workspace& ws, const ResidualPtrs& R, const float* w, float eps,
                      const iwp_threshold* thr, uint32_t* idx_out, float* val_out, hipStream_t s) {
     if (!T.any_k || T.tiles == 0) return IWP_OK;
-    IWP_LAUNCH("k_load_thresholds", k_load_thresholds, (T.n_layers + BLOCK - 1) / BLOCK, s, T.layers, T.n_layers, thr,
-               ws.state);
+    IWP_LAUNCH("k_stage_records", k_stage_records, T.tiles, s, R.r[0], w, T.layers, T.n_layers, thr, eps, ws.state, ws.stage,
+               ws.A);
     IWP_LAUNCH("k_count", k_count<true>, std::min<uint32_t>(T.stiles, STILE_MAX_GRID), s, R, w, T.layers, T.n_layers,
                T.stiles, nullptr, 1u, eps, ws.state, ws.hist, nullptr, ws.stage, ws.A, ws.tile_counts, ws.stile_counts);
-    return launch_write<false>(T, ws, R, w, nullptr, 1u, eps, true, idx_out, val_out, s);
+    return launch_write<false>(T, ws, R, w, nullptr, 1u, eps, idx_out, val_out, s);
 }
 
 }  // namespace

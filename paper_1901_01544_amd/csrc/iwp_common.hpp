@@ -305,7 +305,7 @@ __device__ __forceinline__ uint32_t bitmap_rank(const uint32_t* map, const uint3
     return prefix[wd] + __popc(map[wd] & ((1u << b) - 1u));
 }
 
-// Copy the elements of one tile whose top key digit is >= bin into the tile's slot,
+// Copy the elements of one tile whose key is >= from into the tile's slot,
 // in index order, so that the ordered split can rank a slot's entries by their place in it.  key[u][q] / val[u][q]: the
 // lane's element q of chunk u (the lane's elements are consecutive, chunks follow each other), NOT_AN_ELEMENT past
 // the layer's end.  Returns the number of copies, or RAW_TILE if they exceed the
@@ -313,7 +313,7 @@ __device__ __forceinline__ uint32_t bitmap_rank(const uint32_t* map, const uint3
 // before the next __syncthreads().
 constexpr uint32_t STAGE_WORDS = 2 * BLOCK / WAVE;
 __device__ __forceinline__ uint32_t stage_tile(const uint32_t (&key)[CHUNKS_PER_TILE][4],
-                                               const float (&val)[CHUNKS_PER_TILE][4], uint32_t base, uint32_t bin,
+                                               const float (&val)[CHUNKS_PER_TILE][4], uint32_t base, uint32_t from,
                                                uint32_t cap, uint64_t sb, const StageArrays& A, uint32_t* slot) {
     static_assert(CHUNKS_PER_TILE == 4 && CHUNK < 65536, "two chunks' counts in one word");
     const uint32_t lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
@@ -322,7 +322,7 @@ __device__ __forceinline__ uint32_t stage_tile(const uint32_t (&key)[CHUNKS_PER_
     for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            c[u / 2] += (key[u][q] != NOT_AN_ELEMENT && (key[u][q] >> digit_shift(0)) >= bin) ? 1u << (16 * (u % 2)) : 0u;
+            c[u / 2] += (key[u][q] != NOT_AN_ELEMENT && key[u][q] >= from) ? 1u << (16 * (u % 2)) : 0u;
     const uint32_t i0 = wave_inclusive_scan(c[0]), i1 = wave_inclusive_scan(c[1]);
     if (lane == WAVE - 1) { slot[2 * wave] = i0; slot[2 * wave + 1] = i1; }
     __syncthreads();
@@ -344,7 +344,7 @@ __device__ __forceinline__ uint32_t stage_tile(const uint32_t (&key)[CHUNKS_PER_
             uint32_t o = first[u];
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if (key[u][q] != NOT_AN_ELEMENT && (key[u][q] >> digit_shift(0)) >= bin) {
+                if (key[u][q] != NOT_AN_ELEMENT && key[u][q] >= from) {
                     A.key[sb + o] = key[u][q];
                     A.idx[sb + o] = base + u * CHUNK + threadIdx.x * VEC + q;
                     A.val[sb + o] = val[u][q];

@@ -252,25 +252,50 @@ __global__ __launch_bounds__(BLOCK) void k_final_pick(const DevLayer* __restrict
     }
 }
 
-// Threshold records supplied by the caller -> selection state (compact_pairs).
-__global__ __launch_bounds__(BLOCK) void k_load_thresholds(const DevLayer* __restrict__ layers, uint32_t n_layers,
-                                                           const iwp_threshold* __restrict__ thr,
-                                                           LayerState* __restrict__ state) {
-    const uint32_t j = blockIdx.x * BLOCK + threadIdx.x;
-    if (j >= n_layers || layers[j].k == 0) return;
-    LayerState st;
-    st.b1 = 0; st.k_rem0 = 0; st.p22 = 0; st.k_rem1 = 0;
-    st.thr = thr[j].key; st.n_eq_take = thr[j].n_eq_take;
-    st.stage_bin = NO_STAGE_BIN; st.shift = 0; st.prestaged = 0;
-    state[j] = st;
-}
-
 // LDS histogram -> global, non-empty bins only.
 template <int NB>
 __device__ __forceinline__ void flush_hist(const uint32_t* lh, uint32_t* __restrict__ gh) {
     for (uint32_t b = threadIdx.x; b < NB; b += BLOCK) {
         const uint32_t v = lh[b];
         if (v) atomicAdd(&gh[b], v);
+    }
+}
+
+// One tile's residuals and keys in registers, every load issued before the first use; NOT_AN_ELEMENT past the layer's end.
+__device__ __forceinline__ void scored_tile(const float* __restrict__ rl, const float* __restrict__ wl, uint32_t n,
+                                            uint32_t base, float eps, uint32_t shift,
+                                            uint32_t (&key)[CHUNKS_PER_TILE][4], float (&val)[CHUNKS_PER_TILE][4]) {
+    const uint32_t tid = threadIdx.x;
+    float wgt[CHUNKS_PER_TILE][4];
+    const bool full = base + TILE <= n;
+    if (full) {
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+            const uint32_t i = base + u * CHUNK + tid * VEC;
+            const v4f a = load_v4<true>(rl + i);
+            const v4f b = load_v4<true>(wl + i);
+            val[u][0] = a.x; val[u][1] = a.y; val[u][2] = a.z; val[u][3] = a.w;
+            wgt[u][0] = b.x; wgt[u][1] = b.y; wgt[u][2] = b.z; wgt[u][3] = b.w;
+        }
+    } else {
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+            const uint32_t i = base + u * CHUNK + tid * VEC;
+            if (i < n) {
+                load_quad(rl, i, n, val[u]);
+                load_quad(wl, i, n, wgt[u], 1.0f);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) { val[u][q] = 0.0f; wgt[u][q] = 1.0f; }
+            }
+        }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+        const uint32_t i = base + u * CHUNK + tid * VEC;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            key[u][q] = (full || i + q < n) ? shifted(score_key(val[u][q], wgt[u][q], eps), shift) : NOT_AN_ELEMENT;
     }
 }
 
@@ -385,42 +410,7 @@ __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __
             const uint32_t base = lt * TILE;
             uint32_t key[CHUNKS_PER_TILE][4];
             float val[CHUNKS_PER_TILE][4];
-            float wgt[CHUNKS_PER_TILE][4];
-            const bool full = base + TILE <= L.n;
-            if (full) {
-#pragma unroll
-                for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-                    const uint32_t i = base + u * CHUNK + tid * VEC;
-                    const v4f a = load_v4<true>(rl + i);
-                    const v4f b = load_v4<true>(wl + i);
-                    val[u][0] = a.x; val[u][1] = a.y; val[u][2] = a.z; val[u][3] = a.w;
-                    wgt[u][0] = b.x; wgt[u][1] = b.y; wgt[u][2] = b.z; wgt[u][3] = b.w;
-                }
-            } else {
-#pragma unroll
-                for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-                    const uint32_t i = base + u * CHUNK + tid * VEC;
-                    if (i < L.n) {
-                        load_quad(rl, i, L.n, val[u]);
-                        load_quad(wl, i, L.n, wgt[u], 1.0f);
-                    } else {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) { val[u][q] = 0.0f; wgt[u][q] = 1.0f; }
-                    }
-                }
-            }
-#pragma unroll
-            for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-                const uint32_t i = base + u * CHUNK + tid * VEC;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (full || i + q < L.n) {
-                        key[u][q] = shifted(score_key(val[u][q], wgt[u][q], eps), shift);
-                    } else {
-                        key[u][q] = NOT_AN_ELEMENT;
-                    }
-                }
-            }
+            scored_tile(rl, wl, L.n, base, eps, shift, key, val);
             // a tile whose keys are all the same (typically a tile of zero residuals in a layer whose threshold is
             // zero, where everything ties) is recorded as such: one entry instead of an overflowing slot
             const uint32_t k0 = shifted(score_key(rl[base], wl[base], eps), shift);   // the tile's first element
@@ -445,7 +435,7 @@ __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __
                     for (int q = 0; q < 4; ++q)
                         if (key[u][q] != NOT_AN_ELEMENT && (key[u][q] >> digit_shift(0)) == b1)
                             atomicAdd(&lh[(key[u][q] >> digit_shift(1)) & (HIST1 - 1)], 1u);
-                const uint32_t cnt = stage_tile(key, val, base, b1, L.slot_cap, sb, A, slot);
+                const uint32_t cnt = stage_tile(key, val, base, b1 << digit_shift(0), L.slot_cap, sb, A, slot);
                 if (tid == 0) stage_cnt[t] = (prestaged && cnt != RAW_TILE) ? (cnt | RESTAGED) : cnt;
             }
         }
@@ -571,12 +561,44 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
 }
 
 // ---------------------------------------------------------------------------
+// Threshold records given by the caller (compact_pairs): one pass over the layer that copies the elements at or above the
+// threshold into the tiles' slots, one workgroup per tile as in look 1; the ordered split then works on the slots, as
+// after a selection.  A layer's first workgroup leaves the record in its selection state.
+// Bound by reading r and w once.  Counting and writing from r and w directly read them twice, and the counts with one
+// dword per lane and access: 73 + 44 us on a 25.6 M-element table, now 34 us here and 5 + 6 us there.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(BLOCK) void k_stage_records(const float* __restrict__ r, const float* __restrict__ w,
+                                                         const DevLayer* __restrict__ layers, uint32_t n_layers,
+                                                         const iwp_threshold* __restrict__ thr, float eps,
+                                                         LayerState* __restrict__ state,
+                                                         uint32_t* __restrict__ stage_cnt, StageArrays A) {
+    __shared__ uint32_t slot[STAGE_WORDS];
+    const uint32_t t = blockIdx.x;
+    const uint32_t j = find_layer<false>(layers, n_layers, t);
+    const DevLayer L = layers[j];
+    if (L.k == 0) return;
+    const uint32_t lt = t - L.tile_begin;
+    const uint32_t from = thr[j].key;
+    if (lt == 0 && threadIdx.x == 0) {
+        LayerState st;
+        st.b1 = 0; st.k_rem0 = 0; st.p22 = 0; st.k_rem1 = 0;
+        st.thr = from; st.n_eq_take = thr[j].n_eq_take;
+        st.stage_bin = NO_STAGE_BIN; st.shift = 0; st.prestaged = 0;
+        state[j] = st;
+    }
+    uint32_t key[CHUNKS_PER_TILE][4];
+    float val[CHUNKS_PER_TILE][4];
+    scored_tile(r + L.offset, w + L.offset, L.n, lt * TILE, eps, 0u, key, val);
+    const uint32_t cnt = stage_tile(key, val, lt * TILE, from, L.slot_cap, L.slot_begin + (uint64_t)lt * L.slot_cap, A, slot);
+    if (threadIdx.x == 0) stage_cnt[t] = cnt;
+}
+
+// ---------------------------------------------------------------------------
 // Ordered split, part 1: per tile, how many elements lie above the threshold and
 // how many tie with it.  One workgroup per super-tile; writes each tile's exclusive
 // prefix inside the super-tile and the super-tile's totals.  The threshold is the
 // prologue's third pick (recorded, with thr_out, by the layer's first workgroup), or with
-// FROM_RECORDS the caller's record (compact_pairs): then there is no stage table and
-// every tile is re-read.
+// FROM_RECORDS the caller's record (compact_pairs).
 // ---------------------------------------------------------------------------
 template <bool FROM_RECORDS>
 __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __restrict__ w,
@@ -590,7 +612,6 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
     __shared__ uint32_t sh[PICK_WORDS];
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = tid & (WAVE - 1), wave = tid >> 6;
-    constexpr bool all_raw = FROM_RECORDS;
     const uint32_t per = (stiles + gridDim.x - 1) / gridDim.x;
     const uint32_t s0 = blockIdx.x * per, s1 = min(s0 + per, stiles);
     uint32_t cur_j = 0xFFFFFFFFu, thr = 0, shift = 0;
@@ -628,7 +649,7 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
         const float* wl = w + L.offset;
         // each wavefront takes tiles of its own (tiles wave and wave + 4; the counts and the first 256 entries of
         // both requested before any of them is used); nothing workgroup-wide until the end
-        const uint32_t my_cnt = (!all_raw && lane < nt) ? staged_entries(stage_cnt[L.tile_begin + lt0 + lane]) : RAW_TILE;
+        const uint32_t my_cnt = lane < nt ? staged_entries(stage_cnt[L.tile_begin + lt0 + lane]) : RAW_TILE;
         constexpr uint32_t MINE = GROUP / (BLOCK / WAVE);
         uint32_t cnt[MINE];
         uint32_t key[MINE][4];
@@ -861,7 +882,7 @@ __global__ __launch_bounds__(BLOCK) void k_write(ResidualPtrs R, const float* __
                                                  const DevLayer* __restrict__ layers, uint32_t n_layers,
                                                  const uint32_t* __restrict__ leader, uint32_t W, float eps,
                                                  const LayerState* __restrict__ state,
-                                                 const uint32_t* __restrict__ stage_cnt, StageArrays A, bool all_raw,
+                                                 const uint32_t* __restrict__ stage_cnt, StageArrays A,
                                                  const uint2* __restrict__ tile_counts,
                                                  const uint2* __restrict__ stile_counts,
                                                  uint32_t* __restrict__ tile_out,
@@ -910,7 +931,7 @@ __global__ __launch_bounds__(BLOCK) void k_write(ResidualPtrs R, const float* __
     float* vo = val_out + L.out_offset;
     float* go = FUSED ? gathered + (size_t)lead * K + L.out_offset : nullptr;
     if (lane == 0) tile_out[t] = Gt + min(Et, quota);
-    const uint32_t cnt = all_raw ? RAW_TILE : staged_entries(stage_cnt[t]);
+    const uint32_t cnt = staged_entries(stage_cnt[t]);
 
     write_tile<FUSED>(L, lt, cnt, thr, quota, st.shift, Gt, Et, rl, w + L.offset, eps, A, io, vo, go);
 }

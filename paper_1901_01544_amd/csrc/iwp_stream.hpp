@@ -154,7 +154,7 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
         if ((tid & (WAVE - 1)) == 0) atomicAdd(&C.lh[0], zeros);
     }
     if (C.stage_bin != NO_STAGE_BIN) {                      // uniform
-        const uint32_t cnt = stage_tile(key, val, base, C.stage_bin, C.cap, C.slot_begin + (uint64_t)lt * C.cap, C.A,
+        const uint32_t cnt = stage_tile(key, val, base, C.stage_bin << digit_shift(0), C.cap, C.slot_begin + (uint64_t)lt * C.cap, C.A,
                                         C.slot + (lt & 1u) * STAGE_WORDS);
         if (tid == 0) C.stage_cnt[lt] = cnt;
     }
