@@ -15,6 +15,7 @@
 #include "iwp_common.hpp"
 #include "iwp_exchange.hpp"
 #include "iwp_select.hpp"
+#include "iwp_small.hpp"
 #include "iwp_stream.hpp"
 #include "iwp_threshold.hpp"
 
@@ -293,6 +294,30 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
     return launch_write<false>(T, ws, R, w, leader, W, eps, idx_out, val_out, s);
 }
 
+// Are all of a table's layers small enough for k_small, which then replaces k_init, look 1 and the selection?
+constexpr uint32_t SMALL_MAX_N = SMALL_CHUNKS_MAX * SMALL_CHUNK;
+
+// row: a single layer (layers == NULL); fused: whole-step route.
+int launch_small(const DevLayer* layers, const DevLayer* row, uint32_t n_layers, uint32_t max_n, uint64_t pairs,
+                 const Workspace& ws, const WorkerPtrs& P, const float* w, const uint32_t* leader, uint32_t W, float eps,
+                 Stop stop, bool fused, uint32_t* idx_out, float* val_out, iwp_threshold* thr_out, hipStream_t s) {
+    DevLayer none;
+    memset(&none, 0, sizeof none);
+    const DevLayer r = row ? *row : none;
+    const bool emit = stop == FULL;
+    float* gathered = fused ? ws.gathered : nullptr;
+#define IWP_SMALL(FUSED, CHUNKS)                                                                                      \
+    IWP_LAUNCH_BLOCK("k_small", (k_small<FUSED, CHUNKS>), n_layers, SMALL_BLOCK, s, P, w, layers, r, leader, W, eps, \
+                     thr_out, emit, ws.tile_out, idx_out, val_out, gathered, pairs)
+    if (max_n <= SMALL_MAX_N / 2) {
+        if (fused) IWP_SMALL(true, SMALL_CHUNKS_MAX / 2); else IWP_SMALL(false, SMALL_CHUNKS_MAX / 2);
+    } else {
+        if (fused) IWP_SMALL(true, SMALL_CHUNKS_MAX); else IWP_SMALL(false, SMALL_CHUNKS_MAX);
+    }
+#undef IWP_SMALL
+    return IWP_OK;
+}
+
 // Ordered split from threshold records given by the caller.
 int run_compact_from(const Table& T, const Workspace& ws, const ResidualPtrs& R, const float* w, float eps,
                      const iwp_threshold* thr, uint32_t* idx_out, float* val_out, hipStream_t s) {
@@ -314,6 +339,7 @@ struct iwp_plan {
     bool any_k = false;
     bool all_k = true;            // every non-empty layer selects something
     uint32_t max_layer_stiles = 0;
+    uint32_t max_n = 0;           // elements of the longest layer
     float momentum = 1.0f;        // r <- momentum * r + g in every call that accumulates through this plan
 };
 
@@ -381,6 +407,9 @@ static int single_common(SingleOp op, const float* w, const float* g, float* r, 
     row.sample = sample_of(n, k);
     row.hist_begin = 0; row.h0_copies = h0_copies_of(n, k);
     sentinel.tile_begin = z.tiles; sentinel.stile_begin = z.stiles; sentinel.out_offset = k;
+    if (op != OP_COMPACT && k > 0 && n <= SMALL_MAX_N)
+        return launch_small(nullptr, &row, 1u, n, k, ws, P, w, nullptr, 1u, eps, op == OP_SELECT ? STOP_AT_THRESHOLD : FULL,
+                            false, idx_out, val_out, thr_out, s);
     SampleSource S = sample_from(P, w, nullptr, 1u, eps);
     if (op == OP_COMPACT || k == 0) S.on = 0;
     int rc = launch_init(ws, 1, nullptr, nullptr, &row, &sentinel, S, s);
@@ -472,7 +501,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     std::vector<DevLayer> dev(n_layers + 1);
     uint64_t pairs = 0, slots = 0, tiles = 0, stiles = 0, end = 0, mask_words = 0, hist_words = 0;
     bool any_k = false, all_k = true;
-    uint32_t max_stiles = 0;
+    uint32_t max_stiles = 0, max_n = 0;
     for (uint32_t j = 0; j < n_layers; ++j) {
         const iwp_layer& L = layers[j];
         if (L.offset < 0 || L.k > L.n) return IWP_EINVAL;
@@ -502,6 +531,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
         mask_words += ((uint64_t)L.n + 31) / 32;
         any_k = any_k || L.k > 0;
         max_stiles = std::max(max_stiles, stiles_of(L.n));
+        max_n = std::max(max_n, L.n);
         if (L.n > 0 && L.k == 0) all_k = false;
         if (pairs > 0xFFFFFFFFull || tiles > 0x7FFFFFFFull / IWP_MAX_WORKERS || hist_words > 0xFFFFFFFFull) return IWP_ERANGE;
     }
@@ -518,6 +548,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     plan->any_k = any_k;
     plan->all_k = all_k;
     plan->max_layer_stiles = max_stiles;
+    plan->max_n = max_n;
     plan->flat_end = end;
     // the table, then the layer of every tile and of every super-tile (find_layer reads them)
     std::vector<uint32_t> map;
@@ -611,15 +642,23 @@ static int compress_segmented_on(const iwp_plan* plan, const float* w, const flo
     if (rc) return rc;
     if (plan->z.tiles == 0) return IWP_OK;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    rc = launch_init(ws, plan->z.n_layers, thr_hint, plan->dev, nullptr, nullptr, sample_from(P, w, leader, W, eps), s);
-    if (rc) return rc;
     Table T{plan->dev, plan->z.n_layers, plan->z.tiles, plan->z.stiles, plan->z.pairs, plan->any_k, plan->max_layer_stiles};
-    if (T.any_k) {
-        rc = launch_leader_pass(T, ws, P, w, leader, W, eps, s);
+    const bool small = T.any_k && plan->max_n <= SMALL_MAX_N;
+    if (small) {
+        rc = launch_small(T.layers, nullptr, T.n_layers, plan->max_n, T.pairs, ws, P, w, leader, W, eps, FULL, false, idx_out,
+                          val_out, thr_out, s);
         if (rc) return rc;
+    } else {
+        rc = launch_init(ws, T.n_layers, thr_hint, T.layers, nullptr, nullptr, sample_from(P, w, leader, W, eps), s);
+        if (rc) return rc;
+        if (T.any_k) {
+            rc = launch_leader_pass(T, ws, P, w, leader, W, eps, s);
+            if (rc) return rc;
+        }
     }
     if (W > 1 || !plan->all_k)
         IWP_LAUNCH("k_accumulate_rest", k_accumulate_rest, W * T.tiles, s, P, T.layers, T.n_layers, T.tiles, leader, W);
+    if (small) return IWP_OK;
     return run_select(T, ws, R, w, leader, W, eps, FULL, false, idx_out, val_out, thr_out, s);
 }
 
@@ -661,10 +700,14 @@ int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, fl
     if (rc) return rc;
     if (z.tiles == 0) return IWP_OK;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    rc = launch_init(ws, z.n_layers, thr_hint, plan->dev, nullptr, nullptr, sample_from(P, w, leader, W, eps), s);
-    if (rc) return rc;
     Table T{plan->dev, z.n_layers, z.tiles, z.stiles, z.pairs, plan->any_k, plan->max_layer_stiles};
-    if (T.any_k) {
+    if (T.any_k && plan->max_n <= SMALL_MAX_N) {
+        rc = launch_small(T.layers, nullptr, T.n_layers, plan->max_n, T.pairs, ws, P, w, leader, W, eps, FULL, true, idx_out,
+                          val_out, thr_out, s);
+        if (rc) return rc;
+    } else if (T.any_k) {
+        rc = launch_init(ws, z.n_layers, thr_hint, plan->dev, nullptr, nullptr, sample_from(P, w, leader, W, eps), s);
+        if (rc) return rc;
         rc = launch_leader_pass(T, ws, P, w, leader, W, eps, s);
         if (rc) return rc;
         rc = run_select(T, ws, R, w, leader, W, eps, FULL, true, idx_out, val_out, thr_out, s);
@@ -705,6 +748,9 @@ int select_threshold_segmented(const iwp_plan* plan, const float* w, const float
     memset(&P, 0, sizeof P);
     P.r[0] = const_cast<float*>(r);       // no gradient pointer: the residual is only read
     P.momentum = 1.0f;
+    if (plan->max_n <= SMALL_MAX_N)
+        return launch_small(plan->dev, nullptr, plan->z.n_layers, plan->max_n, plan->z.pairs, ws, P, w, nullptr, 1u, eps,
+                            STOP_AT_THRESHOLD, false, nullptr, nullptr, thr_out, s);
     rc = launch_init(ws, plan->z.n_layers, nullptr, plan->dev, nullptr, nullptr, sample_from(P, w, nullptr, 1u, eps), s);
     if (rc) return rc;
     ResidualPtrs R;
