@@ -188,6 +188,7 @@ struct Table {                // what the launches need to know about a layer ta
     uint64_t pairs;
     bool any_k;
     uint32_t max_layer_stiles;   // super-tiles of the longest layer
+    uint32_t max_copies;         // copies of its first-digit histogram
 };
 
 // Up to this many super-tiles per layer (128 Mi elements) k_write adds up the earlier super-tiles'
@@ -270,7 +271,8 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
                uint32_t W, float eps, Stop stop, bool fused, uint32_t* idx_out, float* val_out,
                iwp_threshold* thr_out, hipStream_t s) {
     if (!T.any_k || T.tiles == 0) return IWP_OK;
-    IWP_LAUNCH("k_first_pick", k_first_pick, T.n_layers, s, T.layers, ws.hist, ws.state);
+    const bool own_pick = T.max_copies <= PICK_MAX_COPIES && T.tiles <= PICK_MAX_TILES;
+    if (!own_pick) IWP_LAUNCH("k_first_pick", k_first_pick, T.n_layers, s, T.layers, ws.hist, ws.state);
     // Consecutive tiles per look-2 workgroup, by the tiles of the average layer.  Look 1's copies are complete for
     // nearly every layer, and then only every STAGE_GROUP-th tile has work: few workgroups, few flushes into a layer's
     // one second-digit histogram.  Tables of short layers keep one tile each: a workgroup pays a chain of loads per layer.
@@ -279,8 +281,12 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
         : std::min<uint32_t>(std::max<uint32_t>(avg_tiles / 64u, STAGE_GROUP), STAGE_TILES_MAX);
     const uint32_t stage_grid = std::max<uint32_t>(std::min<uint32_t>((T.tiles + per_wg - 1) / per_wg, STAGE_MAX_GRID),
                                                    (T.tiles + WAVE - 1) / WAVE);
-    IWP_LAUNCH("k_stage", k_stage, stage_grid, s, R, w, T.layers, T.n_layers, T.tiles,
-               leader, W, eps, ws.state, ws.hist, ws.stage, ws.A);
+    if (own_pick)
+        IWP_LAUNCH("k_stage", k_stage<true>, stage_grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
+                   ws.hist, ws.stage, ws.A);
+    else
+        IWP_LAUNCH("k_stage", k_stage<false>, stage_grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
+                   ws.hist, ws.stage, ws.A);
     const uint32_t stile_grid = std::min<uint32_t>(T.stiles, STILE_MAX_GRID);
     IWP_LAUNCH("k_refine2", k_refine2, stile_grid, s, R, w, T.layers, T.n_layers, T.stiles, leader, W, eps, ws.state,
                ws.stage, ws.A, ws.hist);
@@ -340,6 +346,7 @@ struct iwp_plan {
     bool all_k = true;            // every non-empty layer selects something
     uint32_t max_layer_stiles = 0;
     uint32_t max_n = 0;           // elements of the longest layer
+    uint32_t max_copies = 1;      // most copies of a layer's first-digit histogram
     float momentum = 1.0f;        // r <- momentum * r + g in every call that accumulates through this plan
 };
 
@@ -414,7 +421,7 @@ static int single_common(SingleOp op, const float* w, const float* g, float* r, 
     if (op == OP_COMPACT || k == 0) S.on = 0;
     int rc = launch_init(ws, 1, nullptr, nullptr, &row, &sentinel, S, s);
     if (rc) return rc;
-    Table T{ws.single_table, 1, z.tiles, z.stiles, k, k > 0, z.stiles};
+    Table T{ws.single_table, 1, z.tiles, z.stiles, k, k > 0, z.stiles, row.h0_copies};
     if (op == OP_COMPACT) return run_compact_from(T, ws, R, w, eps, from_thr, idx_out, val_out, s);
     if (k > 0) {
         rc = launch_leader_pass(T, ws, P, w, nullptr, 1u, eps, s);
@@ -549,6 +556,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     plan->all_k = all_k;
     plan->max_layer_stiles = max_stiles;
     plan->max_n = max_n;
+    for (const DevLayer& D : dev) plan->max_copies = std::max(plan->max_copies, D.h0_copies);
     plan->flat_end = end;
     // the table, then the layer of every tile and of every super-tile (find_layer reads them)
     std::vector<uint32_t> map;
@@ -642,7 +650,7 @@ static int compress_segmented_on(const iwp_plan* plan, const float* w, const flo
     if (rc) return rc;
     if (plan->z.tiles == 0) return IWP_OK;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    Table T{plan->dev, plan->z.n_layers, plan->z.tiles, plan->z.stiles, plan->z.pairs, plan->any_k, plan->max_layer_stiles};
+    Table T{plan->dev, plan->z.n_layers, plan->z.tiles, plan->z.stiles, plan->z.pairs, plan->any_k, plan->max_layer_stiles, plan->max_copies};
     const bool small = T.any_k && plan->max_n <= SMALL_MAX_N;
     if (small) {
         rc = launch_small(T.layers, nullptr, T.n_layers, plan->max_n, T.pairs, ws, P, w, leader, W, eps, FULL, false, idx_out,
@@ -700,7 +708,7 @@ int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, fl
     if (rc) return rc;
     if (z.tiles == 0) return IWP_OK;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    Table T{plan->dev, z.n_layers, z.tiles, z.stiles, z.pairs, plan->any_k, plan->max_layer_stiles};
+    Table T{plan->dev, z.n_layers, z.tiles, z.stiles, z.pairs, plan->any_k, plan->max_layer_stiles, plan->max_copies};
     if (T.any_k && plan->max_n <= SMALL_MAX_N) {
         rc = launch_small(T.layers, nullptr, T.n_layers, plan->max_n, T.pairs, ws, P, w, leader, W, eps, FULL, true, idx_out,
                           val_out, thr_out, s);
@@ -756,7 +764,7 @@ int select_threshold_segmented(const iwp_plan* plan, const float* w, const float
     ResidualPtrs R;
     memset(&R, 0, sizeof R);
     R.r[0] = const_cast<float*>(r);
-    Table T{plan->dev, plan->z.n_layers, plan->z.tiles, plan->z.stiles, plan->z.pairs, plan->any_k, plan->max_layer_stiles};
+    Table T{plan->dev, plan->z.n_layers, plan->z.tiles, plan->z.stiles, plan->z.pairs, plan->any_k, plan->max_layer_stiles, plan->max_copies};
     rc = launch_leader_pass(T, ws, P, w, nullptr, 1u, eps, s);
     if (rc) return rc;
     return run_select(T, ws, R, w, nullptr, 1u, eps, STOP_AT_THRESHOLD, false, nullptr, nullptr, thr_out, s);
@@ -777,7 +785,7 @@ int compact_pairs_segmented(const iwp_plan* plan, const float* w, const float* r
     ResidualPtrs R;
     memset(&R, 0, sizeof R);
     R.r[0] = const_cast<float*>(r);
-    Table T{plan->dev, plan->z.n_layers, plan->z.tiles, plan->z.stiles, plan->z.pairs, plan->any_k, plan->max_layer_stiles};
+    Table T{plan->dev, plan->z.n_layers, plan->z.tiles, plan->z.stiles, plan->z.pairs, plan->any_k, plan->max_layer_stiles, plan->max_copies};
     return run_compact_from(T, ws, R, w, eps, thr, idx_out, val_out, s);
 }
 

@@ -247,19 +247,26 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* s
 // Digit pick over a histogram of NB bins (LDS or global): the bin that holds rank
 // k_rem counted from the top bin down, and the rank inside that bin.  All THREADS
 // threads call it; the result is broadcast through `sh` (PICK_WORDS words of LDS).
+// copies: histograms of NB bins one behind the other, added up.
 // Requires sum(hist) >= k_rem >= 1.  Suffix sums inside each wavefront by lane shuffles, then over the
 // wavefronts' totals: three barriers, where a scan over all threads in LDS takes two per doubling.
 constexpr uint32_t PICK_WORDS = 16 + 2;
 template <int NB, int THREADS = BLOCK>
 __device__ __forceinline__ void block_pick(const uint32_t* hist, uint32_t k_rem, uint32_t* sh,
-                                           uint32_t* bin_out, uint32_t* k_rem_out) {
+                                           uint32_t* bin_out, uint32_t* k_rem_out, uint32_t copies = 1) {
     constexpr int PER = NB / THREADS, WAVES = THREADS / WAVE;
     static_assert(WAVES + 2 <= (int)PICK_WORDS, "one word per wavefront, two for the result");
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
     uint32_t h[PER];
     uint32_t local = 0;
 #pragma unroll
-    for (int q = 0; q < PER; ++q) { h[q] = hist[tid * PER + q]; local += h[q]; }
+    for (int q = 0; q < PER; ++q) h[q] = hist[tid * PER + q];
+#pragma unroll 4
+    for (uint32_t c = 1; c < copies; ++c)
+#pragma unroll
+        for (int q = 0; q < PER; ++q) h[q] += hist[c * NB + tid * PER + q];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) local += h[q];
     uint32_t incl = local;                 // this lane's bins and those of the lanes above it
 #pragma unroll
     for (int d = 1; d < WAVE; d <<= 1) {

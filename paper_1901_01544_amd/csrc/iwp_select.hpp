@@ -175,56 +175,35 @@ __global__ __launch_bounds__(INIT_BLOCK, 8) void k_init(uint32_t* __restrict__ w
 }
 
 // ---------------------------------------------------------------------------
-// First digit pick, one workgroup per layer: the bin b1 of the 4096-bin histogram that holds
-// rank k, and whether look 1's copies already cover it.  This pick
-// keeps a launch of its own: its histogram is too large for every tile's workgroup to re-read,
-// and a summary of it would have to be built with atomics on a handful of addresses that all
-// workgroups of look 1 hit (measured: look 1 nearly twice as slow).  A layer whose look 1
-// flushed into several copies has them added up here first.
+// First digit pick: the bin b1 of the 4096-bin histogram that holds rank k, whether look 1's copies already cover it.
+// On tables that the chip holds at one workgroup per tile (PICK_MAX_TILES), with at most two copies of a histogram, every
+// workgroup of look 2 redoes the pick of its layer itself: a launch less (235 k elements 46.4 -> 45.0 us a step, one layer of
+// a million 40.5 -> 39.5 us).  On larger ones that costs more than the launch (25.6 M elements: 18.8 us against
+// 10.5 + 4.8), so one workgroup per layer adds the copies up in a launch of its own.  A summary
+// would have to be built with atomics on a handful of addresses that all
+// workgroups of look 1 hit (measured: look 1 nearly twice as slow).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_first_pick(const DevLayer* __restrict__ layers, uint32_t* __restrict__ hist,
+constexpr uint32_t PICK_MAX_COPIES = 2, PICK_MAX_TILES = 2048;
+
+__device__ __forceinline__ void first_pick(const DevLayer& L, const uint32_t* __restrict__ hist, uint32_t stage_bin,
+                                           uint32_t* sh, uint32_t* b1, uint32_t* k_rem0, bool* prestaged) {
+    block_pick<(int)HIST0>(layer_hist(hist, L, 0), L.k, sh, b1, k_rem0, L.h0_copies);
+    *prestaged = stage_bin != NO_STAGE_BIN && stage_bin <= *b1;
+}
+
+__global__ __launch_bounds__(BLOCK) void k_first_pick(const DevLayer* __restrict__ layers, const uint32_t* __restrict__ hist,
                                                       LayerState* __restrict__ state) {
     __shared__ uint32_t sh[PICK_WORDS];
     const uint32_t j = blockIdx.x;
     const DevLayer L = layers[j];
     if (L.k == 0) return;
-    uint32_t* h0 = layer_hist(hist, L, 0);
-    if (L.h0_copies > 1) {
-        // fold the copies into the first one (this workgroup is the layer's only reader and writer here)
-        constexpr uint32_t PER = HIST0 / BLOCK;                  // 16 consecutive bins per thread
-        constexpr uint32_t Q = PER / 4;
-        uint4 acc[Q];
-#pragma unroll
-        for (uint32_t q = 0; q < Q; ++q) acc[q] = make_uint4(0u, 0u, 0u, 0u);
-        // the copies come in powers of two: two at a time, or four at a time with all loads issued first
-        const uint32_t step = L.h0_copies == 2 ? 2u : 4u;
-        for (uint32_t c0 = 0; c0 < L.h0_copies; c0 += step) {
-            uint4 v[4][Q];
-#pragma unroll
-            for (uint32_t c = 0; c < 4; ++c)
-#pragma unroll
-                for (uint32_t q = 0; q < Q; ++q)
-                    v[c][q] = c < step ? reinterpret_cast<const uint4*>(h0 + (size_t)(c0 + c) * HIST0 + threadIdx.x * PER)[q]
-                                       : make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-            for (uint32_t c = 0; c < 4; ++c)
-#pragma unroll
-                for (uint32_t q = 0; q < Q; ++q) {
-                    acc[q].x += v[c][q].x; acc[q].y += v[c][q].y; acc[q].z += v[c][q].z; acc[q].w += v[c][q].w;
-                }
-        }
-        uint4* mine = reinterpret_cast<uint4*>(h0 + threadIdx.x * PER);
-#pragma unroll
-        for (uint32_t q = 0; q < Q; ++q) mine[q] = acc[q];
-        __syncthreads();                                         // the pick below reads what the others stored
-    }
-    uint32_t bin, k_rem;
-    block_pick<(int)HIST0>(h0, L.k, sh, &bin, &k_rem);
+    uint32_t b1, k_rem0;
+    bool prestaged;
+    first_pick(L, hist, state[j].stage_bin, sh, &b1, &k_rem0, &prestaged);
     if (threadIdx.x == 0) {
-        const uint32_t stage_bin = state[j].stage_bin;
-        state[j].b1 = bin;
-        state[j].k_rem0 = k_rem;
-        state[j].prestaged = (stage_bin != NO_STAGE_BIN && stage_bin <= bin) ? 1u : 0u;
+        state[j].b1 = b1;
+        state[j].k_rem0 = k_rem0;
+        state[j].prestaged = prestaged ? 1u : 0u;
     }
 }
 
@@ -320,14 +299,16 @@ constexpr uint32_t STAGE_GROUP = 16;               // tiles whose slots one unit
 constexpr uint32_t STAGE_MAX_GRID = 32768;         // with at most 2^20 tiles per table: at most 32 tiles per workgroup
 constexpr uint32_t STAGE_TILES_MAX = 64;           // tiles per workgroup, at most (their look-1 counts: one per lane)
 
+template <bool PICK>
 __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __restrict__ w,
                                                  const DevLayer* __restrict__ layers, uint32_t n_layers,
                                                  uint32_t tiles, const uint32_t* __restrict__ leader, uint32_t W,
-                                                 float eps, const LayerState* __restrict__ state,
+                                                 float eps, LayerState* __restrict__ state,
                                                  uint32_t* __restrict__ hist, uint32_t* __restrict__ stage_cnt,
                                                  StageArrays A) {
     __shared__ uint32_t lh[HIST1];
     __shared__ uint32_t slot[STAGE_WORDS];
+    __shared__ uint32_t sh[PICK_WORDS];
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
     // the workgroup's tiles are consecutive (at most 64: the host sizes the grid accordingly); their counts
     // from look 1 are fetched in one go, and a layer's row and state only when the layer changes, so that a
@@ -349,10 +330,20 @@ __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __
                 filled = false;
             }
             L = layers[j];
-            b1 = state[j].b1;
-            shift = state[j].shift;
-            prestaged = state[j].prestaged != 0;
             cur_j = j;
+            if (L.k == 0) continue;
+            shift = state[j].shift;
+            if (PICK) {
+                uint32_t k_rem0;
+                first_pick(L, hist, state[j].stage_bin, sh, &b1, &k_rem0, &prestaged);
+                if (t == L.tile_begin && tid == 0) {       // for the launches that follow
+                    state[j].b1 = b1;
+                    state[j].k_rem0 = k_rem0;
+                }
+            } else {
+                b1 = state[j].b1;
+                prestaged = state[j].prestaged != 0;
+            }
         }
         if (L.k == 0) continue;
         const uint32_t lt = t - L.tile_begin;
