@@ -219,6 +219,62 @@ __device__ __forceinline__ void store_quad(float* __restrict__ base, uint32_t i,
     }
 }
 
+// The 16 elements per lane of the tile that starts at element `base` of a layer of n elements, for the kernel that
+// reads three arrays per tile (look 1).  request_tile() only issues loads, the same whether the tile is full or a layer's
+// ragged last one: the quad that crosses the layer's end is taken from its last four elements instead, and
+// settle_tile() moves what belongs to the lane into place once every array of the tile has been requested, so that one
+// stretch of code serves both forms and a branch per quad does not make the compiler wait for one quad before it asks
+// for the next.  Values past the end are not meant for use; layers of fewer than four elements are read one by one when
+// they are settled.  Against separate code for the two forms, look 1: 364 -> 347 us on a thousand packed tensors of
+// 115.5 M elements, 1106 -> 1085 us on one layer of 400 M.  The two-array kernels gained nothing from it, and lost on
+// layers of a few hundred elements (6.7 -> 8.2 us).
+template <bool NT>
+__device__ __forceinline__ void request_tile(const float* __restrict__ p, uint32_t n, uint32_t base,
+                                             float (&v)[CHUNKS_PER_TILE][4]) {
+    if (n < 4) return;                                       // uniform
+#pragma unroll
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+        const uint32_t i = base + u * CHUNK + threadIdx.x * VEC;
+        if (i < n) {
+            const v4f t = load_v4<NT>(p + min(i, n - 4u));
+            v[u][0] = t.x; v[u][1] = t.y; v[u][2] = t.z; v[u][3] = t.w;
+        }
+    }
+}
+
+__device__ __forceinline__ void settle_tile(const float* __restrict__ p, uint32_t n, uint32_t base,
+                                            float (&v)[CHUNKS_PER_TILE][4]) {
+    if (base + TILE <= n) return;                            // uniform, as is the next
+    if (n < 4) {
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+#pragma unroll
+            for (uint32_t c = 0; c < 4; ++c) v[u][c] = 0.0f;
+        for (uint32_t c = 0; c < n; ++c) {
+            const float x = p[c];
+            if (c == 0) v[0][0] = x; else if (c == 1) v[0][1] = x; else v[0][2] = x;   // meant for lane 0
+        }
+        return;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+        const uint32_t i = base + u * CHUNK + threadIdx.x * VEC;
+        const uint32_t by = i - min(i, n - 4u);              // 1 to 3 on the one lane whose quad crosses the end
+        const float a = v[u][1], b = v[u][2], c = v[u][3];
+        v[u][0] = by == 1u ? a : by == 2u ? b : by == 3u ? c : v[u][0];
+        v[u][1] = by == 1u ? b : by == 2u ? c : v[u][1];
+        v[u][2] = by == 1u ? c : v[u][2];
+    }
+}
+
+// Stores the tile's elements that lie inside the layer.
+template <bool NT>
+__device__ __forceinline__ void store_tile(float* __restrict__ p, uint32_t n, uint32_t base,
+                                           const float (&v)[CHUNKS_PER_TILE][4]) {
+#pragma unroll
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) store_quad<NT>(p, base + u * CHUNK + threadIdx.x * VEC, n, v[u]);
+}
+
 // Inclusive scan across the 64 lanes of a wavefront.
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
     const int lane = threadIdx.x & (WAVE - 1);

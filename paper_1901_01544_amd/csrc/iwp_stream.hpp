@@ -90,53 +90,27 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
     const uint32_t tid = threadIdx.x;
     const uint32_t base = lt * TILE;
     uint32_t key[CHUNKS_PER_TILE][4];
-    float val[CHUNKS_PER_TILE][4];
-    if (base + TILE <= n) {
-        v4f rr[CHUNKS_PER_TILE], gg[CHUNKS_PER_TILE], ww[CHUNKS_PER_TILE];
+    float val[CHUNKS_PER_TILE][4], gv[CHUNKS_PER_TILE][4], wv[CHUNKS_PER_TILE][4];
+    request_tile<true>(rl, n, base, val);
+    if (ACC) request_tile<true>(gl, n, base, gv);
+    request_tile<(KEEP < KEEP_W)>(wl, n, base, wv);
+    settle_tile(rl, n, base, val);
+    if (ACC) settle_tile(gl, n, base, gv);
+    settle_tile(wl, n, base, wv);
+    if (ACC) {
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            rr[u] = load_v4<true>(rl + i);
-            if (ACC) gg[u] = load_v4<true>(gl + i);
-            ww[u] = load_v4<(KEEP < KEEP_W)>(wl + i);
-        }
+        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            if (ACC) {
-                rr[u] = accum(rr[u], gg[u], m);
-                store_v4<(KEEP < KEEP_W_AND_R)>(rl + i, rr[u]);
-            }
-            val[u][0] = rr[u].x; val[u][1] = rr[u].y; val[u][2] = rr[u].z; val[u][3] = rr[u].w;
-            key[u][0] = shifted(score_key(rr[u].x, ww[u].x, eps), C.shift);
-            key[u][1] = shifted(score_key(rr[u].y, ww[u].y, eps), C.shift);
-            key[u][2] = shifted(score_key(rr[u].z, ww[u].z, eps), C.shift);
-            key[u][3] = shifted(score_key(rr[u].w, ww[u].w, eps), C.shift);
-        }
-    } else {
-        // ragged tail of a layer: the same shape, every load of
-        // the tile that lies inside the layer issued before the first use
-        float gv[CHUNKS_PER_TILE][4], wv[CHUNKS_PER_TILE][4];
+            for (int q = 0; q < 4; ++q) val[u][q] = accum(val[u][q], gv[u][q], m);
+        store_tile<(KEEP < KEEP_W_AND_R)>(rl, n, base, val);
+    }
+    const bool full = base + TILE <= n;
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            if (i < n) {
-                load_quad<true>(rl, i, n, val[u]);
-                if (ACC) load_quad<true>(gl, i, n, gv[u]);
-                load_quad<true>(wl, i, n, wv[u], 1.0f);
-            }
-        }
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+        const uint32_t i = base + u * CHUNK + tid * VEC;
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            if (ACC && i < n) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) val[u][q] = accum(val[u][q], gv[u][q], m);
-                store_quad<true>(rl, i, n, val[u]);
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) key[u][q] = (i + q < n) ? shifted(score_key(val[u][q], wv[u][q], eps), C.shift) : NOT_AN_ELEMENT;
-        }
+        for (int q = 0; q < 4; ++q)
+            key[u][q] = (full || i + q < n) ? shifted(score_key(val[u][q], wv[u][q], eps), C.shift) : NOT_AN_ELEMENT;
     }
     // zero scores (zero residuals: a layer's untouched part) are counted in a register and added once per
     // wavefront: a tile of zeros would otherwise be 4096 atomics on one LDS word
