@@ -219,52 +219,42 @@ __device__ __forceinline__ void store_quad(float* __restrict__ base, uint32_t i,
     }
 }
 
-// The 16 elements per lane of the tile that starts at element `base` of a layer of n elements, for the kernel that
-// reads three arrays per tile (look 1).  request_tile() only issues loads, the same whether the tile is full or a layer's
-// ragged last one: the quad that crosses the layer's end is taken from its last four elements instead, and
-// settle_tile() moves what belongs to the lane into place once every array of the tile has been requested, so that one
-// stretch of code serves both forms and a branch per quad does not make the compiler wait for one quad before it asks
-// for the next.  Values past the end are not meant for use; layers of fewer than four elements are read one by one when
-// they are settled.  Against separate code for the two forms, look 1: 364 -> 347 us on a thousand packed tensors of
-// 115.5 M elements, 1106 -> 1085 us on one layer of 400 M.  The two-array kernels gained nothing from it, and lost on
-// layers of a few hundred elements (6.7 -> 8.2 us).
+// The 16 elements per lane of the tile that starts at element `base` of a layer of n elements, in one stretch of code
+// for full and ragged tiles.  request_tile() only issues loads: the whole quads, and the up to three elements behind
+// the layer's last whole quad, on the lane they belong to, into registers of their own; settle_tile() puts those into place
+// once every array of the tile has been requested.  A second branch per quad for the elements behind the last whole one
+// made the compiler wait for one quad before it asked for the next.  Values past the end are not meant for use.
+// Against separate code for the two forms: look 1 364 -> 342 us, followers' pass 1898 -> 1877 us on a thousand packed
+// tensors of 115.5 M elements; with thresholds, tables of 0.3 to 1.2 M elements 39.5 -> 35.5 and 61.3 -> 58.6 us a step.
+struct Rest { float x[3]; };
+__device__ __forceinline__ bool holds_rest(uint32_t n, uint32_t base) {      // does this lane hold those elements?
+    return base + TILE > n && (n & 3u) && (((n & ~3u) - base) & (CHUNK - 1u)) == threadIdx.x * VEC;
+}
 template <bool NT>
 __device__ __forceinline__ void request_tile(const float* __restrict__ p, uint32_t n, uint32_t base,
-                                             float (&v)[CHUNKS_PER_TILE][4]) {
-    if (n < 4) return;                                       // uniform
+                                             float (&v)[CHUNKS_PER_TILE][4], Rest& rest) {
 #pragma unroll
     for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
         const uint32_t i = base + u * CHUNK + threadIdx.x * VEC;
-        if (i < n) {
-            const v4f t = load_v4<NT>(p + min(i, n - 4u));
+        if (i + VEC <= n) {
+            const v4f t = load_v4<NT>(p + i);
             v[u][0] = t.x; v[u][1] = t.y; v[u][2] = t.z; v[u][3] = t.w;
         }
     }
+    if (holds_rest(n, base)) {
+        const uint32_t whole = n & ~3u;
+#pragma unroll
+        for (uint32_t c = 0; c < 3; ++c) rest.x[c] = p[min(whole + c, n - 1u)];
+    }
 }
 
-__device__ __forceinline__ void settle_tile(const float* __restrict__ p, uint32_t n, uint32_t base,
-                                            float (&v)[CHUNKS_PER_TILE][4]) {
-    if (base + TILE <= n) return;                            // uniform, as is the next
-    if (n < 4) {
+__device__ __forceinline__ void settle_tile(uint32_t n, uint32_t base, float (&v)[CHUNKS_PER_TILE][4], const Rest& rest) {
+    if (!holds_rest(n, base)) return;
+    const uint32_t at = ((n & ~3u) - base) / CHUNK;          // which of the lane's quads
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
 #pragma unroll
-            for (uint32_t c = 0; c < 4; ++c) v[u][c] = 0.0f;
-        for (uint32_t c = 0; c < n; ++c) {
-            const float x = p[c];
-            if (c == 0) v[0][0] = x; else if (c == 1) v[0][1] = x; else v[0][2] = x;   // meant for lane 0
-        }
-        return;
-    }
-#pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-        const uint32_t i = base + u * CHUNK + threadIdx.x * VEC;
-        const uint32_t by = i - min(i, n - 4u);              // 1 to 3 on the one lane whose quad crosses the end
-        const float a = v[u][1], b = v[u][2], c = v[u][3];
-        v[u][0] = by == 1u ? a : by == 2u ? b : by == 3u ? c : v[u][0];
-        v[u][1] = by == 1u ? b : by == 2u ? c : v[u][1];
-        v[u][2] = by == 1u ? c : v[u][2];
-    }
+        for (int c = 0; c < 3; ++c) v[u][c] = u == at ? rest.x[c] : v[u][c];
 }
 
 // Stores the tile's elements that lie inside the layer.

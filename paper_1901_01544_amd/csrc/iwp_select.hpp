@@ -247,28 +247,11 @@ __device__ __forceinline__ void scored_tile(const float* __restrict__ rl, const 
     const uint32_t tid = threadIdx.x;
     float wgt[CHUNKS_PER_TILE][4];
     const bool full = base + TILE <= n;
-    if (full) {
-#pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            const v4f a = load_v4<true>(rl + i);
-            const v4f b = load_v4<true>(wl + i);
-            val[u][0] = a.x; val[u][1] = a.y; val[u][2] = a.z; val[u][3] = a.w;
-            wgt[u][0] = b.x; wgt[u][1] = b.y; wgt[u][2] = b.z; wgt[u][3] = b.w;
-        }
-    } else {
-#pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            if (i < n) {
-                load_quad(rl, i, n, val[u]);
-                load_quad(wl, i, n, wgt[u], 1.0f);
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) { val[u][q] = 0.0f; wgt[u][q] = 1.0f; }
-            }
-        }
-    }
+    Rest val_rest, wgt_rest;
+    request_tile<true>(rl, n, base, val, val_rest);
+    request_tile<true>(wl, n, base, wgt, wgt_rest);
+    settle_tile(n, base, val, val_rest);
+    settle_tile(n, base, wgt, wgt_rest);
 #pragma unroll
     for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
         const uint32_t i = base + u * CHUNK + tid * VEC;

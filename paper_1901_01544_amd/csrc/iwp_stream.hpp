@@ -33,42 +33,17 @@ struct LeadCtx {
 // One tile of a plain worker: r <- m * r + g, streaming (non-temporal) accesses.
 __device__ __forceinline__ void stream_tile(const float* __restrict__ gl, float* __restrict__ rl, uint32_t n,
                                             uint32_t base, float m) {
-    const uint32_t tid = threadIdx.x;
-    if (base + TILE <= n) {
-        v4f rr[CHUNKS_PER_TILE], gg[CHUNKS_PER_TILE];
+    float rv[CHUNKS_PER_TILE][4], gv[CHUNKS_PER_TILE][4];
+    Rest rv_rest, gv_rest;
+    request_tile<true>(rl, n, base, rv, rv_rest);
+    request_tile<true>(gl, n, base, gv, gv_rest);
+    settle_tile(n, base, rv, rv_rest);
+    settle_tile(n, base, gv, gv_rest);
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            rr[u] = load_v4<true>(rl + i);
-            gg[u] = load_v4<true>(gl + i);
-        }
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            store_v4<true>(rl + i, accum(rr[u], gg[u], m));
-        }
-    } else {
-        // ragged tail of a layer: the same shape, every load of
-        // the tile that lies inside the layer issued before the first use
-        float rv[CHUNKS_PER_TILE][4], gv[CHUNKS_PER_TILE][4];
-#pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            if (i < n) {
-                load_quad<true>(rl, i, n, rv[u]);
-                load_quad<true>(gl, i, n, gv[u]);
-            }
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            if (i < n) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) rv[u][q] = accum(rv[u][q], gv[u][q], m);
-                store_quad<true>(rl, i, n, rv[u]);
-            }
-        }
-    }
+        for (int q = 0; q < 4; ++q) rv[u][q] = accum(rv[u][q], gv[u][q], m);
+    store_tile<true>(rl, n, base, rv);
 }
 
 // One tile of a layer's leader: accumulate (ACC), score every element, histogram
@@ -91,12 +66,13 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
     const uint32_t base = lt * TILE;
     uint32_t key[CHUNKS_PER_TILE][4];
     float val[CHUNKS_PER_TILE][4], gv[CHUNKS_PER_TILE][4], wv[CHUNKS_PER_TILE][4];
-    request_tile<true>(rl, n, base, val);
-    if (ACC) request_tile<true>(gl, n, base, gv);
-    request_tile<(KEEP < KEEP_W)>(wl, n, base, wv);
-    settle_tile(rl, n, base, val);
-    if (ACC) settle_tile(gl, n, base, gv);
-    settle_tile(wl, n, base, wv);
+    Rest val_rest, gv_rest, wv_rest;
+    request_tile<true>(rl, n, base, val, val_rest);
+    if (ACC) request_tile<true>(gl, n, base, gv, gv_rest);
+    request_tile<(KEEP < KEEP_W)>(wl, n, base, wv, wv_rest);
+    settle_tile(n, base, val, val_rest);
+    if (ACC) settle_tile(n, base, gv, gv_rest);
+    settle_tile(n, base, wv, wv_rest);
     if (ACC) {
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
@@ -260,28 +236,11 @@ __global__ __launch_bounds__(BLOCK) void k_follow_gather(WorkerPtrs P, WorkerLis
     float* go = gathered + (size_t)p * K + L.out_offset + lo;
     const uint32_t first = (uint32_t)L.offset + base;           // flat position of the tile's first element
     const float* gl = gp + L.offset;
-    const bool full = base + TILE <= L.n;
     // the tile's loads go out first; the bitmap of sent positions is built while they are in flight
-    float rv[CHUNKS_PER_TILE][4], gv[CHUNKS_PER_TILE][4];      // one set of registers for both forms of the tile
-    if (full) {
-#pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            const v4f a = load_v4<true>(rl + i);
-            const v4f b = load_v4<true>(gl + i);
-            rv[u][0] = a.x; rv[u][1] = a.y; rv[u][2] = a.z; rv[u][3] = a.w;
-            gv[u][0] = b.x; gv[u][1] = b.y; gv[u][2] = b.z; gv[u][3] = b.w;
-        }
-    } else {
-#pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            if (i < L.n) {
-                load_quad<true>(rl, i, L.n, rv[u]);
-                load_quad<true>(gl, i, L.n, gv[u]);
-            }
-        }
-    }
+    float rv[CHUNKS_PER_TILE][4], gv[CHUNKS_PER_TILE][4];
+    Rest rv_rest, gv_rest;
+    request_tile<true>(rl, L.n, base, rv, rv_rest);
+    request_tile<true>(gl, L.n, base, gv, gv_rest);
     if (cnt) {                                                   // uniform
         if (tid < TILE_WORDS) map[tid] = 0u;
         __syncthreads();
@@ -292,40 +251,22 @@ __global__ __launch_bounds__(BLOCK) void k_follow_gather(WorkerPtrs P, WorkerLis
         __syncthreads();
         bitmap_prefix(map, pre, slot);
     }
-    if (full) {
+    settle_tile(L.n, base, rv, rv_rest);
+    settle_tile(L.n, base, gv, gv_rest);
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t loc = u * CHUNK + tid * VEC;
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+        const uint32_t loc = u * CHUNK + tid * VEC;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) rv[u][q] = accum(rv[u][q], gv[u][q], P.momentum);
-            const uint32_t nib = cnt ? (map[loc >> 5] >> (loc & 31u)) & 0xFu : 0u;
-            if (nib) {
-                uint32_t rank = bitmap_rank(map, pre, loc);
+        for (int q = 0; q < 4; ++q) rv[u][q] = accum(rv[u][q], gv[u][q], P.momentum);
+        const uint32_t nib = cnt ? (map[loc >> 5] >> (loc & 31u)) & 0xFu : 0u;      // no bits past the layer's end
+        if (nib) {
+            uint32_t rank = bitmap_rank(map, pre, loc);
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if ((nib >> q) & 1u) { go[rank++] = rv[u][q]; rv[u][q] = 0.0f; }
-            }
-            v4f out; out.x = rv[u][0]; out.y = rv[u][1]; out.z = rv[u][2]; out.w = rv[u][3];
-            store_v4<true>(rl + base + loc, out);
-        }
-    } else {
-        // ragged tail of a layer (loaded above)
-#pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t loc = u * CHUNK + tid * VEC;
-            const uint32_t i = base + loc;
-            if (i < L.n) {
-                const uint32_t nib = cnt ? (map[loc >> 5] >> (loc & 31u)) & 0xFu : 0u;
-                uint32_t rank = nib ? bitmap_rank(map, pre, loc) : 0u;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    rv[u][q] = accum(rv[u][q], gv[u][q], P.momentum);
-                    if ((nib >> q) & 1u) { go[rank++] = rv[u][q]; rv[u][q] = 0.0f; }
-                }
-                store_quad<true>(rl, i, L.n, rv[u]);
-            }
+            for (int q = 0; q < 4; ++q)
+                if ((nib >> q) & 1u) { go[rank++] = rv[u][q]; rv[u][q] = 0.0f; }
         }
     }
+    store_tile<true>(rl, L.n, base, rv);
 }
 
 }  // namespace iwp

@@ -66,55 +66,25 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 }
 
 // One tile of a chosen node in registers: residual (after adding the gradient and storing
-// it back when gp is set) and weights, 16 values per lane; positions past the layer's end
-// read as r = 0, w = 1.
+// it back when gp is set) and weights, 16 values per lane; positions past the layer's end hold
+// values that are not meant for use.
 __device__ __forceinline__ void chosen_tile(const float* gp, float* rl, const float* gl, const float* wl, float m,
                                             uint32_t n, uint32_t base, uint32_t tid, float (&rv)[CHUNKS_PER_TILE][4],
                                             float (&wv)[CHUNKS_PER_TILE][4]) {
-    if (base + TILE <= n) {
-        v4f rr[CHUNKS_PER_TILE], gg[CHUNKS_PER_TILE], ww[CHUNKS_PER_TILE];
+    float gv[CHUNKS_PER_TILE][4];
+    Rest rv_rest, gv_rest, wv_rest;
+    request_tile<true>(rl, n, base, rv, rv_rest);
+    if (gp) request_tile<true>(gl, n, base, gv, gv_rest);
+    request_tile<true>(wl, n, base, wv, wv_rest);
+    settle_tile(n, base, rv, rv_rest);
+    settle_tile(n, base, wv, wv_rest);
+    if (gp) {
+        settle_tile(n, base, gv, gv_rest);
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            rr[u] = load_v4<true>(rl + i);
-            if (gp) gg[u] = load_v4<true>(gl + i);
-            ww[u] = load_v4<true>(wl + i);
-        }
+        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            if (gp) {
-                rr[u] = accum(rr[u], gg[u], m);
-                store_v4<true>(rl + i, rr[u]);
-            }
-            rv[u][0] = rr[u].x; rv[u][1] = rr[u].y; rv[u][2] = rr[u].z; rv[u][3] = rr[u].w;
-            wv[u][0] = ww[u].x; wv[u][1] = ww[u].y; wv[u][2] = ww[u].z; wv[u][3] = ww[u].w;
-        }
-    } else {
-        // ragged tail: the same shape, every load inside the layer issued before the first use
-        float gv[CHUNKS_PER_TILE][4];
-#pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) { rv[u][c] = 0.0f; wv[u][c] = 1.0f; }
-            if (i < n) {
-                load_quad<true>(rl, i, n, rv[u]);
-                if (gp) load_quad<true>(gl, i, n, gv[u]);
-                load_quad<true>(wl, i, n, wv[u], 1.0f);
-            }
-        }
-        if (gp) {
-#pragma unroll
-            for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-                const uint32_t i = base + u * CHUNK + tid * VEC;
-                if (i < n) {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) rv[u][c] = accum(rv[u][c], gv[u][c], m);
-                    store_quad<true>(rl, i, n, rv[u]);
-                }
-            }
-        }
+            for (int c = 0; c < 4; ++c) rv[u][c] = accum(rv[u][c], gv[u][c], m);
+        store_tile<true>(rl, n, base, rv);
     }
 }
 
@@ -417,27 +387,10 @@ __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLa
     const uint32_t base = lt * TILE;
     float* rl = P.r[p] + L.offset;
     const float* gl = gp + L.offset;
-    const bool full = base + TILE <= L.n;
-    float rv[CHUNKS_PER_TILE][4], gv[CHUNKS_PER_TILE][4];      // one set of registers for both forms of the tile
-    if (full) {
-#pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            const v4f a = load_v4<true>(rl + i);
-            const v4f b = load_v4<true>(gl + i);
-            rv[u][0] = a.x; rv[u][1] = a.y; rv[u][2] = a.z; rv[u][3] = a.w;
-            gv[u][0] = b.x; gv[u][1] = b.y; gv[u][2] = b.z; gv[u][3] = b.w;
-        }
-    } else {
-#pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            if (i < L.n) {
-                load_quad<true>(rl, i, L.n, rv[u]);
-                load_quad<true>(gl, i, L.n, gv[u]);
-            }
-        }
-    }
+    float rv[CHUNKS_PER_TILE][4], gv[CHUNKS_PER_TILE][4];
+    Rest rv_rest, gv_rest;
+    request_tile<true>(rl, L.n, base, rv, rv_rest);
+    request_tile<true>(gl, L.n, base, gv, gv_rest);
     const bool exchange = !overflowed(count_out, n_layers);
     const uint32_t nwords = (L.n + 31) / 32;
     if (tid < TILE_WORDS) {
@@ -449,39 +402,22 @@ __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLa
     const uint64_t row = (uint64_t)lay_out[j] + tile_out[t];
     float* go = gathered + (size_t)p * max_pairs + min(row, (uint64_t)max_pairs);
     const uint32_t room = (uint32_t)((uint64_t)max_pairs - min(row, (uint64_t)max_pairs));
-    if (full) {
+    settle_tile(L.n, base, rv, rv_rest);
+    settle_tile(L.n, base, gv, gv_rest);
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t loc = u * CHUNK + tid * VEC;
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+        const uint32_t loc = u * CHUNK + tid * VEC;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) rv[u][q] = accum(rv[u][q], gv[u][q], P.momentum);
-            const uint32_t nib = (map[loc >> 5] >> (loc & 31u)) & 0xFu;
-            if (nib) {
-                uint32_t rank = bitmap_rank(map, pre, loc);
+        for (int q = 0; q < 4; ++q) rv[u][q] = accum(rv[u][q], gv[u][q], P.momentum);
+        const uint32_t nib = (map[loc >> 5] >> (loc & 31u)) & 0xFu;                // no bits past the layer's end
+        if (nib) {
+            uint32_t rank = bitmap_rank(map, pre, loc);
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if ((nib >> q) & 1u) { if (rank < room) go[rank] = rv[u][q]; ++rank; rv[u][q] = 0.0f; }
-            }
-            v4f out; out.x = rv[u][0]; out.y = rv[u][1]; out.z = rv[u][2]; out.w = rv[u][3];
-            store_v4<true>(rl + base + loc, out);
-        }
-    } else {
-#pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            const uint32_t loc = u * CHUNK + tid * VEC;
-            const uint32_t i = base + loc;
-            if (i < L.n) {
-                const uint32_t nib = (map[loc >> 5] >> (loc & 31u)) & 0xFu;
-                uint32_t rank = nib ? bitmap_rank(map, pre, loc) : 0u;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    rv[u][q] = accum(rv[u][q], gv[u][q], P.momentum);
-                    if ((nib >> q) & 1u) { if (rank < room) go[rank] = rv[u][q]; ++rank; rv[u][q] = 0.0f; }
-                }
-                store_quad<true>(rl, i, L.n, rv[u]);
-            }
+            for (int q = 0; q < 4; ++q)
+                if ((nib >> q) & 1u) { if (rank < room) go[rank] = rv[u][q]; ++rank; rv[u][q] = 0.0f; }
         }
     }
+    store_tile<true>(rl, L.n, base, rv);
 }
 
 // ---------------------------------------------------------------------------
