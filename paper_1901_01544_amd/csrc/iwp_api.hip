@@ -456,9 +456,6 @@ int compact_pairs(const float* w, const float* r, uint32_t n, float eps, const i
 
 // ----------------------------------------------------------------- exchange
 
-// Do the lines that k pairs touch in W buffers exceed the memory-side cache (see iwp_exchange.hpp)?
-static bool scatter_exceeds_cache(uint32_t k, uint32_t W) { return (uint64_t)k * W * SCATTER_LINE > SCATTER_CACHE_BYTES; }
-
 int gather_sum_at_indices(const float* const* residuals, uint32_t W, const uint32_t* idx, uint32_t k,
                           float* sum_out, void* hip_stream) {
     if (W == 0 || W > IWP_MAX_WORKERS || !residuals) return IWP_EINVAL;
@@ -473,9 +470,7 @@ int gather_sum_at_indices(const float* const* residuals, uint32_t W, const uint3
         R.r[p] = const_cast<float*>(residuals[p]);
     }
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    const uint32_t grid = (k + BLOCK - 1) / BLOCK;
-    if (scatter_exceeds_cache(k, W)) IWP_LAUNCH("k_gather_sum", k_gather_sum<true>, grid, s, R, W, idx, k, sum_out);
-    else IWP_LAUNCH("k_gather_sum", k_gather_sum<false>, grid, s, R, W, idx, k, sum_out);
+    IWP_LAUNCH("k_gather_sum", k_gather_sum, (k + BLOCK - 1) / BLOCK, s, R, W, idx, k, sum_out);
     return IWP_OK;
 }
 
@@ -493,9 +488,7 @@ int apply_sparse_update(float* w, const uint32_t* idx, const float* sum, uint32_
         R.r[p] = residuals_to_clear[p];
     }
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    const uint32_t grid = (k + BLOCK - 1) / BLOCK;
-    if (scatter_exceeds_cache(k, W)) IWP_LAUNCH("k_apply_update", k_apply_update<true>, grid, s, w, idx, sum, k, scale, R, W);
-    else IWP_LAUNCH("k_apply_update", k_apply_update<false>, grid, s, w, idx, sum, k, scale, R, W);
+    IWP_LAUNCH("k_apply_update", k_apply_update, (k + BLOCK - 1) / BLOCK, s, w, idx, sum, k, scale, R, W);
     return IWP_OK;
 }
 

@@ -186,14 +186,6 @@ __device__ __forceinline__ void store_v4(float* p, v4f v) {
     else *reinterpret_cast<v4f_any*>(p) = v;
 }
 
-template <bool NT>
-__device__ __forceinline__ float load_f(const float* p) { return NT ? __builtin_nontemporal_load(p) : *p; }
-template <bool NT>
-__device__ __forceinline__ void store_f(float* p, float v) {
-    if (NT) __builtin_nontemporal_store(v, p);
-    else *p = v;
-}
-
 // Four consecutive elements starting at element i of a layer of n elements: one 128-bit load, except at the layer's
 // end.  Lanes past the end read nothing and get `fill`.  NT: streaming (non-temporal) access for whole quads.
 template <bool NT = false>

@@ -8,26 +8,24 @@
 
 namespace iwp {
 
-// Scattered 4-byte accesses, one 128-byte line each: bound by lines moved (the sums read 955 k pairs of eight workers
-// at 5.9 TB/s counted in lines) and, for the clears, by partial writes to memory (about 22 G/s).  More loads in flight
-// per lane, more pairs per lane or one worker per workgroup change neither.  NT: where the workers' lines do not fit
-// the 256 MB memory-side cache anyway, non-temporal accesses keep them from pushing each other's dirty lines out
-// (955 k pairs, eight workers: sum and update 578 -> 546 us together); where they fit, the update finds the lines that
-// the sum has read, and non-temporal accesses lose (118 k pairs, seven workers: 32 -> 50 us).
-constexpr uint64_t SCATTER_LINE = 128, SCATTER_CACHE_BYTES = 256ull << 20;
-
-template <bool NT>
+// Scattered 4-byte accesses, one 128-byte line each: bound by lines moved (955 k pairs of 61 M elements, eight workers:
+// the sums at 5.9 TB/s counted in lines) and, for the clears, by partial writes to memory (about 22 G/s).  More loads in
+// flight per lane, more pairs per lane or one worker per workgroup change neither.  Ordinary accesses: with a new index
+// set and freshly written residuals in every pass the clears find the lines that the sum has just read, and
+// non-temporal ones miss them.  Sum and update together, ordinary against non-temporal, eight workers, one pair in 64:
+// 300 k pairs 147 / 181 us, 600 k 336 / 360, 955 k 532 / 557; after compress_segmented 410 / 461 us (61 M elements)
+// and 168 / 203 us (25.6 M).  Non-temporal accesses win where pairs lie closer than about one in 28 and the lines exceed
+// 1 GB (2 M pairs of one in 20: 832 / 732 us), a density that these calls cannot know from their arguments.
 __global__ __launch_bounds__(BLOCK) void k_gather_sum(ResidualPtrs R, uint32_t W, const uint32_t* __restrict__ idx,
                                                       uint32_t k, float* __restrict__ sum_out) {
     const uint32_t j = blockIdx.x * BLOCK + threadIdx.x;
     if (j >= k) return;
     const uint32_t i = idx[j];
-    float acc = load_f<NT>(R.r[0] + i);          // the fold starts from worker 0's value, not from 0
-    for (uint32_t p = 1; p < W; ++p) acc = acc + load_f<NT>(R.r[p] + i);
+    float acc = R.r[0][i];                       // the fold starts from worker 0's value, not from 0
+    for (uint32_t p = 1; p < W; ++p) acc = acc + R.r[p][i];
     sum_out[j] = acc;
 }
 
-template <bool NT>
 __global__ __launch_bounds__(BLOCK) void k_apply_update(float* __restrict__ w, const uint32_t* __restrict__ idx,
                                                         const float* __restrict__ sum, uint32_t k, float scale,
                                                         ResidualPtrs R, uint32_t W) {
@@ -36,7 +34,7 @@ __global__ __launch_bounds__(BLOCK) void k_apply_update(float* __restrict__ w, c
     const uint32_t i = idx[j];
     const float t = scale * sum[j];              // rounded product ...
     w[i] = w[i] + t;                             // ... then rounded sum (contraction is off)
-    for (uint32_t p = 0; p < W; ++p) store_f<NT>(R.r[p] + i, 0.0f);
+    for (uint32_t p = 0; p < W; ++p) R.r[p][i] = 0.0f;
 }
 
 // Whole-step route: the workers that streamed (and each layer's leader) left their

@@ -1,5 +1,8 @@
-"""GPU parity of the two exchange calls on both sides of the line at which they switch to non-temporal accesses (pairs x
-workers x 128 bytes = 256 MiB), and at the smallest calls: sums, weights and cleared residuals against numpy, bit for bit."""
+"""GPU parity of the two exchange calls where the lines they touch (pairs x workers x 128 bytes) just fit the 256 MiB
+memory-side cache, where they just exceed it, and at the smallest calls: sums, weights and cleared residuals against
+numpy, bit for bit.  And their speed beyond the cache, on index sets and residuals that no call has touched before."""
+import statistics
+
 import numpy as np
 import pytest
 
@@ -34,3 +37,38 @@ def test_exchange_on_both_sides_of_the_cache_line(gpu_lib, k, W):
     for p in range(W):
         r[p][idx] = 0.0
         assert np.array_equal(bits(rd[p].cpu().numpy()), bits(r[p])), "residual %d" % p
+
+
+def test_clears_beyond_the_cache_on_untouched_inputs(gpu_lib):
+    """300 k pairs in eight residuals of 20 M elements (293 MiB of lines), a new index set and rewritten residuals in every
+    pass, as in training: summed and updated in one go, the updates take no longer than in two halves, whose lines fit the
+    cache (1.5 times as long at most: 0.95 measured, 2.1 where the larger call misses the lines that the sum has read)."""
+    import torch
+    iwp, dev = gpu_lib, "cuda:0"
+    k, n, W = 300_000, 20_000_000, 8
+    step = n // k
+    gen = torch.Generator(device=dev).manual_seed(3)
+    r = [torch.randn(n, device=dev, generator=gen) for _ in range(W)]
+    g = torch.randn(n, device=dev, generator=gen)
+    w = torch.randn(n, device=dev, generator=gen)
+    total = torch.empty(k, device=dev)
+    took = {1: [], 2: []}
+    for i in range(16):
+        parts = 1 + i % 2
+        idx = (torch.arange(k, device=dev) * step + torch.randint(0, step, (k,), device=dev, generator=gen)).to(torch.int32)
+        for x in r:
+            x.add_(g)
+        start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        cut = [slice(q * k // parts, (q + 1) * k // parts) for q in range(parts)]
+        for part in cut:
+            iwp.gather_sum_at_indices(r, idx[part], k // parts, total[part])
+        start.record()
+        for part in cut:
+            iwp.apply_sparse_update(w, idx[part], total[part], k // parts, -1e-3, r)
+        stop.record()
+        stop.synchronize()
+        if i >= 2:
+            took[parts].append(start.elapsed_time(stop))
+    one, two = (statistics.median(took[p]) for p in (1, 2))
+    print("one update %.1f us, two halves %.1f us" % (one * 1e3, two * 1e3))
+    assert one < 1.5 * two
