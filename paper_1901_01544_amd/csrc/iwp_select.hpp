@@ -279,7 +279,9 @@ __device__ __forceinline__ void scored_tile(const float* __restrict__ rl, const 
 //    slot holds is marked RAW), those inside b1 go into the histogram.
 // ---------------------------------------------------------------------------
 constexpr uint32_t STAGE_GROUP = 16;               // tiles whose slots one unit histograms
-constexpr uint32_t STAGE_MAX_GRID = 32768;         // with at most 2^20 tiles per table: at most 32 tiles per workgroup
+constexpr uint32_t STAGE_LARGE_TABLE = 32768;      // tiles from which the grid is what the chip holds at once ...
+constexpr uint32_t STAGE_RESIDENT = 1280;          // ... five workgroups per compute unit
+constexpr uint32_t STAGE_MAX_GRID = 32768;         // at most this many workgroups, unless that takes more than 64 tiles each
 constexpr uint32_t STAGE_TILES_MAX = 64;           // tiles per workgroup, at most (their look-1 counts: one per lane)
 
 template <bool PICK>
