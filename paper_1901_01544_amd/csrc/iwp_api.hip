@@ -300,7 +300,7 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
         IWP_LAUNCH("k_final_pick", k_final_pick, T.n_layers, s, T.layers, ws.hist, ws.state, thr_out);
         return IWP_OK;
     }
-    IWP_LAUNCH("k_count", k_count<false>, stile_grid, s, R, w, T.layers, T.n_layers, T.stiles, leader, W, eps, ws.state,
+    IWP_LAUNCH("k_count", k_count, stile_grid, s, R, w, T.layers, T.n_layers, T.stiles, leader, W, eps, ws.state,
                ws.hist, thr_out, ws.stage, ws.A, ws.tile_counts, ws.stile_counts);
     if (fused) return launch_write<true>(T, ws, R, w, leader, W, eps, idx_out, val_out, s);
     return launch_write<false>(T, ws, R, w, leader, W, eps, idx_out, val_out, s);
@@ -335,9 +335,9 @@ int run_compact_from(const Table& T, const Workspace& ws, const ResidualPtrs& R,
                      const iwp_threshold* thr, uint32_t* idx_out, float* val_out, hipStream_t s) {
     if (!T.any_k || T.tiles == 0) return IWP_OK;
     IWP_LAUNCH("k_stage_records", k_stage_records, T.tiles, s, R.r[0], w, T.layers, T.n_layers, thr, eps, ws.state, ws.stage,
-               ws.A);
-    IWP_LAUNCH("k_count", k_count<true>, std::min<uint32_t>(T.stiles, STILE_MAX_GRID), s, R, w, T.layers, T.n_layers,
-               T.stiles, nullptr, 1u, eps, ws.state, ws.hist, nullptr, ws.stage, ws.A, ws.tile_counts, ws.stile_counts);
+               ws.A, ws.tile_counts);
+    IWP_LAUNCH("k_fold_counts", k_fold_counts, (T.stiles + BLOCK - 1) / BLOCK, s, T.layers, T.n_layers, T.stiles,
+               ws.tile_counts, ws.stile_counts);
     return launch_write<false>(T, ws, R, w, nullptr, 1u, eps, idx_out, val_out, s);
 }
 

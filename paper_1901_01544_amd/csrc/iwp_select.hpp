@@ -537,18 +537,25 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
 }
 
 // ---------------------------------------------------------------------------
-// Threshold records given by the caller (compact_pairs): one pass over the layer that copies the elements at or above the
-// threshold into the tiles' slots, one workgroup per tile as in look 1; the ordered split then works on the slots, as
-// after a selection.  A layer's first workgroup leaves the record in its selection state.
+// Threshold records given by the caller (compact_pairs): one pass over the layer that counts, per tile, the elements above
+// the threshold and those that tie with it, and copies both into the tile's slot, one workgroup per tile as in look 1;
+// k_fold_counts sums the counts up, and the ordered split works on the slots, as after a selection.  A layer's first
+// workgroup leaves the record in its selection state.
 // Bound by reading r and w once.  Counting and writing from r and w directly read them twice, and the counts with one
-// dword per lane and access: 73 + 44 us on a 25.6 M-element table, now 34 us here and 5 + 6 us there.
+// dword per lane and access: 126 us for a table of 25 M elements at one pair in 64, now 48 us.
+// A tile is marked RAW, to be read again by the split, where copies do not pay: its elements overflow the slot, the
+// threshold is zero (everything is at or above it), or the layer keeps half of its elements or more, where a copy and its
+// reading back move 24 bytes per pair against 8 per element read again.  One layer of 25 M elements, copies / read again:
+// keep 0.4 125 / 112 us, 0.5 149 / 118, 0.999 254 / 163; of 1 M elements 24 / 39, 27 / 37, 40 / 38.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(BLOCK) void k_stage_records(const float* __restrict__ r, const float* __restrict__ w,
                                                          const DevLayer* __restrict__ layers, uint32_t n_layers,
                                                          const iwp_threshold* __restrict__ thr, float eps,
                                                          LayerState* __restrict__ state,
-                                                         uint32_t* __restrict__ stage_cnt, StageArrays A) {
+                                                         uint32_t* __restrict__ stage_cnt, StageArrays A,
+                                                         uint2* __restrict__ tile_counts) {
     __shared__ uint32_t slot[STAGE_WORDS];
+    __shared__ uint32_t part[BLOCK / WAVE];
     const uint32_t t = blockIdx.x;
     const uint32_t j = find_layer<false>(layers, n_layers, t);
     const DevLayer L = layers[j];
@@ -565,18 +572,57 @@ __global__ __launch_bounds__(BLOCK) void k_stage_records(const float* __restrict
     uint32_t key[CHUNKS_PER_TILE][4];
     float val[CHUNKS_PER_TILE][4];
     scored_tile(r + L.offset, w + L.offset, L.n, lt * TILE, eps, 0u, key, val);
-    const uint32_t cnt = stage_tile(key, val, lt * TILE, from, L.slot_cap, L.slot_begin + (uint64_t)lt * L.slot_cap, A, slot);
-    if (threadIdx.x == 0) stage_cnt[t] = cnt;
+    uint32_t c = 0;                                        // above the threshold; high half: tying with it
+#pragma unroll
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            c += key[u][q] == NOT_AN_ELEMENT ? 0u : key[u][q] > from ? 1u : key[u][q] == from ? 0x10000u : 0u;
+#pragma unroll
+    for (int d = WAVE / 2; d > 0; d >>= 1) c += __shfl_xor(c, d, WAVE);
+    if ((threadIdx.x & (WAVE - 1)) == 0) part[threadIdx.x >> 6] = c;
+    uint32_t cnt = RAW_TILE;
+    if (from != 0u && L.k < L.n - L.k)                     // uniform; either way a barrier before the sum below
+        cnt = stage_tile(key, val, lt * TILE, from, L.slot_cap, L.slot_begin + (uint64_t)lt * L.slot_cap, A, slot);
+    else
+        __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t sum = part[0] + part[1] + part[2] + part[3];
+        stage_cnt[t] = cnt;
+        tile_counts[t] = make_uint2(sum & 0xffffu, sum >> 16);
+    }
+}
+
+// The tiles' counts that k_stage_records left -> what k_count leaves: each tile's exclusive prefix inside its super-tile and
+// the super-tile's totals.  One super-tile per lane.
+__global__ __launch_bounds__(BLOCK) void k_fold_counts(const DevLayer* __restrict__ layers, uint32_t n_layers, uint32_t stiles,
+                                                       uint2* __restrict__ tile_counts, uint2* __restrict__ stile_counts) {
+    const uint32_t s = blockIdx.x * BLOCK + threadIdx.x;
+    if (s >= stiles) return;
+    const DevLayer& L = layers[find_layer<true>(layers, n_layers, s)];
+    if (L.k == 0) return;
+    const uint32_t lt0 = (s - L.stile_begin) * GROUP;
+    const uint32_t nt = min(GROUP, (L.n + TILE - 1) / TILE - lt0);
+    uint2* tc = tile_counts + L.tile_begin + lt0;
+    uint2 v[GROUP];
+#pragma unroll
+    for (uint32_t q = 0; q < GROUP; ++q) v[q] = q < nt ? tc[q] : make_uint2(0u, 0u);
+    uint32_t above = 0, ties = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < GROUP; ++q) {
+        if (q < nt) tc[q] = make_uint2(above, ties);
+        above += v[q].x;
+        ties += v[q].y;
+    }
+    stile_counts[s] = make_uint2(above, ties);
 }
 
 // ---------------------------------------------------------------------------
 // Ordered split, part 1: per tile, how many elements lie above the threshold and
 // how many tie with it.  One workgroup per super-tile; writes each tile's exclusive
 // prefix inside the super-tile and the super-tile's totals.  The threshold is the
-// prologue's third pick (recorded, with thr_out, by the layer's first workgroup), or with
-// FROM_RECORDS the caller's record (compact_pairs).
+// prologue's third pick (recorded, with thr_out, by the layer's first workgroup).
 // ---------------------------------------------------------------------------
-template <bool FROM_RECORDS>
 __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __restrict__ w,
                                                  const DevLayer* __restrict__ layers, uint32_t n_layers, uint32_t stiles,
                                                  const uint32_t* __restrict__ leader, uint32_t W, float eps,
@@ -599,21 +645,17 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
             cur_j = j;
             if (L.k == 0) continue;
             shift = state[j].shift;
-            if (FROM_RECORDS) {
-                thr = state[j].thr;
-            } else {
-                // third pick, redone by every workgroup of the layer: the exact k-th largest key
-                uint32_t bin2, k_rem2;
-                block_pick<(int)HIST2>(layer_hist(hist, L, 2), state[j].k_rem1, sh, &bin2, &k_rem2);
-                thr = (state[j].p22 << digit_bits(2)) | bin2;
-                if (s == L.stile_begin && tid == 0) {
-                    state[j].thr = thr;
-                    state[j].n_eq_take = k_rem2;
-                    if (thr_out) {
-                        iwp_threshold th;
-                        th.key = unshifted(thr, state[j].shift); th.n_gt = L.k - k_rem2; th.n_eq_take = k_rem2;
-                        thr_out[j] = th;
-                    }
+            // third pick, redone by every workgroup of the layer: the exact k-th largest key
+            uint32_t bin2, k_rem2;
+            block_pick<(int)HIST2>(layer_hist(hist, L, 2), state[j].k_rem1, sh, &bin2, &k_rem2);
+            thr = (state[j].p22 << digit_bits(2)) | bin2;
+            if (s == L.stile_begin && tid == 0) {
+                state[j].thr = thr;
+                state[j].n_eq_take = k_rem2;
+                if (thr_out) {
+                    iwp_threshold th;
+                    th.key = unshifted(thr, state[j].shift); th.n_gt = L.k - k_rem2; th.n_eq_take = k_rem2;
+                    thr_out[j] = th;
                 }
             }
         }

@@ -1,6 +1,9 @@
 """GPU parity of compact_pairs, which copies what is at or above the record's threshold into per-tile slots in one pass:
 sizes around the tile and super-tile edges, ties cut by the record's quota, tiles whose kept elements overflow their slot
-(they are read again by the ordered split), every element kept, infinite and zero thresholds."""
+(they are read again by the ordered split), every element kept, infinite and zero thresholds; half of a layer kept, from
+where on nothing is copied; records that do not belong to the layer.  And the time where copies do not pay."""
+import statistics
+
 import numpy as np
 import pytest
 
@@ -53,3 +56,76 @@ def test_ties_overflowing_slots_and_extremes(gpu_lib):
     r[::5] = np.float32(3.0e38)
     w[::5] = 0.0                                             # 3e38 / 1e-8: infinite scores
     _select_and_compact(gpu_lib, w, r, n // 10, "infinite threshold")
+
+
+@pytest.mark.parametrize("n", [2, 3, 4096, 4097, 70_003])
+def test_half_of_the_layer(gpu_lib, n):
+    rng = np.random.default_rng(n)
+    w = (rng.standard_normal(n) * 0.05).astype(np.float32)
+    r = (rng.standard_t(3, n) * 1e-3).astype(np.float32)
+    for k in {max(1, n // 2 - 1), n // 2, (n + 1) // 2, n // 2 + 1}:
+        _select_and_compact(gpu_lib, w, r, k, "n=%d k=%d" % (n, k))
+
+
+@pytest.mark.parametrize("layers", [1, 3])
+def test_records_that_do_not_belong_to_the_layer(gpu_lib, layers):
+    """A record is taken as it is: at most k pairs are written, in index order, from the elements above its key and its quota
+    of ties; a key that no score can have selects nothing."""
+    import torch
+    iwp = gpu_lib
+    rng = np.random.default_rng(9)
+    n = 5 * TILE + 13
+    w = np.ones(layers * n, np.float32)
+    r = rng.integers(1, 40, layers * n).astype(np.float32)   # many ties
+    wd, rd = torch.from_numpy(w).cuda(), torch.from_numpy(r).cuda()
+    k = 700
+    plan = iwp.Plan([(j * n, n, k, j * k) for j in range(layers)])
+    ws = torch.empty(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+    key_of = oracle.score(w, r, EPS).view(np.uint32)
+    for key, quota in ((0xFFFFFFFF, 5), (0x80000001, 0xFFFFFFFF), (int(key_of[7]), 3), (int(key_of[7]), 0xFFFFFFFF), (1, 0), (0, 9)):
+        thr = torch.tensor([key, 0, quota] * layers, dtype=torch.int64, device="cuda").to(torch.int32)
+        idx = torch.full((layers * k,), -1, dtype=torch.int32, device="cuda")
+        val = torch.full((layers * k,), float("nan"), device="cuda")
+        iwp.compact_pairs_segmented(plan, wd, rd, EPS, thr, idx, val, ws)
+        torch.cuda.synchronize()
+        for j in range(layers):
+            keys = key_of[j * n:(j + 1) * n].astype(np.int64)
+            ties = np.cumsum(keys == key)
+            take = np.nonzero((keys > key) | ((keys == key) & (ties <= quota)))[0][:k]
+            got = idx[j * k:(j + 1) * k].cpu().numpy()
+            assert np.array_equal(got[:take.size], (take + j * n).astype(np.int32)), (layers, hex(key), quota, j)
+            assert (got[take.size:] == -1).all(), (layers, hex(key), quota, j)
+            assert np.array_equal(bits(val[j * k:j * k + take.size].cpu().numpy()), bits(r[j * n + take])), (hex(key), quota)
+
+
+@pytest.mark.parametrize("kind,most", [("threshold zero", 2.4), ("everything kept", 4.3)])
+def test_time_where_copies_do_not_pay(gpu_lib, kind, most):
+    """Against one pair in 64 of the same layer of 25 M elements: a threshold of zero 1.7 times as long (3.0 with every tile
+    read three times), every element kept 3.3 times (5.3 with every element copied and read back)."""
+    import torch
+    iwp = gpu_lib
+    n = 25_000_000
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    w = torch.randn(n, device="cuda", generator=gen)
+    took = []
+    for case in ("ordinary", kind):
+        r = torch.randn(n, device="cuda", generator=gen)
+        if case == "threshold zero":
+            r *= torch.rand(n, device="cuda", generator=gen) < 0.005
+        k = n if case == "everything kept" else n // 64
+        thr = torch.zeros(3, dtype=torch.int32, device="cuda")
+        idx, val = torch.empty(k, dtype=torch.int32, device="cuda"), torch.empty(k, device="cuda")
+        ws = torch.empty(iwp.workspace_bytes(n, k), dtype=torch.uint8, device="cuda")
+        iwp.select_threshold(w, r, k, EPS, thr, ws)
+        times = []
+        for _ in range(12):
+            start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(5):
+                iwp.compact_pairs(w, r, EPS, thr, k, idx, val, ws)
+            stop.record()
+            stop.synchronize()
+            times.append(start.elapsed_time(stop) / 5)
+        took.append(statistics.median(times[2:]))
+    print("ordinary %.1f us, %s %.1f us" % (took[0] * 1e3, kind, took[1] * 1e3))
+    assert took[1] < most * took[0]
