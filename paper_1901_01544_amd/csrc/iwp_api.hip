@@ -200,12 +200,14 @@ int check_eps(float eps) { return (eps >= 0.0f && std::isfinite(eps)) ? IWP_OK :
 // Sampling source of a call: the leaders' residuals and gradients (NULL entries allowed), or nothing.
 SampleSource sample_from(const WorkerPtrs& P, const float* w, const uint32_t* leader, uint32_t W, float eps) {
     SampleSource S;
-    S.P = P; S.w = w; S.leader = leader; S.W = W; S.eps = eps; S.on = w ? 1u : 0u;
+    S.P = P; S.w = w; S.leader = leader; S.W = W; S.eps = eps; S.on = w ? 1u : 0u; S.trust_hint = 0u;
     return S;
 }
 
-int launch_init(const Workspace& ws, uint32_t n_layers, const iwp_threshold* hint, const DevLayer* layers,
-                const DevLayer* row, const DevLayer* sentinel, const SampleSource& S, hipStream_t s) {
+int launch_init(const Workspace& ws, uint32_t n_layers, uint32_t tiles, const iwp_threshold* hint, const DevLayer* layers,
+                const DevLayer* row, const DevLayer* sentinel, SampleSource S, hipStream_t s) {
+    if (hint && (tiles <= HINT_MAX_TILES || tiles / n_layers < STAGE_GROUP))
+        S.trust_hint = n_layers <= HINT_FEW_LAYERS ? TRUST_ALWAYS : TRUST_DENSE;
     uint32_t zero_blocks = (uint32_t)std::min<uint64_t>((ws.hist_words + 4 * INIT_BLOCK - 1) / (4 * INIT_BLOCK), 1024);
     if (zero_blocks == 0) zero_blocks = 1;
     DevLayer zero;
@@ -425,7 +427,7 @@ static int single_common(SingleOp op, const float* w, const float* g, float* r, 
                             false, idx_out, val_out, thr_out, s);
     SampleSource S = sample_from(P, w, nullptr, 1u, eps);
     if (op == OP_COMPACT || k == 0) S.on = 0;
-    int rc = launch_init(ws, 1, nullptr, nullptr, &row, &sentinel, S, s);
+    int rc = launch_init(ws, 1, z.tiles, nullptr, nullptr, &row, &sentinel, S, s);
     if (rc) return rc;
     Table T{ws.single_table, 1, z.tiles, z.stiles, k, k > 0, z.stiles, row.h0_copies};
     if (op == OP_COMPACT) return run_compact_from(T, ws, R, w, eps, from_thr, idx_out, val_out, s);
@@ -656,7 +658,7 @@ static int compress_segmented_on(const iwp_plan* plan, const float* w, const flo
                           val_out, thr_out, s);
         if (rc) return rc;
     } else {
-        rc = launch_init(ws, T.n_layers, thr_hint, T.layers, nullptr, nullptr, sample_from(P, w, leader, W, eps), s);
+        rc = launch_init(ws, T.n_layers, T.tiles, thr_hint, T.layers, nullptr, nullptr, sample_from(P, w, leader, W, eps), s);
         if (rc) return rc;
         if (T.any_k) {
             rc = launch_leader_pass(T, ws, P, w, leader, W, eps, s);
@@ -713,7 +715,7 @@ int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, fl
                           val_out, thr_out, s);
         if (rc) return rc;
     } else if (T.any_k) {
-        rc = launch_init(ws, z.n_layers, thr_hint, plan->dev, nullptr, nullptr, sample_from(P, w, leader, W, eps), s);
+        rc = launch_init(ws, z.n_layers, z.tiles, thr_hint, plan->dev, nullptr, nullptr, sample_from(P, w, leader, W, eps), s);
         if (rc) return rc;
         rc = launch_leader_pass(T, ws, P, w, leader, W, eps, s);
         if (rc) return rc;
@@ -758,7 +760,7 @@ int select_threshold_segmented(const iwp_plan* plan, const float* w, const float
     if (plan->max_n <= SMALL_MAX_N)
         return launch_small(plan->dev, nullptr, plan->z.n_layers, plan->max_n, plan->z.pairs, ws, P, w, nullptr, 1u, eps,
                             STOP_AT_THRESHOLD, false, nullptr, nullptr, thr_out, s);
-    rc = launch_init(ws, plan->z.n_layers, nullptr, plan->dev, nullptr, nullptr, sample_from(P, w, nullptr, 1u, eps), s);
+    rc = launch_init(ws, plan->z.n_layers, plan->z.tiles, nullptr, plan->dev, nullptr, nullptr, sample_from(P, w, nullptr, 1u, eps), s);
     if (rc) return rc;
     ResidualPtrs R;
     memset(&R, 0, sizeof R);
