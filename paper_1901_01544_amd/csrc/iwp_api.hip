@@ -308,11 +308,24 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
     return launch_write<false>(T, ws, R, w, leader, W, eps, idx_out, val_out, s);
 }
 
-// Are all of a table's layers small enough for k_small, which then replaces k_init, look 1 and the selection?
 constexpr uint32_t SMALL_MAX_N = SMALL_CHUNKS_MAX * SMALL_CHUNK;
 
-// row: a single layer (layers == NULL); fused: whole-step route.
-int launch_small(const DevLayer* layers, const DevLayer* row, uint32_t n_layers, uint32_t max_n, uint64_t pairs,
+// Does k_small replace k_init, look 1 and the selection?  Where all layers have at most 32768 elements; beyond 16384 a
+// compute unit holds one layer at a time and nothing overlaps its loads with its barriers, so only up to 512 layers of more
+// than a tile with a hint, 1024 without (the long route samples then); the selection alone, which writes nothing, always.
+// Layers of 16385 elements, k_small against the long route: 512 hinted 69 / 72 us, 768 107 / 97; unhinted 1024 137 / 145,
+// 2048 253 / 243; of 32768: 114 / 119, 165 / 168, 213 / 212, 401 / 395; selection of 6000 layers of 16385 366 / 398.
+bool takes_small(uint32_t max_n, uint32_t n_long, bool hinted, bool select) {
+    if (max_n > SMALL_MAX_N) return false;
+    return select || max_n <= SMALL_MAX_N / 2 || n_long <= (hinted ? 512u : 1024u);
+}
+
+// Up to this many layers a table of short and long ones takes one launch: two workgroups of 16 wavefronts per compute unit.
+// Ragged tables, one launch / two: 300 layers 25.6 / 30.3 us, 512 28.1 / 31.6, 1000 45.5 / 31.9.
+constexpr uint32_t SMALL_ONE_LAUNCH = 512;
+
+// row: a single layer (layers == NULL); n_long: layers of more than a tile; fused: whole-step route.
+int launch_small(const DevLayer* layers, const DevLayer* row, uint32_t n_layers, uint32_t n_long, uint32_t max_n, uint64_t pairs,
                  const Workspace& ws, const WorkerPtrs& P, const float* w, const uint32_t* leader, uint32_t W, float eps,
                  Stop stop, bool fused, uint32_t* idx_out, float* val_out, iwp_threshold* thr_out, hipStream_t s) {
     DevLayer none;
@@ -320,13 +333,21 @@ int launch_small(const DevLayer* layers, const DevLayer* row, uint32_t n_layers,
     const DevLayer r = row ? *row : none;
     const bool emit = stop == FULL;
     float* gathered = fused ? ws.gathered : nullptr;
-#define IWP_SMALL(FUSED, CHUNKS)                                                                                      \
-    IWP_LAUNCH_BLOCK("k_small", (k_small<FUSED, CHUNKS>), n_layers, SMALL_BLOCK, s, P, w, layers, r, leader, W, eps, \
-                     thr_out, emit, ws.tile_out, idx_out, val_out, gathered, pairs)
-    if (max_n <= SMALL_MAX_N / 2) {
-        if (fused) IWP_SMALL(true, SMALL_CHUNKS_MAX / 2); else IWP_SMALL(false, SMALL_CHUNKS_MAX / 2);
-    } else {
-        if (fused) IWP_SMALL(true, SMALL_CHUNKS_MAX); else IWP_SMALL(false, SMALL_CHUNKS_MAX);
+    const bool apart = max_n > TILE && n_layers > SMALL_ONE_LAUNCH && n_long < n_layers;
+#define IWP_SMALL(FUSED, THREADS, CHUNKS, FROM, TO)                                                                               \
+    IWP_LAUNCH_BLOCK("k_small", (k_small<FUSED, THREADS, CHUNKS>), n_layers, THREADS, s, P, w, layers, r, FROM, TO, leader, W, \
+                     eps, thr_out, emit, ws.tile_out, idx_out, val_out, gathered, pairs)
+    if (max_n <= TILE || apart) {
+        if (fused) IWP_SMALL(true, TINY_BLOCK, TINY_CHUNKS, 0u, TILE);
+        else IWP_SMALL(false, TINY_BLOCK, TINY_CHUNKS, 0u, TILE);
+    }
+    const uint32_t from = apart ? TILE + 1 : 0u;
+    if (max_n > SMALL_MAX_N / 2) {
+        if (fused) IWP_SMALL(true, SMALL_BLOCK, SMALL_CHUNKS_MAX, from, SMALL_MAX_N);
+        else IWP_SMALL(false, SMALL_BLOCK, SMALL_CHUNKS_MAX, from, SMALL_MAX_N);
+    } else if (max_n > TILE) {
+        if (fused) IWP_SMALL(true, SMALL_BLOCK, SMALL_CHUNKS_MAX / 2, from, SMALL_MAX_N / 2);
+        else IWP_SMALL(false, SMALL_BLOCK, SMALL_CHUNKS_MAX / 2, from, SMALL_MAX_N / 2);
     }
 #undef IWP_SMALL
     return IWP_OK;
@@ -354,6 +375,7 @@ struct iwp_plan {
     bool all_k = true;            // every non-empty layer selects something
     uint32_t max_layer_stiles = 0;
     uint32_t max_n = 0;           // elements of the longest layer
+    uint32_t n_long = 0;          // layers of more than one tile
     uint32_t max_copies = 1;      // most copies of a layer's first-digit histogram
     float momentum = 1.0f;        // r <- momentum * r + g in every call that accumulates through this plan
 };
@@ -423,7 +445,7 @@ static int single_common(SingleOp op, const float* w, const float* g, float* r, 
     row.hist_begin = 0; row.h0_copies = h0_copies_of(n, k);
     sentinel.tile_begin = z.tiles; sentinel.stile_begin = z.stiles; sentinel.out_offset = k;
     if (op != OP_COMPACT && k > 0 && n <= SMALL_MAX_N)
-        return launch_small(nullptr, &row, 1u, n, k, ws, P, w, nullptr, 1u, eps, op == OP_SELECT ? STOP_AT_THRESHOLD : FULL,
+        return launch_small(nullptr, &row, 1u, 1u, n, k, ws, P, w, nullptr, 1u, eps, op == OP_SELECT ? STOP_AT_THRESHOLD : FULL,
                             false, idx_out, val_out, thr_out, s);
     SampleSource S = sample_from(P, w, nullptr, 1u, eps);
     if (op == OP_COMPACT || k == 0) S.on = 0;
@@ -509,7 +531,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     std::vector<DevLayer> dev(n_layers + 1);
     uint64_t pairs = 0, slots = 0, tiles = 0, stiles = 0, end = 0, mask_words = 0, hist_words = 0;
     bool any_k = false, all_k = true;
-    uint32_t max_stiles = 0, max_n = 0;
+    uint32_t max_stiles = 0, max_n = 0, n_long = 0;
     for (uint32_t j = 0; j < n_layers; ++j) {
         const iwp_layer& L = layers[j];
         if (L.offset < 0 || L.k > L.n) return IWP_EINVAL;
@@ -540,6 +562,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
         any_k = any_k || L.k > 0;
         max_stiles = std::max(max_stiles, stiles_of(L.n));
         max_n = std::max(max_n, L.n);
+        n_long += L.n > TILE ? 1u : 0u;
         if (L.n > 0 && L.k == 0) all_k = false;
         if (pairs > 0xFFFFFFFFull || tiles > 0x7FFFFFFFull / IWP_MAX_WORKERS || hist_words > 0xFFFFFFFFull) return IWP_ERANGE;
     }
@@ -557,6 +580,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     plan->all_k = all_k;
     plan->max_layer_stiles = max_stiles;
     plan->max_n = max_n;
+    plan->n_long = n_long;
     for (const DevLayer& D : dev) plan->max_copies = std::max(plan->max_copies, D.h0_copies);
     plan->flat_end = end;
     // the table, then the layer of every tile and of every super-tile (find_layer reads them)
@@ -652,9 +676,9 @@ static int compress_segmented_on(const iwp_plan* plan, const float* w, const flo
     if (plan->z.tiles == 0) return IWP_OK;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     Table T{plan->dev, plan->z.n_layers, plan->z.tiles, plan->z.stiles, plan->z.pairs, plan->any_k, plan->max_layer_stiles, plan->max_copies};
-    const bool small = T.any_k && plan->max_n <= SMALL_MAX_N;
+    const bool small = T.any_k && takes_small(plan->max_n, plan->n_long, thr_hint != nullptr, false);
     if (small) {
-        rc = launch_small(T.layers, nullptr, T.n_layers, plan->max_n, T.pairs, ws, P, w, leader, W, eps, FULL, false, idx_out,
+        rc = launch_small(T.layers, nullptr, T.n_layers, plan->n_long, plan->max_n, T.pairs, ws, P, w, leader, W, eps, FULL, false, idx_out,
                           val_out, thr_out, s);
         if (rc) return rc;
     } else {
@@ -710,8 +734,8 @@ int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, fl
     if (z.tiles == 0) return IWP_OK;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     Table T{plan->dev, z.n_layers, z.tiles, z.stiles, z.pairs, plan->any_k, plan->max_layer_stiles, plan->max_copies};
-    if (T.any_k && plan->max_n <= SMALL_MAX_N) {
-        rc = launch_small(T.layers, nullptr, T.n_layers, plan->max_n, T.pairs, ws, P, w, leader, W, eps, FULL, true, idx_out,
+    if (T.any_k && takes_small(plan->max_n, plan->n_long, thr_hint != nullptr, false)) {
+        rc = launch_small(T.layers, nullptr, T.n_layers, plan->n_long, plan->max_n, T.pairs, ws, P, w, leader, W, eps, FULL, true, idx_out,
                           val_out, thr_out, s);
         if (rc) return rc;
     } else if (T.any_k) {
@@ -757,8 +781,8 @@ int select_threshold_segmented(const iwp_plan* plan, const float* w, const float
     memset(&P, 0, sizeof P);
     P.r[0] = const_cast<float*>(r);       // no gradient pointer: the residual is only read
     P.momentum = 1.0f;
-    if (plan->max_n <= SMALL_MAX_N)
-        return launch_small(plan->dev, nullptr, plan->z.n_layers, plan->max_n, plan->z.pairs, ws, P, w, nullptr, 1u, eps,
+    if (takes_small(plan->max_n, plan->n_long, false, true))
+        return launch_small(plan->dev, nullptr, plan->z.n_layers, plan->n_long, plan->max_n, plan->z.pairs, ws, P, w, nullptr, 1u, eps,
                             STOP_AT_THRESHOLD, false, nullptr, nullptr, thr_out, s);
     rc = launch_init(ws, plan->z.n_layers, plan->z.tiles, nullptr, plan->dev, nullptr, nullptr, sample_from(P, w, nullptr, 1u, eps), s);
     if (rc) return rc;

@@ -1,9 +1,13 @@
 // Tables of small layers: the leader's whole part of a step -- accumulate, score, select, split -- in one launch, one
-// workgroup of 16 wavefronts per layer with the layer in registers.
+// workgroup per layer with the layer in registers.
 //
 // Latency bound: a small layer's seven launches (k_init ... k_write) take about 4 us each, whatever the layer holds, and
 // every one reads back what the one before has written.  Here the layer is read once and the three digits of the k-th
-// largest key are found by three histograms in LDS.  One layer of 1000 elements: 30.6 -> 10.5 us a call.
+// largest key are found by three histograms in LDS.  One layer of 1000 elements: 30.6 -> 10.8 us a call.
+// Layers of one tile take a workgroup of 4 wavefronts, eight of which a compute unit holds, longer ones 16 wavefronts,
+// two or (beyond 16384 elements) one a unit; a large table of both takes a launch for each kind.  3000 layers of 300
+// elements 119 us by 16 wavefronts, 30 by 4, 94 to 123 by the long route; 6000 ragged ones of 1 M elements, the longest
+// 24 759, 394 us by 16 wavefronts, 87 in two launches, 171 to 225 by the long route.
 // Beyond 32768 elements a lane would hold more than 32 keys and values (128 registers at 16 wavefronts), and one compute
 // unit's share of the memory rate outweighs the launches.
 #pragma once
@@ -13,29 +17,32 @@
 namespace iwp {
 
 constexpr int SMALL_BLOCK = 1024;
-constexpr uint32_t SMALL_WAVES = SMALL_BLOCK / WAVE;
-constexpr uint32_t SMALL_CHUNK = SMALL_BLOCK * VEC;        // 4096 elements: a tile
+constexpr uint32_t SMALL_CHUNK = SMALL_BLOCK * VEC;        // elements that the workgroup takes at a time
 constexpr uint32_t SMALL_CHUNKS_MAX = 8;                   // layers of up to 32768 elements
-static_assert(SMALL_CHUNK == TILE, "a chunk is a tile: its first pair's position is the tile's");
+constexpr int TINY_BLOCK = 256;                            // tables whose layers all fit one tile
+constexpr uint32_t TINY_CHUNKS = TILE / (TINY_BLOCK * VEC);
 
 // FUSED: as in k_write -- the values also go into the leader's row of the gather matrix and the sent positions are
 // cleared.  emit: write the pairs; otherwise (select_threshold) only the record, and the residual is only read.
-// A single layer comes as `row` (layers == NULL).
-template <bool FUSED, uint32_t CHUNKS>
-__global__ __launch_bounds__(SMALL_BLOCK) void k_small(WorkerPtrs P, const float* __restrict__ w,
+// A single layer comes as `row` (layers == NULL).  Layers of less than min_n or more than max_n elements are another launch's.
+template <bool FUSED, int THREADS, uint32_t CHUNKS>
+__global__ __launch_bounds__(THREADS) void k_small(WorkerPtrs P, const float* __restrict__ w,
                                                        const DevLayer* __restrict__ layers, DevLayer row,
+                                                       uint32_t min_n, uint32_t max_n,
                                                        const uint32_t* __restrict__ leader, uint32_t W, float eps,
                                                        iwp_threshold* __restrict__ thr_out, bool emit,
                                                        uint32_t* __restrict__ tile_out, uint32_t* __restrict__ idx_out,
                                                        float* __restrict__ val_out, float* __restrict__ gathered,
                                                        uint64_t K) {
+    constexpr uint32_t WAVES = THREADS / WAVE, STEP = THREADS * VEC;         // STEP: elements of a chunk
+    static_assert(TILE % STEP == 0, "tiles start where chunks start");
     __shared__ uint32_t lh[HIST0];
     __shared__ uint32_t sh[PICK_WORDS];
-    __shared__ uint32_t tot[CHUNKS * SMALL_WAVES];
+    __shared__ uint32_t tot[CHUNKS * WAVES];
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
     const uint32_t j = blockIdx.x;
     const DevLayer L = layers ? layers[j] : row;
-    if (L.k == 0) return;
+    if (L.k == 0 || L.n < min_n || L.n > max_n) return;
     const uint32_t p = leader_of(leader, j, W);
     const float* gp = P.g[p];
     float* rl = P.r[p] + L.offset;
@@ -48,7 +55,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small(WorkerPtrs P, const float
         float gv[4][4], wv[4][4];
 #pragma unroll
         for (uint32_t c = 0; c < 4; ++c) {
-            const uint32_t i = (u0 + c) * SMALL_CHUNK + tid * VEC;
+            const uint32_t i = (u0 + c) * STEP + tid * VEC;
             if (i < L.n) {
                 load_quad(rl, i, L.n, val[u0 + c]);
                 if (gp) load_quad(gl, i, L.n, gv[c]);
@@ -57,7 +64,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small(WorkerPtrs P, const float
         }
 #pragma unroll
         for (uint32_t c = 0; c < 4; ++c) {
-            const uint32_t u = u0 + c, i = u * SMALL_CHUNK + tid * VEC;
+            const uint32_t u = u0 + c, i = u * STEP + tid * VEC;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 key[u][q] = NOT_AN_ELEMENT;
@@ -69,7 +76,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small(WorkerPtrs P, const float
             if (!FUSED && gp && i < L.n) store_quad(rl, i, L.n, val[u]);
         }
     }
-    for (uint32_t b = tid; b < HIST0; b += SMALL_BLOCK) lh[b] = 0u;
+    for (uint32_t b = tid; b < HIST0; b += THREADS) lh[b] = 0u;
     __syncthreads();
     uint32_t zeros = 0;                                    // counted in a register, as in look 1
 #pragma unroll
@@ -86,11 +93,11 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small(WorkerPtrs P, const float
     }
     __syncthreads();
     uint32_t prefix, rank;
-    block_pick<(int)HIST0, SMALL_BLOCK>(lh, L.k, sh, &prefix, &rank);
+    block_pick<(int)HIST0, THREADS>(lh, L.k, sh, &prefix, &rank);
 #pragma unroll
     for (int level = 1; level < DIGITS; ++level) {
-        static_assert(HIST1 == SMALL_BLOCK && HIST2 <= HIST1, "one bin per thread; the third digit leaves the upper half empty");
-        lh[tid] = 0u;
+        static_assert(HIST2 <= HIST1, "the third digit leaves the upper half of the bins empty");
+        for (uint32_t b = tid; b < HIST1; b += THREADS) lh[b] = 0u;
         __syncthreads();
         const uint32_t mask = (1u << digit_bits(level)) - 1u;
 #pragma unroll
@@ -101,7 +108,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small(WorkerPtrs P, const float
                     atomicAdd(&lh[(key[u][q] >> digit_shift(level)) & mask], 1u);
         __syncthreads();
         uint32_t bin, rest;
-        block_pick<(int)HIST1, SMALL_BLOCK>(lh, rank, sh, &bin, &rest);
+        block_pick<(int)HIST1, THREADS>(lh, rank, sh, &bin, &rest);
         prefix = (prefix << digit_bits(level)) | bin;
         rank = rest;
     }
@@ -123,20 +130,21 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small(WorkerPtrs P, const float
             mine[u] += key[u][q] == NOT_AN_ELEMENT ? 0u : key[u][q] > thr ? 1u : key[u][q] == thr ? 0x10000u : 0u;
         const uint32_t inc = wave_inclusive_scan(mine[u]);
         before[u] = inc - mine[u];
-        if (lane == WAVE - 1) tot[u * SMALL_WAVES + wave] = inc;
+        if (lane == WAVE - 1) tot[u * WAVES + wave] = inc;
     }
     __syncthreads();
     uint32_t carry = 0;                                    // at most 32768 of either kind in a layer: the halves hold them
+    constexpr uint32_t PER_SCAN = CHUNKS < WAVE / WAVES ? CHUNKS : WAVE / WAVES;
 #pragma unroll
-    for (uint32_t u0 = 0; u0 < CHUNKS; u0 += WAVE / SMALL_WAVES) {
-        const uint32_t v = tot[u0 * SMALL_WAVES + lane];
+    for (uint32_t u0 = 0; u0 < CHUNKS; u0 += PER_SCAN) {
+        const uint32_t v = lane < PER_SCAN * WAVES ? tot[u0 * WAVES + lane] : 0u;
         const uint32_t inc = wave_inclusive_scan(v);
 #pragma unroll
-        for (uint32_t c = 0; c < WAVE / SMALL_WAVES; ++c) {
+        for (uint32_t c = 0; c < PER_SCAN; ++c) {
             const uint32_t u = u0 + c;
-            const uint32_t base = carry + __shfl(inc - v, (int)(c * SMALL_WAVES + wave), WAVE);
-            if (FUSED && tid == 0 && u * SMALL_CHUNK < L.n)
-                tile_out[L.tile_begin + u] = (base & 0xffffu) + min(base >> 16, quota);
+            const uint32_t base = carry + __shfl(inc - v, (int)(c * WAVES + wave), WAVE);
+            if (FUSED && tid == 0 && u * STEP % TILE == 0 && u * STEP < L.n)
+                tile_out[L.tile_begin + u * STEP / TILE] = (base & 0xffffu) + min(base >> 16, quota);
             before[u] += base;
         }
         carry += __shfl(inc, WAVE - 1, WAVE);
@@ -146,7 +154,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small(WorkerPtrs P, const float
     float* go = FUSED ? gathered + (size_t)p * K + L.out_offset : nullptr;
 #pragma unroll
     for (uint32_t u = 0; u < CHUNKS; ++u) {
-        const uint32_t i = u * SMALL_CHUNK + tid * VEC;
+        const uint32_t i = u * STEP + tid * VEC;
         if (mine[u]) {
             uint32_t g = before[u] & 0xffffu, e = before[u] >> 16;
 #pragma unroll

@@ -1,6 +1,9 @@
-"""GPU parity of the one-launch route for tables whose layers all have at most 32768 elements, and of the first sizes
-beyond it: lengths around a chunk (4096), the two instantiations (16384, 32768) and the line itself; ties at the cut,
-zeros of both signs, every element kept; whole steps with layers that keep nothing and workers without a gradient."""
+"""GPU parity of the short route for tables whose layers all have at most 32768 elements, and of the first sizes
+beyond it: lengths around a tile (4096), the three instantiations (4096, 16384, 32768) and the line itself; ties at the cut,
+zeros of both signs, every element kept; whole steps with layers that keep nothing and workers without a gradient; large
+tables, where layers of one tile and longer ones take a launch each, on both sides of the lines of that rule."""
+import statistics
+
 import numpy as np
 import pytest
 
@@ -47,3 +50,69 @@ def test_tables(gpu_lib, top, fused):
         ref = oracle.step(w_ref, [sets[i] for i in ids], r_ref, ps.rows(), lead, float(ps.eps), float(ps.scale))
         gs.step(ids, lead)
         assert_step_equal(gs.download(), w_ref, r_ref, *ref, ps.layers, tag="top %d step %d" % (top, t))
+
+
+def _steps(gpu_lib, sizes, fused, hint, steps=2):
+    ps = wl.custom_set(sizes, W=2, seed=len(sizes), align=1, start=1, zero_frac=0.01)
+    w = wl.gen_weights(ps)
+    sets = [wl.gen_gradient(ps, s) for s in range(2)]
+    gs = GpuSet(gpu_lib, ps, w, sets, fused=fused, hint=hint)
+    w_ref = w.copy()
+    r_ref = [np.zeros(ps.flat, np.float32) for _ in range(2)]
+    for t in range(steps):
+        lead = wl.leaders(ps, t)
+        ids = [(p + t) % 2 for p in range(2)]
+        ref = oracle.step(w_ref, [sets[i] for i in ids], r_ref, ps.rows(), lead, float(ps.eps), float(ps.scale))
+        gs.step(ids, lead)
+        assert_step_equal(gs.download(), w_ref, r_ref, *ref, ps.layers, tag="%d layers step %d" % (len(sizes), t))
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("top", [4096, 4097, 16384, 16385, 32768])
+@pytest.mark.parametrize("layers", [512, 513, 3000])
+@pytest.mark.parametrize("fused", [False, True])
+def test_large_tables_of_both_kinds(gpu_lib, top, layers, fused):
+    rng = np.random.default_rng(layers)
+    sizes = [(int(n), int(rng.integers(0, n + 1))) for n in rng.integers(1, 300, layers - 4)]
+    for at, n in ((0, top), (7, 4096), (layers // 2, max(1, top - 1)), (len(sizes), top)):
+        sizes.insert(at, (n, n // 40))
+    _steps(gpu_lib, sizes, fused, "none")
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("hint,layers", [("previous", 512), ("previous", 513), ("none", 1024), ("none", 1025)])
+def test_lines_of_the_longest_layers(gpu_lib, hint, layers):
+    _steps(gpu_lib, [(16385, 300)] * layers + [(50, 3)], True, hint)
+
+
+def test_thousands_of_tiny_layers(gpu_lib):
+    """6000 layers of 150 elements beside one of 24 000 take at most four times as long as one layer of them all (1.9
+    measured; 9.7 with a workgroup of 16 wavefronts for each)."""
+    import torch
+    iwp = gpu_lib
+    sizes = [150] * 3000 + [24_000] + [150] * 3000
+    total = sum(sizes)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    w, g, r = (torch.randn(total, device="cuda", generator=gen) for _ in range(3))
+    took = []
+    for split in (sizes, [total]):
+        rows, off, out = [], 0, 0
+        for n in split:
+            rows.append((off, n, -(-n // 64), out))
+            off, out = off + n, out + -(-n // 64)
+        plan = iwp.Plan(rows)
+        idx, val = torch.empty(out, dtype=torch.int32, device="cuda"), torch.empty(out, device="cuda")
+        thr = torch.zeros(3 * len(rows), dtype=torch.int32, device="cuda")
+        ws = torch.empty(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+        times = []
+        for _ in range(12):
+            start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(10):
+                iwp.compress_segmented(plan, w, [g], [r], None, 1e-8, idx, val, thr, ws)
+            stop.record()
+            stop.synchronize()
+            times.append(start.elapsed_time(stop) / 10)
+        took.append(statistics.median(times[2:]))
+    print("6001 layers %.1f us, one layer %.1f us" % (took[0] * 1e3, took[1] * 1e3))
+    assert took[0] < 4 * took[1]
