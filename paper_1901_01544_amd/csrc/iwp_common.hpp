@@ -214,7 +214,7 @@ __device__ __forceinline__ void store_quad(float* __restrict__ base, uint32_t i,
 // The 16 elements per lane of the tile that starts at element `base` of a layer of n elements, in one stretch of code
 // for full and ragged tiles.  request_tile() only issues loads: the whole quads, and the up to three elements behind
 // the layer's last whole quad, on the lane they belong to, into registers of their own; settle_tile() puts those into place
-// once every array of the tile has been requested.  A second branch per quad for the elements behind the last whole one
+// once every array of the tile has been requested.  CHUNKS: fewer than CHUNKS_PER_TILE for tiles known to end there.  A second branch per quad for the elements behind the last whole one
 // made the compiler wait for one quad before it asked for the next.  Values past the end are not meant for use.
 // Against separate code for the two forms: look 1 364 -> 342 us, followers' pass 1898 -> 1877 us on a thousand packed
 // tensors of 115.5 M elements; with thresholds, tables of 0.3 to 1.2 M elements 39.5 -> 35.5 and 61.3 -> 58.6 us a step.
@@ -222,11 +222,11 @@ struct Rest { float x[3]; };
 __device__ __forceinline__ bool holds_rest(uint32_t n, uint32_t base) {      // does this lane hold those elements?
     return base + TILE > n && (n & 3u) && (((n & ~3u) - base) & (CHUNK - 1u)) == threadIdx.x * VEC;
 }
-template <bool NT>
+template <bool NT, uint32_t CHUNKS>
 __device__ __forceinline__ void request_tile(const float* __restrict__ p, uint32_t n, uint32_t base,
-                                             float (&v)[CHUNKS_PER_TILE][4], Rest& rest) {
+                                             float (&v)[CHUNKS][4], Rest& rest) {
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+    for (uint32_t u = 0; u < CHUNKS; ++u) {
         const uint32_t i = base + u * CHUNK + threadIdx.x * VEC;
         if (i + VEC <= n) {
             const v4f t = load_v4<NT>(p + i);
@@ -240,21 +240,22 @@ __device__ __forceinline__ void request_tile(const float* __restrict__ p, uint32
     }
 }
 
-__device__ __forceinline__ void settle_tile(uint32_t n, uint32_t base, float (&v)[CHUNKS_PER_TILE][4], const Rest& rest) {
+template <uint32_t CHUNKS>
+__device__ __forceinline__ void settle_tile(uint32_t n, uint32_t base, float (&v)[CHUNKS][4], const Rest& rest) {
     if (!holds_rest(n, base)) return;
     const uint32_t at = ((n & ~3u) - base) / CHUNK;          // which of the lane's quads
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+    for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
         for (int c = 0; c < 3; ++c) v[u][c] = u == at ? rest.x[c] : v[u][c];
 }
 
 // Stores the tile's elements that lie inside the layer.
-template <bool NT>
+template <bool NT, uint32_t CHUNKS>
 __device__ __forceinline__ void store_tile(float* __restrict__ p, uint32_t n, uint32_t base,
-                                           const float (&v)[CHUNKS_PER_TILE][4]) {
+                                           const float (&v)[CHUNKS][4]) {
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) store_quad<NT>(p, base + u * CHUNK + threadIdx.x * VEC, n, v[u]);
+    for (uint32_t u = 0; u < CHUNKS; ++u) store_quad<NT>(p, base + u * CHUNK + threadIdx.x * VEC, n, v[u]);
 }
 
 // Inclusive scan across the 64 lanes of a wavefront.

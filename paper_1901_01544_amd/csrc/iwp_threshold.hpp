@@ -68,10 +68,10 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 // One tile of a chosen node in registers: residual (after adding the gradient and storing
 // it back when gp is set) and weights, 16 values per lane; positions past the layer's end hold
 // values that are not meant for use.
+template <uint32_t CHUNKS>
 __device__ __forceinline__ void chosen_tile(const float* gp, float* rl, const float* gl, const float* wl, float m,
-                                            uint32_t n, uint32_t base, uint32_t tid, float (&rv)[CHUNKS_PER_TILE][4],
-                                            float (&wv)[CHUNKS_PER_TILE][4]) {
-    float gv[CHUNKS_PER_TILE][4];
+                                            uint32_t n, uint32_t base, float (&rv)[CHUNKS][4], float (&wv)[CHUNKS][4]) {
+    float gv[CHUNKS][4];
     Rest rv_rest, gv_rest, wv_rest;
     request_tile<true>(rl, n, base, rv, rv_rest);
     if (gp) request_tile<true>(gl, n, base, gv, gv_rest);
@@ -81,42 +81,26 @@ __device__ __forceinline__ void chosen_tile(const float* gp, float* rl, const fl
     if (gp) {
         settle_tile(n, base, gv, gv_rest);
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+        for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
             for (int c = 0; c < 4; ++c) rv[u][c] = accum(rv[u][c], gv[u][c], m);
         store_tile<true>(rl, n, base, rv);
     }
 }
 
-// ---------------------------------------------------------------------------
-// Chosen nodes: accumulate (if asked), score, compare, encode.  Grid: n_lead * tiles.
-// A node that appears in an earlier slot of the same layer is skipped (same mask).
-// lmask: n_lead masks of mask_words words each, laid out like the final mask.
-// thr: one value per layer, or per (layer, slot) with thr_per_slot.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_leader_mask(WorkerPtrs P, const float* __restrict__ w,
-                                                       const DevLayer* __restrict__ layers, uint32_t n_layers,
-                                                       uint32_t tiles, const uint32_t* __restrict__ leaders,
-                                                       uint32_t n_lead, uint32_t W, const float* __restrict__ thr,
-                                                       bool thr_per_slot, bool accumulate, RandomSel rs, float eps,
-                                                       uint32_t* __restrict__ lmask, uint64_t mask_words) {
+// The tile of a chosen node that starts at element `base` of its layer, CHUNKS chunks of it: accumulate (gp), score, compare,
+// encode.  Layers that end within a tile's first chunk take one chunk only, which spares them three quarters of the divides
+// (and draws): 903 layers of 55 elements 7.3 -> 6.2 us, the pass of the three other nodes below 8.8 -> 7.4 us.
+template <uint32_t CHUNKS>
+__device__ __forceinline__ void mask_tile(const float* gp, float* rl, const float* wl, const DevLayer& L, uint32_t j,
+                                          uint32_t base, float m, float th, const RandomSel& rs, float eps,
+                                          uint32_t* __restrict__ mw) {
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1);
-    const uint32_t q = blockIdx.x / tiles;
-    const uint32_t t = blockIdx.x - q * tiles;
-    const uint32_t j = find_layer<false>(layers, n_layers, t);
-    const DevLayer L = layers[j];
-    const uint32_t p = chosen_at(leaders, n_lead, j, q, W);
-    if (chosen_before(leaders, n_lead, j, q, W, p)) return;
-    const uint32_t lt = t - L.tile_begin;
-    const uint32_t base = lt * TILE;
-    const float* gp = accumulate ? P.g[p] : nullptr;
-    const float th = thr_per_slot ? thr[(size_t)j * n_lead + q] : thr[j];
     const uint32_t nwords = (L.n + 31) / 32;
-    uint32_t* mw = lmask + (size_t)q * mask_words + L.mask_begin;
-    float rv[CHUNKS_PER_TILE][4], wv[CHUNKS_PER_TILE][4];
-    chosen_tile(gp, P.r[p] + L.offset, gp ? gp + L.offset : nullptr, w + L.offset, P.momentum, L.n, base, tid, rv, wv);
+    float rv[CHUNKS][4], wv[CHUNKS][4];
+    chosen_tile(gp, rl, gp ? gp + L.offset : nullptr, wl, m, L.n, base, rv, wv);
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+    for (uint32_t u = 0; u < CHUNKS; ++u) {
         const uint32_t i = base + u * CHUNK + tid * VEC;
         uint32_t nib = 0;
         uint32_t word4[4] = {0u, 0u, 0u, 0u};
@@ -137,9 +121,35 @@ __global__ __launch_bounds__(BLOCK) void k_leader_mask(WorkerPtrs P, const float
         word |= __shfl_xor(word, 1, WAVE);
         word |= __shfl_xor(word, 2, WAVE);
         word |= __shfl_xor(word, 4, WAVE);
-        const uint32_t widx = lt * TILE_WORDS + u * (CHUNK / 32) + (tid >> 3);
+        const uint32_t widx = base / 32 + u * (CHUNK / 32) + (tid >> 3);
         if ((lane & 7u) == 0u && widx < nwords) mw[widx] = word;
     }
+}
+
+// ---------------------------------------------------------------------------
+// Chosen nodes: accumulate (if asked), score, compare, encode.  Grid: n_lead * tiles.
+// A node that appears in an earlier slot of the same layer is skipped (same mask).
+// lmask: n_lead masks of mask_words words each, laid out like the final mask.
+// thr: one value per layer, or per (layer, slot) with thr_per_slot.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(BLOCK) void k_leader_mask(WorkerPtrs P, const float* __restrict__ w,
+                                                       const DevLayer* __restrict__ layers, uint32_t n_layers,
+                                                       uint32_t tiles, const uint32_t* __restrict__ leaders,
+                                                       uint32_t n_lead, uint32_t W, const float* __restrict__ thr,
+                                                       bool thr_per_slot, bool accumulate, RandomSel rs, float eps,
+                                                       uint32_t* __restrict__ lmask, uint64_t mask_words) {
+    const uint32_t q = blockIdx.x / tiles;
+    const uint32_t t = blockIdx.x - q * tiles;
+    const uint32_t j = find_layer<false>(layers, n_layers, t);
+    const DevLayer L = layers[j];
+    const uint32_t p = chosen_at(leaders, n_lead, j, q, W);
+    if (chosen_before(leaders, n_lead, j, q, W, p)) return;
+    const uint32_t base = (t - L.tile_begin) * TILE;
+    const float* gp = accumulate ? P.g[p] : nullptr;
+    const float th = thr_per_slot ? thr[(size_t)j * n_lead + q] : thr[j];
+    uint32_t* mw = lmask + (size_t)q * mask_words + L.mask_begin;
+    if (L.n - base <= CHUNK) mask_tile<1>(gp, P.r[p] + L.offset, w + L.offset, L, j, base, P.momentum, th, rs, eps, mw);
+    else mask_tile<CHUNKS_PER_TILE>(gp, P.r[p] + L.offset, w + L.offset, L, j, base, P.momentum, th, rs, eps, mw);
 }
 
 // ---------------------------------------------------------------------------
@@ -173,7 +183,7 @@ __global__ __launch_bounds__(BLOCK) void k_leader_stats(WorkerPtrs P, const floa
     const uint32_t base = (t - L.tile_begin) * TILE;
     const float* gp = P.g[p];
     float rv[CHUNKS_PER_TILE][4], wv[CHUNKS_PER_TILE][4];
-    chosen_tile(gp, P.r[p] + L.offset, gp ? gp + L.offset : nullptr, w + L.offset, P.momentum, L.n, base, tid, rv, wv);
+    chosen_tile(gp, P.r[p] + L.offset, gp ? gp + L.offset : nullptr, w + L.offset, P.momentum, L.n, base, rv, wv);
     float sc[CHUNKS_PER_TILE][4];
     double lane_sum = 0.0;
 #pragma unroll
@@ -367,48 +377,37 @@ __global__ __launch_bounds__(BLOCK) void k_mask_emit(const DevLayer* __restrict_
 // where the tile's mask has bits, copy the accumulated value into the node's gather
 // row and leave +0 behind.  Grid: W * tiles.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLayer* __restrict__ layers,
-                                                       uint32_t n_layers, uint32_t tiles,
-                                                       const uint32_t* __restrict__ leaders, uint32_t n_lead, uint32_t W,
-                                                       const uint32_t* __restrict__ mask,
-                                                       const uint32_t* __restrict__ tile_out,
-                                                       const uint32_t* __restrict__ lay_out,
-                                                       const uint32_t* __restrict__ count_out, uint32_t max_pairs,
-                                                       float* __restrict__ gathered) {
-    __shared__ uint32_t map[TILE_WORDS], pre[TILE_WORDS], slot[4];
+// The tile of such a node, CHUNKS chunks of it (see mask_tile).  row_out: the node's row of the gather matrix; map, pre, slot:
+// LDS of TILE_WORDS, TILE_WORDS and 4 words.
+template <uint32_t CHUNKS>
+__device__ __forceinline__ void follow_tile(const float* gl, float* rl, const DevLayer& L, uint32_t j, uint32_t t, uint32_t base,
+                                            float m, uint32_t n_layers, const uint32_t* __restrict__ mask,
+                                            const uint32_t* __restrict__ tile_out, const uint32_t* __restrict__ lay_out,
+                                            const uint32_t* __restrict__ count_out, uint32_t max_pairs, float* row_out,
+                                            uint32_t* map, uint32_t* pre, uint32_t* slot) {
     const uint32_t tid = threadIdx.x;
-    const uint32_t p = blockIdx.x / tiles;
-    const uint32_t t = blockIdx.x - p * tiles;
-    const uint32_t j = find_layer<false>(layers, n_layers, t);
-    const DevLayer L = layers[j];
-    const float* gp = P.g[p];
-    if (!gp || chosen_before(leaders, n_lead, j, n_lead, W, p)) return;   // chosen / static nodes: pair by pair later
-    const uint32_t lt = t - L.tile_begin;
-    const uint32_t base = lt * TILE;
-    float* rl = P.r[p] + L.offset;
-    const float* gl = gp + L.offset;
-    float rv[CHUNKS_PER_TILE][4], gv[CHUNKS_PER_TILE][4];
+    float rv[CHUNKS][4], gv[CHUNKS][4];
     Rest rv_rest, gv_rest;
     request_tile<true>(rl, L.n, base, rv, rv_rest);
     request_tile<true>(gl, L.n, base, gv, gv_rest);
     const bool exchange = !overflowed(count_out, n_layers);
     const uint32_t nwords = (L.n + 31) / 32;
     if (tid < TILE_WORDS) {
-        const uint32_t widx = lt * TILE_WORDS + tid;
+        const uint32_t widx = base / 32 + tid;
         map[tid] = (exchange && widx < nwords) ? mask[L.mask_begin + widx] : 0u;
     }
     __syncthreads();
     bitmap_prefix(map, pre, slot);
     const uint64_t row = (uint64_t)lay_out[j] + tile_out[t];
-    float* go = gathered + (size_t)p * max_pairs + min(row, (uint64_t)max_pairs);
+    float* go = row_out + min(row, (uint64_t)max_pairs);
     const uint32_t room = (uint32_t)((uint64_t)max_pairs - min(row, (uint64_t)max_pairs));
     settle_tile(L.n, base, rv, rv_rest);
     settle_tile(L.n, base, gv, gv_rest);
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+    for (uint32_t u = 0; u < CHUNKS; ++u) {
         const uint32_t loc = u * CHUNK + tid * VEC;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) rv[u][q] = accum(rv[u][q], gv[u][q], P.momentum);
+        for (int q = 0; q < 4; ++q) rv[u][q] = accum(rv[u][q], gv[u][q], m);
         const uint32_t nib = (map[loc >> 5] >> (loc & 31u)) & 0xFu;                // no bits past the layer's end
         if (nib) {
             uint32_t rank = bitmap_rank(map, pre, loc);
@@ -418,6 +417,33 @@ __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLa
         }
     }
     store_tile<true>(rl, L.n, base, rv);
+}
+
+__global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLayer* __restrict__ layers,
+                                                       uint32_t n_layers, uint32_t tiles,
+                                                       const uint32_t* __restrict__ leaders, uint32_t n_lead, uint32_t W,
+                                                       const uint32_t* __restrict__ mask,
+                                                       const uint32_t* __restrict__ tile_out,
+                                                       const uint32_t* __restrict__ lay_out,
+                                                       const uint32_t* __restrict__ count_out, uint32_t max_pairs,
+                                                       float* __restrict__ gathered) {
+    __shared__ uint32_t map[TILE_WORDS], pre[TILE_WORDS], slot[4];
+    const uint32_t p = blockIdx.x / tiles;
+    const uint32_t t = blockIdx.x - p * tiles;
+    const uint32_t j = find_layer<false>(layers, n_layers, t);
+    const DevLayer L = layers[j];
+    const float* gp = P.g[p];
+    if (!gp || chosen_before(leaders, n_lead, j, n_lead, W, p)) return;   // chosen / static nodes: pair by pair later
+    const uint32_t base = (t - L.tile_begin) * TILE;
+    float* rl = P.r[p] + L.offset;
+    const float* gl = gp + L.offset;
+    float* row_out = gathered + (size_t)p * max_pairs;
+    if (L.n - base <= CHUNK)
+        follow_tile<1>(gl, rl, L, j, t, base, P.momentum, n_layers, mask, tile_out, lay_out, count_out, max_pairs, row_out, map,
+                       pre, slot);
+    else
+        follow_tile<CHUNKS_PER_TILE>(gl, rl, L, j, t, base, P.momentum, n_layers, mask, tile_out, lay_out, count_out, max_pairs,
+                                     row_out, map, pre, slot);
 }
 
 // ---------------------------------------------------------------------------
