@@ -68,7 +68,6 @@ constexpr uint32_t SAMPLE_RUN = WAVE * VEC;        // 256 consecutive elements, 
 constexpr uint32_t SAMPLE_RUNS = 64;               // at most 16384 sampled elements per layer
 constexpr uint32_t SAMPLE_RUNS_MIN = 16;           // at least 4096 (or the whole layer)
 constexpr uint32_t SAMPLE_RANK = 128;              // rank of the estimated threshold inside the sample, about
-constexpr uint32_t HINT_SLACK = 4u << 19;          // four top-digit bins
 // Where the caller gives a hint, the mark is taken from it instead of from a sample on tables so small that the sample
 // costs more than the second reads it saves: up to HINT_MAX_TILES tiles, where those come from the caches, and tables of
 // short layers, where the samples are a large part of the call.  The mark lies half a top-digit bin (2 to 4 %) below the
@@ -76,6 +75,9 @@ constexpr uint32_t HINT_SLACK = 4u << 19;          // four top-digit bins
 // few layers can miss at once.  Against always sampling: six tensors of 235 k elements 48.8 -> 43.8 us a step, one layer
 // of 200 k at 0.005, four workers, 46 -> 37 us, 600 tensors of 10 M 172 -> 159 us; 45 tensors of 1 M at 0.001 would lose
 // (45 -> 68 us a call), a table of 25.6 M at 1/59 is alike.
+// Where the mark is sampled, a hint below it takes its place: scores that differ from block to block (a convolution's
+// channels) mislead a sample of runs upwards.  One layer of 100 M elements whose gradients' scale changes every 4608: 596
+// -> 530 us; independent scores are alike, with the thresholds of the step before.
 constexpr uint32_t HINT_BELOW = 1u << 18;
 constexpr uint32_t HINT_KEEP = 128;
 constexpr uint32_t HINT_MAX_TILES = 2048, HINT_FEW_LAYERS = 16;
@@ -184,7 +186,7 @@ __global__ __launch_bounds__(INIT_BLOCK, 8) void k_init(uint32_t* __restrict__ w
         st.b1 = 0; st.k_rem0 = 0; st.p22 = 0; st.k_rem1 = 0; st.thr = 0; st.n_eq_take = 0; st.prestaged = 0;
         // a guess in the lowest bin (among zero scores): look 1 stages nothing; among NaN: whole bins
         const uint32_t h = hint ? hint[j].key & 0x7fffffffu : 0u;
-        if (h >= BIN && h + HINT_SLACK < from) from = h;
+        if (h >= 2u * BIN && h < from) from = h;
         st.shift = (from >= BIN && from < QUIET_NAN_KEY) ? (0u - from) & (BIN - 1u) : 0u;
         st.stage_bin = from >= BIN ? shifted(from, st.shift) >> digit_shift(0) : NO_STAGE_BIN;
         state[j] = st;
