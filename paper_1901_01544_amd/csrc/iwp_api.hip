@@ -277,15 +277,17 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
     if (!own_pick) IWP_LAUNCH("k_first_pick", k_first_pick, T.n_layers, s, T.layers, ws.hist, ws.state);
     // Consecutive tiles per look-2 workgroup.  Where look 1's copies are complete only every STAGE_GROUP-th tile has work, and
     // few workgroups mean few flushes into a layer's one second-digit histogram; where they are not (a threshold among
-    // zeros, a sample that misleads), every tile is read again, and few workgroups leave the chip idle.  Up to 32767 tiles
-    // at least about a thousand workgroups, of five tiles at most; beyond, as many as the chip holds at once (1280: five
-    // per compute unit at 91 registers), of 64 tiles at most.  Threshold among zeros, selection alone, against 64 tiles
-    // from 4096 tiles on and 4 below: one layer of 3 M elements 181 -> 92 us, 10 M 371 -> 158, 30 M 641 -> 325, 60 M
-    // 794 -> 588, 150 M 1588 -> 1330; complete copies within 3 % from 1 M to 300 M (keep 0.2 of 10 M elements 192 -> 149).
+    // zeros, a sample that misleads), tiles are read again, and few workgroups leave the chip idle.  Up to 32767 tiles at
+    // least about a thousand workgroups, of three tiles at most; beyond, as many as the chip holds at once (1280: five per
+    // compute unit at 91 registers), of 64 tiles at most.  Threshold among zeros, selection alone, against 64 tiles from
+    // 4096 tiles on and 4 below: one layer of 3 M elements 181 -> 92 us, 10 M 371 -> 158, 30 M 641 -> 319, 60 M 794 -> 580,
+    // 150 M 1588 -> 1330; complete copies within 3 % from 1 M to 300 M (keep 0.2 of 10 M elements 192 -> 150).  Five tiles
+    // instead of three: 326, 586; candidates crowded into blocks of nine tiles in 160 layers of 25 M 241 instead of 230;
+    // one tile: keep 0.2 of 60 M elements 892 instead of 690.
     // Tables of short layers keep one tile each: a workgroup pays a chain of loads per layer.
     const uint32_t avg_tiles = T.tiles / std::max<uint32_t>(1u, T.n_layers);
     const uint32_t per_wg = avg_tiles < STAGE_GROUP ? 1u
-        : T.tiles < STAGE_LARGE_TABLE ? std::min<uint32_t>(std::max<uint32_t>(T.tiles / 1024u, 1u), 5u)
+        : T.tiles < STAGE_LARGE_TABLE ? std::min<uint32_t>(std::max<uint32_t>(T.tiles / 1024u, 1u), 3u)
         : std::min<uint32_t>((T.tiles + STAGE_RESIDENT - 1) / STAGE_RESIDENT, STAGE_TILES_MAX);
     const uint32_t stage_grid = std::max<uint32_t>(std::min<uint32_t>((T.tiles + per_wg - 1) / per_wg, STAGE_MAX_GRID),
                                                    (T.tiles + WAVE - 1) / WAVE);

@@ -1,5 +1,5 @@
 """GPU parity and speed of the second look where every tile is read again: most residuals are zero, the threshold is zero and
-the first look copies nothing out.  Sizes of every grid of that launch: one, two and five tiles a workgroup (the largest,
+the first look copies nothing out.  Sizes of every grid of that launch: one, two and three tiles a workgroup (the largest,
 64, is config 5's), as one layer and behind layers whose copies are complete."""
 import statistics
 
