@@ -3,7 +3,39 @@ HIP library (via the binding) and through the CPU oracle on the same bytes, and
 compare every output bit for bit."""
 from __future__ import annotations
 
+import os
+import re
+
 import numpy as np
+
+import oracle
+
+_SELECT = os.path.join(os.path.dirname(os.path.abspath(__file__)), "..", "paper_1901_01544_amd", "csrc", "iwp_select.hpp")
+
+
+def sample_plan(n, k):
+    """Where the library samples a layer of n elements that keeps k -- runs of 256 -- and which of the sample's largest
+    scores gives the mark from which its first look copies candidates out: (run numbers, runs in all, rank)."""
+    with open(_SELECT) as f:
+        text = f.read()
+    most, least, about = (int(re.search(r"constexpr uint32_t %s = (\d+);" % c, text).group(1))
+                          for c in ("SAMPLE_RUNS", "SAMPLE_RUNS_MIN", "SAMPLE_RANK"))
+    total = (n + 255) // 256
+    runs = min(total, most, max(least, (about * n // k + 255) // 256))
+    rank = k
+    if runs < total:
+        ks = max(1, (k * runs * 256 + n - 1) // n)
+        rank = min(runs * 256, ks + ks // 4 + int(4 * ks ** 0.5) + 2)
+    return [i * total // runs for i in range(runs)], total, rank
+
+
+def sampled_mark(w, v, n, k, eps):
+    """The mark's key for a layer with weights w and accumulated residuals v (None: the first look copies nothing)."""
+    at, _, rank = sample_plan(n, k)
+    pos = np.concatenate([np.arange(q * 256, min(n, (q + 1) * 256)) for q in at])
+    keys = np.sort(oracle.score_keys(np.ascontiguousarray(w[pos]), np.ascontiguousarray(v[pos]), eps))[::-1]
+    mark = int(keys[rank - 1]) >> 7 << 7                     # the low seven bits are not resolved
+    return mark if mark >= 1 << 19 else None
 
 
 def bits(x):

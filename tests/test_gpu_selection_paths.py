@@ -1,7 +1,8 @@
 """GPU parity for the branches of the selection that ordinary data rarely takes, each forced on purpose and
 compared with the CPU oracle bit for bit through the C ABI:
-  * the staging bin guessed from a sample of the layer (no hint given), on layouts that fool a sample:
-    sorted scores, all of the mass in a block between the sampled runs, a pattern with the sample's period;
+  * the first look's mark taken from a sample of the layer (no hint given), on layouts that fool a sample:
+    sorted scores, all of the mass in a block between the sampled runs, a pattern with the sample's period; and
+    tables where such layers and ordinary ones meet in one workgroup of the second look;
   * first-digit histograms kept in several copies (layers of more than 512 tiles);
   * tiles whose keys are all equal, above, at and below the threshold (recorded as one entry);
   * slots that overflow in the first look and are filled again by the second (hints far too low)."""
@@ -10,7 +11,7 @@ import pytest
 
 import oracle
 from paper_1901_01544_amd import workloads as wl
-from harness import GpuSet, assert_step_equal, bits
+from harness import GpuSet, assert_step_equal, bits, sample_plan, sampled_mark
 
 pytestmark = pytest.mark.gpu
 TILE = 4096
@@ -41,8 +42,8 @@ def _check(iwp, torch, w, g, r, k, tag, eps=EPS):
 
 @pytest.mark.parametrize("n", [70_001, 300_007, 1_200_003])
 def test_sampled_staging_bin_on_layouts_that_fool_a_sample(gpu_lib, n):
-    """compress_layer takes no hint, so the first look's staging bin comes from the sample (up to 256 evenly
-    spaced runs of 256 elements).  Whatever the sample suggests, the result is the oracle's."""
+    """compress_layer takes no hint, so the first look's mark comes from the sample (16 to 64 evenly spaced runs of
+    256 elements).  Whatever the sample suggests, the result is the oracle's."""
     import torch
     rng = np.random.default_rng(n)
     one = np.ones(n, np.float32)
@@ -53,21 +54,22 @@ def test_sampled_staging_bin_on_layouts_that_fool_a_sample(gpu_lib, n):
     _check(gpu_lib, torch, one, z, np.sort(base), k, "sorted ascending n=%d" % n)
     _check(gpu_lib, torch, one, z, np.sort(base)[::-1].copy(), k, "sorted descending n=%d" % n)
     # everything that matters inside one block that no sampled run touches: the sample sees only tiny scores
-    # the library's sampling plan (if it changes, these cases still check exactness, only less pointedly)
-    runs_total = (n + 255) // 256
-    runs = min(runs_total, min(256, max(16, (256 * n // k + 255) // 256)))
-    sampled = {(i * runs_total) // runs for i in range(runs)}
-    free = [q for q in range(1, runs_total - 1) if q not in sampled and q + 1 not in sampled]
+    runs, runs_total, _ = sample_plan(n, k)
+    sampled = set(runs)
+    either = sampled | set(sample_plan(n, 300)[0])
+    free = [q for q in range(1, runs_total - 1) if q not in either and q + 1 not in either]
     r = (base * np.float32(1e-4)).astype(np.float32)
     if free:
         q = free[len(free) // 2]
         r[q * 256:(q + 2) * 256] = (1.0 + rng.random(512)).astype(np.float32)
+    assert free and sampled_mark(one, r, n, 300, EPS) < int(np.sort(r.view(np.uint32))[n - 300])
     _check(gpu_lib, torch, one, z, r, k, "block between the runs n=%d" % n)
     _check(gpu_lib, torch, one, z, r, 300, "block between the runs, k inside the block n=%d" % n)
     # a pattern with the sample's own period: large scores exactly where the runs start
     r = (base * np.float32(1e-3)).astype(np.float32)
     for s in sorted(sampled):
         r[s * 256:s * 256 + 64] = (5.0 + rng.random(min(64, n - s * 256))).astype(np.float32)[:max(0, n - s * 256)]
+    assert sampled_mark(one, r, n, k, EPS) > int(np.sort(r.view(np.uint32))[n - k]), "the mark misses candidates"
     _check(gpu_lib, torch, one, z, r, k, "period of the sample n=%d" % n)
     # and the complement: large scores everywhere but in the sampled runs
     r = (1.0 + rng.random(n)).astype(np.float32)
@@ -157,3 +159,37 @@ def test_hints_far_too_low_overflow_the_first_look(gpu_lib, route):
         low[:, 0] = (3 + t) << 19                                    # top-digit bin 3 .. 6: denormal-range scores
         gs.step(ids, lead, hint_records=low)
         assert_step_equal(gs.download(), w_ref, r_ref, *ref, ps.layers, tag="low hints %s step %d" % (route, t))
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("route", ["whole_step", "three_calls"])
+@pytest.mark.parametrize("lengths", [(33_000, 70_001, 40_960, 25_000, 131_072), (5_000_003, 70_001, 4_300_000, 20 * TILE, 25_000)],
+                         ids=["picks in look 2", "picks apart"])
+def test_layers_that_fool_the_sample_beside_ordinary_ones(gpu_lib, route, lengths):
+    """Every other layer has its large scores in the sampled runs, so its mark lies above the threshold and the second look
+    reads it again, beside layers whose copies are complete: on a table whose second look makes the first picks itself and
+    on one beyond 2048 tiles, where they are a launch."""
+    W = 2
+    sizes = [(n, max(1, n // 64)) for n in lengths for _ in (0, 1)]
+    ps = wl.custom_set(sizes, W=W, seed=21, align=1, start=1)
+    w = wl.gen_weights(ps)
+    sets = [wl.gen_gradient(ps, s) for s in range(W)]
+    for j, L in enumerate(ps.layers):
+        if j % 2:
+            for q in sample_plan(L.n, L.k)[0]:
+                for g in sets:
+                    g[L.offset + q * 256:L.offset + min(L.n, q * 256 + 256)] *= np.float32(64)
+    gs = GpuSet(gpu_lib, ps, w, sets, fused=route == "whole_step", hint="none")
+    w_ref = w.copy()
+    r_ref = [np.zeros(ps.flat, np.float32) for _ in range(W)]
+    for t in range(2):
+        lead = wl.leaders(ps, t)
+        ids = [(p + t) % W for p in range(W)]
+        marks = [sampled_mark(w_ref[L.offset:L.offset + L.n], r_ref[lead[j]][L.offset:L.offset + L.n] +
+                              sets[ids[lead[j]]][L.offset:L.offset + L.n], L.n, L.k, float(ps.eps)) for j, L in enumerate(ps.layers)]
+        ref = oracle.step(w_ref, [sets[i] for i in ids], r_ref, ps.rows(), lead, float(ps.eps), float(ps.scale))
+        if t == 0:
+            missed = [marks[j] > int(ref[3][j][0]) for j in range(len(sizes))]
+            assert missed == [j % 2 == 1 for j in range(len(sizes))], missed
+        gs.step(ids, lead)
+        assert_step_equal(gs.download(), w_ref, r_ref, *ref, ps.layers, tag="%s step %d" % (route, t))

@@ -41,13 +41,19 @@ def test_tables(gpu_lib, top, fused):
     ps = wl.custom_set(sizes, W=3, seed=top, align=1, start=3, zero_frac=0.05)
     w = wl.gen_weights(ps)
     sets = [wl.gen_gradient(ps, s) for s in range(3)]
-    gs = GpuSet(gpu_lib, ps, w, sets, fused=fused, hint="previous")
+    rng = np.random.default_rng(top)
+    r0 = [(rng.standard_t(3, ps.flat) * 1e-3).astype(np.float32) for _ in range(3)]
+    gs = GpuSet(gpu_lib, ps, w, sets, r_np=r0, fused=fused, hint="previous")
     w_ref = w.copy()
-    r_ref = [np.zeros(ps.flat, np.float32) for _ in range(3)]
+    r_ref = [x.copy() for x in r0]
     for t in range(3):
         lead = wl.leaders(ps, t)
+        lead[0] = t                                          # the longest layer's leader: each worker in turn,
         ids = [(p + t) % 3 for p in range(3)]
-        ref = oracle.step(w_ref, [sets[i] for i in ids], r_ref, ps.rows(), lead, float(ps.eps), float(ps.scale))
+        ids[1] = None                                        # also the one without a gradient
+        g = [sets[i] if i is not None else sets[0] for i in ids]
+        ref = oracle.step(w_ref, g, r_ref, ps.rows(), lead, float(ps.eps), float(ps.scale),
+                          accumulate_mask=[i is not None for i in ids])
         gs.step(ids, lead)
         assert_step_equal(gs.download(), w_ref, r_ref, *ref, ps.layers, tag="top %d step %d" % (top, t))
 
