@@ -103,8 +103,9 @@ inline size_t round256(size_t x) { return (x + 255) & ~size_t(255); }
 inline uint32_t tiles_of(uint32_t n) { return (uint32_t)(((uint64_t)n + TILE - 1) / TILE); }
 inline uint32_t stiles_of(uint32_t n) { return (uint32_t)(((uint64_t)n + STILE - 1) / STILE); }
 // Staging entries per tile of a layer: three times the number of kept elements an
-// average tile holds, plus room for the threshold bin.  A tile that overflows its
-// slot is re-read by the later passes instead, which is exact as well.
+// average tile holds, twice what look 1 copies from its sampled mark (about 1.5 per
+// kept element), plus 64 for tiles that hold more than the average.  A tile that
+// overflows its slot is re-read by the later passes instead, which is exact as well.
 inline uint32_t slot_cap_of(uint32_t n, uint32_t k) {
     if (k == 0) return 0u;
     const uint64_t per_tile = ((uint64_t)TILE * k + n - 1) / n;
@@ -219,9 +220,6 @@ int launch_init(const Workspace& ws, uint32_t n_layers, uint32_t tiles, const iw
 
 enum Stop { STOP_AT_THRESHOLD, FULL };
 
-// Selection on the leaders' residuals after look 1 has filled the first-digit
-// histograms, then (FULL) the ordered split.  fused: whole-step route (leader row
-// of the gather matrix, leader residual cleared).
 // Workgroups of look 1: one per tile, or GROUP / LGROUP per super-tile when a workgroup takes several tiles.
 constexpr uint32_t leader_grid(uint32_t tiles, uint32_t stiles) {
     return LGROUP == 1 ? tiles : stiles * (GROUP / LGROUP);

@@ -29,10 +29,6 @@ __device__ __forceinline__ float accum(float r, float g, float m) {
     const float decayed = m * r;
     return decayed + g;
 }
-__device__ __forceinline__ v4f accum(v4f r, v4f g, float m) {
-    const v4f decayed = r * m;
-    return decayed + g;
-}
 
 constexpr int BLOCK = 256;                         // 4 wavefronts
 constexpr int WAVE = 64;
@@ -110,7 +106,7 @@ struct LayerState {        // selection state of one layer, lives in the workspa
     uint32_t k_rem1;       // rank inside that 22-bit group
     uint32_t thr;          // the threshold key (third pick, or given by the caller)
     uint32_t n_eq_take;    // ties to keep
-    uint32_t stage_bin;    // look 1 copies out every element whose top digit is >= this bin (from a sample of the layer)
+    uint32_t stage_bin;    // look 1 copies out every element whose top digit is >= this bin (from the hint or a sample)
     uint32_t shift;        // what is added to every key of the layer before it is split into digits (see shifted())
     uint32_t prestaged;    // set with the first pick: stage_bin <= b1, so look 1's copies are complete
 };
@@ -187,12 +183,11 @@ __device__ __forceinline__ void store_v4(float* p, v4f v) {
 }
 
 // Four consecutive elements starting at element i of a layer of n elements: one 128-bit load, except at the layer's
-// end.  Lanes past the end read nothing and get `fill`.  NT: streaming (non-temporal) access for whole quads.
-template <bool NT = false>
+// end.  Lanes past the end read nothing and get `fill`.
 __device__ __forceinline__ void load_quad(const float* __restrict__ base, uint32_t i, uint32_t n, float (&v)[4],
                                           float fill = 0.0f) {
     if (i + 4 <= n) {
-        const v4f t = load_v4<NT>(base + i);
+        const v4f t = load_v4<false>(base + i);
         v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     } else {
 #pragma unroll
@@ -200,6 +195,7 @@ __device__ __forceinline__ void load_quad(const float* __restrict__ base, uint32
     }
 }
 
+// NT: streaming (non-temporal) access for whole quads.
 template <bool NT = false>
 __device__ __forceinline__ void store_quad(float* __restrict__ base, uint32_t i, uint32_t n, const float (&v)[4]) {
     if (i + 4 <= n) {
@@ -216,8 +212,9 @@ __device__ __forceinline__ void store_quad(float* __restrict__ base, uint32_t i,
 // the layer's last whole quad, on the lane they belong to, into registers of their own; settle_tile() puts those into place
 // once every array of the tile has been requested.  CHUNKS: fewer than CHUNKS_PER_TILE for tiles known to end there.  A second branch per quad for the elements behind the last whole one
 // made the compiler wait for one quad before it asked for the next.  Values past the end are not meant for use.
-// Against separate code for the two forms: look 1 364 -> 342 us, followers' pass 1898 -> 1877 us on a thousand packed
+// Against separate code for the two forms: look 1 364 -> 347 us, followers' pass 1898 -> 1877 us on a thousand packed
 // tensors of 115.5 M elements; with thresholds, tables of 0.3 to 1.2 M elements 39.5 -> 35.5 and 61.3 -> 58.6 us a step.
+// Look 1 holds 78 registers instead of 67 for it (6 wavefronts per SIMD instead of 7).
 struct Rest { float x[3]; };
 __device__ __forceinline__ bool holds_rest(uint32_t n, uint32_t base) {      // does this lane hold those elements?
     return base + TILE > n && (n & 3u) && (((n & ~3u) - base) & (CHUNK - 1u)) == threadIdx.x * VEC;

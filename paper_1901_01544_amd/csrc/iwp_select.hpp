@@ -4,10 +4,10 @@
 //
 // The selection is an MSB-first radix select on the 31-bit importance key
 // (digits of 12 + 10 + 9 bits).  Look 1 (iwp_stream.hpp) histograms the top digit
-// of every element and copies out, per tile, the elements that can be kept by the estimate of a
-// small sample (k_init).  Every tile owns a fixed slot in the staging arrays, so this needs no
+// of every element and copies out, per tile, the elements that can be kept by the caller's hint or by
+// the estimate of a small sample (k_init).  Every tile owns a fixed slot in the staging arrays, so this needs no
 // cross-workgroup coordination at all.  If b1, the bin that holds rank k, is not below the
-// sample's mark, the copies are complete and look 2 (k_stage) only reads the slots, to histogram the
+// mark, the copies are complete and look 2 (k_stage) only reads the slots, to histogram the
 // second digit of those inside b1; otherwise it reads the leader's residual and weights once
 // more and copies out the elements whose top digit is >= b1 (above b1 all of them are kept, the
 // threshold lies among those inside).  Everything after that works on the staged
@@ -196,8 +196,9 @@ __global__ __launch_bounds__(INIT_BLOCK, 8) void k_init(uint32_t* __restrict__ w
 // ---------------------------------------------------------------------------
 // First digit pick: the bin b1 of the 4096-bin histogram that holds rank k, whether look 1's copies already cover it.
 // On tables that the chip holds at one workgroup per tile (PICK_MAX_TILES), with at most two copies of a histogram, every
-// workgroup of look 2 redoes the pick of its layer itself: a launch less (235 k elements 46.4 -> 45.0 us a step, one layer of
-// a million 40.5 -> 39.5 us).  On larger ones that costs more than the launch (25.6 M elements: 18.8 us against
+// workgroup of look 2 redoes the pick of its layer itself: a launch less, 0.5 to 1.5 us of 31 to 56 us a call (six tensors
+// of 235 k elements, four workers 44.2 -> 42.7 us; 160 of 3 M elements, one worker 48.8 -> 47.2), nothing from 4 M elements
+// on.  On larger ones that costs more than the launch (25.6 M elements: 18.8 us against
 // 10.5 + 4.8), so one workgroup per layer adds the copies up in a launch of its own.  A summary
 // would have to be built with atomics on a handful of addresses that all
 // workgroups of look 1 hit (measured: look 1 nearly twice as slow).
@@ -282,12 +283,12 @@ __device__ __forceinline__ void scored_tile(const float* __restrict__ rl, const 
 
 // ---------------------------------------------------------------------------
 // Look 2: the second digit's histogram of the elements inside b1, and staged candidates
-// for the passes that follow.  The unit of work is a tile; a workgroup takes the tiles
-// blockIdx.x, blockIdx.x + gridDim.x, ... (the grid is capped: a launch of hundreds of
+// for the passes that follow.  The unit of work is a tile; a workgroup takes consecutive
+// tiles (the grid is capped: a launch of hundreds of
 // thousands of workgroups that mostly have nothing to do costs more than their work).
 //  * Look 1 already filled the layer's slots from a bin <= b1:
 //    only the slots are read, by the first tile's unit of every STAGE_GROUP tiles, into one
-//    LDS histogram that is flushed once.  In the steady state of a training run the
+//    LDS histogram that is flushed once per workgroup and layer.  In the steady state of a training run the
 //    threshold's bin holds about as many elements as are kept; that many single atomics per
 //    tile, or one flush per tile, would queue up on the histogram's few cache lines.  A tile
 //    whose candidates overflowed its slot in look 1 (RAW) is read again from r and w by its
