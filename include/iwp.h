@@ -216,8 +216,10 @@ int compress_segmented_static(const iwp_plan* plan, const float* w, const float*
  * which makes a second pass unnecessary; from which importance on, the library
  * takes from the hint on small tables, where it saves a tenth of the call, and
  * otherwise from a small sample of the layer (read-only, inside the call's first
- * launch) or from the hint if that lies lower (a layer whose sample misleads).  Where the copies turn out incomplete, and for
- * records that are wrong or garbage, the layer takes the two-pass route. */
+ * launch) or from the hint if that lies lower (a layer whose sample misleads).
+ * With a momentum below one, where thresholds move more from step to step, it is
+ * the sample unless the hint lies far lower.  Where the copies turn out incomplete,
+ * and for records that are wrong or garbage, the layer takes the two-pass route. */
 int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, float* const* r, uint32_t W,
                        const uint32_t* leader, const iwp_threshold* thr_hint, float eps, float scale,
                        uint32_t* idx_out, float* val_out, float* sum_out, iwp_threshold* thr_out,

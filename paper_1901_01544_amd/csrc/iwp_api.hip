@@ -207,7 +207,7 @@ SampleSource sample_from(const WorkerPtrs& P, const float* w, const uint32_t* le
 
 int launch_init(const Workspace& ws, uint32_t n_layers, uint32_t tiles, const iwp_threshold* hint, const DevLayer* layers,
                 const DevLayer* row, const DevLayer* sentinel, SampleSource S, hipStream_t s) {
-    if (hint && (tiles <= HINT_MAX_TILES || tiles / n_layers < STAGE_GROUP))
+    if (hint && S.P.momentum == 1.0f && (tiles <= HINT_MAX_TILES || tiles / n_layers < STAGE_GROUP))
         S.trust_hint = n_layers <= HINT_FEW_LAYERS ? TRUST_ALWAYS : TRUST_DENSE;
     uint32_t zero_blocks = (uint32_t)std::min<uint64_t>((ws.hist_words + 4 * INIT_BLOCK - 1) / (4 * INIT_BLOCK), 1024);
     if (zero_blocks == 0) zero_blocks = 1;
