@@ -310,16 +310,6 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
 
 constexpr uint32_t SMALL_MAX_N = SMALL_CHUNKS_MAX * SMALL_CHUNK;
 
-// Does k_small replace k_init, look 1 and the selection?  Where all layers have at most 32768 elements; beyond 16384 a
-// compute unit holds one layer at a time and nothing overlaps its loads with its barriers, so only up to 512 layers of more
-// than a tile with a hint, 1024 without (the long route samples then); the selection alone, which writes nothing, always.
-// Layers of 16385 elements, k_small against the long route: 512 hinted 69 / 72 us, 768 107 / 97; unhinted 1024 137 / 145,
-// 2048 253 / 243; of 32768: 114 / 119, 165 / 168, 213 / 212, 401 / 395; selection of 6000 layers of 16385 366 / 398.
-bool takes_small(uint32_t max_n, uint32_t n_long, bool hinted, bool select) {
-    if (max_n > SMALL_MAX_N) return false;
-    return select || max_n <= SMALL_MAX_N / 2 || n_long <= (hinted ? 512u : 1024u);
-}
-
 // Up to this many layers a table of short and long ones takes one launch: two workgroups of 16 wavefronts per compute unit.
 // Ragged tables, one launch / two: 300 layers 25.6 / 30.3 us, 512 28.1 / 31.6, 1000 45.5 / 31.9.
 constexpr uint32_t SMALL_ONE_LAUNCH = 512;
@@ -376,9 +366,24 @@ struct iwp_plan {
     uint32_t max_layer_stiles = 0;
     uint32_t max_n = 0;           // elements of the longest layer
     uint32_t n_long = 0;          // layers of more than one tile
+    bool all_dense = true;        // each of those keeps at least one element in HINT_KEEP
     uint32_t max_copies = 1;      // most copies of a layer's first-digit histogram
     float momentum = 1.0f;        // r <- momentum * r + g in every call that accumulates through this plan
 };
+
+// Does k_small replace k_init, look 1 and the selection?  Where all layers have at most 32768 elements; beyond 16384 a
+// compute unit holds one layer at a time and nothing overlaps its loads with its barriers, so only up to 512 layers of more
+// than a tile where the long route takes every mark from a hint (see HINT_BELOW), 1024 where it samples; the selection
+// alone, which writes nothing, always.
+// Layers of 16385 elements, k_small against the long route: 512 hinted 69 / 72 us, 768 107 / 97; unhinted 1024 137 / 145,
+// 2048 253 / 243; of 32768: 114 / 119, 165 / 168, 213 / 212, 401 / 395; selection of 6000 layers of 16385 366 / 398.
+// 700 layers of 17000 elements with a hint, kept at 0.004: k_small 86 / long route 105 us; at 1/64 92 / 84; at 1/64 and
+// momentum 0.9 92 / 102.
+bool takes_small(const iwp_plan& plan, bool hinted, bool select) {
+    if (plan.max_n > SMALL_MAX_N) return false;
+    const bool no_sample = hinted && plan.all_dense && plan.momentum == 1.0f;
+    return select || plan.max_n <= SMALL_MAX_N / 2 || plan.n_long <= (no_sample ? 512u : 1024u);
+}
 
 extern "C" {
 
@@ -532,6 +537,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     uint64_t pairs = 0, slots = 0, tiles = 0, stiles = 0, end = 0, mask_words = 0, hist_words = 0;
     bool any_k = false, all_k = true;
     uint32_t max_stiles = 0, max_n = 0, n_long = 0;
+    bool all_dense = true;
     for (uint32_t j = 0; j < n_layers; ++j) {
         const iwp_layer& L = layers[j];
         if (L.offset < 0 || L.k > L.n) return IWP_EINVAL;
@@ -563,6 +569,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
         max_stiles = std::max(max_stiles, stiles_of(L.n));
         max_n = std::max(max_n, L.n);
         n_long += L.n > TILE ? 1u : 0u;
+        if (L.n > TILE && (uint64_t)L.k * HINT_KEEP < L.n) all_dense = false;
         if (L.n > 0 && L.k == 0) all_k = false;
         if (pairs > 0xFFFFFFFFull || tiles > 0x7FFFFFFFull / IWP_MAX_WORKERS || hist_words > 0xFFFFFFFFull) return IWP_ERANGE;
     }
@@ -581,6 +588,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     plan->max_layer_stiles = max_stiles;
     plan->max_n = max_n;
     plan->n_long = n_long;
+    plan->all_dense = all_dense;
     for (const DevLayer& D : dev) plan->max_copies = std::max(plan->max_copies, D.h0_copies);
     plan->flat_end = end;
     // the table, then the layer of every tile and of every super-tile (find_layer reads them)
@@ -676,7 +684,7 @@ static int compress_segmented_on(const iwp_plan* plan, const float* w, const flo
     if (plan->z.tiles == 0) return IWP_OK;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     Table T{plan->dev, plan->z.n_layers, plan->z.tiles, plan->z.stiles, plan->z.pairs, plan->any_k, plan->max_layer_stiles, plan->max_copies};
-    const bool small = T.any_k && takes_small(plan->max_n, plan->n_long, thr_hint != nullptr, false);
+    const bool small = T.any_k && takes_small(*plan, thr_hint != nullptr, false);
     if (small) {
         rc = launch_small(T.layers, nullptr, T.n_layers, plan->n_long, plan->max_n, T.pairs, ws, P, w, leader, W, eps, FULL, false, idx_out,
                           val_out, thr_out, s);
@@ -734,7 +742,7 @@ int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, fl
     if (z.tiles == 0) return IWP_OK;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     Table T{plan->dev, z.n_layers, z.tiles, z.stiles, z.pairs, plan->any_k, plan->max_layer_stiles, plan->max_copies};
-    if (T.any_k && takes_small(plan->max_n, plan->n_long, thr_hint != nullptr, false)) {
+    if (T.any_k && takes_small(*plan, thr_hint != nullptr, false)) {
         rc = launch_small(T.layers, nullptr, T.n_layers, plan->n_long, plan->max_n, T.pairs, ws, P, w, leader, W, eps, FULL, true, idx_out,
                           val_out, thr_out, s);
         if (rc) return rc;
@@ -781,7 +789,7 @@ int select_threshold_segmented(const iwp_plan* plan, const float* w, const float
     memset(&P, 0, sizeof P);
     P.r[0] = const_cast<float*>(r);       // no gradient pointer: the residual is only read
     P.momentum = 1.0f;
-    if (takes_small(plan->max_n, plan->n_long, false, true))
+    if (takes_small(*plan, false, true))
         return launch_small(plan->dev, nullptr, plan->z.n_layers, plan->n_long, plan->max_n, plan->z.pairs, ws, P, w, nullptr, 1u, eps,
                             STOP_AT_THRESHOLD, false, nullptr, nullptr, thr_out, s);
     rc = launch_init(ws, plan->z.n_layers, plan->z.tiles, nullptr, plan->dev, nullptr, nullptr, sample_from(P, w, nullptr, 1u, eps), s);

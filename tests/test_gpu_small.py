@@ -91,6 +91,40 @@ def test_lines_of_the_longest_layers(gpu_lib, hint, layers):
     _steps(gpu_lib, [(16385, 300)] * layers + [(50, 3)], True, hint)
 
 
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("k,sparse,momentum,small", [(129, 0, 1.0, False), (128, 0, 1.0, True), (129, 1, 1.0, True), (129, 0, 0.9, True)])
+@pytest.mark.parametrize("fused", [False, True])
+def test_a_hint_moves_the_line_only_where_it_saves_samples(gpu_lib, k, sparse, momentum, small, fused):
+    """600 layers of 16385 elements with a hint: the long route only if every one of them keeps one in 128 and residuals do
+    not decay; the records and pairs of a call without a hint, which is k_small's, either way."""
+    import torch
+    iwp = gpu_lib
+    n, layers = 16385, 600
+    rows, out = [], 0
+    for j in range(layers):
+        rows.append((j * n, n, k - (sparse and j == 300), out))
+        out += rows[-1][2]
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    w, g, r0 = (torch.randn(n * layers, device="cuda", generator=gen) for _ in range(3))
+    plan = iwp.Plan(rows)
+    plan.set_momentum(momentum)
+    ws = torch.empty(plan.step_workspace_bytes(1), dtype=torch.uint8, device="cuda")
+    got, hint = [], None
+    for _ in range(2):
+        idx, val, total = torch.empty(out, dtype=torch.int32, device="cuda"), torch.empty(out, device="cuda"), torch.empty(out, device="cuda")
+        thr, r, wd = torch.zeros(3 * layers, dtype=torch.int32, device="cuda"), r0.clone(), w.clone()
+        iwp.timing_enable("k_small")
+        if fused:
+            iwp.step_segmented(plan, wd, [g], [r], None, 1e-8, -0.01, idx, val, total, thr, ws, thr_hint=hint)
+        else:
+            iwp.compress_segmented(plan, wd, [g], [r], None, 1e-8, idx, val, thr, ws, thr_hint=hint)
+        launches = iwp.timing_collect()[1]
+        assert (launches > 0) == (small or hint is None)
+        got.append([x.view(torch.int32) for x in (idx, val, thr, r, wd)])
+        hint = thr
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
 def test_thousands_of_tiny_layers(gpu_lib):
     """6000 layers of 150 elements beside one of 24 000 take at most four times as long as one layer of them all (1.9
     measured; 9.7 with a workgroup of 16 wavefronts for each)."""
