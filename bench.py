@@ -547,7 +547,8 @@ def main():
                     help="threshold route: also send sub-threshold elements with probability importance / threshold")
     ap.add_argument("--no-hint", action="store_true",
                     help="top-k routes, single workload: measure only without the previous step's thresholds as a "
-                         "hint (results are identical either way; a hint helps where a layer's sample misleads)")
+                         "hint (results are identical either way; a hint saves the sample on small tables and helps "
+                         "where a layer's sample misleads)")
     ap.add_argument("--hinted-only", action="store_true",
                     help="top-k routes, single workload: skip the unhinted measurement (for profiler runs)")
     ap.add_argument("--preroll", type=int, default=200,
