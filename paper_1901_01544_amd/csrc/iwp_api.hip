@@ -256,7 +256,7 @@ int launch_write(const Table& T, const Workspace& ws, const ResidualPtrs& R, con
                    ws.stage, ws.A, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, gathered,
                    T.pairs);
     } else {
-        IWP_LAUNCH("k_scan", k_scan, T.n_layers, s, T.layers, ws.stile_counts, false, nullptr);
+        IWP_LAUNCH("k_scan", k_scan, T.n_layers, s, T.layers, ws.stile_counts);
         IWP_LAUNCH("k_write", (k_write<FUSED, false>), grid, s, R, w, T.layers, T.n_layers, leader, W, eps, ws.state,
                    ws.stage, ws.A, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, gathered,
                    T.pairs);
@@ -827,29 +827,34 @@ int compact_pairs_segmented(const iwp_plan* plan, const float* w, const float* r
 namespace {
 
 struct ThresholdWorkspace {
-    uint32_t* lmask;          // n_lead * mask_words
-    uint2* tile_counts;       // tiles
-    uint2* stile_counts;      // stiles
-    uint32_t* tile_out;       // tiles
-    uint32_t* layer_total;    // n_layers
+    uint32_t* tile_counts;    // tiles
+    uint32_t* tile_pos;       // tiles
     uint32_t* lay_out;        // n_layers + 1
     double2* tile_stats;      // n_lead * tiles (layer-wise thresholds)
+    ChosenSlots slots;        // n_lead * tiles * cap
     float* gathered;          // W * max_pairs
     size_t bytes;
 };
+
+// Values per tile and chosen node that k_leader_mask hands over: four times what an average tile can send within the
+// caller's capacity, since layers differ, plus 64; at most 1024.  What a tile sends beyond that is fetched and cleared later.
+static uint32_t chosen_cap(const Sizes& z, uint32_t max_pairs) {
+    const uint64_t per_tile = z.tiles ? ((uint64_t)max_pairs + z.tiles - 1) / z.tiles : 0;
+    return (uint32_t)std::min<uint64_t>(1024, 64 + 4 * per_tile);
+}
 
 static ThresholdWorkspace carve_threshold(void* base, const Sizes& z, uint32_t W, uint32_t n_lead, uint32_t max_pairs) {
     ThresholdWorkspace ws;
     const uintptr_t b = reinterpret_cast<uintptr_t>(base);
     size_t off = 0;
     auto take = [&](size_t bytes) { uintptr_t p = b + off; off += round256(bytes); return p; };
-    ws.lmask = reinterpret_cast<uint32_t*>(take((size_t)n_lead * z.mask_words * sizeof(uint32_t)));
-    ws.tile_counts = reinterpret_cast<uint2*>(take((size_t)z.tiles * sizeof(uint2)));
-    ws.stile_counts = reinterpret_cast<uint2*>(take((size_t)z.stiles * sizeof(uint2)));
-    ws.tile_out = reinterpret_cast<uint32_t*>(take((size_t)z.tiles * sizeof(uint32_t)));
-    ws.layer_total = reinterpret_cast<uint32_t*>(take((size_t)z.n_layers * sizeof(uint32_t)));
+    ws.tile_counts = reinterpret_cast<uint32_t*>(take((size_t)z.tiles * sizeof(uint32_t)));
+    ws.tile_pos = reinterpret_cast<uint32_t*>(take((size_t)z.tiles * sizeof(uint32_t)));
     ws.lay_out = reinterpret_cast<uint32_t*>(take(((size_t)z.n_layers + 1) * sizeof(uint32_t)));
     ws.tile_stats = reinterpret_cast<double2*>(take((size_t)n_lead * z.tiles * sizeof(double2)));
+    ws.slots.cap = chosen_cap(z, max_pairs);
+    ws.slots.tiles = z.tiles;
+    ws.slots.val = reinterpret_cast<float*>(take((size_t)n_lead * z.tiles * ws.slots.cap * sizeof(float)));
     ws.gathered = reinterpret_cast<float*>(take((size_t)W * max_pairs * sizeof(float)));
     ws.bytes = off;
     return ws;
@@ -892,21 +897,26 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
                    rule->alpha, rule->beta, rule->C, reinterpret_cast<double2*>(rule->stats_out), rule->thr_out);
         thr = rule->thr_out;
     }
+#define IWP_MASK(NL)                                                                                                        \
+    IWP_LAUNCH("k_leader_mask", k_leader_mask<NL>, z.tiles, s, P, w, layers, z.n_layers, leaders, n_lead, W, thr, rule != nullptr, \
+               rule == nullptr, rs, eps, mask32, ws.tile_counts, ws.slots)
     if (z.tiles) {
-        IWP_LAUNCH("k_leader_mask", k_leader_mask, n_lead * z.tiles, s, P, w, layers, z.n_layers, z.tiles, leaders, n_lead, W,
-                   thr, rule != nullptr, rule == nullptr, rs, eps, ws.lmask, z.mask_words);
-        IWP_LAUNCH("k_mask_or_count", k_mask_or_count, z.stiles, s, layers, z.n_layers, leaders, n_lead, W, ws.lmask,
-                   z.mask_words, mask32, ws.tile_counts, ws.stile_counts);
+        if (n_lead == 1) IWP_MASK(1);
+        else if (n_lead == 2) IWP_MASK(2);
+        else if (n_lead == 3) IWP_MASK(3);
+        else IWP_MASK(0);
     }
-    IWP_LAUNCH("k_scan", k_scan, z.n_layers, s, layers, ws.stile_counts, true, ws.layer_total);
-    IWP_LAUNCH("k_layer_offsets", k_layer_offsets, 1u, s, ws.layer_total, z.n_layers, max_pairs, ws.lay_out, count_out);
+#undef IWP_MASK
+    IWP_LAUNCH_BLOCK("k_tile_offsets", k_tile_offsets, 1u, OFFSETS_BLOCK, s, layers, z.n_layers, z.tiles, ws.tile_counts, max_pairs,
+                     ws.tile_pos, ws.lay_out, count_out);
     if (z.tiles == 0) return IWP_OK;
-    IWP_LAUNCH("k_mask_emit", k_mask_emit, (z.tiles + 3) / 4, s, layers, z.n_layers, z.tiles, mask32, ws.tile_counts,
-               ws.stile_counts, ws.lay_out, count_out, max_pairs, ws.tile_out, idx_out);
     IWP_LAUNCH("k_follow_mask", k_follow_mask, W * z.tiles, s, P, layers, z.n_layers, z.tiles, leaders, n_lead, W, mask32,
-               ws.tile_out, ws.lay_out, count_out, max_pairs, ws.gathered);
+               ws.tile_counts, ws.tile_pos, count_out, max_pairs, ws.slots, idx_out, ws.gathered);
+    uint32_t static_mask = 0;
+    for (uint32_t p = 0; p < W; ++p)
+        if (!g[p]) static_mask |= 1u << p;
     const uint32_t pair_blocks = std::min<uint32_t>((max_pairs + BLOCK - 1) / BLOCK, 8192u);
-    IWP_LAUNCH("k_reduce_update_counted", k_reduce_update_counted, pair_blocks, s, P, layers, z.n_layers, leaders, n_lead, W,
+    IWP_LAUNCH("k_reduce_update_counted", k_reduce_update_counted, pair_blocks, s, R, static_mask, z.n_layers, leaders, n_lead, W,
                ws.lay_out, count_out, max_pairs, ws.gathered, idx_out, w, scale, sum_out, plan->flat_end);
     return IWP_OK;
 }

@@ -348,40 +348,65 @@ __device__ __forceinline__ uint32_t bitmap_rank(const uint32_t* map, const uint3
     return prefix[wd] + __popc(map[wd] & ((1u << b) - 1u));
 }
 
+// Of a tile's marked elements, how many stand before each lane's quads.  n[u]: marked elements (0 to 4) in the lane's quad of
+// chunk u (the lane's elements are consecutive, chunks follow each other); first[u]: marked ones of the tile before that
+// quad.  Returns the tile's total.  All 256 threads call it; `slot`: STAGE_WORDS words of LDS, not to be used again before
+// the next __syncthreads().
+constexpr uint32_t STAGE_WORDS = 2 * BLOCK / WAVE;
+template <uint32_t CHUNKS>
+__device__ __forceinline__ uint32_t tile_ranks(const uint32_t (&n)[CHUNKS], uint32_t (&first)[CHUNKS], uint32_t* slot) {
+    static_assert(CHUNKS <= 4 && CHUNK < 65536, "two chunks' counts in one word");
+    constexpr uint32_t PAIRS = (CHUNKS + 1) / 2;
+    const uint32_t lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
+    uint32_t c[PAIRS] = {}, inc[PAIRS], before[PAIRS], tot[PAIRS];
+#pragma unroll
+    for (uint32_t u = 0; u < CHUNKS; ++u) c[u / 2] += n[u] << (16 * (u % 2));
+#pragma unroll
+    for (uint32_t h = 0; h < PAIRS; ++h) {
+        inc[h] = wave_inclusive_scan(c[h]);
+        if (lane == WAVE - 1) slot[PAIRS * wave + h] = inc[h];
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t h = 0; h < PAIRS; ++h) {
+        before[h] = inc[h] - c[h];
+        tot[h] = 0;
+#pragma unroll
+        for (uint32_t v = 0; v < BLOCK / WAVE; ++v) {
+            const uint32_t x = slot[PAIRS * v + h];
+            before[h] += v < wave ? x : 0u;
+            tot[h] += x;
+        }
+    }
+    uint32_t done = 0;                                       // of the chunks so far
+#pragma unroll
+    for (uint32_t u = 0; u < CHUNKS; ++u) {
+        first[u] = done + (before[u / 2] >> (16 * (u % 2)) & 0xffffu);
+        done += tot[u / 2] >> (16 * (u % 2)) & 0xffffu;
+    }
+    return done;
+}
+
 // Copy the elements of one tile whose key is >= from into the tile's slot,
 // in index order, so that the ordered split can rank a slot's entries by their place in it.  key[u][q] / val[u][q]: the
 // lane's element q of chunk u (the lane's elements are consecutive, chunks follow each other), NOT_AN_ELEMENT past
 // the layer's end.  Returns the number of copies, or RAW_TILE if they exceed the
 // slot (then nothing is written).  All 256 threads call it; `slot`: STAGE_WORDS words of LDS, not to be used again
 // before the next __syncthreads().
-constexpr uint32_t STAGE_WORDS = 2 * BLOCK / WAVE;
 __device__ __forceinline__ uint32_t stage_tile(const uint32_t (&key)[CHUNKS_PER_TILE][4],
                                                const float (&val)[CHUNKS_PER_TILE][4], uint32_t base, uint32_t from,
                                                uint32_t cap, uint64_t sb, const StageArrays& A, uint32_t* slot) {
-    static_assert(CHUNKS_PER_TILE == 4 && CHUNK < 65536, "two chunks' counts in one word");
-    const uint32_t lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
-    uint32_t c[2] = {0u, 0u};                                // counts of chunks 0, 1 and of chunks 2, 3
+    uint32_t n[CHUNKS_PER_TILE], first[CHUNKS_PER_TILE], any = 0u;
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+        n[u] = 0u;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            c[u / 2] += (key[u][q] != NOT_AN_ELEMENT && key[u][q] >= from) ? 1u << (16 * (u % 2)) : 0u;
-    const uint32_t i0 = wave_inclusive_scan(c[0]), i1 = wave_inclusive_scan(c[1]);
-    if (lane == WAVE - 1) { slot[2 * wave] = i0; slot[2 * wave + 1] = i1; }
-    __syncthreads();
-    uint32_t b0 = i0 - c[0], b1 = i1 - c[1], t0 = 0, t1 = 0;
-#pragma unroll
-    for (uint32_t v = 0; v < BLOCK / WAVE; ++v) {
-        const uint32_t s0 = slot[2 * v], s1 = slot[2 * v + 1];
-        b0 += v < wave ? s0 : 0u;
-        b1 += v < wave ? s1 : 0u;
-        t0 += s0;
-        t1 += s1;
+        for (int q = 0; q < 4; ++q) n[u] += (key[u][q] != NOT_AN_ELEMENT && key[u][q] >= from) ? 1u : 0u;
+        any |= n[u];
     }
-    const uint32_t n0 = t0 & 0xffffu, n01 = n0 + (t0 >> 16), n012 = n01 + (t1 & 0xffffu), tot = n012 + (t1 >> 16);
+    const uint32_t tot = tile_ranks(n, first, slot);
     if (tot > cap) return RAW_TILE;
-    const uint32_t first[CHUNKS_PER_TILE] = {b0 & 0xffffu, n0 + (b0 >> 16), n01 + (b1 & 0xffffu), n012 + (b1 >> 16)};
-    if (c[0] | c[1]) {
+    if (any) {
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
             uint32_t o = first[u];

@@ -33,6 +33,13 @@ __device__ __forceinline__ bool chosen_before(const uint32_t* __restrict__ leade
     return false;
 }
 
+// Where k_leader_mask leaves the sent values of the chosen nodes, in index order: the tile's slot of the node in slot q of
+// its layer is val[(q * tiles + tile) * cap, + cap).  A tile that sends more than cap elements leaves none.
+struct ChosenSlots {
+    float* val;
+    uint32_t cap, tiles;
+};
+
 // Status words at the end of count_out: [n_layers] = total pairs, [n_layers + 1] = 1 if
 // the total exceeds the caller's capacity (then nothing is exchanged).
 __device__ __forceinline__ bool overflowed(const uint32_t* __restrict__ count_out, uint32_t n_layers) {
@@ -65,13 +72,179 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
     out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
+// The tile that starts at element `base` of its layer, CHUNKS chunks of it, for all chosen nodes of the layer: accumulate,
+// score, compare, encode, and hand over what is sent.  Layers that end within a tile's first chunk take one chunk only, which
+// spares them three quarters of the divides (and draws).  NL: the nodes whose values stay in registers until the common mask
+// is known (n_lead); 0: any number of nodes one after the other, whose sent values are fetched again from what was just stored.
+template <uint32_t CHUNKS, int NL>
+__device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __restrict__ wl, const DevLayer& L, uint32_t j,
+                                          uint32_t t, uint32_t base, const uint32_t* __restrict__ leaders, uint32_t n_lead,
+                                          uint32_t W, const float* __restrict__ thr, bool thr_per_slot, bool accumulate,
+                                          const RandomSel& rs, float eps, uint32_t* __restrict__ mw,
+                                          uint32_t* __restrict__ tile_counts, const ChosenSlots& S, uint32_t* part) {
+    constexpr int KEPT = NL ? NL : 1;
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const uint32_t n = L.n, nwords = (n + 31) / 32;
+    float wv[CHUNKS][4], rv[KEPT][CHUNKS][4], gv[KEPT][CHUNKS][4];
+    Rest wv_rest, rv_rest[KEPT], gv_rest[KEPT];
+    float* rl[KEPT];
+    const float* gl[KEPT];
+    float th[KEPT];
+    bool on[KEPT];
+    uint32_t nib[CHUNKS] = {};
+    request_tile<true>(wl, n, base, wv, wv_rest);
+    auto request = [&](int s, uint32_t q) {                  // node in slot q of the layer -> registers s
+        const uint32_t p = chosen_at(leaders, n_lead, j, q, W);
+        on[s] = !chosen_before(leaders, n_lead, j, q, W, p);
+        th[s] = thr_per_slot ? thr[(size_t)j * n_lead + q] : thr[j];
+        rl[s] = P.r[p] + L.offset;
+        gl[s] = accumulate && P.g[p] ? P.g[p] + L.offset : nullptr;
+        if (!on[s]) return;
+        request_tile<true>(rl[s], n, base, rv[s], rv_rest[s]);
+        if (gl[s]) request_tile<true>(gl[s], n, base, gv[s], gv_rest[s]);
+    };
+    auto settle = [&](int s) {
+        if (!on[s]) return;
+        settle_tile(n, base, rv[s], rv_rest[s]);
+        if (!gl[s]) return;
+        settle_tile(n, base, gv[s], gv_rest[s]);
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) rv[s][u][c] = accum(rv[s][u][c], gv[s][u][c], P.momentum);
+    };
+    auto mark = [&](int s0, int s1) {                        // the elements that one of the nodes in registers sends
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS; ++u) {
+            const uint32_t i = base + u * CHUNK + tid * VEC;
+            uint32_t word4[4] = {0u, 0u, 0u, 0u};
+            if (rs.on) philox4x32_10(i >> 2, j, rs.step0, rs.step1, rs.key0, rs.key1, word4);   // i is a multiple of 4
+#pragma unroll
+            for (int s = s0; s < s1; ++s) {
+                if (!on[s]) continue;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float score = fabsf(rv[s][u][c]) / (fabsf(wv[u][c]) + eps);
+                    bool send = score > th[s];
+                    if (rs.on) {
+                        const float draw = (float)(word4[c] >> 8) * 0x1p-24f;
+                        const float prob = score / th[s];
+                        send = send || draw < prob;
+                    }
+                    if (i + c < n && send) nib[u] |= 1u << c;
+                }
+            }
+        }
+    };
+    if (NL) {
+#pragma unroll
+        for (int q = 0; q < NL; ++q) request(q, q);
+        settle_tile(n, base, wv, wv_rest);
+#pragma unroll
+        for (int q = 0; q < NL; ++q) settle(q);
+        mark(0, NL);
+    } else {
+        for (uint32_t q = 0; q < n_lead; ++q) {
+            request(0, q);
+            if (q == 0) settle_tile(n, base, wv, wv_rest);
+            settle(0);
+            mark(0, 1);
+            if (on[0] && gl[0]) store_tile<true>(rl[0], n, base, rv[0]);
+        }
+    }
+    uint32_t count[CHUNKS], first[CHUNKS], word[CHUNKS];
+#pragma unroll
+    for (uint32_t u = 0; u < CHUNKS; ++u) {
+        // eight lanes (32 consecutive elements) make one word of the encoded mask
+        word[u] = nib[u] << (4u * (lane & 7u));
+        word[u] |= __shfl_xor(word[u], 1, WAVE);
+        word[u] |= __shfl_xor(word[u], 2, WAVE);
+        word[u] |= __shfl_xor(word[u], 4, WAVE);
+        const uint32_t widx = base / 32 + u * (CHUNK / 32) + (tid >> 3);
+        if ((lane & 7u) == 0u && widx < nwords) mw[widx] = word[u];
+        count[u] = __popc(nib[u]);
+    }
+    const uint32_t total = tile_ranks(count, first, part);
+    if (tid == 0) tile_counts[t] = total;
+    const bool hand_over = total <= S.cap;                   // otherwise k_follow_mask fetches and clears them
+    if (NL) {
+#pragma unroll
+        for (int q = 0; q < NL; ++q) {
+            if (!on[q]) continue;
+            float* slot = S.val + ((size_t)q * S.tiles + t) * S.cap;
+#pragma unroll
+            for (uint32_t u = 0; u < CHUNKS; ++u) {
+                if (!hand_over || !nib[u]) continue;
+                uint32_t rank = first[u];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if ((nib[u] >> c) & 1u) { slot[rank++] = rv[q][u][c]; rv[q][u][c] = 0.0f; }
+            }
+            // a node that has not been accumulated here: only what holds a sent element, in whole lines of 32 elements
+            // (single elements, partial lines, take 63 us instead of 49 where one of 59 of 25.6 M elements is sent)
+#pragma unroll
+            for (uint32_t u = 0; u < CHUNKS; ++u)
+                if (gl[q] || (hand_over && word[u])) store_quad<true>(rl[q], base + u * CHUNK + tid * VEC, n, rv[q][u]);
+        }
+    } else if (hand_over) {
+        for (uint32_t q = 0; q < n_lead; ++q) {
+            const uint32_t p = chosen_at(leaders, n_lead, j, q, W);
+            if (chosen_before(leaders, n_lead, j, q, W, p)) continue;
+            float* r = P.r[p] + L.offset;
+            float* slot = S.val + ((size_t)q * S.tiles + t) * S.cap;
+#pragma unroll
+            for (uint32_t u = 0; u < CHUNKS; ++u) {
+                uint32_t rank = first[u];
+                for (uint32_t b = nib[u]; b; b &= b - 1u) {
+                    const uint32_t i = base + u * CHUNK + tid * VEC + (uint32_t)__ffs(b) - 1u;
+                    slot[rank++] = r[i];
+                    r[i] = 0.0f;
+                }
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Chosen nodes, one workgroup per tile for all of them: accumulate (if asked), score, compare, encode the OR of their masks
+// (an output), count its bits, and split the nodes' residuals by it: the sent values go into a slot of the tile and +0 is
+// left behind, as long as the slot holds them (S.cap; the packed position is only known once all tiles are counted).  If the
+// total then exceeds the caller's capacity, k_follow_mask puts them back.
+// thr: one value per layer, or per (layer, slot) with thr_per_slot.
+// Bound by memory (two nodes, 61 M elements: 1.71 GB in 270 us, 6.3 TB/s).  A workgroup per node and tile read the weights
+// once per node and left a mask for each, to be OR-ed and counted in a launch of its own (308 + 9 us), and the nodes' sent
+// values were read and cleared pair by pair behind everything else (the update 177 us, now 66).  Whole steps: that table
+// 1208 -> 1077 us, one node of 25.6 M elements with a line per layer 554 -> 522, three of 1.1 M 38 -> 29 (three launches less).
+// ---------------------------------------------------------------------------
+template <int NL>
+__global__ __launch_bounds__(BLOCK) void k_leader_mask(WorkerPtrs P, const float* __restrict__ w,
+                                                       const DevLayer* __restrict__ layers, uint32_t n_layers,
+                                                       const uint32_t* __restrict__ leaders, uint32_t n_lead, uint32_t W,
+                                                       const float* __restrict__ thr, bool thr_per_slot, bool accumulate,
+                                                       RandomSel rs, float eps, uint32_t* __restrict__ mask_out,
+                                                       uint32_t* __restrict__ tile_counts, ChosenSlots S) {
+    __shared__ uint32_t part[STAGE_WORDS];
+    const uint32_t t = blockIdx.x;
+    const uint32_t j = find_layer<false>(layers, n_layers, t);
+    const DevLayer L = layers[j];
+    const uint32_t base = (t - L.tile_begin) * TILE;
+    const float* wl = w + L.offset;
+    uint32_t* mw = mask_out + L.mask_begin;
+    if (L.n - base <= CHUNK)
+        mask_tile<1, NL>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, rs, eps, mw, tile_counts, S,
+                         part);
+    else
+        mask_tile<CHUNKS_PER_TILE, NL>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, rs, eps, mw,
+                                       tile_counts, S, part);
+}
+
 // One tile of a chosen node in registers: residual (after adding the gradient and storing
 // it back when gp is set) and weights, 16 values per lane; positions past the layer's end hold
 // values that are not meant for use.
-template <uint32_t CHUNKS>
 __device__ __forceinline__ void chosen_tile(const float* gp, float* rl, const float* gl, const float* wl, float m,
-                                            uint32_t n, uint32_t base, float (&rv)[CHUNKS][4], float (&wv)[CHUNKS][4]) {
-    float gv[CHUNKS][4];
+                                            uint32_t n, uint32_t base, float (&rv)[CHUNKS_PER_TILE][4],
+                                            float (&wv)[CHUNKS_PER_TILE][4]) {
+    float gv[CHUNKS_PER_TILE][4];
     Rest rv_rest, gv_rest, wv_rest;
     request_tile<true>(rl, n, base, rv, rv_rest);
     if (gp) request_tile<true>(gl, n, base, gv, gv_rest);
@@ -81,75 +254,11 @@ __device__ __forceinline__ void chosen_tile(const float* gp, float* rl, const fl
     if (gp) {
         settle_tile(n, base, gv, gv_rest);
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS; ++u)
+        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
 #pragma unroll
             for (int c = 0; c < 4; ++c) rv[u][c] = accum(rv[u][c], gv[u][c], m);
         store_tile<true>(rl, n, base, rv);
     }
-}
-
-// The tile of a chosen node that starts at element `base` of its layer, CHUNKS chunks of it: accumulate (gp), score, compare,
-// encode.  Layers that end within a tile's first chunk take one chunk only, which spares them three quarters of the divides
-// (and draws): 903 layers of 55 elements 7.3 -> 6.2 us, the pass of the three other nodes below 8.8 -> 7.4 us.
-template <uint32_t CHUNKS>
-__device__ __forceinline__ void mask_tile(const float* gp, float* rl, const float* wl, const DevLayer& L, uint32_t j,
-                                          uint32_t base, float m, float th, const RandomSel& rs, float eps,
-                                          uint32_t* __restrict__ mw) {
-    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1);
-    const uint32_t nwords = (L.n + 31) / 32;
-    float rv[CHUNKS][4], wv[CHUNKS][4];
-    chosen_tile(gp, rl, gp ? gp + L.offset : nullptr, wl, m, L.n, base, rv, wv);
-#pragma unroll
-    for (uint32_t u = 0; u < CHUNKS; ++u) {
-        const uint32_t i = base + u * CHUNK + tid * VEC;
-        uint32_t nib = 0;
-        uint32_t word4[4] = {0u, 0u, 0u, 0u};
-        if (rs.on) philox4x32_10(i >> 2, j, rs.step0, rs.step1, rs.key0, rs.key1, word4);   // i is a multiple of 4
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float s = fabsf(rv[u][c]) / (fabsf(wv[u][c]) + eps);
-            bool send = s > th;
-            if (rs.on) {
-                const float draw = (float)(word4[c] >> 8) * 0x1p-24f;
-                const float prob = s / th;
-                send = send || draw < prob;
-            }
-            if (i + c < L.n && send) nib |= 1u << c;
-        }
-        // eight lanes (32 consecutive elements) make one word of the encoded mask
-        uint32_t word = nib << (4u * (lane & 7u));
-        word |= __shfl_xor(word, 1, WAVE);
-        word |= __shfl_xor(word, 2, WAVE);
-        word |= __shfl_xor(word, 4, WAVE);
-        const uint32_t widx = base / 32 + u * (CHUNK / 32) + (tid >> 3);
-        if ((lane & 7u) == 0u && widx < nwords) mw[widx] = word;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Chosen nodes: accumulate (if asked), score, compare, encode.  Grid: n_lead * tiles.
-// A node that appears in an earlier slot of the same layer is skipped (same mask).
-// lmask: n_lead masks of mask_words words each, laid out like the final mask.
-// thr: one value per layer, or per (layer, slot) with thr_per_slot.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_leader_mask(WorkerPtrs P, const float* __restrict__ w,
-                                                       const DevLayer* __restrict__ layers, uint32_t n_layers,
-                                                       uint32_t tiles, const uint32_t* __restrict__ leaders,
-                                                       uint32_t n_lead, uint32_t W, const float* __restrict__ thr,
-                                                       bool thr_per_slot, bool accumulate, RandomSel rs, float eps,
-                                                       uint32_t* __restrict__ lmask, uint64_t mask_words) {
-    const uint32_t q = blockIdx.x / tiles;
-    const uint32_t t = blockIdx.x - q * tiles;
-    const uint32_t j = find_layer<false>(layers, n_layers, t);
-    const DevLayer L = layers[j];
-    const uint32_t p = chosen_at(leaders, n_lead, j, q, W);
-    if (chosen_before(leaders, n_lead, j, q, W, p)) return;
-    const uint32_t base = (t - L.tile_begin) * TILE;
-    const float* gp = accumulate ? P.g[p] : nullptr;
-    const float th = thr_per_slot ? thr[(size_t)j * n_lead + q] : thr[j];
-    uint32_t* mw = lmask + (size_t)q * mask_words + L.mask_begin;
-    if (L.n - base <= CHUNK) mask_tile<1>(gp, P.r[p] + L.offset, w + L.offset, L, j, base, P.momentum, th, rs, eps, mw);
-    else mask_tile<CHUNKS_PER_TILE>(gp, P.r[p] + L.offset, w + L.offset, L, j, base, P.momentum, th, rs, eps, mw);
 }
 
 // ---------------------------------------------------------------------------
@@ -253,154 +362,101 @@ __global__ __launch_bounds__(BLOCK) void k_layer_thr(const DevLayer* __restrict_
 }
 
 // ---------------------------------------------------------------------------
-// OR of the chosen nodes' masks -> the layer's mask (an output), and how many bits
-// each tile holds.  One workgroup per super-tile, one wavefront per tile.
+// The tiles' counts -> where each tile's pairs start in the packed outputs (layers in table order), where each layer's do
+// (lay_out[j], lay_out[n_layers] = total), the counts the caller sees, and the capacity check.  One workgroup, four quads of
+// tiles per lane and round: a chain of one load, a scan and a store per 16384 tiles (5.3 us; sixteen dwords per lane, not
+// coalesced, 15.5).  Both arrays hold whole 256-byte blocks.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_mask_or_count(const DevLayer* __restrict__ layers, uint32_t n_layers,
-                                                         const uint32_t* __restrict__ leaders, uint32_t n_lead,
-                                                         uint32_t W, const uint32_t* __restrict__ lmask,
-                                                         uint64_t mask_words, uint32_t* __restrict__ mask_out,
-                                                         uint2* __restrict__ tile_counts,
-                                                         uint2* __restrict__ stile_counts) {
-    __shared__ uint32_t cg[GROUP];
+constexpr int OFFSETS_BLOCK = 1024;
+__global__ __launch_bounds__(OFFSETS_BLOCK) void k_tile_offsets(const DevLayer* __restrict__ layers, uint32_t n_layers,
+                                                                uint32_t tiles, const uint32_t* __restrict__ tile_counts,
+                                                                uint32_t max_pairs, uint32_t* tile_pos,
+                                                                uint32_t* __restrict__ lay_out,
+                                                                uint32_t* __restrict__ count_out) {
+    constexpr uint32_t PER = 4, STEP = OFFSETS_BLOCK * 4, WAVES = OFFSETS_BLOCK / WAVE;
+    __shared__ uint32_t wave_sum[2][PER][WAVES];
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
-    const uint32_t s = blockIdx.x;
-    const uint32_t j = find_layer<true>(layers, n_layers, s);
-    const DevLayer L = layers[j];
-    const uint32_t ntiles = (L.n + TILE - 1) / TILE;
-    const uint32_t nwords = (L.n + 31) / 32;
-    const uint32_t lt0 = (s - L.stile_begin) * GROUP;
-    const uint32_t nt = min(GROUP, ntiles - lt0);
-    for (uint32_t tl = wave; tl < nt; tl += BLOCK / WAVE) {
-        uint32_t c = 0;
+    uint32_t total = 0;
+    for (uint32_t b = 0, round = 0; b < tiles; b += STEP * PER, ++round) {
+        uint4 v[PER];
+        uint32_t sum[PER], inc[PER];
 #pragma unroll
-        for (uint32_t h = 0; h < 2; ++h) {
-            const uint32_t widx = (lt0 + tl) * TILE_WORDS + 2 * lane + h;
-            if (widx < nwords) {
-                uint32_t wd = 0;
-                for (uint32_t q = 0; q < n_lead; ++q) {
-                    const uint32_t p = chosen_at(leaders, n_lead, j, q, W);
-                    if (!chosen_before(leaders, n_lead, j, q, W, p)) wd |= lmask[(size_t)q * mask_words + L.mask_begin + widx];
-                }
-                mask_out[L.mask_begin + widx] = wd;
-                c += __popc(wd);
-            }
+        for (uint32_t x = 0; x < PER; ++x) {
+            const uint32_t t0 = b + x * STEP + tid * 4;
+            v[x] = t0 < tiles ? *reinterpret_cast<const uint4*>(tile_counts + t0) : make_uint4(0u, 0u, 0u, 0u);
+            if (t0 + 1 >= tiles) v[x].y = 0u;                // what lies behind the last tile's count
+            if (t0 + 2 >= tiles) v[x].z = 0u;
+            if (t0 + 3 >= tiles) v[x].w = 0u;
         }
+        auto& ws = wave_sum[round & 1u];                     // the round before may still be reading the other
 #pragma unroll
-        for (int d = WAVE / 2; d > 0; d >>= 1) c += __shfl_xor(c, d, WAVE);
-        if (lane == 0) cg[tl] = c;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t G = 0;
-        for (uint32_t tl = 0; tl < nt; ++tl) {
-            tile_counts[L.tile_begin + lt0 + tl] = make_uint2(G, 0u);
-            G += cg[tl];
+        for (uint32_t x = 0; x < PER; ++x) {
+            sum[x] = v[x].x + v[x].y + v[x].z + v[x].w;
+            inc[x] = wave_inclusive_scan(sum[x]);
+            if (lane == WAVE - 1) ws[x][wave] = inc[x];
         }
-        stile_counts[s] = make_uint2(G, 0u);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Layer totals -> where each layer's pairs start in the packed outputs, the counts
-// the caller sees, and the capacity check.  One workgroup.
-// lay_out[j] = first pair of layer j, lay_out[n_layers] = total.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_layer_offsets(const uint32_t* __restrict__ layer_total, uint32_t n_layers,
-                                                         uint32_t max_pairs, uint32_t* __restrict__ lay_out,
-                                                         uint32_t* __restrict__ count_out) {
-    __shared__ uint32_t slot[4];
-    uint32_t carry = 0;
-    for (uint32_t b = 0; b < n_layers; b += BLOCK) {
-        const uint32_t j = b + threadIdx.x;
-        const uint32_t v = j < n_layers ? layer_total[j] : 0u;
-        uint32_t tot;
-        const uint32_t ex = block_exclusive_scan(v, slot, &tot);
-        if (j < n_layers) {
-            lay_out[j] = carry + ex;
-            count_out[j] = v;
-        }
-        carry += tot;
         __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        lay_out[n_layers] = carry;
-        count_out[n_layers] = carry;
-        count_out[n_layers + 1] = carry > max_pairs ? 1u : 0u;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// The masked positions as ascending flat indices, layers packed in table order.
-// One wavefront per tile; tile_out[t] = first pair of the tile inside its layer.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_mask_emit(const DevLayer* __restrict__ layers, uint32_t n_layers,
-                                                     uint32_t tiles_total, const uint32_t* __restrict__ mask,
-                                                     const uint2* __restrict__ tile_counts,
-                                                     const uint2* __restrict__ stile_counts,
-                                                     const uint32_t* __restrict__ lay_out,
-                                                     const uint32_t* __restrict__ count_out, uint32_t max_pairs,
-                                                     uint32_t* __restrict__ tile_out, uint32_t* __restrict__ idx_out) {
-    const uint32_t lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
-    const uint32_t t = blockIdx.x * (BLOCK / WAVE) + wave;
-    if (t >= tiles_total) return;
-    const uint32_t j = find_layer<false>(layers, n_layers, t);
-    const DevLayer L = layers[j];
-    const uint32_t lt = t - L.tile_begin;
-    const uint32_t in_layer = stile_counts[L.stile_begin + lt / GROUP].x + tile_counts[t].x;
-    if (lane == 0) tile_out[t] = in_layer;
-    if (overflowed(count_out, n_layers)) return;
-    const uint32_t nwords = (L.n + 31) / 32;
-    uint32_t wd[2];
 #pragma unroll
-    for (uint32_t h = 0; h < 2; ++h) {
-        const uint32_t widx = lt * TILE_WORDS + 2 * lane + h;
-        wd[h] = widx < nwords ? mask[L.mask_begin + widx] : 0u;
-    }
-    const uint32_t c = __popc(wd[0]) + __popc(wd[1]);
-    uint32_t pos = lay_out[j] + in_layer + wave_inclusive_scan(c) - c;
-    const uint32_t first = (uint32_t)L.offset + lt * TILE + 2 * lane * 32;
+        for (uint32_t x = 0; x < PER; ++x) {
+            uint32_t pos = total + inc[x] - sum[x];
 #pragma unroll
-    for (uint32_t h = 0; h < 2; ++h) {
-        uint32_t m = wd[h];
-        while (m) {
-            const uint32_t b = __ffs(m) - 1;
-            if (pos < max_pairs) idx_out[pos] = first + h * 32 + b;
-            ++pos;
-            m &= m - 1;
+            for (uint32_t y = 0; y < WAVES; ++y) {
+                pos += y < wave ? ws[x][y] : 0u;
+                total += ws[x][y];
+            }
+            const uint32_t t0 = b + x * STEP + tid * 4;
+            if (t0 < tiles)
+                *reinterpret_cast<uint4*>(tile_pos + t0) =
+                    make_uint4(pos, pos + v[x].x, pos + v[x].x + v[x].y, pos + v[x].x + v[x].y + v[x].z);
         }
+    }
+    __syncthreads();                                         // tile_pos is complete
+    for (uint32_t j = tid; j < n_layers; j += OFFSETS_BLOCK) {
+        const uint32_t f = layers[j].tile_begin, e = layers[j + 1].tile_begin;   // the sentinel row's is `tiles`
+        const uint32_t first = f < tiles ? tile_pos[f] : total, end = e < tiles ? tile_pos[e] : total;
+        lay_out[j] = first;
+        count_out[j] = end - first;
+    }
+    if (tid == 0) {
+        lay_out[n_layers] = total;
+        count_out[n_layers] = total;
+        count_out[n_layers + 1] = total > max_pairs ? 1u : 0u;
     }
 }
 
 // ---------------------------------------------------------------------------
 // Every node that is not chosen for the layer and has a gradient: accumulate, and
 // where the tile's mask has bits, copy the accumulated value into the node's gather
-// row and leave +0 behind.  Grid: W * tiles.
+// row and leave +0 behind.  Grid: W * tiles.  The workgroups of the chosen nodes, whose
+// residuals k_leader_mask has been through, have nothing to stream: those of the first one write the
+// tile's masked positions as ascending flat indices and move the sent values of all of them from the tile's
+// slots to their gather rows.
 // ---------------------------------------------------------------------------
-// The tile of such a node, CHUNKS chunks of it (see mask_tile).  row_out: the node's row of the gather matrix; map, pre, slot:
-// LDS of TILE_WORDS, TILE_WORDS and 4 words.
+// The tile's mask in LDS (no bits without an exchange) and the number of bits before each word; returns all bits.
+// map, pre, slot: LDS of TILE_WORDS, TILE_WORDS and 4 words.
+__device__ __forceinline__ void tile_mask(const uint32_t* __restrict__ mask, const DevLayer& L, uint32_t base, bool wanted,
+                                          uint32_t* map, uint32_t* pre, uint32_t* slot) {
+    const uint32_t tid = threadIdx.x, nwords = (L.n + 31) / 32;
+    if (tid < TILE_WORDS) {
+        const uint32_t widx = base / 32 + tid;
+        map[tid] = (wanted && widx < nwords) ? mask[L.mask_begin + widx] : 0u;
+    }
+    __syncthreads();
+    bitmap_prefix(map, pre, slot);
+}
+
+// The tile of a node that streams, CHUNKS chunks of it (see mask_tile).  row: the tile's first entry in the node's row of the
+// gather matrix, room: entries from there to the row's end.
 template <uint32_t CHUNKS>
-__device__ __forceinline__ void follow_tile(const float* gl, float* rl, const DevLayer& L, uint32_t j, uint32_t t, uint32_t base,
-                                            float m, uint32_t n_layers, const uint32_t* __restrict__ mask,
-                                            const uint32_t* __restrict__ tile_out, const uint32_t* __restrict__ lay_out,
-                                            const uint32_t* __restrict__ count_out, uint32_t max_pairs, float* row_out,
-                                            uint32_t* map, uint32_t* pre, uint32_t* slot) {
+__device__ __forceinline__ void follow_tile(const float* gl, float* rl, const DevLayer& L, uint32_t base, float m, bool exchange,
+                                            const uint32_t* __restrict__ mask, float* row, uint32_t room, uint32_t* map,
+                                            uint32_t* pre, uint32_t* slot) {
     const uint32_t tid = threadIdx.x;
     float rv[CHUNKS][4], gv[CHUNKS][4];
     Rest rv_rest, gv_rest;
     request_tile<true>(rl, L.n, base, rv, rv_rest);
     request_tile<true>(gl, L.n, base, gv, gv_rest);
-    const bool exchange = !overflowed(count_out, n_layers);
-    const uint32_t nwords = (L.n + 31) / 32;
-    if (tid < TILE_WORDS) {
-        const uint32_t widx = base / 32 + tid;
-        map[tid] = (exchange && widx < nwords) ? mask[L.mask_begin + widx] : 0u;
-    }
-    __syncthreads();
-    bitmap_prefix(map, pre, slot);
-    const uint64_t row = (uint64_t)lay_out[j] + tile_out[t];
-    float* go = row_out + min(row, (uint64_t)max_pairs);
-    const uint32_t room = (uint32_t)((uint64_t)max_pairs - min(row, (uint64_t)max_pairs));
+    tile_mask(mask, L, base, exchange, map, pre, slot);
     settle_tile(L.n, base, rv, rv_rest);
     settle_tile(L.n, base, gv, gv_rest);
 #pragma unroll
@@ -413,7 +469,7 @@ __device__ __forceinline__ void follow_tile(const float* gl, float* rl, const De
             uint32_t rank = bitmap_rank(map, pre, loc);
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if ((nib >> q) & 1u) { if (rank < room) go[rank] = rv[u][q]; ++rank; rv[u][q] = 0.0f; }
+                if ((nib >> q) & 1u) { if (rank < room) row[rank] = rv[u][q]; ++rank; rv[u][q] = 0.0f; }
         }
     }
     store_tile<true>(rl, L.n, base, rv);
@@ -423,37 +479,70 @@ __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLa
                                                        uint32_t n_layers, uint32_t tiles,
                                                        const uint32_t* __restrict__ leaders, uint32_t n_lead, uint32_t W,
                                                        const uint32_t* __restrict__ mask,
-                                                       const uint32_t* __restrict__ tile_out,
-                                                       const uint32_t* __restrict__ lay_out,
+                                                       const uint32_t* __restrict__ tile_counts,
+                                                       const uint32_t* __restrict__ tile_pos,
                                                        const uint32_t* __restrict__ count_out, uint32_t max_pairs,
+                                                       ChosenSlots S, uint32_t* __restrict__ idx_out,
                                                        float* __restrict__ gathered) {
     __shared__ uint32_t map[TILE_WORDS], pre[TILE_WORDS], slot[4];
+    const uint32_t tid = threadIdx.x;
     const uint32_t p = blockIdx.x / tiles;
     const uint32_t t = blockIdx.x - p * tiles;
     const uint32_t j = find_layer<false>(layers, n_layers, t);
     const DevLayer L = layers[j];
-    const float* gp = P.g[p];
-    if (!gp || chosen_before(leaders, n_lead, j, n_lead, W, p)) return;   // chosen / static nodes: pair by pair later
     const uint32_t base = (t - L.tile_begin) * TILE;
-    float* rl = P.r[p] + L.offset;
-    const float* gl = gp + L.offset;
-    float* row_out = gathered + (size_t)p * max_pairs;
-    if (L.n - base <= CHUNK)
-        follow_tile<1>(gl, rl, L, j, t, base, P.momentum, n_layers, mask, tile_out, lay_out, count_out, max_pairs, row_out, map,
-                       pre, slot);
-    else
-        follow_tile<CHUNKS_PER_TILE>(gl, rl, L, j, t, base, P.momentum, n_layers, mask, tile_out, lay_out, count_out, max_pairs,
-                                     row_out, map, pre, slot);
+    const float* gp = P.g[p];
+    uint32_t q = 0;
+    while (q < n_lead && chosen_at(leaders, n_lead, j, q, W) != p) ++q;
+    if (q == n_lead ? !gp : q > 0) return;                   // a node without a gradient: pair by pair later
+    const bool exchange = !overflowed(count_out, n_layers);
+    const uint32_t at = min(tile_pos[t], max_pairs), room = max_pairs - at;
+    if (q == n_lead) {
+        float* rl = P.r[p] + L.offset;
+        const float* gl = gp + L.offset;
+        float* row = gathered + (size_t)p * max_pairs + at;
+        if (L.n - base <= CHUNK) follow_tile<1>(gl, rl, L, base, P.momentum, exchange, mask, row, room, map, pre, slot);
+        else follow_tile<CHUNKS_PER_TILE>(gl, rl, L, base, P.momentum, exchange, mask, row, room, map, pre, slot);
+        return;
+    }
+    // the chosen nodes' part of the tile
+    const uint32_t cnt = tile_counts[t];
+    const bool handed_over = cnt <= S.cap;
+    if (!exchange && !handed_over) return;
+    tile_mask(mask, L, base, cnt != 0u, map, pre, slot);
+    const uint32_t mine = (map[tid >> 1] >> (16u * (tid & 1u))) & 0xffffu;   // 16 elements per lane
+    const uint32_t first = bitmap_rank(map, pre, 16u * tid);
+    if (exchange) {
+        uint32_t rank = first;
+        for (uint32_t b = mine; b && rank < room; b &= b - 1u, ++rank)
+            idx_out[at + rank] = (uint32_t)L.offset + base + 16u * tid + (uint32_t)__ffs(b) - 1u;
+    }
+    for (q = 0; q < n_lead; ++q) {
+        const uint32_t c = chosen_at(leaders, n_lead, j, q, W);
+        if (chosen_before(leaders, n_lead, j, q, W, c)) continue;
+        float* rl = P.r[c] + L.offset;
+        float* row = gathered + (size_t)c * max_pairs + at;
+        const float* val = S.val + ((size_t)q * S.tiles + t) * S.cap;
+        if (exchange && handed_over) {
+            for (uint32_t e = tid; e < min(cnt, room); e += BLOCK) row[e] = val[e];
+            continue;
+        }
+        uint32_t rank = first;                               // fetch and clear, or put back where nothing is exchanged
+        for (uint32_t b = mine; b; b &= b - 1u, ++rank) {
+            const uint32_t i = base + 16u * tid + (uint32_t)__ffs(b) - 1u;
+            if (exchange && rank < room) row[rank] = rl[i];
+            rl[i] = exchange ? 0.0f : val[rank];
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
 // Ordered sum over the W nodes and the weight update, for a pair count that lives
-// on the device.  A node that streamed the pair's layer (k_follow_mask) left its
-// value in its gather row; the others (chosen for the layer, or without a gradient)
-// are read and cleared here, pair by pair.  Fixed grid, strided over the pairs.
+// on the device.  Every node has left its value in its gather row (k_follow_mask), except those without a gradient (bits of
+// static_mask) in layers that they are not chosen for: these are read and cleared here, pair by pair.  Fixed grid, strided
+// over the pairs.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_reduce_update_counted(WorkerPtrs P, const DevLayer* __restrict__ layers,
-                                                                 uint32_t n_layers,
+__global__ __launch_bounds__(BLOCK) void k_reduce_update_counted(ResidualPtrs R, uint32_t static_mask, uint32_t n_layers,
                                                                  const uint32_t* __restrict__ leaders, uint32_t n_lead,
                                                                  uint32_t W, const uint32_t* __restrict__ lay_out,
                                                                  const uint32_t* __restrict__ count_out,
@@ -465,23 +554,23 @@ __global__ __launch_bounds__(BLOCK) void k_reduce_update_counted(WorkerPtrs P, c
     const uint32_t total = min(count_out[n_layers], max_pairs);
     for (uint64_t jj64 = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; jj64 < total; jj64 += (uint64_t)gridDim.x * BLOCK) {
         const uint32_t jj = (uint32_t)jj64;
-        uint32_t lo = 0, hi = n_layers;              // layer of pair jj: last layer with lay_out <= jj
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (lay_out[mid] <= jj) lo = mid; else hi = mid;
+        uint32_t direct = static_mask;
+        if (static_mask) {
+            uint32_t lo = 0, hi = n_layers;          // layer of pair jj: last layer with lay_out <= jj
+            while (hi - lo > 1) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (lay_out[mid] <= jj) lo = mid; else hi = mid;
+            }
+            for (uint32_t q = 0; q < n_lead; ++q) direct &= ~(1u << chosen_at(leaders, n_lead, lo, q, W));
         }
-        uint32_t direct = 0;                         // bit p: node p did not stream this layer
-        for (uint32_t p = 0; p < W; ++p)
-            if (!P.g[p]) direct |= 1u << p;
-        for (uint32_t q = 0; q < n_lead; ++q) direct |= 1u << chosen_at(leaders, n_lead, lo, q, W);
         const uint32_t i = idx[jj];
         const bool ok = i < flat_end;
         float acc = 0.0f;
         for (uint32_t p = 0; p < W; ++p) {
             float v;
             if ((direct >> p) & 1u) {
-                v = ok ? P.r[p][i] : 0.0f;
-                if (ok) P.r[p][i] = 0.0f;
+                v = ok ? R.r[p][i] : 0.0f;
+                if (ok) R.r[p][i] = 0.0f;
             } else {
                 v = gathered[(size_t)p * max_pairs + jj];
             }
