@@ -18,8 +18,8 @@ typedef float v4f __attribute__((ext_vector_type(4)));   // one 128-bit access
 // The same in memory at any multiple of 4 bytes: the hardware's 128-bit global accesses need no more than that, so
 // a layer that starts anywhere in a flat buffer (a packed table, behind a tensor of odd length) moves at four
 // elements per lane and access like any other.  Against one dword per lane and access on such layers, a thousand
-// packed tensors of 115.5 M elements, eight workers: followers' pass 2401 -> 1881 us (4.1 -> 5.2 TB/s; 1755 us if
-// every layer starts at a multiple of 64 elements), leader pass 519 -> 378 us, whole step 3285 -> 2704 us.
+// packed tensors of 115.5 M elements, eight workers: followers' pass 2401 -> 1881 us (4.1 -> 5.2 TB/s), leader pass 519
+// -> 378 us, whole step 3285 -> 2704 us.  (Whole lines on top: see follow_tile_from.)
 typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 
 // Local accumulation with momentum (Eq. 3): the product is rounded, then the sum

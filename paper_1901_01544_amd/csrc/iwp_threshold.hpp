@@ -13,6 +13,7 @@
 #pragma once
 
 #include "iwp_common.hpp"
+#include "iwp_stream.hpp"
 
 namespace iwp {
 
@@ -432,7 +433,7 @@ __global__ __launch_bounds__(OFFSETS_BLOCK) void k_tile_offsets(const DevLayer* 
 // tile's masked positions as ascending flat indices and move the sent values of all of them from the tile's
 // slots to their gather rows.
 // ---------------------------------------------------------------------------
-// The tile's mask in LDS (no bits without an exchange) and the number of bits before each word; returns all bits.
+// The tile's mask in LDS (no bits unless wanted) and the number of bits before each word.
 // map, pre, slot: LDS of TILE_WORDS, TILE_WORDS and 4 words.
 __device__ __forceinline__ void tile_mask(const uint32_t* __restrict__ mask, const DevLayer& L, uint32_t base, bool wanted,
                                           uint32_t* map, uint32_t* pre, uint32_t* slot) {
@@ -443,36 +444,6 @@ __device__ __forceinline__ void tile_mask(const uint32_t* __restrict__ mask, con
     }
     __syncthreads();
     bitmap_prefix(map, pre, slot);
-}
-
-// The tile of a node that streams, CHUNKS chunks of it (see mask_tile).  row: the tile's first entry in the node's row of the
-// gather matrix, room: entries from there to the row's end.
-template <uint32_t CHUNKS>
-__device__ __forceinline__ void follow_tile(const float* gl, float* rl, const DevLayer& L, uint32_t base, float m, bool exchange,
-                                            const uint32_t* __restrict__ mask, float* row, uint32_t room, uint32_t* map,
-                                            uint32_t* pre, uint32_t* slot) {
-    const uint32_t tid = threadIdx.x;
-    float rv[CHUNKS][4], gv[CHUNKS][4];
-    Rest rv_rest, gv_rest;
-    request_tile<true>(rl, L.n, base, rv, rv_rest);
-    request_tile<true>(gl, L.n, base, gv, gv_rest);
-    tile_mask(mask, L, base, exchange, map, pre, slot);
-    settle_tile(L.n, base, rv, rv_rest);
-    settle_tile(L.n, base, gv, gv_rest);
-#pragma unroll
-    for (uint32_t u = 0; u < CHUNKS; ++u) {
-        const uint32_t loc = u * CHUNK + tid * VEC;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) rv[u][q] = accum(rv[u][q], gv[u][q], m);
-        const uint32_t nib = (map[loc >> 5] >> (loc & 31u)) & 0xFu;                // no bits past the layer's end
-        if (nib) {
-            uint32_t rank = bitmap_rank(map, pre, loc);
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if ((nib >> q) & 1u) { if (rank < room) row[rank] = rv[u][q]; ++rank; rv[u][q] = 0.0f; }
-        }
-    }
-    store_tile<true>(rl, L.n, base, rv);
 }
 
 __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLayer* __restrict__ layers,
@@ -501,8 +472,14 @@ __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLa
         float* rl = P.r[p] + L.offset;
         const float* gl = gp + L.offset;
         float* row = gathered + (size_t)p * max_pairs + at;
-        if (L.n - base <= CHUNK) follow_tile<1>(gl, rl, L, base, P.momentum, exchange, mask, row, room, map, pre, slot);
-        else follow_tile<CHUNKS_PER_TILE>(gl, rl, L, base, P.momentum, exchange, mask, row, room, map, pre, slot);
+        auto sent = [&]() {
+            tile_mask(mask, L, base, exchange, map, pre, slot);
+            return true;
+        };
+        const uint32_t head = elements_to_line(rl);
+        if (L.n - base <= CHUNK) follow_tile<1>(gl, rl, L.n, base, P.momentum, row, room, map, pre, sent);   // see mask_tile
+        else if (head && base + TILE <= L.n) follow_tile_from(head, gl + base, rl + base, P.momentum, row, room, map, pre, sent);
+        else follow_tile<CHUNKS_PER_TILE>(gl, rl, L.n, base, P.momentum, row, room, map, pre, sent);
         return;
     }
     // the chosen nodes' part of the tile
