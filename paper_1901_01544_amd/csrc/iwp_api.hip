@@ -252,12 +252,12 @@ int launch_write(const Table& T, const Workspace& ws, const ResidualPtrs& R, con
     const uint32_t grid = T.stiles * (GROUP / (BLOCK / WAVE));
     float* gathered = FUSED ? ws.gathered : nullptr;
     if (T.max_layer_stiles <= FOLD_SCAN_MAX_STILES) {
-        IWP_LAUNCH("k_write", (k_write<FUSED, true>), grid, s, R, w, T.layers, T.n_layers, leader, W, eps, ws.state,
+        IWP_LAUNCH("k_write", (k_write<FUSED, true>), grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
                    ws.stage, ws.A, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, gathered,
                    T.pairs);
     } else {
         IWP_LAUNCH("k_scan", k_scan, T.n_layers, s, T.layers, ws.stile_counts);
-        IWP_LAUNCH("k_write", (k_write<FUSED, false>), grid, s, R, w, T.layers, T.n_layers, leader, W, eps, ws.state,
+        IWP_LAUNCH("k_write", (k_write<FUSED, false>), grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
                    ws.stage, ws.A, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, gathered,
                    T.pairs);
     }
@@ -296,13 +296,13 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
         IWP_LAUNCH("k_stage", k_stage<false>, stage_grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
                    ws.hist, ws.stage, ws.A);
     const uint32_t stile_grid = std::min<uint32_t>(T.stiles, STILE_MAX_GRID);
-    IWP_LAUNCH("k_refine2", k_refine2, stile_grid, s, R, w, T.layers, T.n_layers, T.stiles, leader, W, eps, ws.state,
+    IWP_LAUNCH("k_refine2", k_refine2, stile_grid, s, R, w, T.layers, T.n_layers, T.tiles, T.stiles, leader, W, eps, ws.state,
                ws.stage, ws.A, ws.hist);
     if (stop == STOP_AT_THRESHOLD) {
         IWP_LAUNCH("k_final_pick", k_final_pick, T.n_layers, s, T.layers, ws.hist, ws.state, thr_out);
         return IWP_OK;
     }
-    IWP_LAUNCH("k_count", k_count, stile_grid, s, R, w, T.layers, T.n_layers, T.stiles, leader, W, eps, ws.state,
+    IWP_LAUNCH("k_count", k_count, stile_grid, s, R, w, T.layers, T.n_layers, T.tiles, T.stiles, leader, W, eps, ws.state,
                ws.hist, thr_out, ws.stage, ws.A, ws.tile_counts, ws.stile_counts);
     if (fused) return launch_write<true>(T, ws, R, w, leader, W, eps, idx_out, val_out, s);
     return launch_write<false>(T, ws, R, w, leader, W, eps, idx_out, val_out, s);
@@ -349,7 +349,7 @@ int run_compact_from(const Table& T, const Workspace& ws, const ResidualPtrs& R,
     if (!T.any_k || T.tiles == 0) return IWP_OK;
     IWP_LAUNCH("k_stage_records", k_stage_records, T.tiles, s, R.r[0], w, T.layers, T.n_layers, thr, eps, ws.state, ws.stage,
                ws.A, ws.tile_counts);
-    IWP_LAUNCH("k_fold_counts", k_fold_counts, (T.stiles + BLOCK - 1) / BLOCK, s, T.layers, T.n_layers, T.stiles,
+    IWP_LAUNCH("k_fold_counts", k_fold_counts, (T.stiles + BLOCK - 1) / BLOCK, s, T.layers, T.n_layers, T.tiles, T.stiles,
                ws.tile_counts, ws.stile_counts);
     return launch_write<false>(T, ws, R, w, nullptr, 1u, eps, idx_out, val_out, s);
 }
@@ -591,7 +591,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     plan->all_dense = all_dense;
     for (const DevLayer& D : dev) plan->max_copies = std::max(plan->max_copies, D.h0_copies);
     plan->flat_end = end;
-    // the table, then the layer of every tile and of every super-tile (find_layer reads them)
+    // the table, then the layer of every tile and of every super-tile (layer_of_tile and layer_of_stile read them)
     std::vector<uint32_t> map;
     map.reserve(tiles + stiles);
     for (uint32_t j = 0; j < n_layers; ++j) map.insert(map.end(), tiles_of(layers[j].n), j);

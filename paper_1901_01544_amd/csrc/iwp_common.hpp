@@ -160,15 +160,16 @@ __device__ __forceinline__ uint32_t leader_of(const uint32_t* __restrict__ leade
     return l < W ? l : 0u;
 }
 
-// Which layer does tile t (or super-tile t) belong to.  Uniform across the workgroup.
+// Which layer does tile t belong to, or super-tile s.  Uniform across the workgroup.
 // A table of more than one layer comes from a plan, which stores the answer behind the
 // table's sentinel row: one word per tile, then one per super-tile (a binary search over a
 // thousand layers is ten dependent loads before a workgroup can issue its first tile load).
-template <bool SUPER>
-__device__ __forceinline__ uint32_t find_layer(const DevLayer* __restrict__ layers, uint32_t n_layers, uint32_t t) {
-    if (n_layers == 1) return 0u;
-    const uint32_t* map = reinterpret_cast<const uint32_t*>(layers + n_layers + 1);
-    return SUPER ? map[layers[n_layers].tile_begin + t] : map[t];
+__device__ __forceinline__ uint32_t layer_of_tile(const DevLayer* __restrict__ layers, uint32_t n_layers, uint32_t t) {
+    return n_layers == 1 ? 0u : reinterpret_cast<const uint32_t*>(layers + n_layers + 1)[t];
+}
+__device__ __forceinline__ uint32_t layer_of_stile(const DevLayer* __restrict__ layers, uint32_t n_layers, uint32_t tiles,
+                                                   uint32_t s) {
+    return layer_of_tile(layers, n_layers, tiles + s);
 }
 
 template <bool NT>
@@ -255,14 +256,38 @@ __device__ __forceinline__ void store_tile(float* __restrict__ p, uint32_t n, ui
     for (uint32_t u = 0; u < CHUNKS; ++u) store_quad<NT>(p, base + u * CHUNK + threadIdx.x * VEC, n, v[u]);
 }
 
-// Inclusive scan across the 64 lanes of a wavefront.
+// Sums and scans across the 64 lanes of a wavefront, by data-parallel-primitive moves (row shifts by 1, 2, 4 and 8 lanes of
+// 16, then the last lane of a row, and of two rows, broadcast to the rows behind): a handful of cycles a step, where a
+// shuffle goes through the LDS unit and back.  All lanes of the wavefront take part.  The selection's kernels are chains of
+// such scans and of the loads between them: with shuffles one layer of 1 M elements took 40.0 us a call, now 37.9, six
+// tensors of 235 k elements and four workers 45.4 -> 43.0 us a step, one layer of 1000 elements 9.2 -> 8.5.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {        // 0 where the control names no lane
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
+}
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
-    const int lane = threadIdx.x & (WAVE - 1);
-#pragma unroll
-    for (int d = 1; d < WAVE; d <<= 1) {
-        const uint32_t y = __shfl_up(x, d, WAVE);
-        if (lane >= d) x += y;
-    }
+    x += dpp<0x111, 0xf>(x);                                 // row_shr 1, 2, 4, 8
+    x += dpp<0x112, 0xf>(x);
+    x += dpp<0x114, 0xf>(x);
+    x += dpp<0x118, 0xf>(x);
+    x += dpp<0x142, 0xa>(x);                                 // row_bcast 15 into rows 1 and 3
+    x += dpp<0x143, 0xc>(x);                                 // row_bcast 31 into rows 2 and 3
+    return x;
+}
+__device__ __forceinline__ uint32_t wave_last(uint32_t x) {  // lane 63's value, in all lanes
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, WAVE - 1);
+}
+__device__ __forceinline__ uint32_t from_lane(uint32_t x, uint32_t lane) {   // lane: the same in all lanes
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, (int)lane);
+}
+// The wavefront's number in its workgroup, as a scalar: what is indexed by it then is, too.
+__device__ __forceinline__ uint32_t wave_id() { return (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x) { return wave_last(wave_inclusive_scan(x)); }
+// The OR over each group of eight lanes, in all of them: quad_perm [1,0,3,2], [2,3,0,1], then the half row mirrored.
+__device__ __forceinline__ uint32_t or_of_8_lanes(uint32_t x) {
+    x |= dpp<0xB1, 0xf>(x);
+    x |= dpp<0x4E, 0xf>(x);
+    x |= dpp<0x141, 0xf>(x);
     return x;
 }
 
@@ -284,7 +309,7 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* s
 // k_rem counted from the top bin down, and the rank inside that bin.  All THREADS
 // threads call it; the result is broadcast through `sh` (PICK_WORDS words of LDS).
 // copies: histograms of NB bins one behind the other, added up.
-// Requires sum(hist) >= k_rem >= 1.  Suffix sums inside each wavefront by lane shuffles, then over the
+// Requires sum(hist) >= k_rem >= 1.  Suffix sums inside each wavefront, then over the
 // wavefronts' totals: three barriers, where a scan over all threads in LDS takes two per doubling.
 constexpr uint32_t PICK_WORDS = 16 + 2;
 template <int NB, int THREADS = BLOCK>
@@ -303,12 +328,8 @@ __device__ __forceinline__ void block_pick(const uint32_t* hist, uint32_t k_rem,
         for (int q = 0; q < PER; ++q) h[q] += hist[c * NB + tid * PER + q];
 #pragma unroll
     for (int q = 0; q < PER; ++q) local += h[q];
-    uint32_t incl = local;                 // this lane's bins and those of the lanes above it
-#pragma unroll
-    for (int d = 1; d < WAVE; d <<= 1) {
-        const uint32_t y = __shfl_down(incl, d, WAVE);
-        if (lane + d < WAVE) incl += y;
-    }
+    const uint32_t upto = wave_inclusive_scan(local), all = wave_last(upto);
+    uint32_t incl = all - upto + local;    // this lane's bins and those of the lanes above it
     __syncthreads();                       // sh may still be in use by a previous call
     if (lane == 0) sh[wave] = incl;
     if (tid == 0) { sh[WAVES] = 0u; sh[WAVES + 1] = 1u; }

@@ -333,7 +333,7 @@ __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __
                                                            // one flush per workgroup and layer, however many tiles
     DevLayer L;
     for (uint32_t t = t0; t < t1; ++t) {
-        const uint32_t j = find_layer<false>(layers, n_layers, t);
+        const uint32_t j = layer_of_tile(layers, n_layers, t);
         if (j != cur_j) {
             if (filled) {
                 __syncthreads();
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __
         if (L.k == 0) continue;
         const uint32_t lt = t - L.tile_begin;
         const bool do_slots = prestaged && lt % STAGE_GROUP == 0;
-        const bool raw = prestaged && __shfl(my_cnt, (int)(t - t0), WAVE) == RAW_TILE;
+        const bool raw = prestaged && from_lane(my_cnt, t - t0) == RAW_TILE;
         if (prestaged && !do_slots && !raw) continue;      // uniform
         if (!filled) {
             __syncthreads();                               // a flush above has read lh
@@ -458,20 +458,21 @@ constexpr uint32_t STILE_MAX_GRID = 8192;          // k_refine2 / k_count: beyon
 
 __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* __restrict__ w,
                                                    const DevLayer* __restrict__ layers, uint32_t n_layers,
-                                                   uint32_t stiles, const uint32_t* __restrict__ leader, uint32_t W,
+                                                   uint32_t tiles, uint32_t stiles,
+                                                   const uint32_t* __restrict__ leader, uint32_t W,
                                                    float eps, LayerState* __restrict__ state,
                                                    const uint32_t* __restrict__ stage_cnt, StageArrays A,
                                                    uint32_t* __restrict__ hist) {
     __shared__ uint32_t lh[HIST2];
     __shared__ uint32_t sh[PICK_WORDS];
-    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = wave_id();
     const uint32_t per = (stiles + gridDim.x - 1) / gridDim.x;
     const uint32_t s0 = blockIdx.x * per, s1 = min(s0 + per, stiles);
     uint32_t cur_j = 0xFFFFFFFFu, prefix = 0;
     bool filled = false;                                   // lh holds counts of layer cur_j
     DevLayer L;
     for (uint32_t s = s0; s < s1; ++s) {
-        const uint32_t j = find_layer<true>(layers, n_layers, s);
+        const uint32_t j = layer_of_stile(layers, n_layers, tiles, s);
         if (j != cur_j) {
             if (filled) {
                 __syncthreads();
@@ -507,7 +508,7 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
 #pragma unroll
         for (uint32_t m = 0; m < MINE; ++m) {
             const uint32_t tl = wave + m * (BLOCK / WAVE);
-            cnt[m] = __shfl(my_cnt, (int)tl, WAVE);
+            cnt[m] = from_lane(my_cnt, tl);
             const uint64_t sb = L.slot_begin + (uint64_t)(lt0 + tl) * L.slot_cap;
             if (cnt[m] == UNIFORM_TILE) {                  // all keys of the tile are the slot's one entry
                 const uint32_t k0 = A.key[sb];
@@ -583,7 +584,7 @@ __global__ __launch_bounds__(BLOCK) void k_stage_records(const float* __restrict
     __shared__ uint32_t slot[STAGE_WORDS];
     __shared__ uint32_t part[BLOCK / WAVE];
     const uint32_t t = blockIdx.x;
-    const uint32_t j = find_layer<false>(layers, n_layers, t);
+    const uint32_t j = layer_of_tile(layers, n_layers, t);
     const DevLayer L = layers[j];
     if (L.k == 0) return;
     const uint32_t lt = t - L.tile_begin;
@@ -604,8 +605,7 @@ __global__ __launch_bounds__(BLOCK) void k_stage_records(const float* __restrict
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             c += key[u][q] == NOT_AN_ELEMENT ? 0u : key[u][q] > from ? 1u : key[u][q] == from ? 0x10000u : 0u;
-#pragma unroll
-    for (int d = WAVE / 2; d > 0; d >>= 1) c += __shfl_xor(c, d, WAVE);
+    c = wave_sum(c);
     if ((threadIdx.x & (WAVE - 1)) == 0) part[threadIdx.x >> 6] = c;
     uint32_t cnt = RAW_TILE;
     if (from != 0u && L.k < L.n - L.k)                     // uniform; either way a barrier before the sum below
@@ -621,11 +621,11 @@ __global__ __launch_bounds__(BLOCK) void k_stage_records(const float* __restrict
 
 // The tiles' counts that k_stage_records left -> what k_count leaves: each tile's exclusive prefix inside its super-tile and
 // the super-tile's totals.  One super-tile per lane.
-__global__ __launch_bounds__(BLOCK) void k_fold_counts(const DevLayer* __restrict__ layers, uint32_t n_layers, uint32_t stiles,
+__global__ __launch_bounds__(BLOCK) void k_fold_counts(const DevLayer* __restrict__ layers, uint32_t n_layers, uint32_t tiles, uint32_t stiles,
                                                        uint2* __restrict__ tile_counts, uint2* __restrict__ stile_counts) {
     const uint32_t s = blockIdx.x * BLOCK + threadIdx.x;
     if (s >= stiles) return;
-    const DevLayer& L = layers[find_layer<true>(layers, n_layers, s)];
+    const DevLayer& L = layers[layer_of_stile(layers, n_layers, tiles, s)];
     if (L.k == 0) return;
     const uint32_t lt0 = (s - L.stile_begin) * GROUP;
     const uint32_t nt = min(GROUP, (L.n + TILE - 1) / TILE - lt0);
@@ -650,7 +650,8 @@ __global__ __launch_bounds__(BLOCK) void k_fold_counts(const DevLayer* __restric
 // prologue's third pick (recorded, with thr_out, by the layer's first workgroup).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __restrict__ w,
-                                                 const DevLayer* __restrict__ layers, uint32_t n_layers, uint32_t stiles,
+                                                 const DevLayer* __restrict__ layers, uint32_t n_layers,
+                                                 uint32_t tiles, uint32_t stiles,
                                                  const uint32_t* __restrict__ leader, uint32_t W, float eps,
                                                  LayerState* __restrict__ state, const uint32_t* __restrict__ hist,
                                                  iwp_threshold* __restrict__ thr_out,
@@ -659,13 +660,13 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
     __shared__ uint32_t cg[GROUP], ce[GROUP];
     __shared__ uint32_t sh[PICK_WORDS];
     const uint32_t tid = threadIdx.x;
-    const uint32_t lane = tid & (WAVE - 1), wave = tid >> 6;
+    const uint32_t lane = tid & (WAVE - 1), wave = wave_id();
     const uint32_t per = (stiles + gridDim.x - 1) / gridDim.x;
     const uint32_t s0 = blockIdx.x * per, s1 = min(s0 + per, stiles);
     uint32_t cur_j = 0xFFFFFFFFu, thr = 0, shift = 0;
     DevLayer L;
     for (uint32_t s = s0; s < s1; ++s) {
-        const uint32_t j = find_layer<true>(layers, n_layers, s);
+        const uint32_t j = layer_of_stile(layers, n_layers, tiles, s);
         if (j != cur_j) {
             L = layers[j];
             cur_j = j;
@@ -700,7 +701,7 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
 #pragma unroll
         for (uint32_t m = 0; m < MINE; ++m) {
             const uint32_t tl = wave + m * (BLOCK / WAVE);
-            cnt[m] = __shfl(my_cnt, (int)tl, WAVE);
+            cnt[m] = from_lane(my_cnt, tl);
             const uint64_t sb = L.slot_begin + (uint64_t)(lt0 + tl) * L.slot_cap;
 #pragma unroll
             for (uint32_t q = 0; q < 4; ++q) {
@@ -738,11 +739,8 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
                     eq += k2 == thr ? 1u : 0u;
                 }
             }
-#pragma unroll
-            for (int d = WAVE / 2; d > 0; d >>= 1) {
-                gt += __shfl_xor(gt, d, WAVE);
-                eq += __shfl_xor(eq, d, WAVE);
-            }
+            gt = wave_sum(gt);
+            eq = wave_sum(eq);
             if (lane == 0) { cg[tl] = gt; ce[tl] = eq; }
         }
         __syncthreads();
@@ -884,7 +882,7 @@ __device__ __forceinline__ void write_tile(const DevLayer& L, uint32_t lt, uint3
             packed += (valid && key[q] == thr) ? 0x10000u : 0u;
         }
         const uint32_t inc = wave_inclusive_scan(packed);
-        const uint32_t tot = __shfl(inc, WAVE - 1, WAVE);
+        const uint32_t tot = wave_last(inc);
         const uint32_t ex = inc - packed;
         uint32_t gpre = G + (ex & 0xffffu);
         uint32_t epre = E + (ex >> 16);
@@ -919,7 +917,7 @@ __device__ __forceinline__ void write_tile(const DevLayer& L, uint32_t lt, uint3
 // otherwise k_scan has turned them into prefixes.
 template <bool FUSED, bool FOLD>
 __global__ __launch_bounds__(BLOCK) void k_write(ResidualPtrs R, const float* __restrict__ w,
-                                                 const DevLayer* __restrict__ layers, uint32_t n_layers,
+                                                 const DevLayer* __restrict__ layers, uint32_t n_layers, uint32_t tiles,
                                                  const uint32_t* __restrict__ leader, uint32_t W, float eps,
                                                  const LayerState* __restrict__ state,
                                                  const uint32_t* __restrict__ stage_cnt, StageArrays A,
@@ -929,10 +927,10 @@ __global__ __launch_bounds__(BLOCK) void k_write(ResidualPtrs R, const float* __
                                                  uint32_t* __restrict__ idx_out, float* __restrict__ val_out,
                                                  float* __restrict__ gathered, uint64_t K) {
     __shared__ uint32_t red[2][BLOCK / WAVE];
-    const uint32_t lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
+    const uint32_t lane = threadIdx.x & (WAVE - 1), wave = wave_id();
     const uint32_t s = blockIdx.x / (GROUP / (BLOCK / WAVE));            // the workgroup's super-tile
     const uint32_t part = blockIdx.x % (GROUP / (BLOCK / WAVE));
-    const uint32_t j = find_layer<true>(layers, n_layers, s);
+    const uint32_t j = layer_of_stile(layers, n_layers, tiles, s);
     const DevLayer L = layers[j];
     if (L.k == 0) return;
     const uint32_t ntiles = (L.n + TILE - 1) / TILE;
@@ -947,11 +945,8 @@ __global__ __launch_bounds__(BLOCK) void k_write(ResidualPtrs R, const float* __
             g += c.x;
             e += c.y;
         }
-#pragma unroll
-        for (int d = WAVE / 2; d > 0; d >>= 1) {
-            g += __shfl_xor(g, d, WAVE);
-            e += __shfl_xor(e, d, WAVE);
-        }
+        g = wave_sum(g);
+        e = wave_sum(e);
         if (lane == 0) { red[0][wave] = g; red[1][wave] = e; }
         __syncthreads();
         sc.x = red[0][0] + red[0][1] + red[0][2] + red[0][3];

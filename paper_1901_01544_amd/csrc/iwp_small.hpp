@@ -39,7 +39,7 @@ __global__ __launch_bounds__(THREADS) void k_small(WorkerPtrs P, const float* __
     __shared__ uint32_t lh[HIST0];
     __shared__ uint32_t sh[PICK_WORDS];
     __shared__ uint32_t tot[CHUNKS * WAVES];
-    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = wave_id();
     const uint32_t j = blockIdx.x;
     const DevLayer L = layers ? layers[j] : row;
     if (L.k == 0 || L.n < min_n || L.n > max_n) return;
@@ -87,8 +87,7 @@ __global__ __launch_bounds__(THREADS) void k_small(WorkerPtrs P, const float* __
             else if (key[u][q] != NOT_AN_ELEMENT) atomicAdd(&lh[key[u][q] >> digit_shift(0)], 1u);
         }
     if (__any(zeros != 0)) {
-#pragma unroll
-        for (int d = WAVE / 2; d > 0; d >>= 1) zeros += __shfl_xor(zeros, d, WAVE);
+        zeros = wave_sum(zeros);
         if (lane == 0) atomicAdd(&lh[0], zeros);
     }
     __syncthreads();
@@ -142,12 +141,12 @@ __global__ __launch_bounds__(THREADS) void k_small(WorkerPtrs P, const float* __
 #pragma unroll
         for (uint32_t c = 0; c < PER_SCAN; ++c) {
             const uint32_t u = u0 + c;
-            const uint32_t base = carry + __shfl(inc - v, (int)(c * WAVES + wave), WAVE);
+            const uint32_t base = carry + from_lane(inc - v, c * WAVES + wave);
             if (FUSED && tid == 0 && u * STEP % TILE == 0 && u * STEP < L.n)
                 tile_out[L.tile_begin + u * STEP / TILE] = (base & 0xffffu) + min(base >> 16, quota);
             before[u] += base;
         }
-        carry += __shfl(inc, WAVE - 1, WAVE);
+        carry += wave_last(inc);
     }
     uint32_t* io = idx_out + L.out_offset;
     float* vo = val_out + L.out_offset;

@@ -182,8 +182,7 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
             else if (key[u][q] != NOT_AN_ELEMENT) atomicAdd(&C.lh[key[u][q] >> digit_shift(0)], 1u);
         }
     if (__any(zeros != 0)) {
-#pragma unroll
-        for (int d = WAVE / 2; d > 0; d >>= 1) zeros += __shfl_xor(zeros, d, WAVE);
+        zeros = wave_sum(zeros);
         if ((tid & (WAVE - 1)) == 0) atomicAdd(&C.lh[0], zeros);
     }
     if (C.stage_bin != NO_STAGE_BIN) {                      // uniform
@@ -239,7 +238,7 @@ __global__ __launch_bounds__(BLOCK) void k_accumulate_rest(WorkerPtrs P, const D
                                                            const uint32_t* __restrict__ leader, uint32_t W) {
     const uint32_t p = blockIdx.x / tiles;
     const uint32_t t = blockIdx.x - p * tiles;
-    const uint32_t j = find_layer<false>(layers, n_layers, t);
+    const uint32_t j = layer_of_tile(layers, n_layers, t);
     const DevLayer L = layers[j];
     const float* gp = P.g[p];
     if (!gp || (L.k > 0 && leader_of(leader, j, W) == p)) return;
@@ -265,9 +264,9 @@ __global__ __launch_bounds__(BLOCK) void k_leader_pass(WorkerPtrs P, const float
     __shared__ uint32_t slot[2 * STAGE_WORDS];
     uint32_t j, first;
     if (LG == 1) {
-        j = find_layer<false>(layers, n_layers, blockIdx.x);
+        j = layer_of_tile(layers, n_layers, blockIdx.x);
     } else {
-        j = find_layer<true>(layers, n_layers, blockIdx.x / (GROUP / LG));
+        j = layer_of_stile(layers, n_layers, layers[n_layers].tile_begin, blockIdx.x / (GROUP / LG));
     }
     const DevLayer L = layers[j];
     if (L.k == 0) return;
@@ -302,7 +301,7 @@ __global__ __launch_bounds__(BLOCK) void k_follow_gather(WorkerPtrs P, WorkerLis
     const uint32_t a = blockIdx.x / tiles;
     const uint32_t t = blockIdx.x - a * tiles;
     const uint32_t p = acc.id[a];
-    const uint32_t j = find_layer<false>(layers, n_layers, t);
+    const uint32_t j = layer_of_tile(layers, n_layers, t);
     const DevLayer L = layers[j];
     const bool has_sel = L.k > 0;
     if (has_sel && leader_of(leader, j, W) == p) return;       // done by the leader pass

@@ -157,10 +157,7 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
 #pragma unroll
     for (uint32_t u = 0; u < CHUNKS; ++u) {
         // eight lanes (32 consecutive elements) make one word of the encoded mask
-        word[u] = nib[u] << (4u * (lane & 7u));
-        word[u] |= __shfl_xor(word[u], 1, WAVE);
-        word[u] |= __shfl_xor(word[u], 2, WAVE);
-        word[u] |= __shfl_xor(word[u], 4, WAVE);
+        word[u] = or_of_8_lanes(nib[u] << (4u * (lane & 7u)));
         const uint32_t widx = base / 32 + u * (CHUNK / 32) + (tid >> 3);
         if ((lane & 7u) == 0u && widx < nwords) mw[widx] = word[u];
         count[u] = __popc(nib[u]);
@@ -226,7 +223,7 @@ __global__ __launch_bounds__(BLOCK) void k_leader_mask(WorkerPtrs P, const float
                                                        uint32_t* __restrict__ tile_counts, ChosenSlots S) {
     __shared__ uint32_t part[STAGE_WORDS];
     const uint32_t t = blockIdx.x;
-    const uint32_t j = find_layer<false>(layers, n_layers, t);
+    const uint32_t j = layer_of_tile(layers, n_layers, t);
     const DevLayer L = layers[j];
     const uint32_t base = (t - L.tile_begin) * TILE;
     const float* wl = w + L.offset;
@@ -286,7 +283,7 @@ __global__ __launch_bounds__(BLOCK) void k_leader_stats(WorkerPtrs P, const floa
     const uint32_t tid = threadIdx.x;
     const uint32_t q = blockIdx.x / tiles;
     const uint32_t t = blockIdx.x - q * tiles;
-    const uint32_t j = find_layer<false>(layers, n_layers, t);
+    const uint32_t j = layer_of_tile(layers, n_layers, t);
     const DevLayer L = layers[j];
     const uint32_t p = chosen_at(leaders, n_lead, j, q, W);
     if (chosen_before(leaders, n_lead, j, q, W, p)) return;
@@ -459,7 +456,7 @@ __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLa
     const uint32_t tid = threadIdx.x;
     const uint32_t p = blockIdx.x / tiles;
     const uint32_t t = blockIdx.x - p * tiles;
-    const uint32_t j = find_layer<false>(layers, n_layers, t);
+    const uint32_t j = layer_of_tile(layers, n_layers, t);
     const DevLayer L = layers[j];
     const uint32_t base = (t - L.tile_begin) * TILE;
     const float* gp = P.g[p];
