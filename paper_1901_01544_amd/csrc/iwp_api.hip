@@ -128,12 +128,12 @@ uint32_t sample_of(uint32_t n, uint32_t k) {
     return (uint32_t)(runs << 16 | (rank - 1));
 }
 
-// Copies of a layer's first-digit histogram: one per FLUSHES_PER_COPY look-1 workgroups, a power of two.
-inline uint32_t h0_copies_of(uint32_t n, uint32_t k) {
+// Copies of a layer's first-digit histogram: one per `flushes` look-1 workgroups, a power of two.
+inline uint32_t h0_copies_of(uint32_t n, uint32_t k, uint32_t flushes = FLUSHES_PER_COPY) {
     if (k == 0) return 1u;
     const uint32_t groups = (tiles_of(n) + LGROUP - 1) / LGROUP;
     uint32_t c = 1;
-    while (c < MAX_H0_COPIES && c * FLUSHES_PER_COPY < groups) c <<= 1;
+    while (c < MAX_H0_COPIES && c * flushes < groups) c <<= 1;
     return c;
 }
 
@@ -272,7 +272,7 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
                iwp_threshold* thr_out, hipStream_t s) {
     if (!T.any_k || T.tiles == 0) return IWP_OK;
     const bool own_pick = T.max_copies <= PICK_MAX_COPIES && T.tiles <= PICK_MAX_TILES;
-    if (!own_pick) IWP_LAUNCH("k_first_pick", k_first_pick, T.n_layers, s, T.layers, ws.hist, ws.state);
+    if (!own_pick) IWP_LAUNCH_BLOCK("k_first_pick", k_first_pick, T.n_layers, PICK_BLOCK, s, T.layers, ws.hist, ws.state);
     // Consecutive tiles per look-2 workgroup.  Where look 1's copies are complete only every STAGE_GROUP-th tile has work, and
     // few workgroups mean few flushes into a layer's one second-digit histogram; where they are not (a threshold among
     // zeros, a sample that misleads), tiles are read again, and few workgroups leave the chip idle.  Up to 32767 tiles at
@@ -589,6 +589,21 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     plan->max_n = max_n;
     plan->n_long = n_long;
     plan->all_dense = all_dense;
+    if (carve(nullptr, plan->z).bytes > IWP_STATIC_SCRATCH_BYTES) {
+        Sizes few = plan->z;
+        few.hist_words = 0;
+        for (uint32_t j = 0; j < n_layers; ++j)
+            few.hist_words += layer_hist_words(h0_copies_of(layers[j].n, layers[j].k, FLUSHES_PER_COPY_FEW));
+        if (carve(nullptr, few).bytes <= IWP_STATIC_SCRATCH_BYTES) {
+            plan->z = few;
+            hist_words = 0;
+            for (uint32_t j = 0; j < n_layers; ++j) {
+                dev[j].hist_begin = (uint32_t)hist_words;
+                dev[j].h0_copies = h0_copies_of(layers[j].n, layers[j].k, FLUSHES_PER_COPY_FEW);
+                hist_words += layer_hist_words(dev[j].h0_copies);
+            }
+        }
+    }
     for (const DevLayer& D : dev) plan->max_copies = std::max(plan->max_copies, D.h0_copies);
     plan->flat_end = end;
     // the table, then the layer of every tile and of every super-tile (layer_of_tile and layer_of_stile read them)

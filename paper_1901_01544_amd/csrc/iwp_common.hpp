@@ -55,10 +55,13 @@ __host__ __device__ constexpr int digit_bits(int level) { return level == 0 ? 12
 constexpr uint32_t HIST0 = 1u << 12, HIST1 = 1u << 10, HIST2 = 1u << 9;
 // A layer's histograms in the workspace: h0_copies copies of the first digit's (look 1 flushes one LDS
 // histogram per workgroup with atomics, and atomics on one address serialise at about 20 ns each on this
-// chip, so a layer with thousands of workgroups spreads them over several copies), then one of the second
+// chip, so a layer with many workgroups spreads them over several copies), then one of the second
 // digit's and one of the third's.
 constexpr uint32_t MAX_H0_COPIES = 16;
-constexpr uint32_t FLUSHES_PER_COPY = 512;                 // look-1 workgroups that share one copy
+// Look-1 workgroups that share one copy.  128 against 512: one layer of 1 M elements 39.2 -> 36.0 us a call, ten of 25 M 127
+// -> 120, 161 of 25.6 M 130 -> 123 (thresholds and pairs); 256: 37.8, 120, 125; 64: 38.4, 120, 123.  The pick that adds the
+// copies up pays for them.  512 (FEW) only in plans that would otherwise no longer fit the library's static scratch.
+constexpr uint32_t FLUSHES_PER_COPY = 128, FLUSHES_PER_COPY_FEW = 512;
 __host__ __device__ constexpr uint32_t layer_hist_words(uint32_t copies) { return copies * HIST0 + HIST1 + HIST2; }
 
 constexpr uint32_t RAW_TILE = 0xFFFFFFFFu;        // stage count of a tile whose candidates did not fit its slot

@@ -201,23 +201,27 @@ __global__ __launch_bounds__(INIT_BLOCK, 8) void k_init(uint32_t* __restrict__ w
 
 // ---------------------------------------------------------------------------
 // First digit pick: the bin b1 of the 4096-bin histogram that holds rank k, whether look 1's copies already cover it.
-// On tables that the chip holds at one workgroup per tile (PICK_MAX_TILES), with at most two copies of a histogram, every
+// On tables that the chip holds at one workgroup per tile (PICK_MAX_TILES), with at most four copies of a histogram, every
 // workgroup of look 2 redoes the pick of its layer itself: a launch less, 0.5 to 1.5 us of 31 to 56 us a call (six tensors
 // of 235 k elements, four workers 44.2 -> 42.7 us; 160 of 3 M elements, one worker 48.8 -> 47.2), nothing from 4 M elements
 // on.  On larger ones that costs more than the launch (25.6 M elements: 18.8 us against
-// 10.5 + 4.8), so one workgroup per layer adds the copies up in a launch of its own.  A summary
+// 10.5 + 4.8), so one workgroup per layer adds the copies up in a launch of its own, of 16 wavefronts: sixteen copies, 7.6 us
+// by 4, 5.3 by 16.  A summary
 // would have to be built with atomics on a handful of addresses that all
 // workgroups of look 1 hit (measured: look 1 nearly twice as slow).
 // ---------------------------------------------------------------------------
-constexpr uint32_t PICK_MAX_COPIES = 2, PICK_MAX_TILES = 2048;
+constexpr uint32_t PICK_MAX_COPIES = 4, PICK_MAX_TILES = 2048;
 
+constexpr int PICK_BLOCK = 1024;                   // threads of a k_first_pick workgroup
+
+template <int THREADS>
 __device__ __forceinline__ void first_pick(const DevLayer& L, const uint32_t* __restrict__ hist, uint32_t stage_bin,
                                            uint32_t* sh, uint32_t* b1, uint32_t* k_rem0, bool* prestaged) {
-    block_pick<(int)HIST0>(layer_hist(hist, L, 0), L.k, sh, b1, k_rem0, L.h0_copies);
+    block_pick<(int)HIST0, THREADS>(layer_hist(hist, L, 0), L.k, sh, b1, k_rem0, L.h0_copies);
     *prestaged = stage_bin != NO_STAGE_BIN && stage_bin <= *b1;
 }
 
-__global__ __launch_bounds__(BLOCK) void k_first_pick(const DevLayer* __restrict__ layers, const uint32_t* __restrict__ hist,
+__global__ __launch_bounds__(PICK_BLOCK) void k_first_pick(const DevLayer* __restrict__ layers, const uint32_t* __restrict__ hist,
                                                       LayerState* __restrict__ state) {
     __shared__ uint32_t sh[PICK_WORDS];
     const uint32_t j = blockIdx.x;
@@ -225,7 +229,7 @@ __global__ __launch_bounds__(BLOCK) void k_first_pick(const DevLayer* __restrict
     if (L.k == 0) return;
     uint32_t b1, k_rem0;
     bool prestaged;
-    first_pick(L, hist, state[j].stage_bin, sh, &b1, &k_rem0, &prestaged);
+    first_pick<PICK_BLOCK>(L, hist, state[j].stage_bin, sh, &b1, &k_rem0, &prestaged);
     if (threadIdx.x == 0) {
         state[j].b1 = b1;
         state[j].k_rem0 = k_rem0;
@@ -346,7 +350,7 @@ __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __
             shift = state[j].shift;
             if (PICK) {
                 uint32_t k_rem0;
-                first_pick(L, hist, state[j].stage_bin, sh, &b1, &k_rem0, &prestaged);
+                first_pick<BLOCK>(L, hist, state[j].stage_bin, sh, &b1, &k_rem0, &prestaged);
                 if (t == L.tile_begin && tid == 0) {       // for the launches that follow
                     state[j].b1 = b1;
                     state[j].k_rem0 = k_rem0;
