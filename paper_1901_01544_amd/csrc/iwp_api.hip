@@ -226,8 +226,11 @@ constexpr uint32_t leader_grid(uint32_t tiles, uint32_t stiles) {
 }
 
 // Up to these table sizes (bytes of one flat buffer's share of the table) look 1 leaves the weights, or the weights
-// and the residual it writes, in the memory-side cache for the kernels that come back to them (see lead_tile).
-constexpr uint64_t KEEP_W_AND_R_MAX_BYTES = 104ull << 20, KEEP_W_MAX_BYTES = 160ull << 20;
+// and the residual it writes, in the memory-side cache for the kernels that come back to them (see lead_tile).  Three
+// states in turn / one state alone, us a call, r and w kept, w kept, nothing kept: 8 M elements, one worker 65.1 / 65.3, 65.6 /
+// 65.6, 66.9 / 67.6; 15 M 104.6 / 93.3, 98.3 / 96.1, 98.6 / 98.7; 25.6 M 165 / 132, 153 / 137, 146 / 143; 40 M (r and w not
+// tried) 210 / 187 with w kept, 211 / 195 with nothing.
+constexpr uint64_t KEEP_W_AND_R_MAX_BYTES = 40ull << 20, KEEP_W_MAX_BYTES = 160ull << 20;
 
 int launch_leader_pass(const Table& T, const Workspace& ws, const WorkerPtrs& P, const float* w, const uint32_t* leader,
                        uint32_t W, float eps, hipStream_t s) {

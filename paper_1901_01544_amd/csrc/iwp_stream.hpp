@@ -138,8 +138,9 @@ __device__ __forceinline__ void follow_tile_from(uint32_t head, const float* g0,
 // chip's 256 MB memory-side cache the weights (KEEP_W) or the weights and the written
 // residual (KEEP_W_AND_R) are accessed with ordinary loads and stores instead, so that
 // what touches them again within the step (the ordered write clears the sent positions
-// of the residual, the update adds to the weights at them) finds them there: 1-2 % of
-// the step on a 25 M-element table, a loss from about 45 M elements on.
+// of the residual, the update adds to the weights at them) finds them there.  The host
+// picks by the table's size (KEEP_W_MAX_BYTES): a written residual that stays in the
+// cache is written back during whatever comes next.
 constexpr int KEEP_NOTHING = 0, KEEP_W = 1, KEEP_W_AND_R = 2;
 template <bool ACC, int KEEP>
 __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* __restrict__ rl,
