@@ -163,25 +163,27 @@ __global__ __launch_bounds__(INIT_BLOCK, 8) void k_init(uint32_t* __restrict__ w
                                                      SampleSource S) {
     __shared__ uint32_t lh[HIST0];
     __shared__ uint32_t sh[PICK_WORDS];
-    if (blockIdx.x < zero_blocks) {                          // the workspace's parts are whole 256-byte blocks
+    const uint32_t n_layers = gridDim.x - zero_blocks;
+    if (blockIdx.x >= n_layers) {                            // the workspace's parts are whole 256-byte blocks
+        const uint32_t b = blockIdx.x - n_layers;
         const uint64_t quads = (n_words + 3) / 4, stride = (uint64_t)zero_blocks * INIT_BLOCK;
         uint4* w4 = reinterpret_cast<uint4*>(words);
-        for (uint64_t i = (uint64_t)blockIdx.x * INIT_BLOCK + threadIdx.x; i < quads; i += stride) w4[i] = make_uint4(0u, 0u, 0u, 0u);
-        if (single_table && blockIdx.x == 0 && threadIdx.x == 0) {
+        for (uint64_t i = (uint64_t)b * INIT_BLOCK + threadIdx.x; i < quads; i += stride) w4[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (single_table && b == 0 && threadIdx.x == 0) {
             single_table[0] = row;
             single_table[1] = sentinel;
         }
         return;
     }
-    const uint32_t j = blockIdx.x - zero_blocks;
+    const uint32_t j = blockIdx.x;
+    const uint32_t hinted = hint ? hint[j].key & 0x7fffffffu : 0u;
     const DevLayer L = single_table ? row : layers[j];       // the one-row table is only being written by this launch
     constexpr uint32_t BIN = 1u << digit_shift(0);
     const uint32_t below = !S.trust_hint ? 0u : (uint64_t)L.k * HINT_KEEP >= L.n ? HINT_BELOW
                            : S.trust_hint == TRUST_ALWAYS ? HINT_BELOW / 2 : 0u;
-    const uint32_t trusted = below ? hint[j].key & 0x7fffffffu : 0u;
     uint32_t from = 0;
-    if (trusted >= 2u * BIN && trusted < QUIET_NAN_KEY) {
-        from = trusted - below;
+    if (below && hinted >= 2u * BIN && hinted < QUIET_NAN_KEY) {
+        from = hinted - below;
     } else if (S.on && L.k > 0 && L.n > 0) {                 // uniform over the workgroup
         const uint32_t p = leader_of(S.leader, j, S.W);
         from = sample_stage_key(L, S.P.g[p], S.P.r[p], S.w, S.eps, S.P.momentum, lh, sh);
@@ -190,9 +192,8 @@ __global__ __launch_bounds__(INIT_BLOCK, 8) void k_init(uint32_t* __restrict__ w
         LayerState st;
         st.b1 = 0; st.k_rem0 = 0; st.p22 = 0; st.k_rem1 = 0; st.thr = 0; st.n_eq_take = 0; st.prestaged = 0;
         // a guess in the lowest bin (among zero scores): look 1 stages nothing; among NaN: whole bins
-        const uint32_t h = hint ? hint[j].key & 0x7fffffffu : 0u;
         const uint32_t slack = S.P.momentum == 1.0f ? 0u : HINT_SLACK;
-        if (h >= 2u * BIN && h + slack < from) from = h;
+        if (hinted >= 2u * BIN && hinted + slack < from) from = hinted;
         st.shift = (from >= BIN && from < QUIET_NAN_KEY) ? (0u - from) & (BIN - 1u) : 0u;
         st.stage_bin = from >= BIN ? shifted(from, st.shift) >> digit_shift(0) : NO_STAGE_BIN;
         state[j] = st;
