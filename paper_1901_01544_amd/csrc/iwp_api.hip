@@ -17,6 +17,7 @@
 #include "iwp_select.hpp"
 #include "iwp_small.hpp"
 #include "iwp_stream.hpp"
+#include "iwp_sum.hpp"
 #include "iwp_threshold.hpp"
 
 using namespace iwp;
@@ -657,6 +658,13 @@ static int check_ws(size_t need, void* workspace, size_t workspace_bytes) {
     return IWP_OK;
 }
 
+// The first worker with a gradient, or worker 0: the one whose residual k_follow_sum's chunks are aligned to.
+static uint32_t first_streaming(const float* const* g, uint32_t W) {
+    for (uint32_t p = 0; p < W; ++p)
+        if (g[p]) return p;
+    return 0u;
+}
+
 static int worker_tables(const float* const* g, float* const* r, uint32_t W, float momentum, WorkerPtrs* P,
                          ResidualPtrs* R) {
     if (!g || !r || W == 0 || W > IWP_MAX_WORKERS) return IWP_EINVAL;
@@ -781,6 +789,11 @@ int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, fl
     // a single accumulating worker that leads every layer (no leader table: worker 0) has been through look 1 on
     // every tile: nothing follows
     const bool leader_did_all = acc.n == 1 && acc.id[0] == 0 && !leader && plan->all_k;
+    if (acc.n && !leader_did_all && T.tiles <= FOLLOW_SUM_MAX_TILES) {
+        IWP_LAUNCH("k_follow_sum", k_follow_sum, CHUNKS_A_TILE * T.tiles, s, P, first_streaming(g, W), T.layers, T.n_layers,
+                   leader, W, idx_out, val_out, ws.tile_out, w, scale, sum_out);
+        return IWP_OK;
+    }
     if (acc.n && !leader_did_all)
         IWP_LAUNCH("k_follow_gather", k_follow_gather, acc.n * T.tiles, s, P, acc, T.layers, T.n_layers, T.tiles, leader,
                    W, idx_out, ws.tile_out, ws.gathered, T.pairs);
@@ -928,6 +941,12 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
     IWP_LAUNCH_BLOCK("k_tile_offsets", k_tile_offsets, 1u, OFFSETS_BLOCK, s, layers, z.n_layers, z.tiles, ws.tile_counts, max_pairs,
                      ws.tile_pos, ws.lay_out, count_out);
     if (z.tiles == 0) return IWP_OK;
+    if (z.tiles <= FOLLOW_SUM_MAX_TILES) {
+        IWP_LAUNCH("k_follow_mask_sum", k_follow_mask_sum, CHUNKS_A_TILE * z.tiles, s, P, first_streaming(g, W), layers, z.n_layers,
+                   leaders, n_lead, W, mask32, ws.tile_counts, ws.tile_pos, count_out, max_pairs, ws.slots, idx_out, w, scale,
+                   sum_out);
+        return IWP_OK;
+    }
     IWP_LAUNCH("k_follow_mask", k_follow_mask, W * z.tiles, s, P, layers, z.n_layers, z.tiles, leaders, n_lead, W, mask32,
                ws.tile_counts, ws.tile_pos, count_out, max_pairs, ws.slots, idx_out, ws.gathered);
     uint32_t static_mask = 0;
