@@ -1,19 +1,22 @@
-"""Build step of the HIP library: one hipcc invocation, gfx950 only.
+"""Build step: the HIP library (one hipcc invocation, gfx950 only) and the Python module that calls into it.
 
     python -m paper_1901_01544_amd.build
 
-The shared object is written next to this file (``libiwp.so``), in-tree, so it
-travels with the source tree to wherever the GPU is.
+The shared objects are written next to this file (``libiwp.so``, ``_call.so``), in-tree, so they
+travel with the source tree to wherever the GPU is.
 """
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "csrc", "iwp_api.hip")
 LIB = os.path.join(HERE, "libiwp.so")
+CALL_SRC = os.path.join(HERE, "csrc", "call.cpp")
+CALL = os.path.join(HERE, "_call.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
@@ -52,6 +55,19 @@ def build(verbose: bool = False, extra_flags=(), out: str = LIB) -> str:
     return out
 
 
+def build_call(verbose: bool = False, out: str = CALL) -> str:
+    """Compile csrc/call.cpp (host code only) into the extension module _call.so; returns the path."""
+    tmp = out + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           "-I", sysconfig.get_paths()["include"], "-o", tmp, CALL_SRC]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, out)
+    return out
+
+
 if __name__ == "__main__":
     print(build(verbose=True))
+    print(build_call(verbose=True))
     sys.exit(0)

@@ -1,4 +1,5 @@
-"""Thin Python binding of the C-ABI HIP library (``include/iwp.h``).
+"""Thin Python binding of the C-ABI HIP library (``include/iwp.h``): ctypes for what is called now and then, the extension
+module ``_call`` (csrc/call.cpp) for the hot calls.
 
 Argument marshalling only: torch tensors are used for device memory and
 streams, every step of the method runs in the library's kernels.  The function
@@ -31,13 +32,14 @@ class Layer(C.Structure):
 
 
 _lib = None
+_call = None                # the module that converts the hot calls' arguments (csrc/call.cpp)
 _vp = C.c_void_p
 
 
 def load() -> C.CDLL:
     """Open libiwp.so (built beforehand by ``python -m paper_1901_01544_amd.build``
-    or ``__graft_entry__.build()``).  Raises if it is not there."""
-    global _lib
+    or ``__graft_entry__.build()``).  Raises if it, or the module that calls into it, is not there."""
+    global _lib, _call
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -47,7 +49,13 @@ def load() -> C.CDLL:
     # The device pointers and streams this binding passes come from torch, so the library has to
     # bind to the HIP runtime torch carries: torch is imported (its runtime loaded) before the library.
     import torch  # noqa: F401
+    try:
+        from . import _call as call
+    except ImportError as e:
+        raise FileNotFoundError("the module _call is missing beside iwp.py (%s): build it with "
+                                "`python -m paper_1901_01544_amd.build`" % e) from e
     L = C.CDLL(LIB_PATH)
+    call.bind({name: C.cast(getattr(L, name), _vp).value for name in call.names()})
     L.iwp_workspace_bytes.argtypes = [C.c_uint32, C.c_uint32]
     L.iwp_workspace_bytes.restype = C.c_size_t
     L.compress_layer.argtypes = [_vp, _vp, _vp, C.c_uint32, C.c_uint32, C.c_float, _vp, _vp, _vp, C.c_size_t, _vp]
@@ -107,8 +115,15 @@ def load() -> C.CDLL:
                  "apply_sparse_update", "iwp_plan_create", "compress_segmented", "select_threshold_segmented",
                  "compact_pairs_segmented", "iwp_score_keys"):
         getattr(L, name).restype = C.c_int
-    _lib = L
+    _lib, _call = L, call
     return L
+
+
+def _hot():
+    """The module with the hot calls, the library loaded."""
+    if _call is None:
+        load()
+    return _call
 
 
 def _check(rc: int, what: str) -> None:
@@ -130,15 +145,23 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
-def _ptr_table(tensors: Sequence):
-    return (_vp * max(1, len(tensors)))(*[_ptr(t) for t in tensors])
+_current_device = _raw_stream = None
 
 
 def _stream(stream) -> Optional[int]:
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream or None
+    global _current_device, _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        import torch
+        current = torch.cuda.current_stream().cuda_stream     # initialises torch's runtime if nothing has
+        _current_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+        return current
+    return _raw_stream(_current_device())
+
+
+def _bytes(workspace) -> int:
+    return 0 if workspace is None else workspace.nbytes
 
 
 # ------------------------------------------------------------------ one layer
@@ -149,35 +172,32 @@ def workspace_bytes(n: int, k: int) -> int:
 
 def compress_layer(w, g, r, k: int, eps: float, idx_out, val_out, workspace, stream=None, n: Optional[int] = None):
     n = r.numel() if n is None else n
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().compress_layer(_ptr(w), _ptr(g), _ptr(r), n, k, eps, _ptr(idx_out), _ptr(val_out),
-                                 _ptr(workspace), ws_bytes, _stream(stream)), "compress_layer")
+    _check(_hot().compress_layer(w, g, r, n, k, eps, idx_out, val_out, workspace, _bytes(workspace), _stream(stream)),
+           "compress_layer")
 
 
 def select_threshold(w, r, k: int, eps: float, thr_out, workspace, stream=None, n: Optional[int] = None):
     n = r.numel() if n is None else n
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().select_threshold(_ptr(w), _ptr(r), n, k, eps, _ptr(thr_out), _ptr(workspace), ws_bytes,
-                                   _stream(stream)), "select_threshold")
+    _check(_hot().select_threshold(w, r, n, k, eps, thr_out, workspace, _bytes(workspace), _stream(stream)),
+           "select_threshold")
 
 
 def compact_pairs(w, r, eps: float, thr, k: int, idx_out, val_out, workspace, stream=None, n: Optional[int] = None):
     n = r.numel() if n is None else n
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().compact_pairs(_ptr(w), _ptr(r), n, eps, _ptr(thr), k, _ptr(idx_out), _ptr(val_out),
-                                _ptr(workspace), ws_bytes, _stream(stream)), "compact_pairs")
+    _check(_hot().compact_pairs(w, r, n, eps, thr, k, idx_out, val_out, workspace, _bytes(workspace),
+           _stream(stream)), "compact_pairs")
 
 
 # ------------------------------------------------------------------ exchange
 
 def gather_sum_at_indices(residuals: Sequence, idx, k: int, sum_out, stream=None):
-    _check(load().gather_sum_at_indices(_ptr_table(residuals), len(residuals), _ptr(idx), k, _ptr(sum_out),
-                                        _stream(stream)), "gather_sum_at_indices")
+    _check(_hot().gather_sum_at_indices(residuals, len(residuals), idx, k, sum_out, _stream(stream)),
+           "gather_sum_at_indices")
 
 
 def apply_sparse_update(w, idx, sum_, k: int, scale: float, residuals_to_clear: Sequence, stream=None):
-    _check(load().apply_sparse_update(_ptr(w), _ptr(idx), _ptr(sum_), k, scale, _ptr_table(residuals_to_clear),
-                                      len(residuals_to_clear), _stream(stream)), "apply_sparse_update")
+    _check(_hot().apply_sparse_update(w, idx, sum_, k, scale, residuals_to_clear, len(residuals_to_clear),
+           _stream(stream)), "apply_sparse_update")
 
 
 # ------------------------------------------------------------------ all layers in one pass
@@ -193,6 +213,7 @@ class Plan:
         handle = _vp()
         _check(load().iwp_plan_create(tab, len(rows), C.byref(handle)), "iwp_plan_create")
         self._h = handle
+        self._address = handle.value
         self.n_layers = len(rows)
         self.workspace_bytes = int(load().iwp_plan_workspace_bytes(self._h))
         self.total_pairs = int(load().iwp_plan_total_pairs(self._h))
@@ -213,7 +234,7 @@ class Plan:
     def close(self):
         if getattr(self, "_h", None):
             load().iwp_plan_destroy(self._h)
-            self._h = None
+            self._h = self._address = None
 
     def __del__(self):
         try:
@@ -225,76 +246,59 @@ class Plan:
 def compress_segmented(plan: Plan, w, g: Sequence, r: Sequence, leader, eps: float, idx_out, val_out, thr_out,
                        workspace, stream=None, thr_hint=None):
     assert len(g) == len(r)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().compress_segmented(plan._h, _ptr(w), _ptr_table(g), _ptr_table(r), len(r), _ptr(leader),
-                                     _ptr(thr_hint), eps,
-                                     _ptr(idx_out), _ptr(val_out), _ptr(thr_out), _ptr(workspace), ws_bytes,
-                                     _stream(stream)), "compress_segmented")
+    _check(_hot().compress_segmented(plan._address, w, g, r, len(r), leader, thr_hint, eps, idx_out, val_out, thr_out,
+           workspace, _bytes(workspace), _stream(stream)), "compress_segmented")
 
 
 def compress_segmented_static(plan: Plan, w, g: Sequence, r: Sequence, leader, eps: float, idx_out, val_out, thr_out,
                               stream=None, thr_hint=None):
     assert len(g) == len(r)
-    _check(load().compress_segmented_static(plan._h, _ptr(w), _ptr_table(g), _ptr_table(r), len(r), _ptr(leader),
-                                            _ptr(thr_hint), eps, _ptr(idx_out), _ptr(val_out), _ptr(thr_out),
-                                            _stream(stream)), "compress_segmented_static")
+    _check(_hot().compress_segmented_static(plan._address, w, g, r, len(r), leader, thr_hint, eps, idx_out, val_out,
+           thr_out, _stream(stream)), "compress_segmented_static")
 
 
 def step_segmented(plan: Plan, w, g: Sequence, r: Sequence, leader, eps: float, scale: float, idx_out, val_out,
                    sum_out, thr_out, workspace, stream=None, thr_hint=None):
     assert len(g) == len(r)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().iwp_step_segmented(plan._h, _ptr(w), _ptr_table(g), _ptr_table(r), len(r), _ptr(leader),
-                                     _ptr(thr_hint), eps, scale,
-                                     _ptr(idx_out), _ptr(val_out), _ptr(sum_out), _ptr(thr_out), _ptr(workspace),
-                                     ws_bytes, _stream(stream)), "iwp_step_segmented")
+    _check(_hot().iwp_step_segmented(plan._address, w, g, r, len(r), leader, thr_hint, eps, scale, idx_out, val_out,
+           sum_out, thr_out, workspace, _bytes(workspace), _stream(stream)), "iwp_step_segmented")
 
 
 def step_threshold_segmented(plan: Plan, w, g: Sequence, r: Sequence, leaders, n_lead: int, thr, eps: float,
                              scale: float, mask_out, count_out, idx_out, sum_out, max_pairs: int, workspace,
                              stream=None):
     assert len(g) == len(r)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().iwp_step_threshold_segmented(plan._h, _ptr(w), _ptr_table(g), _ptr_table(r), len(r), _ptr(leaders),
-                                               n_lead, _ptr(thr), eps, scale, _ptr(mask_out), _ptr(count_out),
-                                               _ptr(idx_out), _ptr(sum_out), max_pairs, _ptr(workspace), ws_bytes,
-                                               _stream(stream)), "iwp_step_threshold_segmented")
+    _check(_hot().iwp_step_threshold_segmented(plan._address, w, g, r, len(r), leaders, n_lead, thr, eps, scale,
+           mask_out, count_out, idx_out, sum_out, max_pairs, workspace, _bytes(workspace), _stream(stream)),
+           "iwp_step_threshold_segmented")
 
 
 def step_threshold_random_segmented(plan: Plan, w, g: Sequence, r: Sequence, leaders, n_lead: int, thr, seed: int,
                                     step: int, eps: float, scale: float, mask_out, count_out, idx_out, sum_out,
                                     max_pairs: int, workspace, stream=None):
     assert len(g) == len(r)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().iwp_step_threshold_random_segmented(plan._h, _ptr(w), _ptr_table(g), _ptr_table(r), len(r),
-                                                      _ptr(leaders), n_lead, _ptr(thr), seed, step, eps, scale,
-                                                      _ptr(mask_out), _ptr(count_out), _ptr(idx_out), _ptr(sum_out),
-                                                      max_pairs, _ptr(workspace), ws_bytes, _stream(stream)),
-           "iwp_step_threshold_random_segmented")
+    _check(_hot().iwp_step_threshold_random_segmented(plan._address, w, g, r, len(r), leaders, n_lead, thr, seed,
+           step, eps, scale, mask_out, count_out, idx_out, sum_out, max_pairs, workspace, _bytes(workspace),
+           _stream(stream)), "iwp_step_threshold_random_segmented")
 
 
 def step_layerwise_segmented(plan: Plan, w, g: Sequence, r: Sequence, leaders, n_lead: int, alpha: float, beta: float,
                              c: float, eps: float, scale: float, stats_out, thr_out, mask_out, count_out, idx_out,
                              sum_out, max_pairs: int, workspace, stream=None):
     assert len(g) == len(r)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().iwp_step_layerwise_segmented(plan._h, _ptr(w), _ptr_table(g), _ptr_table(r), len(r), _ptr(leaders),
-                                               n_lead, alpha, beta, c, eps, scale, _ptr(stats_out), _ptr(thr_out),
-                                               _ptr(mask_out), _ptr(count_out), _ptr(idx_out), _ptr(sum_out),
-                                               max_pairs, _ptr(workspace), ws_bytes, _stream(stream)),
-           "iwp_step_layerwise_segmented")
+    _check(_hot().iwp_step_layerwise_segmented(plan._address, w, g, r, len(r), leaders, n_lead, alpha, beta, c, eps,
+           scale, stats_out, thr_out, mask_out, count_out, idx_out, sum_out, max_pairs, workspace, _bytes(workspace),
+           _stream(stream)), "iwp_step_layerwise_segmented")
 
 
 def select_threshold_segmented(plan: Plan, w, r, eps: float, thr_out, workspace, stream=None):
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().select_threshold_segmented(plan._h, _ptr(w), _ptr(r), eps, _ptr(thr_out), _ptr(workspace),
-                                             ws_bytes, _stream(stream)), "select_threshold_segmented")
+    _check(_hot().select_threshold_segmented(plan._address, w, r, eps, thr_out, workspace, _bytes(workspace),
+           _stream(stream)), "select_threshold_segmented")
 
 
 def compact_pairs_segmented(plan: Plan, w, r, eps: float, thr, idx_out, val_out, workspace, stream=None):
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().compact_pairs_segmented(plan._h, _ptr(w), _ptr(r), eps, _ptr(thr), _ptr(idx_out), _ptr(val_out),
-                                          _ptr(workspace), ws_bytes, _stream(stream)), "compact_pairs_segmented")
+    _check(_hot().compact_pairs_segmented(plan._address, w, r, eps, thr, idx_out, val_out, workspace,
+           _bytes(workspace), _stream(stream)), "compact_pairs_segmented")
 
 
 def score_keys(w, r, eps: float, key_out, stream=None):
