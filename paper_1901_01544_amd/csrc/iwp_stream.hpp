@@ -141,11 +141,13 @@ __device__ __forceinline__ void follow_tile_from(uint32_t head, const float* g0,
 // of the residual, the update adds to the weights at them) finds them there.  The host
 // picks by the table's size (KEEP_W_MAX_BYTES): a written residual that stays in the
 // cache is written back during whatever comes next.
+// clear: the histogram is cleared first, once the tile's loads are on their way; before them it kept every
+// workgroup from its loads (look 1 of one layer of 1 M elements 13.6 -> 12.8 us, thresholds of 25.6 M 51.4 -> 50.3).
 constexpr int KEEP_NOTHING = 0, KEEP_W = 1, KEEP_W_AND_R = 2;
 template <bool ACC, int KEEP>
 __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* __restrict__ rl,
                                           const float* __restrict__ wl, uint32_t n, uint32_t lt,
-                                          float eps, float m, const LeadCtx& C) {
+                                          float eps, float m, const LeadCtx& C, bool clear) {
     const uint32_t tid = threadIdx.x;
     const uint32_t base = lt * TILE;
     uint32_t key[CHUNKS_PER_TILE][4];
@@ -154,6 +156,10 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
     request_tile<true>(rl, n, base, val, val_rest);
     if (ACC) request_tile<true>(gl, n, base, gv, gv_rest);
     request_tile<(KEEP < KEEP_W)>(wl, n, base, wv, wv_rest);
+    if (clear) {                                            // uniform; the loads are on their way
+        for (uint32_t b = tid; b < HIST0 / 4; b += BLOCK) reinterpret_cast<uint4*>(C.lh)[b] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+    }
     settle_tile(n, base, val, val_rest);
     if (ACC) settle_tile(n, base, gv, gv_rest);
     settle_tile(n, base, wv, wv_rest);
@@ -199,16 +205,14 @@ template <int KEEP>
 __device__ __forceinline__ void leader_group(const float* gp, float* rp, const float* __restrict__ w, const DevLayer& L,
                                              uint32_t first_tile /*in layer*/, uint32_t group_tiles, float eps, float m,
                                              LeadCtx& C, uint32_t* __restrict__ ghist) {
-    for (uint32_t b = threadIdx.x; b < HIST0; b += BLOCK) C.lh[b] = 0u;
-    __syncthreads();
     float* rl = rp + L.offset;
     const float* gl = gp ? gp + L.offset : nullptr;
     const float* wl = w + L.offset;
     const uint32_t ntiles = (L.n + TILE - 1) / TILE;
     const uint32_t last = min(first_tile + group_tiles, ntiles);
     for (uint32_t t = first_tile; t < last; ++t) {
-        if (gp) lead_tile<true, KEEP>(gl, rl, wl, L.n, t, eps, m, C);
-        else lead_tile<false, KEEP>(gl, rl, wl, L.n, t, eps, m, C);
+        if (gp) lead_tile<true, KEEP>(gl, rl, wl, L.n, t, eps, m, C, t == first_tile);
+        else lead_tile<false, KEEP>(gl, rl, wl, L.n, t, eps, m, C, t == first_tile);
     }
     __syncthreads();
     for (uint32_t b = threadIdx.x; b < HIST0; b += BLOCK) {
@@ -261,7 +265,7 @@ __global__ __launch_bounds__(BLOCK) void k_leader_pass(WorkerPtrs P, const float
                                                        uint32_t* __restrict__ hist,
                                                        const LayerState* __restrict__ state,
                                                        uint32_t* __restrict__ stage_cnt, StageArrays A) {
-    __shared__ uint32_t lh[HIST0];
+    __shared__ alignas(16) uint32_t lh[HIST0];
     __shared__ uint32_t slot[2 * STAGE_WORDS];
     uint32_t j, first;
     if (LG == 1) {
