@@ -197,6 +197,9 @@ struct Table {                // what the launches need to know about a layer ta
 // counts itself (16 loads per thread at most); beyond, a scan launch is cheaper.
 constexpr uint32_t FOLD_SCAN_MAX_STILES = 4096;
 
+// Do the followers' passes take the tiles in runs (see in_runs)?
+uint32_t takes_runs(uint32_t tiles, uint32_t n_layers) { return tiles <= (uint64_t)RUN_TILES * n_layers ? 1u : 0u; }
+
 int check_eps(float eps) { return (eps >= 0.0f && std::isfinite(eps)) ? IWP_OK : IWP_EINVAL; }
 
 // Sampling source of a call: the leaders' residuals and gradients (NULL entries allowed), or nothing.
@@ -466,7 +469,7 @@ static int single_common(SingleOp op, const float* w, const float* g, float* r, 
         rc = launch_leader_pass(T, ws, P, w, nullptr, 1u, eps, s);
         if (rc) return rc;
     } else if (g)
-        IWP_LAUNCH("k_accumulate_rest", k_accumulate_rest, z.tiles, s, P, T.layers, 1u, z.tiles, nullptr, 1u);
+        IWP_LAUNCH("k_accumulate_rest", k_accumulate_rest, z.tiles, s, P, T.layers, 1u, z.tiles, 0u, nullptr, 1u);
     return run_select(T, ws, R, w, nullptr, 1u, eps, op == OP_SELECT ? STOP_AT_THRESHOLD : FULL, false, idx_out,
                       val_out, thr_out, s);
 }
@@ -724,7 +727,8 @@ static int compress_segmented_on(const iwp_plan* plan, const float* w, const flo
         }
     }
     if (W > 1 || !plan->all_k)
-        IWP_LAUNCH("k_accumulate_rest", k_accumulate_rest, W * T.tiles, s, P, T.layers, T.n_layers, T.tiles, leader, W);
+        IWP_LAUNCH("k_accumulate_rest", k_accumulate_rest, W * T.tiles, s, P, T.layers, T.n_layers, T.tiles,
+                   takes_runs(T.tiles, T.n_layers), leader, W);
     if (small) return IWP_OK;
     return run_select(T, ws, R, w, leader, W, eps, FULL, false, idx_out, val_out, thr_out, s);
 }
@@ -795,8 +799,8 @@ int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, fl
         return IWP_OK;
     }
     if (acc.n && !leader_did_all)
-        IWP_LAUNCH("k_follow_gather", k_follow_gather, acc.n * T.tiles, s, P, acc, T.layers, T.n_layers, T.tiles, leader,
-                   W, idx_out, ws.tile_out, ws.gathered, T.pairs);
+        IWP_LAUNCH("k_follow_gather", k_follow_gather, acc.n * T.tiles, s, P, acc, T.layers, T.n_layers, T.tiles,
+                   takes_runs(T.tiles, T.n_layers), leader, W, idx_out, ws.tile_out, ws.gathered, T.pairs);
     if (T.any_k) {
         uint32_t static_mask = 0;
         for (uint32_t q = 0; q < stat.n; ++q) static_mask |= 1u << stat.id[q];
@@ -947,7 +951,8 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
                    sum_out);
         return IWP_OK;
     }
-    IWP_LAUNCH("k_follow_mask", k_follow_mask, W * z.tiles, s, P, layers, z.n_layers, z.tiles, leaders, n_lead, W, mask32,
+    IWP_LAUNCH("k_follow_mask", k_follow_mask, W * z.tiles, s, P, layers, z.n_layers, z.tiles, takes_runs(z.tiles, z.n_layers),
+               leaders, n_lead, W, mask32,
                ws.tile_counts, ws.tile_pos, count_out, max_pairs, ws.slots, idx_out, ws.gathered);
     uint32_t static_mask = 0;
     for (uint32_t p = 0; p < W; ++p)

@@ -237,12 +237,13 @@ __device__ __forceinline__ LeadCtx lead_ctx(uint32_t* lh, uint32_t* slot, const 
 
 // Every worker that is not the leader of the tile's layer (and every worker of a layer
 // without selection): plain accumulation, W * tiles workgroups, worker-major.  A worker
-// without a gradient pointer is not accumulated.  The leaders go through k_leader_pass.
+// without a gradient pointer is not accumulated.  runs: see in_runs().  The leaders go through k_leader_pass.
 __global__ __launch_bounds__(BLOCK) void k_accumulate_rest(WorkerPtrs P, const DevLayer* __restrict__ layers,
-                                                           uint32_t n_layers, uint32_t tiles,
+                                                           uint32_t n_layers, uint32_t tiles, uint32_t runs,
                                                            const uint32_t* __restrict__ leader, uint32_t W) {
-    const uint32_t p = blockIdx.x / tiles;
-    const uint32_t t = blockIdx.x - p * tiles;
+    const uint32_t b = runs ? in_runs(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t p = b / tiles;
+    const uint32_t t = b - p * tiles;
     const uint32_t j = layer_of_tile(layers, n_layers, t);
     const DevLayer L = layers[j];
     const float* gp = P.g[p];
@@ -294,17 +295,18 @@ __global__ __launch_bounds__(BLOCK) void k_leader_pass(WorkerPtrs P, const float
 // the gather matrix and leave +0 behind.  tile_out[t] = position (inside the
 // layer's pairs) of the first pair that falls into tile t; the pairs are ascending,
 // so a tile's pairs are contiguous.  `acc`: the workers that accumulate (have a
-// gradient); the grid is acc.n * tiles.
+// gradient); the grid is acc.n * tiles.  runs: see in_runs().
 __global__ __launch_bounds__(BLOCK) void k_follow_gather(WorkerPtrs P, WorkerList acc, const DevLayer* __restrict__ layers,
-                                                         uint32_t n_layers, uint32_t tiles,
+                                                         uint32_t n_layers, uint32_t tiles, uint32_t runs,
                                                          const uint32_t* __restrict__ leader, uint32_t W,
                                                          const uint32_t* __restrict__ idx,
                                                          const uint32_t* __restrict__ tile_out,
                                                          float* __restrict__ gathered, uint64_t K) {
     __shared__ uint32_t map[TILE_WORDS], pre[TILE_WORDS], slot[4];
     const uint32_t tid = threadIdx.x;
-    const uint32_t a = blockIdx.x / tiles;
-    const uint32_t t = blockIdx.x - a * tiles;
+    const uint32_t b = runs ? in_runs(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t a = b / tiles;
+    const uint32_t t = b - a * tiles;
     const uint32_t p = acc.id[a];
     const uint32_t j = layer_of_tile(layers, n_layers, t);
     const DevLayer L = layers[j];

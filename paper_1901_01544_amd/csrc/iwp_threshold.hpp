@@ -425,7 +425,7 @@ __global__ __launch_bounds__(OFFSETS_BLOCK) void k_tile_offsets(const DevLayer* 
 // ---------------------------------------------------------------------------
 // Every node that is not chosen for the layer and has a gradient: accumulate, and
 // where the tile's mask has bits, copy the accumulated value into the node's gather
-// row and leave +0 behind.  Grid: W * tiles.  The workgroups of the chosen nodes, whose
+// row and leave +0 behind.  Grid: W * tiles; runs: see in_runs().  The workgroups of the chosen nodes, whose
 // residuals k_leader_mask has been through, have nothing to stream: those of the first one write the
 // tile's masked positions as ascending flat indices and move the sent values of all of them from the tile's
 // slots to their gather rows.
@@ -444,7 +444,7 @@ __device__ __forceinline__ void tile_mask(const uint32_t* __restrict__ mask, con
 }
 
 __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLayer* __restrict__ layers,
-                                                       uint32_t n_layers, uint32_t tiles,
+                                                       uint32_t n_layers, uint32_t tiles, uint32_t runs,
                                                        const uint32_t* __restrict__ leaders, uint32_t n_lead, uint32_t W,
                                                        const uint32_t* __restrict__ mask,
                                                        const uint32_t* __restrict__ tile_counts,
@@ -454,8 +454,9 @@ __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLa
                                                        float* __restrict__ gathered) {
     __shared__ uint32_t map[TILE_WORDS], pre[TILE_WORDS], slot[4];
     const uint32_t tid = threadIdx.x;
-    const uint32_t p = blockIdx.x / tiles;
-    const uint32_t t = blockIdx.x - p * tiles;
+    const uint32_t b = runs ? in_runs(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t p = b / tiles;
+    const uint32_t t = b - p * tiles;
     const uint32_t j = layer_of_tile(layers, n_layers, t);
     const DevLayer L = layers[j];
     const uint32_t base = (t - L.tile_begin) * TILE;
