@@ -113,6 +113,13 @@ inline uint32_t slot_cap_of(uint32_t n, uint32_t k) {
     return (uint32_t)std::min<uint64_t>(TILE, 64 + 3 * per_tile);
 }
 
+// Small tables (LOOK_TWICE_TILES, see iwp_select.hpp) have no sampled mark, and the second look copies out whole bins of the
+// first digit: up to 1/16 of a tile where the scores lie evenly below the threshold, for which their slots have LOOK_TWICE_ROOM
+// entries more.  Larger tables hold the same number of entries in reserve, so that a workspace that fits a table fits
+// the smaller ones of its kind.
+inline uint32_t roomy(uint32_t slot_cap) { return slot_cap ? std::min<uint32_t>(TILE, slot_cap + LOOK_TWICE_ROOM) : 0u; }
+inline uint64_t roomy_reserve(uint64_t tiles) { return std::min<uint64_t>(tiles, LOOK_TWICE_TILES) * LOOK_TWICE_ROOM; }
+
 // How k_init samples a layer: enough runs for the threshold's rank in the sample to be about SAMPLE_RANK, and the rank
 // of the sample's element from whose key look 1 copies out (see iwp_select.hpp).
 uint32_t sample_of(uint32_t n, uint32_t k) {
@@ -202,10 +209,10 @@ uint32_t takes_runs(uint32_t tiles, uint32_t n_layers) { return tiles <= (uint64
 
 int check_eps(float eps) { return (eps >= 0.0f && std::isfinite(eps)) ? IWP_OK : IWP_EINVAL; }
 
-// Sampling source of a call: the leaders' residuals and gradients (NULL entries allowed), or nothing.
-SampleSource sample_from(const WorkerPtrs& P, const float* w, const uint32_t* leader, uint32_t W, float eps) {
+// Sampling source of a call: the leaders' residuals and gradients (NULL entries allowed), or nothing (on: false, or no w).
+SampleSource sample_from(const WorkerPtrs& P, const float* w, const uint32_t* leader, uint32_t W, float eps, bool on = true) {
     SampleSource S;
-    S.P = P; S.w = w; S.leader = leader; S.W = W; S.eps = eps; S.on = w ? 1u : 0u; S.trust_hint = 0u;
+    S.P = P; S.w = w; S.leader = leader; S.W = W; S.eps = eps; S.on = w && on ? 1u : 0u; S.trust_hint = 0u;
     return S;
 }
 
@@ -374,6 +381,7 @@ struct iwp_plan {
     uint32_t max_n = 0;           // elements of the longest layer
     uint32_t n_long = 0;          // layers of more than one tile
     bool all_dense = true;        // each of those keeps at least one element in HINT_KEEP
+    bool look_twice = false;      // no marks by samples, roomy slots (LOOK_TWICE_TILES)
     uint32_t max_copies = 1;      // most copies of a layer's first-digit histogram
     float momentum = 1.0f;        // r <- momentum * r + g in every call that accumulates through this plan
 };
@@ -414,7 +422,7 @@ const char* iwp_last_hip_error(void) { return g_hip_error; }
 static Sizes single_sizes(uint32_t n, uint32_t k) {
     Sizes z;
     z.n_layers = 1; z.tiles = tiles_of(n); z.stiles = stiles_of(n);
-    z.pairs = k; z.slots = (uint64_t)z.tiles * slot_cap_of(n, k); z.mask_words = ((uint64_t)n + 31) / 32;
+    z.pairs = k; z.slots = (uint64_t)z.tiles * slot_cap_of(n, k) + (k ? roomy_reserve(z.tiles) : 0u); z.mask_words = ((uint64_t)n + 31) / 32;
     z.hist_words = layer_hist_words(h0_copies_of(n, k));
     z.W_gather = 0;
     return z;
@@ -452,7 +460,7 @@ static int single_common(SingleOp op, const float* w, const float* g, float* r, 
     DevLayer row, sentinel;
     memset(&row, 0, sizeof row);
     memset(&sentinel, 0, sizeof sentinel);
-    row.n = n; row.k = k; row.slot_cap = slot_cap_of(n, k);
+    row.n = n; row.k = k; row.slot_cap = z.tiles <= LOOK_TWICE_TILES ? roomy(slot_cap_of(n, k)) : slot_cap_of(n, k);
     row.sample = sample_of(n, k);
     row.hist_begin = 0; row.h0_copies = h0_copies_of(n, k);
     sentinel.tile_begin = z.tiles; sentinel.stile_begin = z.stiles; sentinel.out_offset = k;
@@ -460,7 +468,7 @@ static int single_common(SingleOp op, const float* w, const float* g, float* r, 
         return launch_small(nullptr, &row, 1u, 1u, n, k, ws, P, w, nullptr, 1u, eps, op == OP_SELECT ? STOP_AT_THRESHOLD : FULL,
                             false, idx_out, val_out, thr_out, s);
     SampleSource S = sample_from(P, w, nullptr, 1u, eps);
-    if (op == OP_COMPACT || k == 0) S.on = 0;
+    if (op == OP_COMPACT || k == 0 || z.tiles <= LOOK_TWICE_TILES) S.on = 0;
     int rc = launch_init(ws, 1, z.tiles, nullptr, nullptr, &row, &sentinel, S, s);
     if (rc) return rc;
     Table T{ws.single_table, 1, z.tiles, z.stiles, k, k > 0, z.stiles, row.h0_copies};
@@ -596,6 +604,21 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     plan->max_n = max_n;
     plan->n_long = n_long;
     plan->all_dense = all_dense;
+    // roomy slots, or what larger tables hold in reserve for them, unless the library's static scratch would no longer do
+    Sizes roomier = plan->z;
+    roomier.slots += any_k ? roomy_reserve(tiles) : 0u;
+    if (carve(nullptr, roomier).bytes <= IWP_STATIC_SCRATCH_BYTES) {
+        plan->z = roomier;
+        plan->look_twice = tiles <= LOOK_TWICE_TILES;
+    }
+    if (plan->look_twice) {
+        slots = 0;
+        for (DevLayer& D : dev) {
+            D.slot_begin = slots;
+            D.slot_cap = roomy(D.slot_cap);
+            slots += (uint64_t)tiles_of(D.n) * D.slot_cap;
+        }
+    }
     if (carve(nullptr, plan->z).bytes > IWP_STATIC_SCRATCH_BYTES) {
         Sizes few = plan->z;
         few.hist_words = 0;
@@ -719,7 +742,8 @@ static int compress_segmented_on(const iwp_plan* plan, const float* w, const flo
                           val_out, thr_out, s);
         if (rc) return rc;
     } else {
-        rc = launch_init(ws, T.n_layers, T.tiles, thr_hint, T.layers, nullptr, nullptr, sample_from(P, w, leader, W, eps), s);
+        rc = launch_init(ws, T.n_layers, T.tiles, thr_hint, T.layers, nullptr, nullptr,
+                         sample_from(P, w, leader, W, eps, !plan->look_twice), s);
         if (rc) return rc;
         if (T.any_k) {
             rc = launch_leader_pass(T, ws, P, w, leader, W, eps, s);
@@ -777,7 +801,8 @@ int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, fl
                           val_out, thr_out, s);
         if (rc) return rc;
     } else if (T.any_k) {
-        rc = launch_init(ws, z.n_layers, z.tiles, thr_hint, plan->dev, nullptr, nullptr, sample_from(P, w, leader, W, eps), s);
+        rc = launch_init(ws, z.n_layers, z.tiles, thr_hint, plan->dev, nullptr, nullptr,
+                         sample_from(P, w, leader, W, eps, !plan->look_twice), s);
         if (rc) return rc;
         rc = launch_leader_pass(T, ws, P, w, leader, W, eps, s);
         if (rc) return rc;
@@ -827,7 +852,8 @@ int select_threshold_segmented(const iwp_plan* plan, const float* w, const float
     if (takes_small(*plan, false, true))
         return launch_small(plan->dev, nullptr, plan->z.n_layers, plan->n_long, plan->max_n, plan->z.pairs, ws, P, w, nullptr, 1u, eps,
                             STOP_AT_THRESHOLD, false, nullptr, nullptr, thr_out, s);
-    rc = launch_init(ws, plan->z.n_layers, plan->z.tiles, nullptr, plan->dev, nullptr, nullptr, sample_from(P, w, nullptr, 1u, eps), s);
+    rc = launch_init(ws, plan->z.n_layers, plan->z.tiles, nullptr, plan->dev, nullptr, nullptr,
+                     sample_from(P, w, nullptr, 1u, eps, !plan->look_twice), s);
     if (rc) return rc;
     ResidualPtrs R;
     memset(&R, 0, sizeof R);

@@ -36,8 +36,8 @@ namespace iwp {
 // states reset; for the single-layer entry points also the one-row layer table.
 //
 // The first zero_blocks workgroups clear the histograms.  The others each reset one layer's state and
-// decide from which key look 1 copies candidates out: on small tables from the caller's hint (HINT_BELOW),
-// otherwise by a sample of the layer: 16 to 64 evenly spaced
+// decide from which key look 1 copies candidates out: on small tables from the caller's hint (HINT_BELOW) or not at all
+// (LOOK_TWICE_TILES), otherwise by a sample of the layer: 16 to 64 evenly spaced
 // runs of 256 elements (the whole layer if it has no more), scored exactly as look 1 will score them.  The key
 // is the sample's of rank 1.25 ks + 4 sqrt(ks) + 2, ks = k * (sample size / n): four standard
 // deviations and a quarter on top, so that look 1 copies about 1.5 elements per kept one and
@@ -86,6 +86,15 @@ constexpr uint32_t HINT_BELOW = 1u << 18;
 constexpr uint32_t HINT_SLACK = 4u << 19;          // four top-digit bins
 constexpr uint32_t HINT_KEEP = 128;
 constexpr uint32_t HINT_MAX_TILES = 2048, HINT_FEW_LAYERS = 16;
+// Tables of up to LOOK_TWICE_TILES tiles have no sampled mark: where no hint is taken, look 1 copies nothing and look 2 reads
+// the tiles again, from the caches, and copies from the threshold's bin on.  A sample costs 4 to 5 us there and look 1's copies
+// 1 to 2, the second reading 3.  us a call, one worker, its update included, sampled / read twice: 0.3 M elements 35.8 / 31.4 in
+// one layer, 36.9 / 32.1 in 20, 1 M 38.3 / 36.1 and 39.0 / 35.6, 2 M 44.1 / 44.0 and 43.0 / 40.0 (kept at 1/64), 43.9 / 40.1 and
+// 42.8 / 37.1 (at 0.001); 3 M 47.8 / 52.0 and 46.4 / 44.4, 6 M 60.5 / 74.4 and 59.2 / 65.1.  A hint that is taken
+// (HINT_BELOW) is better than either: 1 M 32.7 and 33.3.  A whole bin holds up to 1/16 of the elements where
+// scores lie evenly below the threshold, hence LOOK_TWICE_ROOM more entries a slot: without them 100 layers of 3 M elements kept
+// at 0.004 overflowed (48 us sampled, 94 read twice; with them 42).
+constexpr uint32_t LOOK_TWICE_TILES = 512, LOOK_TWICE_ROOM = 320;
 constexpr uint32_t TRUST_DENSE = 1, TRUST_ALWAYS = 2;
 constexpr int INIT_BLOCK = 1024;                   // threads of a k_init workgroup
 constexpr uint32_t SAMPLE_LOW_BITS = 7;            // the key's low bits that the sample does not resolve
