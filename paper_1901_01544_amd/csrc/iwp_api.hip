@@ -266,12 +266,12 @@ int launch_write(const Table& T, const Workspace& ws, const ResidualPtrs& R, con
     const uint32_t grid = T.stiles * (GROUP / (BLOCK / WAVE));
     float* gathered = FUSED ? ws.gathered : nullptr;
     if (T.max_layer_stiles <= FOLD_SCAN_MAX_STILES) {
-        IWP_LAUNCH("k_write", (k_write<FUSED, true>), grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
+        IWP_LAUNCH("k_write", (k_write<FUSED, FOLD_STILES>), grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
                    ws.stage, ws.A, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, gathered,
                    T.pairs);
     } else {
         IWP_LAUNCH("k_scan", k_scan, T.n_layers, s, T.layers, ws.stile_counts);
-        IWP_LAUNCH("k_write", (k_write<FUSED, false>), grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
+        IWP_LAUNCH("k_write", (k_write<FUSED, FOLDED>), grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
                    ws.stage, ws.A, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, gathered,
                    T.pairs);
     }
@@ -363,6 +363,12 @@ int run_compact_from(const Table& T, const Workspace& ws, const ResidualPtrs& R,
     if (!T.any_k || T.tiles == 0) return IWP_OK;
     IWP_LAUNCH("k_stage_records", k_stage_records, T.tiles, s, R.r[0], w, T.layers, T.n_layers, thr, eps, ws.state, ws.stage,
                ws.A, ws.tile_counts);
+    if (T.max_layer_stiles <= FOLD_MAX_TILES / GROUP) {
+        IWP_LAUNCH("k_write", (k_write<false, FOLD_TILES>), T.stiles * (GROUP / (BLOCK / WAVE)), s, R, w, T.layers, T.n_layers, T.tiles,
+                   nullptr, 1u, eps, ws.state, ws.stage, ws.A, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, nullptr,
+                   T.pairs);
+        return IWP_OK;
+    }
     IWP_LAUNCH("k_fold_counts", k_fold_counts, (T.stiles + BLOCK - 1) / BLOCK, s, T.layers, T.n_layers, T.tiles, T.stiles,
                ws.tile_counts, ws.stile_counts);
     return launch_write<false>(T, ws, R, w, nullptr, 1u, eps, idx_out, val_out, s);

@@ -926,10 +926,14 @@ __device__ __forceinline__ void write_tile(const DevLayer& L, uint32_t lt, uint3
 // residual itself).  tile_out[t] receives the position of the tile's first pair.
 // FUSED (whole-step entry point): the value also goes into the leader's row of the
 // gather matrix and the leader's residual is cleared at the sent position.
-// One wavefront per tile, four tiles (half a super-tile) per workgroup.  FOLD: the super-tile
-// totals are as k_count left them and the workgroup adds up the layer's earlier ones itself;
-// otherwise k_scan has turned them into prefixes.
-template <bool FUSED, bool FOLD>
+// One wavefront per tile, four tiles (half a super-tile) per workgroup.  What stands before a tile in its layer:
+// FOLD_STILES: the super-tile totals are as k_count left them and the workgroup adds up the layer's earlier ones itself;
+// FOLD_TILES: the tiles' own counts are (k_stage_records), and it adds up those, which saves k_fold_counts, 5 us, on layers of
+// up to FOLD_MAX_TILES tiles (thresholds and pairs of 25.6 M elements 119.1 -> 116.3 us, one layer of 1 M, pairs alone, 15 -> 9); FOLDED: k_scan has turned the
+// super-tile totals into prefixes.
+constexpr int FOLDED = 0, FOLD_STILES = 1, FOLD_TILES = 2;
+constexpr uint32_t FOLD_MAX_TILES = 4096;          // 16 loads per thread at most
+template <bool FUSED, int FOLD>
 __global__ __launch_bounds__(BLOCK) void k_write(ResidualPtrs R, const float* __restrict__ w,
                                                  const DevLayer* __restrict__ layers, uint32_t n_layers, uint32_t tiles,
                                                  const uint32_t* __restrict__ leader, uint32_t W, float eps,
@@ -951,11 +955,14 @@ __global__ __launch_bounds__(BLOCK) void k_write(ResidualPtrs R, const float* __
     const uint32_t lt = (s - L.stile_begin) * GROUP + part * (BLOCK / WAVE) + wave;
     if (lt - wave >= ntiles) return;                                      // uniform: nothing of this part exists
     uint2 sc;
-    if (FOLD) {
-        // elements above / tying in the layer's earlier super-tiles: summed here, by everybody
+    if (FOLD != FOLDED) {
+        // elements above / tying in the layer's earlier super-tiles, or tiles: summed here, by everybody
+        const uint2* counts = FOLD == FOLD_TILES ? tile_counts : stile_counts;
+        const uint32_t begin = FOLD == FOLD_TILES ? L.tile_begin : L.stile_begin;
+        const uint32_t end = FOLD == FOLD_TILES ? L.tile_begin + lt - wave : s;
         uint32_t g = 0, e = 0;
-        for (uint32_t q = L.stile_begin + threadIdx.x; q < s; q += BLOCK) {
-            const uint2 c = stile_counts[q];
+        for (uint32_t q = begin + threadIdx.x; q < end; q += BLOCK) {
+            const uint2 c = counts[q];
             g += c.x;
             e += c.y;
         }
@@ -974,7 +981,13 @@ __global__ __launch_bounds__(BLOCK) void k_write(ResidualPtrs R, const float* __
     const uint32_t thr = st.thr, quota = st.n_eq_take;
     const uint32_t lead = leader_of(leader, j, W);
     float* rl = R.r[lead] + L.offset;
-    const uint2 tc = tile_counts[t];
+    uint2 tc = make_uint2(0u, 0u);                                        // before the tile, from where sc ends
+    if (FOLD == FOLD_TILES) {
+        const uint2 c = lane < wave ? tile_counts[t - wave + lane] : tc;
+        tc = make_uint2(wave_sum(c.x), wave_sum(c.y));
+    } else {
+        tc = tile_counts[t];
+    }
     const uint32_t Gt = sc.x + tc.x, Et = sc.y + tc.y;         // elements above / tying, before this tile
     uint32_t* io = idx_out + L.out_offset;
     float* vo = val_out + L.out_offset;
