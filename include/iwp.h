@@ -189,7 +189,7 @@ int compress_segmented(const iwp_plan* plan, const float* w, const float* const*
  * library runs on holds one copy until the process ends.  The call allocates and frees nothing
  * (its first call on a device looks the buffer's address up, nothing more).  A plan whose
  * iwp_plan_workspace_bytes() exceeds the buffer is refused with IWP_ESCRATCH before anything is
- * launched (the AlexNet-shaped set needs 49.1 MB, the ResNet-50-shaped one 27.2 MB).  All calls
+ * launched (the AlexNet-shaped set needs 51.0 MB, the ResNet-50-shaped one 29.2 MB).  All calls
  * on one GPU share that one buffer, which keeps the last call's contents; each call clears what
  * it needs cleared.  Calls that overlap on one GPU (two streams, two threads) race on it: run them
  * one after the other on one stream, or use compress_segmented with separate workspaces. */

@@ -113,12 +113,15 @@ inline uint32_t slot_cap_of(uint32_t n, uint32_t k) {
     return (uint32_t)std::min<uint64_t>(TILE, 64 + 3 * per_tile);
 }
 
-// Small tables (LOOK_TWICE_TILES, see iwp_select.hpp) have no sampled mark, and the second look copies out whole bins of the
-// first digit: up to 1/16 of a tile where the scores lie evenly below the threshold, for which their slots have LOOK_TWICE_ROOM
-// entries more.  Larger tables hold the same number of entries in reserve, so that a workspace that fits a table fits
+// Small tables (looks_twice(), see LOOK_TWICE_TILES in iwp_select.hpp) have no sampled mark, and the second look copies out
+// whole bins of the first digit: up to 1/16 of a tile where the scores lie evenly below the threshold, for which their slots
+// have LOOK_TWICE_ROOM entries more.  Larger tables hold the same number of entries in reserve, so that a workspace that fits a table fits
 // the smaller ones of its kind.
 inline uint32_t roomy(uint32_t slot_cap) { return slot_cap ? std::min<uint32_t>(TILE, slot_cap + LOOK_TWICE_ROOM) : 0u; }
-inline uint64_t roomy_reserve(uint64_t tiles) { return std::min<uint64_t>(tiles, LOOK_TWICE_TILES) * LOOK_TWICE_ROOM; }
+inline uint64_t roomy_reserve(uint64_t tiles) { return std::min<uint64_t>(tiles, LOOK_TWICE_TILES_MANY) * LOOK_TWICE_ROOM; }
+inline bool looks_twice(uint64_t tiles, uint32_t n_layers) {
+    return tiles <= LOOK_TWICE_TILES || (tiles <= LOOK_TWICE_TILES_MANY && n_layers >= LOOK_TWICE_MANY);
+}
 
 // How k_init samples a layer: enough runs for the threshold's rank in the sample to be about SAMPLE_RANK, and the rank
 // of the sample's element from whose key look 1 copies out (see iwp_select.hpp).
@@ -466,7 +469,7 @@ static int single_common(SingleOp op, const float* w, const float* g, float* r, 
     DevLayer row, sentinel;
     memset(&row, 0, sizeof row);
     memset(&sentinel, 0, sizeof sentinel);
-    row.n = n; row.k = k; row.slot_cap = z.tiles <= LOOK_TWICE_TILES ? roomy(slot_cap_of(n, k)) : slot_cap_of(n, k);
+    row.n = n; row.k = k; row.slot_cap = looks_twice(z.tiles, 1) ? roomy(slot_cap_of(n, k)) : slot_cap_of(n, k);
     row.sample = sample_of(n, k);
     row.hist_begin = 0; row.h0_copies = h0_copies_of(n, k);
     sentinel.tile_begin = z.tiles; sentinel.stile_begin = z.stiles; sentinel.out_offset = k;
@@ -474,7 +477,7 @@ static int single_common(SingleOp op, const float* w, const float* g, float* r, 
         return launch_small(nullptr, &row, 1u, 1u, n, k, ws, P, w, nullptr, 1u, eps, op == OP_SELECT ? STOP_AT_THRESHOLD : FULL,
                             false, idx_out, val_out, thr_out, s);
     SampleSource S = sample_from(P, w, nullptr, 1u, eps);
-    if (op == OP_COMPACT || k == 0 || z.tiles <= LOOK_TWICE_TILES) S.on = 0;
+    if (op == OP_COMPACT || k == 0 || looks_twice(z.tiles, 1)) S.on = 0;
     int rc = launch_init(ws, 1, z.tiles, nullptr, nullptr, &row, &sentinel, S, s);
     if (rc) return rc;
     Table T{ws.single_table, 1, z.tiles, z.stiles, k, k > 0, z.stiles, row.h0_copies};
@@ -615,7 +618,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     roomier.slots += any_k ? roomy_reserve(tiles) : 0u;
     if (carve(nullptr, roomier).bytes <= IWP_STATIC_SCRATCH_BYTES) {
         plan->z = roomier;
-        plan->look_twice = tiles <= LOOK_TWICE_TILES;
+        plan->look_twice = looks_twice(tiles, n_layers);
     }
     if (plan->look_twice) {
         slots = 0;

@@ -1,4 +1,4 @@
-"""Tables of up to 512 tiles have no sampled mark: the second look reads them again and copies whole bins of the first digit
+"""Tables of up to 512 tiles, or 1024 in 16 layers or more, have no sampled mark: the second look reads them again and copies whole bins of the first digit
 into roomier slots.  GPU parity on both sides of that line: evenly spread scores, sorted ones, a pattern with the sample's
 period (which misleads it above the line), all scores inside one bin (slots overflow); and the workspace of a layer still
 serves every shorter one."""
@@ -36,9 +36,12 @@ def test_layer_on_both_sides(gpu_lib, n, keep):
 @pytest.mark.gpu
 @pytest.mark.parametrize("fused", [True, False])
 @pytest.mark.parametrize("last", [TILE, TILE + 1])
-def test_table_on_both_sides(gpu_lib, fused, last):
+@pytest.mark.parametrize("layers", [4, 15, 16])
+def test_table_on_both_sides(gpu_lib, fused, last, layers):
     W = 2
     sizes = [(300 * TILE - 7, 50_000), (100 * TILE, 300), (111 * TILE - 1, 0), (last, last // 2)]
+    if layers > 4:                                           # 1024 or 1025 tiles
+        sizes = [((512 - (layers - 5)) * TILE, 9000)] + [(TILE - j, 40) for j in range(layers - 5)] + sizes
     ps = wl.custom_set(sizes, W=W, seed=last, align=1, start=1)
     w = wl.gen_weights(ps)
     sets = [wl.gen_gradient(ps, s) for s in range(W)]
