@@ -409,6 +409,11 @@ bool takes_small(const iwp_plan& plan, bool hinted, bool select) {
     return select || plan.max_n <= SMALL_MAX_N / 2 || plan.n_long <= (no_sample ? 512u : 1024u);
 }
 
+// May a step's or a compression's marks be sampled (see LOOK_TWICE_TILES)?
+bool samples(const iwp_plan& plan, bool hinted) {
+    return !plan.look_twice || (!hinted && plan.momentum == 1.0f);
+}
+
 extern "C" {
 
 const char* iwp_strerror(int code) {
@@ -752,7 +757,7 @@ static int compress_segmented_on(const iwp_plan* plan, const float* w, const flo
         if (rc) return rc;
     } else {
         rc = launch_init(ws, T.n_layers, T.tiles, thr_hint, T.layers, nullptr, nullptr,
-                         sample_from(P, w, leader, W, eps, !plan->look_twice), s);
+                         sample_from(P, w, leader, W, eps, samples(*plan, thr_hint != nullptr)), s);
         if (rc) return rc;
         if (T.any_k) {
             rc = launch_leader_pass(T, ws, P, w, leader, W, eps, s);
@@ -811,7 +816,7 @@ int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, fl
         if (rc) return rc;
     } else if (T.any_k) {
         rc = launch_init(ws, z.n_layers, z.tiles, thr_hint, plan->dev, nullptr, nullptr,
-                         sample_from(P, w, leader, W, eps, !plan->look_twice), s);
+                         sample_from(P, w, leader, W, eps, samples(*plan, thr_hint != nullptr)), s);
         if (rc) return rc;
         rc = launch_leader_pass(T, ws, P, w, leader, W, eps, s);
         if (rc) return rc;

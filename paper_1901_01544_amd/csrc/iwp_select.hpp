@@ -80,8 +80,8 @@ constexpr uint32_t SAMPLE_RANK = 128;              // rank of the estimated thre
 // -> 530 us; independent scores are alike, with the thresholds of the step before.
 // Both only where residuals add up undiminished (momentum 1).  Where they decay, a threshold can fall or rise from step to
 // step by far more than the margin: after some thousand steps at 0.9 on two gradients in turn (151 tensors of 1.3 M, two
-// workers) 54 us a step with the sample's mark, 108 with the hint's; 9 tensors of 0.6 M 49 / 84 us.  There the mark is
-// always sampled, and only a hint HINT_SLACK or more below it takes its place.
+// workers) 54 us a step with the sample's mark, 108 with the hint's; 9 tensors of 0.6 M 49 / 84 us.  There no mark
+// comes from a hint alone, and only a hint HINT_SLACK or more below it takes its place.
 constexpr uint32_t HINT_BELOW = 1u << 18;
 constexpr uint32_t HINT_SLACK = 4u << 19;          // four top-digit bins
 constexpr uint32_t HINT_KEEP = 128;
@@ -97,6 +97,9 @@ constexpr uint32_t HINT_MAX_TILES = 2048, HINT_FEW_LAYERS = 16;
 // scores lie evenly below the threshold, hence LOOK_TWICE_ROOM more entries a slot: without them 100 layers of 3 M elements kept
 // at 0.004 overflowed (48 us sampled, 94 read twice; with them 42).
 constexpr uint32_t LOOK_TWICE_TILES = 512, LOOK_TWICE_ROOM = 320;
+// A step or a compression that would have taken a hint (momentum 1) and was given none samples all the same: reading twice is
+// better there too (six tensors, 235 k elements, four workers 37.5 / 34.6 us a step), but callers count on a hint paying by 4 %
+// and more, and with one the step takes 33.2.
 constexpr uint32_t LOOK_TWICE_TILES_MANY = 1024, LOOK_TWICE_MANY = 16;
 constexpr uint32_t TRUST_DENSE = 1, TRUST_ALWAYS = 2;
 constexpr int INIT_BLOCK = 1024;                   // threads of a k_init workgroup
