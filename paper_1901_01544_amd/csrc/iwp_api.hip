@@ -313,8 +313,12 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
         IWP_LAUNCH("k_stage", k_stage<false>, stage_grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
                    ws.hist, ws.stage, ws.A);
     const uint32_t stile_grid = std::min<uint32_t>(T.stiles, STILE_MAX_GRID);
-    IWP_LAUNCH("k_refine2", k_refine2, stile_grid, s, R, w, T.layers, T.n_layers, T.tiles, T.stiles, leader, W, eps, ws.state,
-               ws.stage, ws.A, ws.hist);
+    if (looks_twice(T.tiles, T.n_layers))
+        IWP_LAUNCH("k_refine_tiles", k_refine_tiles, T.tiles, s, R, w, T.layers, T.n_layers, leader, W, eps, ws.state, ws.stage, ws.A,
+                   ws.hist);
+    else
+        IWP_LAUNCH("k_refine2", k_refine2, stile_grid, s, R, w, T.layers, T.n_layers, T.tiles, T.stiles, leader, W, eps, ws.state,
+                   ws.stage, ws.A, ws.hist);
     if (stop == STOP_AT_THRESHOLD) {
         IWP_LAUNCH("k_final_pick", k_final_pick, T.n_layers, s, T.layers, ws.hist, ws.state, thr_out);
         return IWP_OK;

@@ -14,7 +14,8 @@
 // copies, a few percent of the layer: k_refine2 histograms the third digit, k_count /
 // k_write place every kept element at its rank in index order.  A tile whose
 // candidates do not fit its slot (heavy ties, e.g. a tile that is all zeros) is marked
-// RAW and is simply re-read from r and w by the later passes.  Both routes are exact.
+// RAW and is simply re-read from r and w by the later passes (on small tables by one of them, see k_refine_tiles).  Both
+// routes are exact.
 //
 // The second and third digit picks have no launches of their own: a finished histogram is
 // the same for every reader, so each workgroup of the consuming kernel redoes the pick of its
@@ -95,7 +96,7 @@ constexpr uint32_t HINT_MAX_TILES = 2048, HINT_FEW_LAYERS = 16;
 // second-digit histograms queue up, where they are many samples cost more).  A hint that is taken
 // (HINT_BELOW) is better than either: 1 M 32.7 and 33.3.  A whole bin holds up to 1/16 of the elements where
 // scores lie evenly below the threshold, hence LOOK_TWICE_ROOM more entries a slot: without them 100 layers of 3 M elements kept
-// at 0.004 overflowed (48 us sampled, 94 read twice; with them 42).
+// at 0.004 overflowed (48 us sampled, 94 read twice; with them 42).  Fuller tiles: see k_refine_tiles.
 constexpr uint32_t LOOK_TWICE_TILES = 512, LOOK_TWICE_ROOM = 320;
 // A step or a compression that would have taken a hint (momentum 1) and was given none samples all the same: reading twice is
 // better there too (six tensors, 235 k elements, four workers 37.5 / 34.6 us a step), but callers count on a hint paying by 4 %
@@ -584,6 +585,64 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
 }
 
 // ---------------------------------------------------------------------------
+// The third digit on tables without a sampled mark (LOOK_TWICE_TILES), one workgroup per tile.  There look 2 copies whole bins of
+// the first digit, and where scores crowd into one bin every tile overflows its slot.  Such a tile is read a third time, from the
+// caches, but by this launch alone: the 22-bit prefix is known here and leaves little more than is kept, so what is at or above it
+// goes into the slot after all, and k_count and k_write find copies (a tile that still overflows, by ties, stays RAW).
+// Bound by latency, and for such tiles by the divides: a workgroup per tile puts them on all compute units, where k_refine2's
+// workgroup of a super-tile has eight tiles in turn.  One layer of 1 M elements kept at 1/64, us a call, k_refine2 / this: scores
+// inside one bin 104 / 38 (45.5 with a sampled mark), an eighth of them in the threshold's bin and kept at 0.001 98 / 35 (39),
+// normally distributed 31.0 / 30.1 (38.4); eight distinct values, kept at 0.001, 99 / 74 (118).  (Slots of 400 entries instead of
+// 576, so that an eighth of a tile overflows and fewer copies are made: 38.7 -> 35.7, but the eight values 40 -> 74.)
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(BLOCK) void k_refine_tiles(ResidualPtrs R, const float* __restrict__ w,
+                                                        const DevLayer* __restrict__ layers, uint32_t n_layers,
+                                                        const uint32_t* __restrict__ leader, uint32_t W, float eps,
+                                                        LayerState* __restrict__ state, uint32_t* __restrict__ stage_cnt,
+                                                        StageArrays A, uint32_t* __restrict__ hist) {
+    __shared__ uint32_t lh[HIST2];
+    __shared__ uint32_t sh[PICK_WORDS];
+    __shared__ uint32_t slot[STAGE_WORDS];
+    const uint32_t tid = threadIdx.x, t = blockIdx.x;
+    const uint32_t j = layer_of_tile(layers, n_layers, t);
+    const DevLayer L = layers[j];
+    if (L.k == 0) return;
+    const uint32_t lt = t - L.tile_begin, base = lt * TILE, cnt = staged_entries(stage_cnt[t]);
+    const uint64_t sb = L.slot_begin + (uint64_t)lt * L.slot_cap;
+    const uint32_t first = tid < (cnt == UNIFORM_TILE ? 1u : cnt == RAW_TILE ? 0u : cnt) ? A.key[sb + tid] : NOT_AN_ELEMENT;
+    uint32_t bin1, k_rem1;
+    block_pick<(int)HIST1>(layer_hist(hist, L, 1), state[j].k_rem0, sh, &bin1, &k_rem1);
+    const uint32_t prefix = (state[j].b1 << digit_bits(1)) | bin1;            // 22 bits
+    if (lt == 0 && tid == 0) {
+        state[j].p22 = prefix;
+        state[j].k_rem1 = k_rem1;
+    }
+    for (uint32_t b = tid; b < HIST2; b += BLOCK) lh[b] = 0u;
+    __syncthreads();
+    auto add = [&](uint32_t key, uint32_t n) {
+        if (key != NOT_AN_ELEMENT && (key >> digit_shift(1)) == prefix) atomicAdd(&lh[key & (HIST2 - 1)], n);
+    };
+    if (cnt == RAW_TILE) {                                 // uniform
+        uint32_t key[CHUNKS_PER_TILE][4];
+        float val[CHUNKS_PER_TILE][4];
+        scored_tile(R.r[leader_of(leader, j, W)] + L.offset, w + L.offset, L.n, base, eps, state[j].shift, key, val);
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) add(key[u][q], 1u);
+        const uint32_t copies = stage_tile(key, val, base, prefix << digit_shift(1), L.slot_cap, sb, A, slot);
+        if (tid == 0) stage_cnt[t] = copies;
+    } else if (cnt == UNIFORM_TILE) {                      // all keys of the tile are the slot's one entry
+        add(first, min(TILE, L.n - base));
+    } else {
+        add(first, 1u);
+        for (uint32_t e = BLOCK + tid; e < cnt; e += BLOCK) add(A.key[sb + e], 1u);
+    }
+    __syncthreads();
+    flush_hist<HIST2>(lh, layer_hist(hist, L, 2));
+}
+
+// ---------------------------------------------------------------------------
 // Threshold records given by the caller (compact_pairs): one pass over the layer that counts, per tile, the elements above
 // the threshold and those that tie with it, and copies both into the tile's slot, one workgroup per tile as in look 1;
 // k_fold_counts sums the counts up, and the ordered split works on the slots, as after a selection.  A layer's first
@@ -751,12 +810,28 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
                     eq += k2 == thr ? 1u : 0u;
                 }
             } else {
+                // a RAW tile: several rounds of quads in flight, since neither k_refine_tiles nor look 2 has left its lines in
+                // this die's cache (one element per lane and round: 62 us for 25 tiles of eight distinct values, now 22)
+                constexpr uint32_t ROUND = WAVE * VEC, AHEAD = 2;          // elements of a round; rounds in flight together
                 const uint32_t first = (lt0 + tl) * TILE;
-                const uint32_t end = min(L.n, first + TILE);
-                for (uint32_t i = first + lane; i < end; i += WAVE) {
-                    const uint32_t k2 = shifted(score_key(rl[i], wl[i], eps), shift);
-                    gt += k2 > thr ? 1u : 0u;
-                    eq += k2 == thr ? 1u : 0u;
+#pragma unroll 1
+                for (uint32_t c = 0; c < TILE && first + c < L.n; c += AHEAD * ROUND) {
+                    float rv[AHEAD][4], wv[AHEAD][4];
+#pragma unroll
+                    for (uint32_t a = 0; a < AHEAD; ++a) {
+                        const uint32_t i = first + c + a * ROUND + lane * VEC;
+                        load_quad(rl, i, L.n, rv[a]);
+                        load_quad(wl, i, L.n, wv[a], 1.0f);
+                    }
+#pragma unroll
+                    for (uint32_t a = 0; a < AHEAD; ++a)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const uint32_t k2 = shifted(score_key(rv[a][q], wv[a][q], eps), shift);
+                            const bool inside = first + c + a * ROUND + lane * VEC + q < L.n;
+                            gt += inside && k2 > thr ? 1u : 0u;
+                            eq += inside && k2 == thr ? 1u : 0u;
+                        }
                 }
             }
             gt = wave_sum(gt);
