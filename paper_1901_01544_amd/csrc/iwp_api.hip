@@ -976,14 +976,16 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
                    rule->alpha, rule->beta, rule->C, reinterpret_cast<double2*>(rule->stats_out), rule->thr_out);
         thr = rule->thr_out;
     }
-#define IWP_MASK(NL)                                                                                                        \
-    IWP_LAUNCH("k_leader_mask", k_leader_mask<NL>, z.tiles, s, P, w, layers, z.n_layers, leaders, n_lead, W, thr, rule != nullptr, \
-               rule == nullptr, rs, eps, mask32, ws.tile_counts, ws.slots)
+#define IWP_MASK(NL, GROUPS)                                                                                                 \
+    IWP_LAUNCH_BLOCK("k_leader_mask", (k_leader_mask<NL, GROUPS>), z.tiles, dim3(BLOCK, GROUPS), s, P, w, layers, z.n_layers, leaders, \
+                     n_lead, W, thr, rule != nullptr, rule == nullptr, rs, eps, mask32, ws.tile_counts, ws.slots)
     if (z.tiles) {
-        if (n_lead == 1) IWP_MASK(1);
-        else if (n_lead == 2) IWP_MASK(2);
-        else if (n_lead == 3) IWP_MASK(3);
-        else IWP_MASK(0);
+        if (n_lead == 1) IWP_MASK(1, 1);
+        else if (n_lead == 2) IWP_MASK(2, 1);
+        else if (n_lead == 3) IWP_MASK(3, 1);
+        else if (n_lead == 4) IWP_MASK(2, 2);
+        else if (n_lead <= 6) IWP_MASK(2, 3);
+        else IWP_MASK(2, 4);
     }
 #undef IWP_MASK
     IWP_LAUNCH_BLOCK("k_tile_offsets", k_tile_offsets, 1u, OFFSETS_BLOCK, s, layers, z.n_layers, z.tiles, ws.tile_counts, max_pairs,

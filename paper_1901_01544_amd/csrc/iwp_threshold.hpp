@@ -75,83 +75,82 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 
 // The tile that starts at element `base` of its layer, CHUNKS chunks of it, for all chosen nodes of the layer: accumulate,
 // score, compare, encode, and hand over what is sent.  Layers that end within a tile's first chunk take one chunk only, which
-// spares them three quarters of the divides (and draws).  NL: the nodes whose values stay in registers until the common mask
-// is known (n_lead); 0: any number of nodes one after the other, whose sent values are fetched again from what was just stored.
-template <uint32_t CHUNKS, int NL>
+// spares them three quarters of the divides (and draws).  The nodes' values stay in registers until the common mask is known:
+// NL nodes per group of 256 threads (threadIdx.y), the groups' masks meet in LDS (meet, BLOCK words each; one group has none).
+template <uint32_t CHUNKS, int NL, int GROUPS>
 __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __restrict__ wl, const DevLayer& L, uint32_t j,
                                           uint32_t t, uint32_t base, const uint32_t* __restrict__ leaders, uint32_t n_lead,
                                           uint32_t W, const float* __restrict__ thr, bool thr_per_slot, bool accumulate,
                                           const RandomSel& rs, float eps, uint32_t* __restrict__ mw,
-                                          uint32_t* __restrict__ tile_counts, const ChosenSlots& S, uint32_t* part) {
-    constexpr int KEPT = NL ? NL : 1;
+                                          uint32_t* __restrict__ tile_counts, const ChosenSlots& S, uint32_t* part,
+                                          uint32_t (*meet)[BLOCK]) {
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const uint32_t group = GROUPS > 1 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.y) : 0u;   // the same in a wavefront
+    const uint32_t q0 = group * NL;
     const uint32_t n = L.n, nwords = (n + 31) / 32;
-    float wv[CHUNKS][4], rv[KEPT][CHUNKS][4], gv[KEPT][CHUNKS][4];
-    Rest wv_rest, rv_rest[KEPT], gv_rest[KEPT];
-    float* rl[KEPT];
-    const float* gl[KEPT];
-    float th[KEPT];
-    bool on[KEPT];
+    float wv[CHUNKS][4], rv[NL][CHUNKS][4], gv[NL][CHUNKS][4];
+    Rest wv_rest, rv_rest[NL], gv_rest[NL];
+    float* rl[NL];
+    const float* gl[NL];
+    float th[NL];
+    bool on[NL];
     uint32_t nib[CHUNKS] = {};
     request_tile<true>(wl, n, base, wv, wv_rest);
-    auto request = [&](int s, uint32_t q) {                  // node in slot q of the layer -> registers s
-        const uint32_t p = chosen_at(leaders, n_lead, j, q, W);
-        on[s] = !chosen_before(leaders, n_lead, j, q, W, p);
+#pragma unroll
+    for (int s = 0; s < NL; ++s) {                           // node in slot q0 + s of the layer -> registers s
+        const uint32_t q = min(q0 + s, n_lead - 1u), p = chosen_at(leaders, n_lead, j, q, W);
+        on[s] = q0 + s < n_lead && !chosen_before(leaders, n_lead, j, q, W, p);
         th[s] = thr_per_slot ? thr[(size_t)j * n_lead + q] : thr[j];
         rl[s] = P.r[p] + L.offset;
         gl[s] = accumulate && P.g[p] ? P.g[p] + L.offset : nullptr;
-        if (!on[s]) return;
+        if (!on[s]) continue;
         request_tile<true>(rl[s], n, base, rv[s], rv_rest[s]);
         if (gl[s]) request_tile<true>(gl[s], n, base, gv[s], gv_rest[s]);
-    };
-    auto settle = [&](int s) {
-        if (!on[s]) return;
+    }
+    settle_tile(n, base, wv, wv_rest);
+#pragma unroll
+    for (int s = 0; s < NL; ++s) {
+        if (!on[s]) continue;
         settle_tile(n, base, rv[s], rv_rest[s]);
-        if (!gl[s]) return;
+        if (!gl[s]) continue;
         settle_tile(n, base, gv[s], gv_rest[s]);
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
             for (int c = 0; c < 4; ++c) rv[s][u][c] = accum(rv[s][u][c], gv[s][u][c], P.momentum);
-    };
-    auto mark = [&](int s0, int s1) {                        // the elements that one of the nodes in registers sends
+    }
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
-            uint32_t word4[4] = {0u, 0u, 0u, 0u};
-            if (rs.on) philox4x32_10(i >> 2, j, rs.step0, rs.step1, rs.key0, rs.key1, word4);   // i is a multiple of 4
+    for (uint32_t u = 0; u < CHUNKS; ++u) {                  // the elements that one of the nodes in registers sends
+        const uint32_t i = base + u * CHUNK + tid * VEC;
+        uint32_t word4[4] = {0u, 0u, 0u, 0u};
+        if (rs.on) philox4x32_10(i >> 2, j, rs.step0, rs.step1, rs.key0, rs.key1, word4);   // i is a multiple of 4
 #pragma unroll
-            for (int s = s0; s < s1; ++s) {
-                if (!on[s]) continue;
+        for (int s = 0; s < NL; ++s) {
+            if (!on[s]) continue;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const float score = fabsf(rv[s][u][c]) / (fabsf(wv[u][c]) + eps);
-                    bool send = score > th[s];
-                    if (rs.on) {
-                        const float draw = (float)(word4[c] >> 8) * 0x1p-24f;
-                        const float prob = score / th[s];
-                        send = send || draw < prob;
-                    }
-                    if (i + c < n && send) nib[u] |= 1u << c;
+            for (int c = 0; c < 4; ++c) {
+                const float score = fabsf(rv[s][u][c]) / (fabsf(wv[u][c]) + eps);
+                bool send = score > th[s];
+                if (rs.on) {
+                    const float draw = (float)(word4[c] >> 8) * 0x1p-24f;
+                    const float prob = score / th[s];
+                    send = send || draw < prob;
                 }
+                if (i + c < n && send) nib[u] |= 1u << c;
             }
         }
-    };
-    if (NL) {
+    }
+    if (GROUPS > 1) {
+        uint32_t bits = 0;
 #pragma unroll
-        for (int q = 0; q < NL; ++q) request(q, q);
-        settle_tile(n, base, wv, wv_rest);
+        for (uint32_t u = 0; u < CHUNKS; ++u) bits |= nib[u] << (4u * u);
+        meet[group][tid] = bits;
+        __syncthreads();
+        bits = 0;
 #pragma unroll
-        for (int q = 0; q < NL; ++q) settle(q);
-        mark(0, NL);
-    } else {
-        for (uint32_t q = 0; q < n_lead; ++q) {
-            request(0, q);
-            if (q == 0) settle_tile(n, base, wv, wv_rest);
-            settle(0);
-            mark(0, 1);
-            if (on[0] && gl[0]) store_tile<true>(rl[0], n, base, rv[0]);
-        }
+        for (int y = 0; y < GROUPS; ++y) bits |= meet[y][tid];
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS; ++u) nib[u] = (bits >> (4u * u)) & 0xFu;
     }
     uint32_t count[CHUNKS], first[CHUNKS], word[CHUNKS];
 #pragma unroll
@@ -159,47 +158,29 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
         // eight lanes (32 consecutive elements) make one word of the encoded mask
         word[u] = or_of_8_lanes(nib[u] << (4u * (lane & 7u)));
         const uint32_t widx = base / 32 + u * (CHUNK / 32) + (tid >> 3);
-        if ((lane & 7u) == 0u && widx < nwords) mw[widx] = word[u];
+        if (group == 0 && (lane & 7u) == 0u && widx < nwords) mw[widx] = word[u];
         count[u] = __popc(nib[u]);
     }
-    const uint32_t total = tile_ranks(count, first, part);
-    if (tid == 0) tile_counts[t] = total;
+    const uint32_t total = tile_ranks(count, first, part + group * STAGE_WORDS);
+    if (group == 0 && tid == 0) tile_counts[t] = total;
     const bool hand_over = total <= S.cap;                   // otherwise k_follow_mask fetches and clears them
-    if (NL) {
 #pragma unroll
-        for (int q = 0; q < NL; ++q) {
-            if (!on[q]) continue;
-            float* slot = S.val + ((size_t)q * S.tiles + t) * S.cap;
+    for (int s = 0; s < NL; ++s) {
+        if (!on[s]) continue;
+        float* slot = S.val + ((size_t)(q0 + s) * S.tiles + t) * S.cap;
 #pragma unroll
-            for (uint32_t u = 0; u < CHUNKS; ++u) {
-                if (!hand_over || !nib[u]) continue;
-                uint32_t rank = first[u];
+        for (uint32_t u = 0; u < CHUNKS; ++u) {
+            if (!hand_over || !nib[u]) continue;
+            uint32_t rank = first[u];
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if ((nib[u] >> c) & 1u) { slot[rank++] = rv[q][u][c]; rv[q][u][c] = 0.0f; }
-            }
-            // a node that has not been accumulated here: only what holds a sent element, in whole lines of 32 elements
-            // (single elements, partial lines, take 63 us instead of 49 where one of 59 of 25.6 M elements is sent)
-#pragma unroll
-            for (uint32_t u = 0; u < CHUNKS; ++u)
-                if (gl[q] || (hand_over && word[u])) store_quad<true>(rl[q], base + u * CHUNK + tid * VEC, n, rv[q][u]);
+            for (int c = 0; c < 4; ++c)
+                if ((nib[u] >> c) & 1u) { slot[rank++] = rv[s][u][c]; rv[s][u][c] = 0.0f; }
         }
-    } else if (hand_over) {
-        for (uint32_t q = 0; q < n_lead; ++q) {
-            const uint32_t p = chosen_at(leaders, n_lead, j, q, W);
-            if (chosen_before(leaders, n_lead, j, q, W, p)) continue;
-            float* r = P.r[p] + L.offset;
-            float* slot = S.val + ((size_t)q * S.tiles + t) * S.cap;
+        // a node that has not been accumulated here: only what holds a sent element, in whole lines of 32 elements
+        // (single elements, partial lines, take 63 us instead of 49 where one of 59 of 25.6 M elements is sent)
 #pragma unroll
-            for (uint32_t u = 0; u < CHUNKS; ++u) {
-                uint32_t rank = first[u];
-                for (uint32_t b = nib[u]; b; b &= b - 1u) {
-                    const uint32_t i = base + u * CHUNK + tid * VEC + (uint32_t)__ffs(b) - 1u;
-                    slot[rank++] = r[i];
-                    r[i] = 0.0f;
-                }
-            }
-        }
+        for (uint32_t u = 0; u < CHUNKS; ++u)
+            if (gl[s] || (hand_over && word[u])) store_quad<true>(rl[s], base + u * CHUNK + tid * VEC, n, rv[s][u]);
     }
 }
 
@@ -213,15 +194,21 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
 // once per node and left a mask for each, to be OR-ed and counted in a launch of its own (308 + 9 us), and the nodes' sent
 // values were read and cleared pair by pair behind everything else (the update 177 us, now 66).  Whole steps: that table
 // 1208 -> 1077 us, one node of 25.6 M elements with a line per layer 554 -> 522, three of 1.1 M 38 -> 29 (three launches less).
+// Up to three nodes are one group's (73, 104 and 141 registers); more are taken two to a group, by workgroups of two to four
+// groups, which read the weights once each.  One group that takes them one after the other, storing each and fetching
+// its sent values again, had every node's loads wait for the one before: eight workers, four and eight nodes, us a step, against
+// that (and against a workgroup per node and tile): 30 k elements 35 / 24 (31) and 47 / 27 (35), 1.2 M 69 / 43 (60) and 88 / 49
+// (70), 61 M 1374 / 1064 (1327) and 1618 / 1268 (1571).
 // ---------------------------------------------------------------------------
-template <int NL>
-__global__ __launch_bounds__(BLOCK) void k_leader_mask(WorkerPtrs P, const float* __restrict__ w,
+template <int NL, int GROUPS>
+__global__ __launch_bounds__(BLOCK * GROUPS) void k_leader_mask(WorkerPtrs P, const float* __restrict__ w,
                                                        const DevLayer* __restrict__ layers, uint32_t n_layers,
                                                        const uint32_t* __restrict__ leaders, uint32_t n_lead, uint32_t W,
                                                        const float* __restrict__ thr, bool thr_per_slot, bool accumulate,
                                                        RandomSel rs, float eps, uint32_t* __restrict__ mask_out,
                                                        uint32_t* __restrict__ tile_counts, ChosenSlots S) {
-    __shared__ uint32_t part[STAGE_WORDS];
+    __shared__ uint32_t part[GROUPS * STAGE_WORDS];
+    __shared__ uint32_t meet[GROUPS > 1 ? GROUPS : 1][BLOCK];
     const uint32_t t = blockIdx.x;
     const uint32_t j = layer_of_tile(layers, n_layers, t);
     const DevLayer L = layers[j];
@@ -229,11 +216,11 @@ __global__ __launch_bounds__(BLOCK) void k_leader_mask(WorkerPtrs P, const float
     const float* wl = w + L.offset;
     uint32_t* mw = mask_out + L.mask_begin;
     if (L.n - base <= CHUNK)
-        mask_tile<1, NL>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, rs, eps, mw, tile_counts, S,
-                         part);
+        mask_tile<1, NL, GROUPS>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, rs, eps, mw, tile_counts,
+                                 S, part, meet);
     else
-        mask_tile<CHUNKS_PER_TILE, NL>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, rs, eps, mw,
-                                       tile_counts, S, part);
+        mask_tile<CHUNKS_PER_TILE, NL, GROUPS>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, rs, eps, mw,
+                                               tile_counts, S, part, meet);
 }
 
 // One tile of a chosen node in registers: residual (after adding the gradient and storing
