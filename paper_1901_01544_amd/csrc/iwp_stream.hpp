@@ -33,21 +33,22 @@ struct LeadCtx {
 // One tile of a worker that follows: accumulate, copy the values at sent positions into the worker's row of the gather
 // matrix (row: the tile's first entry there, room: entries it may take), leave +0 behind.  sent(): builds the tile's bitmap
 // in map / pre (LDS, TILE_WORDS words each) while the tile's loads are in flight; false: nothing of the tile is sent.
-template <uint32_t CHUNKS, class Sent>
+// ACC: false: nothing is accumulated (gl is not read).
+template <uint32_t CHUNKS, bool ACC = true, class Sent>
 __device__ __forceinline__ void follow_tile(const float* gl, float* rl, uint32_t n, uint32_t base, float m, float* row,
                                             uint32_t room, const uint32_t* map, const uint32_t* pre, Sent sent) {
     float rv[CHUNKS][4], gv[CHUNKS][4];
     Rest rv_rest, gv_rest;
     request_tile<true>(rl, n, base, rv, rv_rest);
-    request_tile<true>(gl, n, base, gv, gv_rest);
+    if (ACC) request_tile<true>(gl, n, base, gv, gv_rest);
     const bool any = sent();
     settle_tile(n, base, rv, rv_rest);
-    settle_tile(n, base, gv, gv_rest);
+    if (ACC) settle_tile(n, base, gv, gv_rest);
 #pragma unroll
     for (uint32_t u = 0; u < CHUNKS; ++u) {
         const uint32_t loc = u * CHUNK + threadIdx.x * VEC;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) rv[u][q] = accum(rv[u][q], gv[u][q], m);
+        for (int q = 0; ACC && q < 4; ++q) rv[u][q] = accum(rv[u][q], gv[u][q], m);
         const uint32_t nib = any ? (map[loc >> 5] >> (loc & 31u)) & 0xFu : 0u;      // no bits past the layer's end
         if (nib) {
             uint32_t rank = bitmap_rank(map, pre, loc);

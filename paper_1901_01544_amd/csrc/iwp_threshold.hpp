@@ -163,7 +163,7 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
     }
     const uint32_t total = tile_ranks(count, first, part + group * STAGE_WORDS);
     if (group == 0 && tid == 0) tile_counts[t] = total;
-    const bool hand_over = total <= S.cap;                   // otherwise k_follow_mask fetches and clears them
+    const bool hand_over = total <= S.cap;                   // otherwise the next pass fetches and clears them
 #pragma unroll
     for (int s = 0; s < NL; ++s) {
         if (!on[s]) continue;
@@ -413,9 +413,11 @@ __global__ __launch_bounds__(OFFSETS_BLOCK) void k_tile_offsets(const DevLayer* 
 // Every node that is not chosen for the layer and has a gradient: accumulate, and
 // where the tile's mask has bits, copy the accumulated value into the node's gather
 // row and leave +0 behind.  Grid: W * tiles; runs: see in_runs().  The workgroups of the chosen nodes, whose
-// residuals k_leader_mask has been through, have nothing to stream: those of the first one write the
+// residuals k_leader_mask has been through, have nothing to accumulate: those of the first one write the
 // tile's masked positions as ascending flat indices and move the sent values of all of them from the tile's
-// slots to their gather rows.
+// slots to their gather rows.  A tile that sends more than a slot holds they stream, each its own: everything sent, eight workers,
+// 6 M elements, one, two and four chosen nodes 247, 256 and 270 us a step (by the first one's workgroup, element by element for
+// all of them, 344, 459 and 653); about half sent 181, 206 and 233 (215, 312, 506).
 // ---------------------------------------------------------------------------
 // The tile's mask in LDS (no bits unless wanted) and the number of bits before each word.
 // map, pre, slot: LDS of TILE_WORDS, TILE_WORDS and 4 words.
@@ -450,17 +452,17 @@ __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLa
     const float* gp = P.g[p];
     uint32_t q = 0;
     while (q < n_lead && chosen_at(leaders, n_lead, j, q, W) != p) ++q;
-    if (q == n_lead ? !gp : q > 0) return;                   // a node without a gradient: pair by pair later
-    const bool exchange = !overflowed(count_out, n_layers);
+    if (q == n_lead && !gp) return;                          // a node without a gradient: pair by pair later
     const uint32_t at = min(tile_pos[t], max_pairs), room = max_pairs - at;
+    const bool exchange = !overflowed(count_out, n_layers);
+    float* row = gathered + (size_t)p * max_pairs + at;
+    auto sent = [&]() {
+        tile_mask(mask, L, base, exchange, map, pre, slot);
+        return true;
+    };
     if (q == n_lead) {
         float* rl = P.r[p] + L.offset;
         const float* gl = gp + L.offset;
-        float* row = gathered + (size_t)p * max_pairs + at;
-        auto sent = [&]() {
-            tile_mask(mask, L, base, exchange, map, pre, slot);
-            return true;
-        };
         const uint32_t head = elements_to_line(rl);
         if (L.n - base <= CHUNK) follow_tile<1>(gl, rl, L.n, base, P.momentum, row, room, map, pre, sent);   // see mask_tile
         else if (head && base + TILE <= L.n) follow_tile_from(head, gl + base, rl + base, P.momentum, row, room, map, pre, sent);
@@ -470,30 +472,36 @@ __global__ __launch_bounds__(BLOCK) void k_follow_mask(WorkerPtrs P, const DevLa
     // the chosen nodes' part of the tile
     const uint32_t cnt = tile_counts[t];
     const bool handed_over = cnt <= S.cap;
-    if (!exchange && !handed_over) return;
-    tile_mask(mask, L, base, cnt != 0u, map, pre, slot);
-    const uint32_t mine = (map[tid >> 1] >> (16u * (tid & 1u))) & 0xffffu;   // 16 elements per lane
-    const uint32_t first = bitmap_rank(map, pre, 16u * tid);
+    uint32_t mine, first;                                    // the lane's 16 elements: which are sent, how many before them
+    if (!handed_over) {
+        if (!exchange) return;
+        follow_tile<CHUNKS_PER_TILE, false>(nullptr, P.r[p] + L.offset, L.n, base, 1.0f, row, room, map, pre, sent);
+        if (q > 0) return;
+        mine = (map[tid >> 1] >> (16u * (tid & 1u))) & 0xffffu;
+        first = bitmap_rank(map, pre, 16u * tid);
+    } else {
+        if (q > 0 || cnt == 0u) return;
+        const uint32_t widx = base / 32 + (tid >> 1);
+        mine = widx < (L.n + 31) / 32 ? (mask[L.mask_begin + widx] >> (16u * (tid & 1u))) & 0xffffu : 0u;
+        uint32_t all;
+        first = block_exclusive_scan(__popc(mine), slot, &all);
+    }
     if (exchange) {
         uint32_t rank = first;
         for (uint32_t b = mine; b && rank < room; b &= b - 1u, ++rank)
             idx_out[at + rank] = (uint32_t)L.offset + base + 16u * tid + (uint32_t)__ffs(b) - 1u;
     }
+    if (!handed_over) return;
     for (q = 0; q < n_lead; ++q) {
         const uint32_t c = chosen_at(leaders, n_lead, j, q, W);
         if (chosen_before(leaders, n_lead, j, q, W, c)) continue;
-        float* rl = P.r[c] + L.offset;
-        float* row = gathered + (size_t)c * max_pairs + at;
         const float* val = S.val + ((size_t)q * S.tiles + t) * S.cap;
-        if (exchange && handed_over) {
-            for (uint32_t e = tid; e < min(cnt, room); e += BLOCK) row[e] = val[e];
-            continue;
-        }
-        uint32_t rank = first;                               // fetch and clear, or put back where nothing is exchanged
-        for (uint32_t b = mine; b; b &= b - 1u, ++rank) {
-            const uint32_t i = base + 16u * tid + (uint32_t)__ffs(b) - 1u;
-            if (exchange && rank < room) row[rank] = rl[i];
-            rl[i] = exchange ? 0.0f : val[rank];
+        if (exchange) {
+            for (uint32_t e = tid; e < min(cnt, room); e += BLOCK) gathered[(size_t)c * max_pairs + at + e] = val[e];
+        } else {                                             // put back
+            float* rl = P.r[c] + L.offset;
+            uint32_t rank = first;
+            for (uint32_t b = mine; b; b &= b - 1u, ++rank) rl[base + 16u * tid + (uint32_t)__ffs(b) - 1u] = val[rank];
         }
     }
 }
