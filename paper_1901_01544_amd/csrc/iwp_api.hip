@@ -210,6 +210,11 @@ constexpr uint32_t FOLD_SCAN_MAX_STILES = 4096;
 // Do the followers' passes take the tiles in runs (see in_runs)?
 uint32_t takes_runs(uint32_t tiles, uint32_t n_layers) { return tiles <= (uint64_t)RUN_TILES * n_layers ? 1u : 0u; }
 
+// Do k_follow_sum / k_follow_mask_sum take the workers' pass, the exchange and the update?  streaming: workers with a gradient.
+bool follows_together(uint32_t streaming, uint32_t tiles) {
+    return tiles <= FOLLOW_SUM_MAX_TILES && (streaming <= FOLLOW_SUM_FEW || tiles > FOLLOW_SUM_FEW_TILES);
+}
+
 int check_eps(float eps) { return (eps >= 0.0f && std::isfinite(eps)) ? IWP_OK : IWP_EINVAL; }
 
 // Sampling source of a call: the leaders' residuals and gradients (NULL entries allowed), or nothing (on: false, or no w).
@@ -836,7 +841,7 @@ int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, fl
     // a single accumulating worker that leads every layer (no leader table: worker 0) has been through look 1 on
     // every tile: nothing follows
     const bool leader_did_all = acc.n == 1 && acc.id[0] == 0 && !leader && plan->all_k;
-    if (acc.n && !leader_did_all && T.tiles <= FOLLOW_SUM_MAX_TILES) {
+    if (acc.n && !leader_did_all && follows_together(acc.n, T.tiles)) {
         IWP_LAUNCH("k_follow_sum", k_follow_sum, CHUNKS_A_TILE * T.tiles, s, P, first_streaming(g, W), T.layers, T.n_layers,
                    leader, W, idx_out, val_out, ws.tile_out, w, scale, sum_out);
         return IWP_OK;
@@ -991,7 +996,11 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
     IWP_LAUNCH_BLOCK("k_tile_offsets", k_tile_offsets, 1u, OFFSETS_BLOCK, s, layers, z.n_layers, z.tiles, ws.tile_counts, max_pairs,
                      ws.tile_pos, ws.lay_out, count_out);
     if (z.tiles == 0) return IWP_OK;
-    if (z.tiles <= FOLLOW_SUM_MAX_TILES) {
+    uint32_t static_mask = 0, streaming = 0;
+    for (uint32_t p = 0; p < W; ++p) {
+        if (g[p]) ++streaming; else static_mask |= 1u << p;
+    }
+    if (follows_together(streaming, z.tiles)) {
         IWP_LAUNCH("k_follow_mask_sum", k_follow_mask_sum, CHUNKS_A_TILE * z.tiles, s, P, first_streaming(g, W), layers, z.n_layers,
                    leaders, n_lead, W, mask32, ws.tile_counts, ws.tile_pos, count_out, max_pairs, ws.slots, idx_out, w, scale,
                    sum_out);
@@ -1000,9 +1009,6 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
     IWP_LAUNCH("k_follow_mask", k_follow_mask, W * z.tiles, s, P, layers, z.n_layers, z.tiles, takes_runs(z.tiles, z.n_layers),
                leaders, n_lead, W, mask32,
                ws.tile_counts, ws.tile_pos, count_out, max_pairs, ws.slots, idx_out, ws.gathered);
-    uint32_t static_mask = 0;
-    for (uint32_t p = 0; p < W; ++p)
-        if (!g[p]) static_mask |= 1u << p;
     const uint32_t pair_blocks = std::min<uint32_t>((max_pairs + BLOCK - 1) / BLOCK, 8192u);
     IWP_LAUNCH("k_reduce_update_counted", k_reduce_update_counted, pair_blocks, s, R, static_mask, z.n_layers, leaders, n_lead, W,
                ws.lay_out, count_out, max_pairs, ws.gathered, idx_out, w, scale, sum_out, plan->flat_end);

@@ -1,0 +1,67 @@
+"""Small tables: which steps take one launch for all workers, exchange and update.  GPU parity on both sides of the rule (8 and 9
+workers with a gradient, 128 and 129 tiles) on the top-k and the threshold route, and the launches that each side makes: more
+workers on fewer tiles go through the workers' own launch (32 workers on 30 k elements 31 us a step, 40 in one launch)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1901_01544_amd import workloads as wl
+from harness import GpuSet, ThresholdSet, assert_step_equal, bits
+
+pytestmark = pytest.mark.gpu
+TILE = 4096
+W = 11
+CASES = [(8, 20, True), (9, 20, False), (11, 20, False), (8, 128, True), (9, 128, False), (9, 129, True), (11, 129, True)]
+
+
+def _sizes(tiles):
+    return [(tiles - 3) * TILE - 9, 2 * TILE + 5]                  # the second takes three tiles
+
+
+def _gradients(streaming):
+    return [p if p < streaming else None for p in range(W)]
+
+
+def _launches(iwp, kernel, call):
+    iwp.timing_enable(kernel)
+    call()
+    return iwp.timing_collect()[1]
+
+
+@pytest.mark.parametrize("streaming,tiles,together", CASES)
+def test_top_k(gpu_lib, streaming, tiles, together):
+    ps = wl.custom_set([(n, n // 50) for n in _sizes(tiles)], W=W, seed=tiles, align=1, start=3)
+    w = wl.gen_weights(ps)
+    sets = [wl.gen_gradient(ps, s) for s in range(W)]
+    r_ref = [(x * np.float32(0.5)).astype(np.float32) for x in sets]
+    gs = GpuSet(gpu_lib, ps, w.copy(), sets, r_np=[x.copy() for x in r_ref], fused=True, hint="none")
+    g_ids = _gradients(streaming)
+    for t, kernel in enumerate(("k_follow_sum", "k_follow_gather")):
+        lead = np.array([3 + t, 10 - t], np.uint32)                # one without a gradient among them
+        ref = oracle.step(w, sets, r_ref, ps.rows(), lead, float(ps.eps), float(ps.scale),
+                          accumulate_mask=[i is not None for i in g_ids])
+        assert _launches(gpu_lib, kernel, lambda: gs.step(g_ids, lead)) == (1 if together == (t == 0) else 0)
+        assert_step_equal(gs.download(), w, r_ref, *ref, ps.layers, tag="step %d" % t)
+
+
+@pytest.mark.parametrize("streaming,tiles,together", CASES)
+def test_thresholds(gpu_lib, streaming, tiles, together):
+    ps = wl.custom_set([(n, 0) for n in _sizes(tiles)], W=W, seed=tiles, align=1, start=3)
+    w = wl.gen_weights(ps)
+    sets = [wl.gen_gradient(ps, s) for s in range(W)]
+    r_ref = [(x * np.float32(0.5)).astype(np.float32) for x in sets]
+    ts = ThresholdSet(gpu_lib, ps, w.copy(), sets, [x.copy() for x in r_ref], 2, ps.flat)
+    g_ids = _gradients(streaming)
+    thr = np.array([4 * np.median(np.abs(sets[0][L.offset:L.offset + L.n]) / (np.abs(w[L.offset:L.offset + L.n]) + 1e-8))
+                    for L in ps.layers], np.float32)
+    for t, kernel in enumerate(("k_follow_mask_sum", "k_follow_mask")):
+        leaders = np.array([[3 + t, 10], [0, 9]], np.uint32)
+        mask, cnt, idx, sm = oracle.step_threshold(w, sets, r_ref, ps.rows(), leaders, thr, 1e-8, float(np.float32(-0.01)), ps.flat,
+                                                   accumulate_mask=[i is not None for i in g_ids])
+        assert _launches(gpu_lib, kernel, lambda: ts.step(g_ids, leaders, thr, -0.01)) == (1 if together == (t == 0) else 0)
+        got, total = ts.download(), int(cnt.sum())
+        assert 0 < total < ps.flat and np.array_equal(got["mask"], mask)
+        assert np.array_equal(got["idx"][:total], idx) and np.array_equal(bits(got["sum"][:total]), bits(sm))
+        assert np.array_equal(bits(got["w"]), bits(w))
+        for p in range(W):
+            assert np.array_equal(bits(got["r"][p]), bits(r_ref[p])), p
