@@ -572,7 +572,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     *plan_out = nullptr;
     if (!layers || n_layers == 0) return IWP_EINVAL;
     std::vector<DevLayer> dev(n_layers + 1);
-    uint64_t pairs = 0, slots = 0, tiles = 0, stiles = 0, end = 0, mask_words = 0, hist_words = 0;
+    uint64_t pairs = 0, slots = 0, tiles = 0, stiles = 0, end = 0, mask_words = 0;
     bool any_k = false, all_k = true;
     uint32_t max_stiles = 0, max_n = 0, n_long = 0;
     bool all_dense = true;
@@ -594,9 +594,6 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
         D.slot_cap = slot_cap_of(L.n, L.k);
         D.mask_begin = (uint32_t)mask_words;
         D.sample = sample_of(L.n, L.k);
-        D.hist_begin = (uint32_t)hist_words;
-        D.h0_copies = h0_copies_of(L.n, L.k);
-        hist_words += layer_hist_words(D.h0_copies);
         end = (uint64_t)L.offset + L.n;
         pairs += L.k;
         slots += (uint64_t)tiles_of(L.n) * D.slot_cap;
@@ -609,8 +606,21 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
         n_long += L.n > TILE ? 1u : 0u;
         if (L.n > TILE && (uint64_t)L.k * HINT_KEEP < L.n) all_dense = false;
         if (L.n > 0 && L.k == 0) all_k = false;
-        if (pairs > 0xFFFFFFFFull || tiles > 0x7FFFFFFFull / IWP_MAX_WORKERS || hist_words > 0xFFFFFFFFull) return IWP_ERANGE;
+        if (pairs > 0xFFFFFFFFull || tiles > 0x7FFFFFFFull / IWP_MAX_WORKERS) return IWP_ERANGE;
     }
+    // one copy of the first-digit histogram per `flushes` look-1 workgroups of a layer -> words of all layers' histograms
+    auto lay_out_histograms = [&](uint32_t flushes) {
+        uint64_t words = 0;
+        for (uint32_t j = 0; j < n_layers; ++j) {
+            dev[j].hist_begin = (uint32_t)words;
+            dev[j].h0_copies = h0_copies_of(layers[j].n, layers[j].k, flushes);
+            words += layer_hist_words(dev[j].h0_copies);
+        }
+        return words;
+    };
+    uint64_t hist_words = lay_out_histograms(FLUSHES_PER_COPY);
+    if (hist_words > 0xFFFFFFFFull) hist_words = lay_out_histograms(FLUSHES_PER_COPY_FEW);      // hist_begin holds 32 bits
+    if (hist_words > 0xFFFFFFFFull) return IWP_ERANGE;
     DevLayer& S = dev[n_layers];
     memset(&S, 0, sizeof S);
     S.out_offset = (uint32_t)pairs;
@@ -649,12 +659,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
             few.hist_words += layer_hist_words(h0_copies_of(layers[j].n, layers[j].k, FLUSHES_PER_COPY_FEW));
         if (carve(nullptr, few).bytes <= IWP_STATIC_SCRATCH_BYTES) {
             plan->z = few;
-            hist_words = 0;
-            for (uint32_t j = 0; j < n_layers; ++j) {
-                dev[j].hist_begin = (uint32_t)hist_words;
-                dev[j].h0_copies = h0_copies_of(layers[j].n, layers[j].k, FLUSHES_PER_COPY_FEW);
-                hist_words += layer_hist_words(dev[j].h0_copies);
-            }
+            lay_out_histograms(FLUSHES_PER_COPY_FEW);
         }
     }
     for (const DevLayer& D : dev) plan->max_copies = std::max(plan->max_copies, D.h0_copies);

@@ -60,7 +60,8 @@ constexpr uint32_t HIST0 = 1u << 12, HIST1 = 1u << 10, HIST2 = 1u << 9;
 constexpr uint32_t MAX_H0_COPIES = 16;
 // Look-1 workgroups that share one copy.  128 against 512: one layer of 1 M elements 39.2 -> 36.0 us a call, ten of 25 M 127
 // -> 120, 161 of 25.6 M 130 -> 123 (thresholds and pairs); 256: 37.8, 120, 125; 64: 38.4, 120, 123.  The pick that adds the
-// copies up pays for them.  512 (FEW) only in plans that would otherwise no longer fit the library's static scratch.
+// copies up pays for them.  512 (FEW) only in plans that would otherwise no longer fit the library's static scratch,
+// or 32 bits.
 constexpr uint32_t FLUSHES_PER_COPY = 128, FLUSHES_PER_COPY_FEW = 512;
 __host__ __device__ constexpr uint32_t layer_hist_words(uint32_t copies) { return copies * HIST0 + HIST1 + HIST2; }
 
