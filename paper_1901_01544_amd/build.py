@@ -2,7 +2,7 @@
 
     python -m paper_1901_01544_amd.build
 
-The shared objects are written next to this file (``libiwp.so``, ``_call.so``), in-tree, so they
+The shared objects are written next to this file (``libiwp.so``, ``_call`` with the interpreter's suffix), in-tree, so they
 travel with the source tree to wherever the GPU is.
 """
 from __future__ import annotations
@@ -16,7 +16,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "csrc", "iwp_api.hip")
 LIB = os.path.join(HERE, "libiwp.so")
 CALL_SRC = os.path.join(HERE, "csrc", "call.cpp")
-CALL = os.path.join(HERE, "_call.so")
+# named after the interpreter's version, so that another one fails to import it instead of loading it
+CALL = os.path.join(HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))
+UNTAGGED_CALL = os.path.join(HERE, "_call.so")           # an earlier build's, which every interpreter would take
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
@@ -56,7 +58,7 @@ def build(verbose: bool = False, extra_flags=(), out: str = LIB) -> str:
 
 
 def build_call(verbose: bool = False, out: str = CALL) -> str:
-    """Compile csrc/call.cpp (host code only) into the extension module _call.so; returns the path."""
+    """Compile csrc/call.cpp (host code only) into the extension module _call; returns the path."""
     tmp = out + ".tmp.%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
            "-I", sysconfig.get_paths()["include"], "-o", tmp, CALL_SRC]
@@ -64,6 +66,8 @@ def build_call(verbose: bool = False, out: str = CALL) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(tmp, out)
+    if out == CALL and os.path.exists(UNTAGGED_CALL):
+        os.remove(UNTAGGED_CALL)
     return out
 
 
