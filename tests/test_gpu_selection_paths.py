@@ -3,7 +3,7 @@ compared with the CPU oracle bit for bit through the C ABI:
   * the first look's mark taken from a sample of the layer (no hint given), on layouts that fool a sample:
     sorted scores, all of the mass in a block between the sampled runs, a pattern with the sample's period; and
     tables where such layers and ordinary ones meet in one workgroup of the second look;
-  * first-digit histograms kept in several copies (layers of more than 512 tiles);
+  * first-digit histograms kept in several copies (layers of more than 128 tiles);
   * tiles whose keys are all equal, above, at and below the threshold (recorded as one entry);
   * slots that overflow in the first look and are filled again by the second (hints far too low)."""
 import numpy as np
@@ -81,7 +81,7 @@ def test_sampled_staging_bin_on_layouts_that_fool_a_sample(gpu_lib, n):
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("n", [513 * TILE + 5, 1100 * TILE + 1, 2200 * TILE - 3])
 def test_layers_with_several_first_digit_histogram_copies(gpu_lib, n):
-    """More than 512 tiles: the first look's workgroups flush into 2, 4 and 8 copies of the histogram."""
+    """The first look's workgroups flush into 8, 16 and 16 copies of the histogram (one per 128 of them, 16 at most)."""
     import torch
     rng = np.random.default_rng(n)
     w = (rng.standard_normal(n) * 0.05).astype(np.float32)
