@@ -113,7 +113,7 @@ inline uint32_t slot_cap_of(uint32_t n, uint32_t k) {
     return (uint32_t)std::min<uint64_t>(TILE, 64 + 3 * per_tile);
 }
 
-// Small tables (looks_twice(), see LOOK_TWICE_TILES in iwp_select.hpp) have no sampled mark, and the second look copies out
+// On small tables (looks_twice(), see LOOK_TWICE_TILES in iwp_select.hpp) the second look can have to copy out
 // whole bins of the first digit: up to 1/16 of a tile where the scores lie evenly below the threshold, for which their slots
 // have LOOK_TWICE_ROOM entries more.  Larger tables hold the same number of entries in reserve, so that a workspace that fits a table fits
 // the smaller ones of its kind.
@@ -399,7 +399,7 @@ struct iwp_plan {
     uint32_t max_n = 0;           // elements of the longest layer
     uint32_t n_long = 0;          // layers of more than one tile
     bool all_dense = true;        // each of those keeps at least one element in HINT_KEEP
-    bool look_twice = false;      // no marks by samples, roomy slots (LOOK_TWICE_TILES)
+    bool look_twice = false;      // roomy slots; marks by samples only where samples() says so (LOOK_TWICE_TILES)
     uint32_t max_copies = 1;      // most copies of a layer's first-digit histogram
     float momentum = 1.0f;        // r <- momentum * r + g in every call that accumulates through this plan
 };
@@ -418,7 +418,7 @@ bool takes_small(const iwp_plan& plan, bool hinted, bool select) {
     return select || plan.max_n <= SMALL_MAX_N / 2 || plan.n_long <= (no_sample ? 512u : 1024u);
 }
 
-// May a step's or a compression's marks be sampled (see LOOK_TWICE_TILES)?
+// May a step's or a compression's marks be sampled?  The rule and its exception: see LOOK_TWICE_TILES.
 bool samples(const iwp_plan& plan, bool hinted) {
     return !plan.look_twice || (!hinted && plan.momentum == 1.0f);
 }

@@ -87,9 +87,9 @@ constexpr uint32_t HINT_BELOW = 1u << 18;
 constexpr uint32_t HINT_SLACK = 4u << 19;          // four top-digit bins
 constexpr uint32_t HINT_KEEP = 128;
 constexpr uint32_t HINT_MAX_TILES = 2048, HINT_FEW_LAYERS = 16;
-// Tables of up to LOOK_TWICE_TILES tiles, or LOOK_TWICE_TILES_MANY in LOOK_TWICE_MANY layers or more, have no sampled mark:
-// where no hint is taken, look 1 copies nothing and look 2 reads the tiles again, from the caches, and copies from the
-// threshold's bin on.  A sample costs 4 to 5 us there and look 1's copies
+// Tables of up to LOOK_TWICE_TILES tiles, or LOOK_TWICE_TILES_MANY in LOOK_TWICE_MANY layers or more, have no sampled mark, with
+// one exception below: where no hint is taken, look 1 copies nothing and look 2 reads the tiles again, from the caches, and
+// copies from the threshold's bin on.  A sample costs 4 to 5 us there and look 1's copies
 // 1 to 2, the second reading 3.  us a call, one worker, its update included, sampled / read twice: 0.3 M elements 35.8 / 31.4 in
 // one layer, 36.9 / 32.1 in 20, 1 M 38.3 / 36.1 and 39.0 / 35.6, 2 M 44.1 / 44.0 and 43.0 / 40.0 (kept at 1/64), 43.9 / 40.1 and
 // 42.8 / 37.1 (at 0.001); 3 M 47.8 / 52.0 and 46.4 / 44.4 (in 300 layers 51.7 / 46.4), 6 M 60.5 / 74.4 and 59.2 / 65.1 (where layers are few their tiles'
@@ -97,10 +97,10 @@ constexpr uint32_t HINT_MAX_TILES = 2048, HINT_FEW_LAYERS = 16;
 // (HINT_BELOW) is better than either: 1 M 32.7 and 33.3.  A whole bin holds up to 1/16 of the elements where
 // scores lie evenly below the threshold, hence LOOK_TWICE_ROOM more entries a slot: without them 100 layers of 3 M elements kept
 // at 0.004 overflowed (48 us sampled, 94 read twice; with them 42).  Fuller tiles: see k_refine_tiles.
+// The exception (samples() in iwp_api.hip): a step or a compression at momentum 1 that is given no hint samples all the same.  It is
+// the slower route (six tensors, 235 k elements, four workers 36.7 us a step sampled, 33.7 read twice), kept as it was before
+// such tables went without a sample because a hint is tested to save 4 % of that call, and with one it takes 32.6.
 constexpr uint32_t LOOK_TWICE_TILES = 512, LOOK_TWICE_ROOM = 320;
-// A step or a compression that would have taken a hint (momentum 1) and was given none samples all the same: reading twice is
-// better there too (six tensors, 235 k elements, four workers 37.5 / 34.6 us a step), but callers count on a hint paying by 4 %
-// and more, and with one the step takes 33.2.
 constexpr uint32_t LOOK_TWICE_TILES_MANY = 1024, LOOK_TWICE_MANY = 16;
 constexpr uint32_t TRUST_DENSE = 1, TRUST_ALWAYS = 2;
 constexpr int INIT_BLOCK = 1024;                   // threads of a k_init workgroup
