@@ -11,7 +11,7 @@
 // second digit of those inside b1; otherwise it reads the leader's residual and weights once
 // more and copies out the elements whose top digit is >= b1 (above b1 all of them are kept, the
 // threshold lies among those inside).  Everything after that works on the staged
-// copies, a few percent of the layer: k_refine2 histograms the third digit, k_count /
+// copies, a few percent of the layer: k_refine2 (on small tables k_refine_tiles) histograms the third digit, k_count /
 // k_write place every kept element at its rank in index order.  A tile whose
 // candidates do not fit its slot (heavy ties, e.g. a tile that is all zeros) is marked
 // RAW and is simply re-read from r and w by the later passes (on small tables by one of them, see k_refine_tiles).  Both
@@ -19,7 +19,7 @@
 //
 // The second and third digit picks have no launches of their own: a finished histogram is
 // the same for every reader, so each workgroup of the consuming kernel redoes the pick of its
-// layer in its prologue (k_refine2 the second, k_count the third), and one elected workgroup
+// layer in its prologue (k_refine2 or k_refine_tiles the second, k_count the third), and one elected workgroup
 // per layer records it.  Likewise
 // k_write sums the counts of the layer's earlier super-tiles itself unless a layer has so
 // many that a scan launch (k_scan) is cheaper.  Kernel boundaries are the only
@@ -591,9 +591,10 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
 // goes into the slot after all, and k_count and k_write find copies (a tile that still overflows, by ties, stays RAW).
 // Bound by latency, and for such tiles by the divides: a workgroup per tile puts them on all compute units, where k_refine2's
 // workgroup of a super-tile has eight tiles in turn.  One layer of 1 M elements kept at 1/64, us a call, k_refine2 / this: scores
-// inside one bin 104 / 38 (45.5 with a sampled mark), an eighth of them in the threshold's bin and kept at 0.001 98 / 35 (39),
-// normally distributed 31.0 / 30.1 (38.4); eight distinct values, kept at 0.001, 99 / 74 (118).  (Slots of 400 entries instead of
-// 576, so that an eighth of a tile overflows and fewer copies are made: 38.7 -> 35.7, but the eight values 40 -> 74.)
+// inside one bin 104 / 40 (45.5 when such layers were sampled), normally distributed 31.0 / 30.0 (38.4); kept at 0.001, an
+// eighth of the scores in the threshold's bin 98 / 36 (39), eight distinct values 99 / 74 (117).  Where an eighth of a tile just
+// fits its slot nothing is gained: 2 M elements kept at 1/64 46 (42 sampled).  (Slots of 400 entries instead of 576, so that it
+// overflows: 44, but the eight values, kept at 1/64, 39 -> 74.)
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(BLOCK) void k_refine_tiles(ResidualPtrs R, const float* __restrict__ w,
                                                         const DevLayer* __restrict__ layers, uint32_t n_layers,

@@ -56,6 +56,7 @@ def load() -> C.CDLL:
                                 "`python -m paper_1901_01544_amd.build`" % e) from e
     L = C.CDLL(LIB_PATH)
     call.bind({name: C.cast(getattr(L, name), _vp).value for name in call.names()})
+    # prototypes of every call, also of those that go through _call: for callers that use the library by ctypes
     L.iwp_workspace_bytes.argtypes = [C.c_uint32, C.c_uint32]
     L.iwp_workspace_bytes.restype = C.c_size_t
     L.compress_layer.argtypes = [_vp, _vp, _vp, C.c_uint32, C.c_uint32, C.c_float, _vp, _vp, _vp, C.c_size_t, _vp]
@@ -155,6 +156,7 @@ def _stream(stream) -> Optional[int]:
     if _raw_stream is None:
         import torch
         current = torch.cuda.current_stream().cuda_stream     # initialises torch's runtime if nothing has
+        # what torch.cuda.current_stream() itself asks, without its Stream object (1.5 us a call)
         _current_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
         return current
     return _raw_stream(_current_device())

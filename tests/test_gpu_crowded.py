@@ -73,7 +73,7 @@ def test_table_of_all_kinds(gpu_lib, fused):
 
 def test_time(gpu_lib):
     """One layer of a million elements, one pair in 64: scores inside one bin take at most twice as long as normally distributed
-    ones (measured 38 against 30 us; 104 if the later passes read every tile again)."""
+    ones (measured 40 against 30 us; 104 if the later passes read every tile again)."""
     import torch
     n, k = 1_000_000, 1_000_000 // 64
     gen = torch.Generator(device="cuda").manual_seed(3)
