@@ -98,8 +98,9 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
     request_tile<true>(wl, n, base, wv, wv_rest);
 #pragma unroll
     for (int s = 0; s < NL; ++s) {                           // node in slot q0 + s of the layer -> registers s
-        const uint32_t q = min(q0 + s, n_lead - 1u), p = chosen_at(leaders, n_lead, j, q, W);
-        on[s] = q0 + s < n_lead && !chosen_before(leaders, n_lead, j, q, W, p);
+        // one group: exactly NL nodes
+        const uint32_t q = GROUPS > 1 ? min(q0 + s, n_lead - 1u) : (uint32_t)s, p = chosen_at(leaders, n_lead, j, q, W);
+        on[s] = (GROUPS == 1 || q0 + s < n_lead) && !chosen_before(leaders, n_lead, j, q, W, p);
         th[s] = thr_per_slot ? thr[(size_t)j * n_lead + q] : thr[j];
         rl[s] = P.r[p] + L.offset;
         gl[s] = accumulate && P.g[p] ? P.g[p] + L.offset : nullptr;
@@ -194,7 +195,7 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
 // once per node and left a mask for each, to be OR-ed and counted in a launch of its own (308 + 9 us), and the nodes' sent
 // values were read and cleared pair by pair behind everything else (the update 177 us, now 66).  Whole steps: that table
 // 1208 -> 1077 us, one node of 25.6 M elements with a line per layer 554 -> 522, three of 1.1 M 38 -> 29 (three launches less).
-// Up to three nodes are one group's (73, 104 and 141 registers); more are taken two to a group, by workgroups of two to four
+// Up to three nodes are one group's (74, 107 and 144 registers); more are taken two to a group, by workgroups of two to four
 // groups, which read the weights once each.  One group that takes them one after the other, storing each and fetching
 // its sent values again, had every node's loads wait for the one before: eight workers, four and eight nodes, us a step, against
 // that (and against a workgroup per node and tile): 30 k elements 35 / 24 (31) and 47 / 27 (35), 1.2 M 69 / 43 (60) and 88 / 49
