@@ -210,11 +210,6 @@ constexpr uint32_t FOLD_SCAN_MAX_STILES = 4096;
 // Do the followers' passes take the tiles in runs (see in_runs)?
 uint32_t takes_runs(uint32_t tiles, uint32_t n_layers) { return tiles <= (uint64_t)RUN_TILES * n_layers ? 1u : 0u; }
 
-// Do k_follow_sum / k_follow_mask_sum take the workers' pass, the exchange and the update?  streaming: workers with a gradient.
-bool follows_together(uint32_t streaming, uint32_t tiles) {
-    return tiles <= FOLLOW_SUM_MAX_TILES && (streaming <= FOLLOW_SUM_FEW || tiles > FOLLOW_SUM_FEW_TILES);
-}
-
 int check_eps(float eps) { return (eps >= 0.0f && std::isfinite(eps)) ? IWP_OK : IWP_EINVAL; }
 
 // Sampling source of a call: the leaders' residuals and gradients (NULL entries allowed), or nothing (on: false, or no w).
@@ -393,6 +388,7 @@ struct iwp_plan {
     DevLayer* dev = nullptr;      // n_layers + 1 rows
     Sizes z{};
     uint64_t flat_end = 0;        // one past the last element any layer covers
+    uint64_t elements = 0;        // of all layers
     bool any_k = false;
     bool all_k = true;            // every non-empty layer selects something
     uint32_t max_layer_stiles = 0;
@@ -416,6 +412,12 @@ bool takes_small(const iwp_plan& plan, bool hinted, bool select) {
     if (plan.max_n > SMALL_MAX_N) return false;
     const bool no_sample = hinted && plan.all_dense && plan.momentum == 1.0f;
     return select || plan.max_n <= SMALL_MAX_N / 2 || plan.n_long <= (no_sample ? 512u : 1024u);
+}
+
+// Do k_follow_sum / k_follow_mask_sum take the workers' pass, the exchange and the update?  streaming: workers with a gradient.
+bool follows_together(const iwp_plan& plan, uint32_t streaming) {
+    return plan.z.tiles <= FOLLOW_SUM_MAX_TILES &&
+           (streaming <= FOLLOW_SUM_FEW || plan.elements >= (FOLLOW_SUM_CHUNKS + 2ull * plan.z.n_layers) * CHUNK);
 }
 
 // May a step's or a compression's marks be sampled?  The rule and its exception: see LOOK_TWICE_TILES.
@@ -664,6 +666,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     }
     for (const DevLayer& D : dev) plan->max_copies = std::max(plan->max_copies, D.h0_copies);
     plan->flat_end = end;
+    for (const iwp_layer& row : plan->rows) plan->elements += row.n;
     // the table, then the layer of every tile and of every super-tile (layer_of_tile and layer_of_stile read them)
     std::vector<uint32_t> map;
     map.reserve(tiles + stiles);
@@ -846,7 +849,7 @@ int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, fl
     // a single accumulating worker that leads every layer (no leader table: worker 0) has been through look 1 on
     // every tile: nothing follows
     const bool leader_did_all = acc.n == 1 && acc.id[0] == 0 && !leader && plan->all_k;
-    if (acc.n && !leader_did_all && follows_together(acc.n, T.tiles)) {
+    if (acc.n && !leader_did_all && follows_together(*plan, acc.n)) {
         IWP_LAUNCH("k_follow_sum", k_follow_sum, CHUNKS_A_TILE * T.tiles, s, P, first_streaming(g, W), T.layers, T.n_layers,
                    leader, W, idx_out, val_out, ws.tile_out, w, scale, sum_out);
         return IWP_OK;
@@ -1005,7 +1008,7 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
     for (uint32_t p = 0; p < W; ++p) {
         if (g[p]) ++streaming; else static_mask |= 1u << p;
     }
-    if (follows_together(streaming, z.tiles)) {
+    if (follows_together(*plan, streaming)) {
         IWP_LAUNCH("k_follow_mask_sum", k_follow_mask_sum, CHUNKS_A_TILE * z.tiles, s, P, first_streaming(g, W), layers, z.n_layers,
                    leaders, n_lead, W, mask32, ws.tile_counts, ws.tile_pos, count_out, max_pairs, ws.slots, idx_out, w, scale,
                    sum_out);

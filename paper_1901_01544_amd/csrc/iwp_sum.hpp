@@ -12,10 +12,12 @@
 // once) the workers' own launch, one worker at a time, streams faster: 300 tensors of 1 M elements 63 against 72 us, 61 M
 // elements with eight workers 886 us (with the update) against 914.
 // The workers are a serial chain here, TOGETHER at a time, where their own launch has workgroups of their own for each.  More
-// than FOLLOW_SUM_FEW of them therefore take this route only where its chunks fill the chip (more than FOLLOW_SUM_FEW_TILES
-// tiles).  us a step against two launches, 8, 12, 16 and 32 workers: 30 k elements in 20 layers +0.6, +2.3, +4.4, +11 (of 22 to 31),
-// in one -1.5, -0.1, +0.9, +4.8; 300 k in 20 layers -0.9, 0, -0.2, +2.9, in 4 -1.9, -2.1, -2.4, -1.8; 600 k -1.8, -2.9, -2.0, -0.1
-// and -3.3, -4.3, -4.9, -5.2; with thresholds the same to 1 us.
+// than FOLLOW_SUM_FEW of them therefore take this route only where its chunks give the chip enough to do: from
+// FOLLOW_SUM_CHUNKS chunks of elements on, not counting the two a layer that go element by element.  us a step against two launches, in
+// one layer / 4 / 20 / 60 layers (thresholds the same to 1 us): 8 workers, 30 k elements -1.1 / -0.9 / -0.2 / +0.2 (of 36 / 24 / 23 / 21),
+// 300 k -0.2 / -2.0 / -0.8 / -1.6; 9 workers, 60 k -0.6 / +0.6 / +1.1 / +1.1, 160 k -1.6 / -0.3 / -0.2 / +1.0, 300 k -0.1 / -1.5 / +0.1 /
+// -0.6; 16 workers, 60 k +1.9 / +2.7 / +3.9 / +3.6, 160 k -0.5 / +1.5 / +1.5 / +2.9, 220 k -0.6 / -0.4 / -0.9 / +2.8, 400 k -4.0 / -5.4 / -2.3 /
+// +1.6; 32 workers, 60 k +6.2 / +8.4 / +10 / +11, 220 k +0.1 / -1.6 / +0.4 / +9.1, 400 k -4.4 / -6.6 / -1.3 / +6.7.
 #pragma once
 
 #include "iwp_common.hpp"
@@ -24,7 +26,7 @@
 
 namespace iwp {
 
-constexpr uint32_t FOLLOW_SUM_MAX_TILES = 256, FOLLOW_SUM_FEW = 8, FOLLOW_SUM_FEW_TILES = 128;
+constexpr uint32_t FOLLOW_SUM_MAX_TILES = 256, FOLLOW_SUM_FEW = 8, FOLLOW_SUM_CHUNKS = 140;
 constexpr uint32_t CHUNKS_A_TILE = TILE / CHUNK;
 constexpr uint32_t TOGETHER = 4;                            // workers whose loads are in flight together
 constexpr uint32_t NO_WORKER = 0xFFFFFFFFu;

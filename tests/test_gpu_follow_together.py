@@ -1,6 +1,7 @@
 """Small tables: which steps take one launch for all workers, exchange and update.  GPU parity on both sides of the rule (8 and 9
-workers with a gradient, 128 and 129 tiles) on the top-k and the threshold route, and the launches that each side makes: more
-workers on fewer tiles go through the workers' own launch (32 workers on 30 k elements 31 us a step, 40 in one launch)."""
+workers with a gradient, 140 chunks of elements besides two a layer, 256 tiles) on the top-k and the threshold route, and the launches that
+each side makes: more workers on few elements go through the workers' own launch (32 workers on 30 k elements 29 us a step, 40
+in one launch)."""
 import numpy as np
 import pytest
 
@@ -11,11 +12,13 @@ from harness import GpuSet, ThresholdSet, assert_step_equal, bits
 pytestmark = pytest.mark.gpu
 TILE = 4096
 W = 11
-CASES = [(8, 20, True), (9, 20, False), (11, 20, False), (8, 128, True), (9, 128, False), (9, 129, True), (11, 129, True)]
+ENOUGH = (140 + 2 * 2) * 1024                                  # elements, in two layers
+CASES = [(8, 5 * TILE, True), (9, 5 * TILE, False), (9, ENOUGH - 1, False), (9, ENOUGH, True), (11, ENOUGH - 1, False),
+         (11, ENOUGH, True), (11, 256 * TILE - 4091, True), (11, 256 * TILE - 4090, False)]
 
 
-def _sizes(tiles):
-    return [(tiles - 3) * TILE - 9, 2 * TILE + 5]                  # the second takes three tiles
+def _sizes(elements):
+    return [elements - 2 * TILE - 5, 2 * TILE + 5]                 # the second takes three tiles
 
 
 def _gradients(streaming):
@@ -28,9 +31,9 @@ def _launches(iwp, kernel, call):
     return iwp.timing_collect()[1]
 
 
-@pytest.mark.parametrize("streaming,tiles,together", CASES)
-def test_top_k(gpu_lib, streaming, tiles, together):
-    ps = wl.custom_set([(n, n // 50) for n in _sizes(tiles)], W=W, seed=tiles, align=1, start=3)
+@pytest.mark.parametrize("streaming,elements,together", CASES)
+def test_top_k(gpu_lib, streaming, elements, together):
+    ps = wl.custom_set([(n, n // 50) for n in _sizes(elements)], W=W, seed=streaming, align=1, start=3)
     w = wl.gen_weights(ps)
     sets = [wl.gen_gradient(ps, s) for s in range(W)]
     r_ref = [(x * np.float32(0.5)).astype(np.float32) for x in sets]
@@ -44,9 +47,9 @@ def test_top_k(gpu_lib, streaming, tiles, together):
         assert_step_equal(gs.download(), w, r_ref, *ref, ps.layers, tag="step %d" % t)
 
 
-@pytest.mark.parametrize("streaming,tiles,together", CASES)
-def test_thresholds(gpu_lib, streaming, tiles, together):
-    ps = wl.custom_set([(n, 0) for n in _sizes(tiles)], W=W, seed=tiles, align=1, start=3)
+@pytest.mark.parametrize("streaming,elements,together", CASES)
+def test_thresholds(gpu_lib, streaming, elements, together):
+    ps = wl.custom_set([(n, 0) for n in _sizes(elements)], W=W, seed=streaming, align=1, start=3)
     w = wl.gen_weights(ps)
     sets = [wl.gen_gradient(ps, s) for s in range(W)]
     r_ref = [(x * np.float32(0.5)).astype(np.float32) for x in sets]
