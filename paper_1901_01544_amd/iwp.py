@@ -156,7 +156,7 @@ def _stream(stream) -> Optional[int]:
     if _raw_stream is None:
         import torch
         current = torch.cuda.current_stream().cuda_stream     # initialises torch's runtime if nothing has
-        # what torch.cuda.current_stream() itself asks, without its Stream object (1.5 us a call)
+        # what torch.cuda.current_stream() itself asks, without its Stream object (0.2 instead of 2.8 us a call)
         _current_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
         return current
     return _raw_stream(_current_device())
