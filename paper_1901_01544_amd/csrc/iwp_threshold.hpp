@@ -96,30 +96,32 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
     bool on[NL];
     uint32_t nib[CHUNKS] = {};
     request_tile<true>(wl, n, base, wv, wv_rest);
-#pragma unroll
-    for (int s = 0; s < NL; ++s) {                           // node in slot q0 + s of the layer -> registers s
-        // one group: exactly NL nodes
-        const uint32_t q = GROUPS > 1 ? min(q0 + s, n_lead - 1u) : (uint32_t)s, p = chosen_at(leaders, n_lead, j, q, W);
-        on[s] = (GROUPS == 1 || q0 + s < n_lead) && !chosen_before(leaders, n_lead, j, q, W, p);
+    auto request = [&](int s, uint32_t q, bool there) {      // node in slot q of the layer -> registers s
+        const uint32_t p = chosen_at(leaders, n_lead, j, q, W);
+        on[s] = there && !chosen_before(leaders, n_lead, j, q, W, p);
         th[s] = thr_per_slot ? thr[(size_t)j * n_lead + q] : thr[j];
         rl[s] = P.r[p] + L.offset;
         gl[s] = accumulate && P.g[p] ? P.g[p] + L.offset : nullptr;
-        if (!on[s]) continue;
+        if (!on[s]) return;
         request_tile<true>(rl[s], n, base, rv[s], rv_rest[s]);
         if (gl[s]) request_tile<true>(gl[s], n, base, gv[s], gv_rest[s]);
-    }
-    settle_tile(n, base, wv, wv_rest);
-#pragma unroll
-    for (int s = 0; s < NL; ++s) {
-        if (!on[s]) continue;
+    };
+    auto settle = [&](int s) {
+        if (!on[s]) return;
         settle_tile(n, base, rv[s], rv_rest[s]);
-        if (!gl[s]) continue;
+        if (!gl[s]) return;
         settle_tile(n, base, gv[s], gv_rest[s]);
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
             for (int c = 0; c < 4; ++c) rv[s][u][c] = accum(rv[s][u][c], gv[s][u][c], P.momentum);
-    }
+    };
+    // one group: exactly NL nodes, their slots constants
+#pragma unroll
+    for (int s = 0; s < NL; ++s) request(s, GROUPS > 1 ? min(q0 + s, n_lead - 1u) : (uint32_t)s, GROUPS == 1 || q0 + s < n_lead);
+    settle_tile(n, base, wv, wv_rest);
+#pragma unroll
+    for (int s = 0; s < NL; ++s) settle(s);
 #pragma unroll
     for (uint32_t u = 0; u < CHUNKS; ++u) {                  // the elements that one of the nodes in registers sends
         const uint32_t i = base + u * CHUNK + tid * VEC;
@@ -195,7 +197,7 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
 // once per node and left a mask for each, to be OR-ed and counted in a launch of its own (308 + 9 us), and the nodes' sent
 // values were read and cleared pair by pair behind everything else (the update 177 us, now 66).  Whole steps: that table
 // 1208 -> 1077 us, one node of 25.6 M elements with a line per layer 554 -> 522, three of 1.1 M 38 -> 29 (three launches less).
-// Up to three nodes are one group's (74, 107 and 144 registers); more are taken two to a group, by workgroups of two to four
+// Up to three nodes are one group's (76, 107 and 144 registers); more are taken two to a group, by workgroups of two to four
 // groups, which read the weights once each.  One group that takes them one after the other, storing each and fetching
 // its sent values again, had every node's loads wait for the one before: eight workers, four and eight nodes, us a step, against
 // that (and against a workgroup per node and tile): 30 k elements 35 / 24 (31) and 47 / 27 (35), 1.2 M 69 / 43 (60) and 88 / 49
