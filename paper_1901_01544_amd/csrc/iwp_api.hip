@@ -415,9 +415,12 @@ bool takes_small(const iwp_plan& plan, bool hinted, bool select) {
 }
 
 // Do k_follow_sum / k_follow_mask_sum take the workers' pass, the exchange and the update?  streaming: workers with a gradient.
+// The lines: see iwp_sum.hpp.
 bool follows_together(const iwp_plan& plan, uint32_t streaming) {
-    return plan.z.tiles <= FOLLOW_SUM_MAX_TILES &&
-           (streaming <= FOLLOW_SUM_FEW || plan.elements >= (FOLLOW_SUM_CHUNKS + 2ull * plan.z.n_layers) * CHUNK);
+    if (plan.z.tiles > FOLLOW_SUM_MAX_TILES) return false;
+    if (streaming <= FOLLOW_SUM_ANY) return true;
+    const uint64_t layers = plan.z.n_layers, chunks = std::max(FOLLOW_SUM_CHUNKS, FOLLOW_SUM_CHUNKS_EACH * streaming);
+    return plan.elements >= (streaming <= FOLLOW_SUM_FEW ? layers : chunks + 2 * layers) * CHUNK;
 }
 
 // May a step's or a compression's marks be sampled?  The rule and its exception: see LOOK_TWICE_TILES.

@@ -4,20 +4,22 @@
 // Work unit: a chunk of 1024 elements, one quad per lane, for all workers: up to TOGETHER workers' loads are in flight at a
 // time, the chunk's bits of sent elements are found once, and every lane keeps the running sums of its four elements, so that
 // nothing is gathered into memory and read back by another launch.  The quads start at a multiple of 64 bytes of one worker's
-// residual (see follow_tile_from); a layer's first and last chunk (EDGE) go element by element.
+// residual (see follow_tile_from); a layer's first and last chunk (PART) read a cut quad from the
+// nearest whole one.
 //
 // Latency bound: launches count here, and a layer that takes a few workgroups.  Six tensors of 235 k elements, four workers
 // 43.4 -> 40.7 us a step; 40 tensors of 300 k with two, four and eight workers 38.5, 40.8, 43.6 -> 36.4, 38.8, 43.4; with
 // thresholds 21.8, 23.0, 24.8 -> 17.7, 18.7, 21.8.  From FOLLOW_SUM_MAX_TILES on (where the chip no longer holds all chunks at
 // once) the workers' own launch, one worker at a time, streams faster: 300 tensors of 1 M elements 63 against 72 us, 61 M
 // elements with eight workers 886 us (with the update) against 914.
-// The workers are a serial chain here, TOGETHER at a time, where their own launch has workgroups of their own for each.  More
-// than FOLLOW_SUM_FEW of them therefore take this route only where its chunks give the chip enough to do: from
-// FOLLOW_SUM_CHUNKS chunks of elements on, not counting the two a layer that go element by element.  us a step against two launches, in
-// one layer / 4 / 20 / 60 layers (thresholds the same to 1 us): 8 workers, 30 k elements -1.1 / -0.9 / -0.2 / +0.2 (of 36 / 24 / 23 / 21),
-// 300 k -0.2 / -2.0 / -0.8 / -1.6; 9 workers, 60 k -0.6 / +0.6 / +1.1 / +1.1, 160 k -1.6 / -0.3 / -0.2 / +1.0, 300 k -0.1 / -1.5 / +0.1 /
-// -0.6; 16 workers, 60 k +1.9 / +2.7 / +3.9 / +3.6, 160 k -0.5 / +1.5 / +1.5 / +2.9, 220 k -0.6 / -0.4 / -0.9 / +2.8, 400 k -4.0 / -5.4 / -2.3 /
-// +1.6; 32 workers, 60 k +6.2 / +8.4 / +10 / +11, 220 k +0.1 / -1.6 / +0.4 / +9.1, 400 k -4.4 / -6.6 / -1.3 / +6.7.
+// The workers are a serial chain here, TOGETHER at a time, where their own launch has workgroups of their own for each.  What the
+// one launch gains over two, us a step, median over layouts, hints and keep ratios (steps of 20 to 110 us): up to 6 workers 1 to 4
+// from 20 k to 1 M elements, -0.3 to 1.5 below.  7 and 8 lose 0.6 to 1.4 (thresholds; top-k 0.1 to 0.8) where layers average less than
+// a chunk, gain up to 1 above that and 2.4 to 6 from 300 k elements on: they take it from a chunk a layer on.  More workers take it where
+// its chunks give the chip enough to do, 14 a worker (140 for 9), not counting the two a layer that the layer may fill in part: 16
+// workers -2.0 at 8 to 12 chunks a worker, -0.3 at 12, 0.6 at 16, 2.9 at 20; 24 -1.0, 1.2, 3.8, 5.1; 32 (thresholds) 1.7, 6.7, 8.4, 13.
+// Cut quads were read and written element by element before, 32 loads in a row for four workers: packed layers then lost up to
+// 14 us (60 layers of 270 k elements, 32 workers 60 us a step in two launches, 72 in one).
 #pragma once
 
 #include "iwp_common.hpp"
@@ -26,7 +28,9 @@
 
 namespace iwp {
 
-constexpr uint32_t FOLLOW_SUM_MAX_TILES = 256, FOLLOW_SUM_FEW = 8, FOLLOW_SUM_CHUNKS = 140;
+constexpr uint32_t FOLLOW_SUM_MAX_TILES = 256;
+constexpr uint32_t FOLLOW_SUM_ANY = 6, FOLLOW_SUM_FEW = 8;      // workers: always; from a chunk a layer on
+constexpr uint32_t FOLLOW_SUM_CHUNKS = 140, FOLLOW_SUM_CHUNKS_EACH = 14;
 constexpr uint32_t CHUNKS_A_TILE = TILE / CHUNK;
 constexpr uint32_t TOGETHER = 4;                            // workers whose loads are in flight together
 constexpr uint32_t NO_WORKER = 0xFFFFFFFFu;
@@ -35,23 +39,40 @@ constexpr uint32_t NO_WORKER = 0xFFFFFFFFu;
 __device__ __forceinline__ uint32_t elements_past_line(const float* p) {
     return (uint32_t)(reinterpret_cast<uintptr_t>(p) / sizeof(float)) & (LINE - 1u);
 }
-// The lane's quad from element i of a layer of n on; i counts modulo 2^32, elements outside the layer are left alone.
-template <bool EDGE>
+// How a chunk's elements are reached.  WHOLE: all of them are the layer's.  PART: some are not (i counts modulo 2^32, elements
+// outside the layer are left alone): a lane whose quad is cut reads the layer's nearest whole quad and shifts it (settle_quad)
+// once all loads have been requested; ONES: layers of fewer elements than a quad.
+enum ChunkForm { WHOLE, PART, ONES };
+template <ChunkForm FORM>
 __device__ __forceinline__ void chunk_load(const float* p, uint32_t i, uint32_t n, float (&v)[4]) {
-    if (!EDGE) {
-        const v4f t = load_v4<true>(p + i);
-        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-    } else {
+    if (FORM == ONES) {
 #pragma unroll
         for (uint32_t c = 0; c < VEC; ++c) {
             const uint32_t e = i + c;
             if (e < n) v[c] = p[e];
         }
+        return;
+    }
+    const int at = FORM == WHOLE ? (int)i : min(max((int)i, 0), (int)(n - VEC));
+    if (FORM == WHOLE || i < n || i + (VEC - 1u) < n) {
+        const v4f t = load_v4<true>(p + at);
+        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     }
 }
-template <bool EDGE>
+template <ChunkForm FORM>
+__device__ __forceinline__ void settle_quad(uint32_t i, uint32_t n, float (&v)[4]) {
+    if (FORM != PART) return;
+    const int by = (int)i - min(max((int)i, 0), (int)(n - VEC));    // v[c] is to be what v[c + by] is
+    if (by == 0) return;
+    const float t[4] = {v[0], v[1], v[2], v[3]};
+#pragma unroll
+    for (int c = 0; c < (int)VEC; ++c)
+#pragma unroll
+        for (int k = 0; k < (int)VEC; ++k) v[c] = c + by == k ? t[k] : v[c];
+}
+template <ChunkForm FORM>
 __device__ __forceinline__ void chunk_store(float* p, uint32_t i, uint32_t n, const float (&v)[4]) {
-    if (!EDGE) {
+    if (FORM == WHOLE || (FORM == PART && i < n && n - i >= VEC)) {
         v4f t; t.x = v[0]; t.y = v[1]; t.z = v[2]; t.w = v[3];
         store_v4<true>(p + i, t);
     } else {
@@ -82,7 +103,7 @@ __device__ __forceinline__ void layer_chunk(const DevLayer& L, uint32_t c, uint3
 // lane's bits of sent elements and the position of the first of them among the pairs.  special.is(p): a worker that does not
 // stream the layer though it may have a gradient; special.take(p, bits, pos, i, r, v): its values there.  exchange: the sent
 // positions are cleared, and done(bits, pos, acc) gets the ordered sums.
-template <bool EDGE, class Sent, class Special, class Done>
+template <ChunkForm FORM, class Sent, class Special, class Done>
 __device__ __forceinline__ void follow_chunk(const WorkerPtrs& P, uint64_t offset, uint32_t n, uint32_t W, uint32_t i,
                                              bool exchange, Sent sent, Special special, Done done) {
     float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -93,8 +114,8 @@ __device__ __forceinline__ void follow_chunk(const WorkerPtrs& P, uint64_t offse
         for (uint32_t q = 0; q < TOGETHER; ++q) {
             const uint32_t p = p0 + q;
             if (p < W && P.g[p] && !special.is(p)) {
-                chunk_load<EDGE>(P.r[p] + offset, i, n, rv[q]);
-                chunk_load<EDGE>(P.g[p] + offset, i, n, gv[q]);
+                chunk_load<FORM>(P.r[p] + offset, i, n, rv[q]);
+                chunk_load<FORM>(P.g[p] + offset, i, n, gv[q]);
             }
         }
         if (p0 == 0) sent(bits, pos);
@@ -108,12 +129,14 @@ __device__ __forceinline__ void follow_chunk(const WorkerPtrs& P, uint64_t offse
             if (special.is(p)) {
                 if (bits) special.take(p, bits, pos, i, r, v);
             } else if (P.g[p]) {
+                settle_quad<FORM>(i, n, rv[q]);
+                settle_quad<FORM>(i, n, gv[q]);
 #pragma unroll
                 for (uint32_t c = 0; c < VEC; ++c) {
                     v[c] = accum(rv[q][c], gv[q][c], P.momentum);
                     rv[q][c] = (cut >> c) & 1u ? 0.0f : v[c];
                 }
-                chunk_store<EDGE>(r, i, n, rv[q]);
+                chunk_store<FORM>(r, i, n, rv[q]);
             } else if (cut) {                               // holds a residual and does not stream: only what is sent
 #pragma unroll
                 for (uint32_t c = 0; c < VEC; ++c)
@@ -194,8 +217,9 @@ __global__ __launch_bounds__(BLOCK) void k_follow_sum(WorkerPtrs P, uint32_t ali
                     wl[i + c] = wl[i + c] + u;               // ... then rounded sum
                 }
         };
-        if (whole) follow_chunk<false>(P, L.offset, L.n, W, i, true, sent, special, done);
-        else follow_chunk<true>(P, L.offset, L.n, W, i, true, sent, special, done);
+        if (whole) follow_chunk<WHOLE>(P, L.offset, L.n, W, i, true, sent, special, done);
+        else if (L.n >= VEC) follow_chunk<PART>(P, L.offset, L.n, W, i, true, sent, special, done);
+        else follow_chunk<ONES>(P, L.offset, L.n, W, i, true, sent, special, done);
     });
 }
 
@@ -284,8 +308,9 @@ __global__ __launch_bounds__(BLOCK) void k_follow_mask_sum(WorkerPtrs P, uint32_
                     wl[i + q] = wl[i + q] + u;
                 }
         };
-        if (whole) follow_chunk<false>(P, L.offset, L.n, W, i, exchange, sent, special, done);
-        else follow_chunk<true>(P, L.offset, L.n, W, i, exchange, sent, special, done);
+        if (whole) follow_chunk<WHOLE>(P, L.offset, L.n, W, i, exchange, sent, special, done);
+        else if (L.n >= VEC) follow_chunk<PART>(P, L.offset, L.n, W, i, exchange, sent, special, done);
+        else follow_chunk<ONES>(P, L.offset, L.n, W, i, exchange, sent, special, done);
     });
 }
 
