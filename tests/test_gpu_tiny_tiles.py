@@ -1,11 +1,11 @@
-"""GPU parity of the threshold modes where a layer ends within a tile's first chunk of 1024 elements (such tiles take a shorter
+"""GPU parity of the threshold modes, and of the three-call route, where a layer ends within a tile's first chunk of 1024 elements (such tiles take a shorter
 path): on the edge and one element to either side, as a layer's only tile and as its last, at every alignment."""
 import numpy as np
 import pytest
 
 import oracle
 from paper_1901_01544_amd import workloads as wl
-from harness import ThresholdSet, bits
+from harness import GpuSet, ThresholdSet, assert_step_equal, bits
 
 pytestmark = pytest.mark.gpu
 SIZES = [1, 3, 55, 1020, 1023, 1024, 1025, 1027, 2048, 4095, 4096, 4097, 4096 + 1023, 4096 + 1024, 4096 + 1025, 8192 + 5]
@@ -44,3 +44,18 @@ def test_layers_around_the_first_chunk(gpu_lib, start, mode):
         assert np.array_equal(bits(got["sum"][:n]), bits(total)) and np.array_equal(bits(got["w"]), bits(w_ref)), tag
         for p in range(W):
             assert np.array_equal(bits(got["r"][p]), bits(r_ref[p])), "%s residual %d" % (tag, p)
+
+
+@pytest.mark.parametrize("start", [0, 1, 2, 3])
+def test_three_calls_around_the_first_chunk(gpu_lib, start):
+    W = 3
+    ps = wl.custom_set([(n, (n + 3) // 4) for n in SIZES], W=W, seed=start + 1, align=1, start=start, zero_frac=0.01)
+    w = wl.gen_weights(ps)
+    sets = [wl.gen_gradient(ps, s) for s in range(W)]
+    gs = GpuSet(gpu_lib, ps, w.copy(), sets, fused=False, hint="none")
+    r_ref = [np.zeros(ps.flat, np.float32) for _ in range(W)]
+    for t in range(2):
+        ids, lead = [(p + t) % W for p in range(W)], wl.leaders(ps, t)
+        ref = oracle.step(w, [sets[i] for i in ids], r_ref, ps.rows(), lead, float(ps.eps), float(ps.scale))
+        gs.step(ids, lead)
+        assert_step_equal(gs.download(), w, r_ref, *ref, ps.layers, tag="step %d" % t)
