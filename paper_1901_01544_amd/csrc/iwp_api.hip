@@ -119,6 +119,8 @@ inline uint32_t slot_cap_of(uint32_t n, uint32_t k) {
 // the smaller ones of its kind.
 inline uint32_t roomy(uint32_t slot_cap) { return slot_cap ? std::min<uint32_t>(TILE, slot_cap + LOOK_TWICE_ROOM) : 0u; }
 inline uint64_t roomy_reserve(uint64_t tiles) { return std::min<uint64_t>(tiles, LOOK_TWICE_TILES_MANY) * LOOK_TWICE_ROOM; }
+// Likewise for the records of their tiles.
+inline uint32_t record_reserve(uint64_t tiles) { return (uint32_t)std::min<uint64_t>(tiles, LOOK_TWICE_TILES_MANY); }
 inline bool looks_twice(uint64_t tiles, uint32_t n_layers) {
     return tiles <= LOOK_TWICE_TILES || (tiles <= LOOK_TWICE_TILES_MANY && n_layers >= LOOK_TWICE_MANY);
 }
@@ -148,11 +150,26 @@ inline uint32_t h0_copies_of(uint32_t n, uint32_t k, uint32_t flushes = FLUSHES_
     return c;
 }
 
+// Units (see tie_record) of a layer, and how many of their records do not fit into its first-digit histograms.
+inline uint32_t records_apart(uint32_t n, uint32_t k, uint32_t copies, bool per_tile) {
+    const uint32_t units = k == 0 ? 0u : per_tile ? tiles_of(n) : stiles_of(n), inside = records_inside(copies);
+    return units > inside ? units - inside : 0u;
+}
+// Plans whose slots hold at most RECORD_MAX_CAP entries (an eighth of the elements kept) and whose layers at most RECORD_MAX_STILES
+// super-tiles go by records.  Fuller slots are read twice by k_split: 25 M elements kept at 0.1 gain 0 to 1 %, small tables still 8.  Longer
+// layers have every workgroup add up thousands of records; with a launch that does so once, 400 M elements kept at 1/1000
+// took 107 us where k_count, k_scan and k_write take 75.
+constexpr uint32_t RECORD_MAX_CAP = 64 + 3 * TILE / 8, RECORD_MAX_STILES = 4096;
+inline bool goes_by_records(uint32_t max_cap, uint32_t max_stiles) {
+    return max_cap <= RECORD_MAX_CAP && max_stiles <= RECORD_MAX_STILES;
+}
+
 struct Sizes {                // everything the workspace layout depends on
     uint32_t n_layers, tiles, stiles;
     uint64_t pairs, slots;    // slots: staging entries over all tiles
     uint64_t mask_words;      // 32-bit words of all layers' encoded masks (threshold mode)
     uint64_t hist_words;      // words of all layers' histograms
+    uint64_t records;         // units' records outside the histograms (see tie_record)
     uint32_t W_gather;        // rows of the gather matrix (whole-step entry point), else 0
 };
 
@@ -166,6 +183,7 @@ struct Workspace {
     uint2* tile_counts;       // tiles
     uint2* stile_counts;      // stiles
     uint32_t* tile_out;       // tiles
+    uint32_t* records;        // RECORD_WORDS each
     StageArrays A;            // `slots` entries each
     float* gathered;          // W_gather * pairs
     size_t bytes;
@@ -186,6 +204,7 @@ Workspace carve(void* base, const Sizes& z) {
     ws.tile_counts = reinterpret_cast<uint2*>(take((size_t)z.tiles * sizeof(uint2)));
     ws.stile_counts = reinterpret_cast<uint2*>(take((size_t)z.stiles * sizeof(uint2)));
     ws.tile_out = reinterpret_cast<uint32_t*>(take((size_t)z.tiles * sizeof(uint32_t)));
+    ws.records = reinterpret_cast<uint32_t*>(take(z.records * RECORD_WORDS * sizeof(uint32_t)));
     ws.A.key = reinterpret_cast<uint32_t*>(take(z.slots * sizeof(uint32_t)));
     ws.A.idx = reinterpret_cast<uint32_t*>(take(z.slots * sizeof(uint32_t)));
     ws.A.val = reinterpret_cast<float*>(take(z.slots * sizeof(float)));
@@ -201,6 +220,8 @@ struct Table {                // what the launches need to know about a layer ta
     bool any_k;
     uint32_t max_layer_stiles;   // super-tiles of the longest layer
     uint32_t max_copies;         // copies of its first-digit histogram
+    bool look_twice;             // roomy slots, no sampled mark (LOOK_TWICE_TILES)
+    bool by_records;             // the split goes by the units' records
 };
 
 // Up to this many super-tiles per layer (128 Mi elements) k_write adds up the earlier super-tiles'
@@ -281,6 +302,24 @@ int launch_write(const Table& T, const Workspace& ws, const ResidualPtrs& R, con
     return IWP_OK;
 }
 
+template <bool FUSED>
+int launch_split(const Table& T, const Workspace& ws, const ResidualPtrs& R, const float* w, const uint32_t* leader,
+                 uint32_t W, float eps, iwp_threshold* thr_out, uint32_t* idx_out, float* val_out, hipStream_t s) {
+    const uint32_t* units = reinterpret_cast<const uint32_t*>(ws.tile_counts);
+    float* gathered = FUSED ? ws.gathered : nullptr;
+#define IWP_SPLIT(BEFORE)                                                                                                        \
+    IWP_LAUNCH_BLOCK("k_split", (k_split<FUSED, BEFORE>), T.stiles, SPLIT_BLOCK, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, \
+                     eps, ws.state, ws.hist, units, ws.records, ws.stage, ws.A, thr_out, ws.tile_out, idx_out,    \
+                     val_out, gathered, T.pairs)
+    if (T.look_twice) {
+        IWP_SPLIT(SPLIT_TILES);
+    } else {
+        IWP_SPLIT(SPLIT_STILES);
+    }
+#undef IWP_SPLIT
+    return IWP_OK;
+}
+
 // Selection on the leaders' residuals after look 1 has filled the first-digit
 // histograms, then (FULL) the ordered split.  fused: whole-step route (leader row
 // of the gather matrix, leader residual cleared).
@@ -313,14 +352,24 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
         IWP_LAUNCH("k_stage", k_stage<false>, stage_grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
                    ws.hist, ws.stage, ws.A);
     const uint32_t stile_grid = std::min<uint32_t>(T.stiles, STILE_MAX_GRID);
-    if (looks_twice(T.tiles, T.n_layers))
-        IWP_LAUNCH("k_refine_tiles", k_refine_tiles, T.tiles, s, R, w, T.layers, T.n_layers, leader, W, eps, ws.state, ws.stage, ws.A,
-                   ws.hist);
-    else
-        IWP_LAUNCH("k_refine2", k_refine2, stile_grid, s, R, w, T.layers, T.n_layers, T.tiles, T.stiles, leader, W, eps, ws.state,
-                   ws.stage, ws.A, ws.hist);
+    const bool record = T.by_records && stop == FULL;
+    uint32_t* units = reinterpret_cast<uint32_t*>(ws.tile_counts);       // a word per tile or super-tile
+#define IWP_REFINE(RECORD)                                                                                                       \
+    do {                                                                                                                         \
+        if (T.look_twice)                                                                                                        \
+            IWP_LAUNCH("k_refine_tiles", k_refine_tiles<RECORD>, T.tiles, s, R, w, T.layers, T.n_layers, leader, W, eps, ws.state, \
+                       ws.stage, ws.A, ws.hist, units, ws.records);                                                              \
+        else                                                                                                                     \
+            IWP_LAUNCH("k_refine2", k_refine2<RECORD>, stile_grid, s, R, w, T.layers, T.n_layers, T.tiles, T.stiles, leader, W,  \
+                       eps, ws.state, ws.stage, ws.A, ws.hist, units, ws.records);                                               \
+    } while (0)
+    if (record) IWP_REFINE(true);
+    else IWP_REFINE(false);
+#undef IWP_REFINE
+    if (record) return fused ? launch_split<true>(T, ws, R, w, leader, W, eps, thr_out, idx_out, val_out, s)
+                             : launch_split<false>(T, ws, R, w, leader, W, eps, thr_out, idx_out, val_out, s);
     if (stop == STOP_AT_THRESHOLD) {
-        IWP_LAUNCH("k_final_pick", k_final_pick, T.n_layers, s, T.layers, ws.hist, ws.state, thr_out);
+        IWP_LAUNCH_BLOCK("k_final_pick", k_final_pick, T.n_layers, WAVE, s, T.layers, ws.hist, ws.state, thr_out);
         return IWP_OK;
     }
     IWP_LAUNCH("k_count", k_count, stile_grid, s, R, w, T.layers, T.n_layers, T.tiles, T.stiles, leader, W, eps, ws.state,
@@ -396,6 +445,7 @@ struct iwp_plan {
     uint32_t n_long = 0;          // layers of more than one tile
     bool all_dense = true;        // each of those keeps at least one element in HINT_KEEP
     bool look_twice = false;      // roomy slots; marks by samples only where samples() says so (LOOK_TWICE_TILES)
+    bool by_records = false;      // the split goes by the units' records
     uint32_t max_copies = 1;      // most copies of a layer's first-digit histogram
     float momentum = 1.0f;        // r <- momentum * r + g in every call that accumulates through this plan
 };
@@ -428,6 +478,11 @@ bool samples(const iwp_plan& plan, bool hinted) {
     return !plan.look_twice || (!hinted && plan.momentum == 1.0f);
 }
 
+static Table table_of(const iwp_plan& p) {
+    return Table{p.dev, p.z.n_layers, p.z.tiles, p.z.stiles, p.z.pairs, p.any_k, p.max_layer_stiles, p.max_copies, p.look_twice,
+                 p.by_records};
+}
+
 extern "C" {
 
 const char* iwp_strerror(int code) {
@@ -452,6 +507,7 @@ static Sizes single_sizes(uint32_t n, uint32_t k) {
     z.n_layers = 1; z.tiles = tiles_of(n); z.stiles = stiles_of(n);
     z.pairs = k; z.slots = (uint64_t)z.tiles * slot_cap_of(n, k) + (k ? roomy_reserve(z.tiles) : 0u); z.mask_words = ((uint64_t)n + 31) / 32;
     z.hist_words = layer_hist_words(h0_copies_of(n, k));
+    z.records = k ? std::max(records_apart(n, k, h0_copies_of(n, k), looks_twice(z.tiles, 1)), record_reserve(z.tiles)) : 0u;
     z.W_gather = 0;
     return z;
 }
@@ -488,9 +544,9 @@ static int single_common(SingleOp op, const float* w, const float* g, float* r, 
     DevLayer row, sentinel;
     memset(&row, 0, sizeof row);
     memset(&sentinel, 0, sizeof sentinel);
-    row.n = n; row.k = k; row.slot_cap = looks_twice(z.tiles, 1) ? roomy(slot_cap_of(n, k)) : slot_cap_of(n, k);
+    row.n = n; row.k = k; row.slot_cap = (uint16_t)(looks_twice(z.tiles, 1) ? roomy(slot_cap_of(n, k)) : slot_cap_of(n, k));
     row.sample = sample_of(n, k);
-    row.hist_begin = 0; row.h0_copies = h0_copies_of(n, k);
+    row.hist_begin = 0; row.h0_copies = (uint16_t)h0_copies_of(n, k);
     sentinel.tile_begin = z.tiles; sentinel.stile_begin = z.stiles; sentinel.out_offset = k;
     if (op != OP_COMPACT && k > 0 && n <= SMALL_MAX_N)
         return launch_small(nullptr, &row, 1u, 1u, n, k, ws, P, w, nullptr, 1u, eps, op == OP_SELECT ? STOP_AT_THRESHOLD : FULL,
@@ -499,7 +555,8 @@ static int single_common(SingleOp op, const float* w, const float* g, float* r, 
     if (op == OP_COMPACT || k == 0 || looks_twice(z.tiles, 1)) S.on = 0;
     int rc = launch_init(ws, 1, z.tiles, nullptr, nullptr, &row, &sentinel, S, s);
     if (rc) return rc;
-    Table T{ws.single_table, 1, z.tiles, z.stiles, k, k > 0, z.stiles, row.h0_copies};
+    const Table T{ws.single_table, 1, z.tiles, z.stiles, k, k > 0, z.stiles, row.h0_copies, looks_twice(z.tiles, 1),
+                  goes_by_records(slot_cap_of(n, k), z.stiles)};
     if (op == OP_COMPACT) return run_compact_from(T, ws, R, w, eps, from_thr, idx_out, val_out, s);
     if (k > 0) {
         rc = launch_leader_pass(T, ws, P, w, nullptr, 1u, eps, s);
@@ -579,7 +636,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     std::vector<DevLayer> dev(n_layers + 1);
     uint64_t pairs = 0, slots = 0, tiles = 0, stiles = 0, end = 0, mask_words = 0;
     bool any_k = false, all_k = true;
-    uint32_t max_stiles = 0, max_n = 0, n_long = 0;
+    uint32_t max_stiles = 0, max_n = 0, n_long = 0, max_cap = 0;
     bool all_dense = true;
     for (uint32_t j = 0; j < n_layers; ++j) {
         const iwp_layer& L = layers[j];
@@ -596,7 +653,8 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
         D.out_offset = L.out_offset;
         D.tile_begin = (uint32_t)tiles;
         D.stile_begin = (uint32_t)stiles;
-        D.slot_cap = slot_cap_of(L.n, L.k);
+        D.slot_cap = (uint16_t)slot_cap_of(L.n, L.k);
+        max_cap = std::max<uint32_t>(max_cap, D.slot_cap);
         D.mask_begin = (uint32_t)mask_words;
         D.sample = sample_of(L.n, L.k);
         end = (uint64_t)L.offset + L.n;
@@ -618,10 +676,19 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
         uint64_t words = 0;
         for (uint32_t j = 0; j < n_layers; ++j) {
             dev[j].hist_begin = (uint32_t)words;
-            dev[j].h0_copies = h0_copies_of(layers[j].n, layers[j].k, flushes);
+            dev[j].h0_copies = (uint16_t)h0_copies_of(layers[j].n, layers[j].k, flushes);
             words += layer_hist_words(dev[j].h0_copies);
         }
         return words;
+    };
+    // the records that do not fit there, behind one another -> their number
+    auto lay_out_records = [&](bool per_tile) {
+        uint64_t records = 0;
+        for (uint32_t j = 0; j < n_layers; ++j) {
+            dev[j].record_begin = (uint32_t)records;
+            records += records_apart(layers[j].n, layers[j].k, dev[j].h0_copies, per_tile);
+        }
+        return records;
     };
     uint64_t hist_words = lay_out_histograms(FLUSHES_PER_COPY);
     if (hist_words > 0xFFFFFFFFull) hist_words = lay_out_histograms(FLUSHES_PER_COPY_FEW);      // hist_begin holds 32 bits
@@ -635,7 +702,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     iwp_plan* plan = new (std::nothrow) iwp_plan;
     if (!plan) return IWP_EINVAL;
     plan->rows.assign(layers, layers + n_layers);
-    plan->z = Sizes{n_layers, (uint32_t)tiles, (uint32_t)stiles, pairs, slots, mask_words, hist_words, 0};
+    plan->z = Sizes{n_layers, (uint32_t)tiles, (uint32_t)stiles, pairs, slots, mask_words, hist_words, 0, 0};
     plan->any_k = any_k;
     plan->all_k = all_k;
     plan->max_layer_stiles = max_stiles;
@@ -645,17 +712,20 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     // roomy slots, or what larger tables hold in reserve for them, unless the library's static scratch would no longer do
     Sizes roomier = plan->z;
     roomier.slots += any_k ? roomy_reserve(tiles) : 0u;
+    roomier.records = any_k ? std::max<uint64_t>(lay_out_records(false), record_reserve(tiles)) : 0u;
     if (carve(nullptr, roomier).bytes <= IWP_STATIC_SCRATCH_BYTES) {
         plan->z = roomier;
         plan->look_twice = looks_twice(tiles, n_layers);
+        plan->by_records = goes_by_records(max_cap, max_stiles);
     }
     if (plan->look_twice) {
         slots = 0;
         for (DevLayer& D : dev) {
             D.slot_begin = slots;
-            D.slot_cap = roomy(D.slot_cap);
+            D.slot_cap = (uint16_t)roomy(D.slot_cap);
             slots += (uint64_t)tiles_of(D.n) * D.slot_cap;
         }
+        lay_out_records(true);                               // no more than the reserve: the table has no more tiles
     }
     if (carve(nullptr, plan->z).bytes > IWP_STATIC_SCRATCH_BYTES) {
         Sizes few = plan->z;
@@ -667,7 +737,14 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
             lay_out_histograms(FLUSHES_PER_COPY_FEW);
         }
     }
-    for (const DevLayer& D : dev) plan->max_copies = std::max(plan->max_copies, D.h0_copies);
+    // the records, unless a plan that the static scratch holds without them would no longer fit
+    if (!plan->by_records && goes_by_records(max_cap, max_stiles)) {
+        Sizes with = plan->z;
+        with.records = lay_out_records(false);
+        plan->by_records = carve(nullptr, with).bytes <= IWP_STATIC_SCRATCH_BYTES || carve(nullptr, plan->z).bytes > IWP_STATIC_SCRATCH_BYTES;
+        if (plan->by_records) plan->z = with;
+    }
+    for (const DevLayer& D : dev) plan->max_copies = std::max<uint32_t>(plan->max_copies, D.h0_copies);
     plan->flat_end = end;
     for (const iwp_layer& row : plan->rows) plan->elements += row.n;
     // the table, then the layer of every tile and of every super-tile (layer_of_tile and layer_of_stile read them)
@@ -769,7 +846,7 @@ static int compress_segmented_on(const iwp_plan* plan, const float* w, const flo
     if (rc) return rc;
     if (plan->z.tiles == 0) return IWP_OK;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    Table T{plan->dev, plan->z.n_layers, plan->z.tiles, plan->z.stiles, plan->z.pairs, plan->any_k, plan->max_layer_stiles, plan->max_copies};
+    const Table T = table_of(*plan);
     const bool small = T.any_k && takes_small(*plan, thr_hint != nullptr, false);
     if (small) {
         rc = launch_small(T.layers, nullptr, T.n_layers, plan->n_long, plan->max_n, T.pairs, ws, P, w, leader, W, eps, FULL, false, idx_out,
@@ -829,7 +906,7 @@ int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, fl
     if (rc) return rc;
     if (z.tiles == 0) return IWP_OK;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    Table T{plan->dev, z.n_layers, z.tiles, z.stiles, z.pairs, plan->any_k, plan->max_layer_stiles, plan->max_copies};
+    const Table T = table_of(*plan);
     if (T.any_k && takes_small(*plan, thr_hint != nullptr, false)) {
         rc = launch_small(T.layers, nullptr, T.n_layers, plan->n_long, plan->max_n, T.pairs, ws, P, w, leader, W, eps, FULL, true, idx_out,
                           val_out, thr_out, s);
@@ -892,7 +969,7 @@ int select_threshold_segmented(const iwp_plan* plan, const float* w, const float
     ResidualPtrs R;
     memset(&R, 0, sizeof R);
     R.r[0] = const_cast<float*>(r);
-    Table T{plan->dev, plan->z.n_layers, plan->z.tiles, plan->z.stiles, plan->z.pairs, plan->any_k, plan->max_layer_stiles, plan->max_copies};
+    const Table T = table_of(*plan);
     rc = launch_leader_pass(T, ws, P, w, nullptr, 1u, eps, s);
     if (rc) return rc;
     return run_select(T, ws, R, w, nullptr, 1u, eps, STOP_AT_THRESHOLD, false, nullptr, nullptr, thr_out, s);
@@ -913,7 +990,7 @@ int compact_pairs_segmented(const iwp_plan* plan, const float* w, const float* r
     ResidualPtrs R;
     memset(&R, 0, sizeof R);
     R.r[0] = const_cast<float*>(r);
-    Table T{plan->dev, plan->z.n_layers, plan->z.tiles, plan->z.stiles, plan->z.pairs, plan->any_k, plan->max_layer_stiles, plan->max_copies};
+    const Table T = table_of(*plan);
     return run_compact_from(T, ws, R, w, eps, thr, idx_out, val_out, s);
 }
 

@@ -78,7 +78,7 @@ __device__ __forceinline__ uint32_t staged_entries(uint32_t stage_count) {
 constexpr uint32_t NO_STAGE_BIN = 0xFFFFFFFFu;    // LayerState.stage_bin: look 1 stages nothing for this layer
 constexpr uint32_t NOT_AN_ELEMENT = 0xFFFFFFFFu;  // key slot of a lane position past the layer's end
 
-struct DevLayer {
+struct alignas(64) DevLayer {      // a cache line's half: one scalar load
     uint64_t offset;       // first element in the flat buffers
     uint64_t slot_begin;   // first entry of the layer's first tile slot in the staging arrays
     uint32_t n;
@@ -86,12 +86,14 @@ struct DevLayer {
     uint32_t out_offset;   // first pair in idx_out / val_out
     uint32_t tile_begin;   // first TILE of the layer in the per-worker tile numbering
     uint32_t stile_begin;  // first STILE of the layer
-    uint32_t slot_cap;     // staging entries per tile of this layer
+    uint16_t slot_cap;     // staging entries per tile of this layer
+    uint16_t h0_copies;    // copies of the first-digit histogram (a power of two)
     uint32_t mask_begin;   // first 32-bit word of the layer's encoded mask (threshold mode)
     uint32_t hist_begin;   // first word of the layer's histograms
-    uint32_t h0_copies;    // copies of the first-digit histogram (a power of two)
     uint32_t sample;       // how k_init samples the layer: rank - 1 in the low half, runs in the high half
+    uint32_t record_begin; // first of the layer's records outside its histograms (see tie_record)
 };
+static_assert(TILE <= 0xFFFF && MAX_H0_COPIES <= 0xFFFF, "16-bit fields of DevLayer");
 
 // Where digit `level`'s histogram of a layer starts (level 0: the first copy).
 __device__ __forceinline__ uint32_t* layer_hist(uint32_t* hist, const DevLayer& L, int level) {
@@ -100,6 +102,19 @@ __device__ __forceinline__ uint32_t* layer_hist(uint32_t* hist, const DevLayer& 
 }
 __device__ __forceinline__ const uint32_t* layer_hist(const uint32_t* hist, const DevLayer& L, int level) {
     return layer_hist(const_cast<uint32_t*>(hist), L, level);
+}
+
+// What the ordered split needs to know of a unit (a tile, or a super-tile) before it can know the threshold's last digit: how many
+// of its elements lie above the threshold's 22-bit prefix, how many share it (one word, the latter in the high half), and
+// if any do, how many of those have a last digit of b or more, for every b: HIST2 counts of 16 bits (a unit holds at most
+// 32768 elements), two to a word.  A layer's records lie in its first-digit histograms, which nobody reads any more by
+// then; those that do not fit there lie apart.
+constexpr uint32_t RECORD_WORDS = HIST2 / 2;
+__host__ __device__ constexpr uint32_t records_inside(uint32_t copies) { return copies * (HIST0 / RECORD_WORDS); }
+__device__ __forceinline__ uint32_t* tie_record(uint32_t* hist, uint32_t* apart, const DevLayer& L, uint32_t unit) {
+    const uint32_t inside = records_inside(L.h0_copies);
+    return unit < inside ? hist + L.hist_begin + unit * RECORD_WORDS
+                         : apart + (size_t)(L.record_begin + unit - inside) * RECORD_WORDS;
 }
 
 struct LayerState {        // selection state of one layer, lives in the workspace.  Every field has one writer
@@ -370,6 +385,37 @@ __device__ __forceinline__ void block_pick(const uint32_t* hist, uint32_t k_rem,
     __syncthreads();
     *bin_out = sh[WAVES];
     *k_rem_out = sh[WAVES + 1];
+}
+
+// The same pick by one wavefront, from a histogram in global memory that starts at a multiple of 16 bytes: no barriers, so a
+// workgroup's wavefronts each do it for themselves.  For the later digits' histograms; the first digit's is too long for it.
+template <int NB>
+__device__ __forceinline__ void wave_pick(const uint32_t* __restrict__ hist, uint32_t k_rem, uint32_t* bin_out, uint32_t* k_rem_out) {
+    constexpr int PER = NB / WAVE;
+    const uint32_t lane = threadIdx.x & (WAVE - 1);
+    uint32_t h[PER], local = 0;
+#pragma unroll
+    for (int q = 0; q < PER; q += 4) {
+        const uint4 x = reinterpret_cast<const uint4*>(hist)[(lane * PER + q) / 4];
+        h[q] = x.x; h[q + 1] = x.y; h[q + 2] = x.z; h[q + 3] = x.w;
+        local += x.x + x.y + x.z + x.w;
+    }
+    const uint32_t upto = wave_inclusive_scan(local);
+    const uint32_t incl = wave_last(upto) - upto + local, above = incl - local;
+    uint32_t acc = above, bin = 0, rest = 1;
+    bool found = false;
+#pragma unroll
+    for (int q = PER - 1; q >= 0; --q) {
+        const bool here = !found && acc + h[q] >= k_rem;
+        bin = here ? lane * PER + q : bin;
+        rest = here ? k_rem - acc : rest;
+        found = found || here;
+        acc += h[q];
+    }
+    const uint64_t hit = __ballot(above < k_rem && k_rem <= incl);         // one lane, if sum(hist) >= k_rem >= 1
+    const uint32_t src = hit ? (uint32_t)__ffsll((unsigned long long)hit) - 1u : 0u;
+    *bin_out = from_lane(bin, src);
+    *k_rem_out = from_lane(rest, src);
 }
 
 // One bit per element of a tile.  prefix[w] = number of set bits in words < w.

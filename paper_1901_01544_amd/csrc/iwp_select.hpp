@@ -11,20 +11,22 @@
 // second digit of those inside b1; otherwise it reads the leader's residual and weights once
 // more and copies out the elements whose top digit is >= b1 (above b1 all of them are kept, the
 // threshold lies among those inside).  Everything after that works on the staged
-// copies, a few percent of the layer: k_refine2 (on small tables k_refine_tiles) histograms the third digit, k_count /
-// k_write place every kept element at its rank in index order.  A tile whose
+// copies, a few percent of the layer: k_refine2 (on small tables k_refine_tiles) histograms the third digit, k_split, or k_count and
+// k_write where slots are full or a layer is very long, place every kept element at its rank in index order.  A tile whose
 // candidates do not fit its slot (heavy ties, e.g. a tile that is all zeros) is marked
 // RAW and is simply re-read from r and w by the later passes (on small tables by one of them, see k_refine_tiles).  Both
 // routes are exact.
 //
 // The second and third digit picks have no launches of their own: a finished histogram is
 // the same for every reader, so each workgroup of the consuming kernel redoes the pick of its
-// layer in its prologue (k_refine2 or k_refine_tiles the second, k_count the third), and one elected workgroup
+// layer in its prologue (k_refine2 or k_refine_tiles the second, k_split or k_count the third), and one elected workgroup
 // per layer records it.  Likewise
-// k_write sums the counts of the layer's earlier super-tiles itself unless a layer has so
+// k_split and k_write sum the counts of the layer's earlier super-tiles themselves unless a layer has so
 // many that a scan launch (k_scan) is cheaper.  Kernel boundaries are the only
 // synchronisation between workgroups.
 #pragma once
+
+#include <type_traits>
 
 #include "iwp_common.hpp"
 
@@ -258,15 +260,14 @@ __global__ __launch_bounds__(PICK_BLOCK) void k_first_pick(const DevLayer* __res
 // Last digit pick on its own, one workgroup per layer, for the call that stops at the
 // threshold (select_threshold): the exact k-th largest key and the number of ties to keep.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_final_pick(const DevLayer* __restrict__ layers, const uint32_t* __restrict__ hist,
+__global__ __launch_bounds__(WAVE) void k_final_pick(const DevLayer* __restrict__ layers, const uint32_t* __restrict__ hist,
                                                       LayerState* __restrict__ state, iwp_threshold* __restrict__ thr_out) {
-    __shared__ uint32_t sh[PICK_WORDS];
     const uint32_t j = blockIdx.x;
     const DevLayer L = layers[j];
     if (L.k == 0) return;
     const uint32_t p22 = state[j].p22, k_rem1 = state[j].k_rem1;
     uint32_t bin, k_rem;
-    block_pick<(int)HIST2>(layer_hist(hist, L, 2), k_rem1, sh, &bin, &k_rem);
+    wave_pick<(int)HIST2>(layer_hist(hist, L, 2), k_rem1, &bin, &k_rem);
     if (threadIdx.x == 0) {
         state[j].thr = (p22 << digit_bits(2)) | bin;
         state[j].n_eq_take = k_rem;
@@ -475,17 +476,39 @@ __global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __
 // tiles).  One workgroup per super-tile.
 // ---------------------------------------------------------------------------
 constexpr uint32_t STILE_MAX_GRID = 8192;          // k_refine2 / k_count: beyond this many super-tiles a workgroup takes
-                                                   // several consecutive ones (one pick, one flush for all of them)
+                                                   // several consecutive ones (one pick for all of them)
 
+// Closes a unit that holds elements with the threshold's prefix: lh (complete, synchronised) is added to the layer's third-digit
+// histogram and the unit's record is written.  Clears lh, for which the caller synchronises.  red: a word per wavefront.
+__device__ __forceinline__ void close_unit(uint32_t* lh, uint32_t* __restrict__ gh, uint32_t* __restrict__ record, uint32_t* red) {
+    static_assert(RECORD_WORDS == BLOCK, "a word of the record per thread");
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
+    const uint2 h = reinterpret_cast<const uint2*>(lh)[tid];
+    if (h.x) atomicAdd(&gh[2 * tid], h.x);
+    if (h.y) atomicAdd(&gh[2 * tid + 1], h.y);
+    reinterpret_cast<uint2*>(lh)[tid] = make_uint2(0u, 0u);
+    const uint32_t mine = h.x + h.y, upto = wave_inclusive_scan(mine), all = wave_last(upto);
+    if (lane == 0) red[wave] = all;
+    __syncthreads();
+    uint32_t from = all - upto + mine;                     // of bin 2 tid or more
+#pragma unroll
+    for (uint32_t v = 1; v < BLOCK / WAVE; ++v) from += wave < v ? red[v] : 0u;
+    record[tid] = from | (from - h.x) << 16;
+}
+
+// RECORD: what the split needs to know of every super-tile is left as well (units, records: see tie_record), so that it
+// finds the threshold itself and k_count has no launch.
+template <bool RECORD>
 __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* __restrict__ w,
                                                    const DevLayer* __restrict__ layers, uint32_t n_layers,
                                                    uint32_t tiles, uint32_t stiles,
                                                    const uint32_t* __restrict__ leader, uint32_t W,
                                                    float eps, LayerState* __restrict__ state,
                                                    const uint32_t* __restrict__ stage_cnt, StageArrays A,
-                                                   uint32_t* __restrict__ hist) {
-    __shared__ uint32_t lh[HIST2];
-    __shared__ uint32_t sh[PICK_WORDS];
+                                                   uint32_t* __restrict__ hist, uint32_t* __restrict__ units,
+                                                   uint32_t* __restrict__ records) {
+    __shared__ alignas(8) uint32_t lh[HIST2];
+    __shared__ uint32_t part[BLOCK / WAVE], red[BLOCK / WAVE];
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = wave_id();
     const uint32_t per = (stiles + gridDim.x - 1) / gridDim.x;
     const uint32_t s0 = blockIdx.x * per, s1 = min(s0 + per, stiles);
@@ -505,7 +528,7 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
             if (L.k == 0) continue;
             // second pick, redone by every workgroup of the layer, from the finished second-digit histogram
             uint32_t bin1, k_rem1;
-            block_pick<(int)HIST1>(layer_hist(hist, L, 1), state[j].k_rem0, sh, &bin1, &k_rem1);
+            wave_pick<(int)HIST1>(layer_hist(hist, L, 1), state[j].k_rem0, &bin1, &k_rem1);
             prefix = (state[j].b1 << digit_bits(1)) | bin1;                   // 22 bits
             if (s == L.stile_begin && tid == 0) {
                 state[j].p22 = prefix;
@@ -514,7 +537,7 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
             __syncthreads();                               // the flush above has read lh
             for (uint32_t b = tid; b < HIST2; b += BLOCK) lh[b] = 0u;
             __syncthreads();
-            filled = true;
+            filled = !RECORD;
         }
         if (L.k == 0) continue;
         const uint32_t ntiles = (L.n + TILE - 1) / TILE;
@@ -526,6 +549,12 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
         constexpr uint32_t MINE = GROUP / (BLOCK / WAVE);
         uint32_t cnt[MINE];
         uint32_t key[MINE][4];
+        uint32_t c = 0;                                    // above the prefix; high half: sharing it
+        auto add = [&](uint32_t k2, uint32_t n) {          // n elements of key k2 (NOT_AN_ELEMENT: none)
+            const uint32_t top = k2 >> digit_shift(1);
+            if (RECORD) c += k2 == NOT_AN_ELEMENT ? 0u : top > prefix ? n : top == prefix ? n << 16 : 0u;
+            if (k2 != NOT_AN_ELEMENT && top == prefix) atomicAdd(&lh[k2 & (HIST2 - 1)], n);
+        };
 #pragma unroll
         for (uint32_t m = 0; m < MINE; ++m) {
             const uint32_t tl = wave + m * (BLOCK / WAVE);
@@ -533,8 +562,7 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
             const uint64_t sb = L.slot_begin + (uint64_t)(lt0 + tl) * L.slot_cap;
             if (cnt[m] == UNIFORM_TILE) {                  // all keys of the tile are the slot's one entry
                 const uint32_t k0 = A.key[sb];
-                if (lane == 0 && (k0 >> digit_shift(1)) == prefix)
-                    atomicAdd(&lh[k0 & (HIST2 - 1)], min(TILE, L.n - (lt0 + tl) * TILE));
+                if (lane == 0) add(k0, min(TILE, L.n - (lt0 + tl) * TILE));
                 cnt[m] = 0u;
             }
             if (cnt[m] == RAW_TILE) cnt[m] = 0u;           // read again below
@@ -547,14 +575,9 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
 #pragma unroll
         for (uint32_t m = 0; m < MINE; ++m) {
 #pragma unroll
-            for (uint32_t q = 0; q < 4; ++q)
-                if (key[m][q] != NOT_AN_ELEMENT && (key[m][q] >> digit_shift(1)) == prefix)
-                    atomicAdd(&lh[key[m][q] & (HIST2 - 1)], 1u);
+            for (uint32_t q = 0; q < 4; ++q) add(key[m][q], 1u);
             const uint64_t sb = L.slot_begin + (uint64_t)(lt0 + wave + m * (BLOCK / WAVE)) * L.slot_cap;
-            for (uint32_t e = 4 * WAVE + lane; e < cnt[m]; e += WAVE) {        // fuller slots: the rest
-                const uint32_t k2 = A.key[sb + e];
-                if ((k2 >> digit_shift(1)) == prefix) atomicAdd(&lh[k2 & (HIST2 - 1)], 1u);
-            }
+            for (uint32_t e = 4 * WAVE + lane; e < cnt[m]; e += WAVE) add(A.key[sb + e], 1u);   // fuller slots: the rest
         }
         const uint64_t raw_tiles = __ballot(my_cnt == RAW_TILE) & 0xFFull;    // the same in every wavefront
         if (raw_tiles) {                                                       // uniform
@@ -572,10 +595,20 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const uint32_t key2 = shifted(score_key(rv[q], wv[q], eps), shift);
-                        if (i + q < L.n && (key2 >> digit_shift(1)) == prefix) atomicAdd(&lh[key2 & (HIST2 - 1)], 1u);
+                        if (i + q < L.n) add(key2, 1u);
                     }
                 }
             }
+        }
+        if (RECORD) {
+            c = wave_sum(c);                               // at most 32768 of either kind
+            if (lane == 0) part[wave] = c;
+            __syncthreads();                               // lh is complete, too
+            const uint32_t all = part[0] + part[1] + part[2] + part[3];
+            if (tid == 0) units[s] = all;
+            if (all >> 16) close_unit(lh, layer_hist(hist, L, 2), tie_record(hist, records, L, s - L.stile_begin), red);
+            filled = false;
+            if (s + 1 < s1) __syncthreads();               // part and lh are written again
         }
     }
     if (filled) {
@@ -596,15 +629,17 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
 // fits its slot nothing is gained: 2 M elements kept at 1/64 46 (42 sampled).  (Slots of 400 entries instead of 576, so that it
 // overflows: 44, but the eight values, kept at 1/64, 39 -> 74.)
 // ---------------------------------------------------------------------------
+template <bool RECORD>
 __global__ __launch_bounds__(BLOCK) void k_refine_tiles(ResidualPtrs R, const float* __restrict__ w,
                                                         const DevLayer* __restrict__ layers, uint32_t n_layers,
                                                         const uint32_t* __restrict__ leader, uint32_t W, float eps,
                                                         LayerState* __restrict__ state, uint32_t* __restrict__ stage_cnt,
-                                                        StageArrays A, uint32_t* __restrict__ hist) {
-    __shared__ uint32_t lh[HIST2];
-    __shared__ uint32_t sh[PICK_WORDS];
+                                                        StageArrays A, uint32_t* __restrict__ hist, uint32_t* __restrict__ units,
+                                                        uint32_t* __restrict__ records) {
+    __shared__ alignas(8) uint32_t lh[HIST2];
     __shared__ uint32_t slot[STAGE_WORDS];
-    const uint32_t tid = threadIdx.x, t = blockIdx.x;
+    __shared__ uint32_t part[BLOCK / WAVE], red[BLOCK / WAVE];
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), t = blockIdx.x;
     const uint32_t j = layer_of_tile(layers, n_layers, t);
     const DevLayer L = layers[j];
     if (L.k == 0) return;
@@ -617,7 +652,7 @@ __global__ __launch_bounds__(BLOCK) void k_refine_tiles(ResidualPtrs R, const fl
     if (lt % GROUP == 0 && tid < GROUP && lt + tid < (L.n + TILE - 1) / TILE && stage_cnt[t + tid] == UNIFORM_TILE)
         equal = A.key[sb + (uint64_t)tid * L.slot_cap];
     uint32_t bin1, k_rem1;
-    block_pick<(int)HIST1>(layer_hist(hist, L, 1), state[j].k_rem0, sh, &bin1, &k_rem1);
+    wave_pick<(int)HIST1>(layer_hist(hist, L, 1), state[j].k_rem0, &bin1, &k_rem1);
     const uint32_t prefix = (state[j].b1 << digit_bits(1)) | bin1;            // 22 bits
     if (lt == 0 && tid == 0) {
         state[j].p22 = prefix;
@@ -625,8 +660,11 @@ __global__ __launch_bounds__(BLOCK) void k_refine_tiles(ResidualPtrs R, const fl
     }
     for (uint32_t b = tid; b < HIST2; b += BLOCK) lh[b] = 0u;
     __syncthreads();
+    uint32_t c = 0;                                        // above the prefix; high half: sharing it
     auto add = [&](uint32_t key, uint32_t n) {
-        if (key != NOT_AN_ELEMENT && (key >> digit_shift(1)) == prefix) atomicAdd(&lh[key & (HIST2 - 1)], n);
+        const uint32_t top = key >> digit_shift(1);
+        if (RECORD) c += key == NOT_AN_ELEMENT ? 0u : top > prefix ? n : top == prefix ? n << 16 : 0u;
+        if (key != NOT_AN_ELEMENT && top == prefix) atomicAdd(&lh[key & (HIST2 - 1)], n);
     };
     if (cnt == RAW_TILE) {                                 // uniform
         uint32_t key[CHUNKS_PER_TILE][4];
@@ -642,9 +680,37 @@ __global__ __launch_bounds__(BLOCK) void k_refine_tiles(ResidualPtrs R, const fl
         add(first, 1u);
         for (uint32_t e = BLOCK + tid; e < cnt; e += BLOCK) add(A.key[sb + e], 1u);
     }
-    add(equal, min(TILE, L.n - min(base + tid * TILE, L.n)));
-    __syncthreads();
-    flush_hist<HIST2>(lh, layer_hist(hist, L, 2));
+    const uint32_t n_equal = min(TILE, L.n - min(base + tid * TILE, L.n));
+    if (!RECORD) {
+        add(equal, n_equal);
+        __syncthreads();
+        flush_hist<HIST2>(lh, layer_hist(hist, L, 2));
+        return;
+    }
+    uint32_t* gh = layer_hist(hist, L, 2);
+    uint32_t* record = tie_record(hist, records, L, lt);
+    if (tid < WAVE) {                                      // the super-tile's tiles of equal keys, key by key
+        const bool hit = equal != NOT_AN_ELEMENT && (equal >> digit_shift(1)) == prefix;
+        for (uint64_t left = __ballot(hit); left;) {
+            const uint32_t key = from_lane(equal, (uint32_t)__ffsll((unsigned long long)left) - 1u);
+            const bool same = hit && equal == key;
+            const uint32_t n = wave_sum(same ? n_equal : 0u);
+            if (lane == 0) atomicAdd(&gh[key & (HIST2 - 1)], n);
+            left &= ~__ballot(same);
+        }
+    }
+    if (cnt == UNIFORM_TILE) {                             // uniform
+        const uint32_t key = A.key[sb], top = key >> digit_shift(1), low = key & (HIST2 - 1), n = min(TILE, L.n - base);
+        if (tid == 0) units[t] = top > prefix ? n : top == prefix ? n << 16 : 0u;
+        if (top == prefix) record[tid] = (2 * tid <= low ? n : 0u) | (2 * tid + 1 <= low ? n << 16 : 0u);
+        return;
+    }
+    c = wave_sum(c);
+    if (lane == 0) part[tid >> 6] = c;
+    __syncthreads();                                       // lh is complete, too
+    const uint32_t all = part[0] + part[1] + part[2] + part[3];
+    if (tid == 0) units[t] = all;
+    if (all >> 16) close_unit(lh, gh, record, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -727,6 +793,40 @@ __global__ __launch_bounds__(BLOCK) void k_fold_counts(const DevLayer* __restric
     stile_counts[s] = make_uint2(above, ties);
 }
 
+// A RAW tile read again by one wavefront, RAW_AHEAD rounds of 256 elements in flight together, since neither k_refine_tiles nor look 2
+// has left its lines in this die's cache.  body(packed, key, val, i): the lane's four elements of a round, i the first one's position;
+// packed: of those above the threshold, in the high half of those tying with it; key[q] is NOT_AN_ELEMENT where position i + q is not
+// the lane's.  Every lane reads whole quads, at the layer's end the last one (a RAW tile has more than 64 elements), and leaves
+// out what comes before its own: loads in branches would wait for each other.
+constexpr uint32_t RAW_ROUND = WAVE * VEC, RAW_AHEAD = 4;
+template <class Body>
+__device__ __forceinline__ void read_raw_tile(const float* rl, const float* wl, uint32_t n, uint32_t first, float eps, uint32_t shift,
+                                              uint32_t thr, Body body) {
+    const uint32_t lane = threadIdx.x & (WAVE - 1);
+#pragma unroll 1
+    for (uint32_t c = 0; c < TILE && first + c < n; c += RAW_AHEAD * RAW_ROUND) {
+        v4f rv[RAW_AHEAD], wv[RAW_AHEAD];
+#pragma unroll
+        for (uint32_t a = 0; a < RAW_AHEAD; ++a) {
+            const uint32_t at = min(first + c + a * RAW_ROUND + lane * VEC, n - VEC);
+            rv[a] = load_v4<false>(rl + at);
+            wv[a] = load_v4<false>(wl + at);
+        }
+#pragma unroll
+        for (uint32_t a = 0; a < RAW_AHEAD; ++a) {
+            const uint32_t i = first + c + a * RAW_ROUND + lane * VEC, at = min(i, n - VEC);
+            const float val[4] = {rv[a].x, rv[a].y, rv[a].z, rv[a].w}, wgt[4] = {wv[a].x, wv[a].y, wv[a].z, wv[a].w};
+            uint32_t key[4], packed = 0;
+#pragma unroll
+            for (uint32_t q = 0; q < VEC; ++q) {
+                key[q] = at + q >= i ? shifted(score_key(val[q], wgt[q], eps), shift) : NOT_AN_ELEMENT;
+                packed += key[q] == NOT_AN_ELEMENT ? 0u : key[q] > thr ? 1u : key[q] == thr ? 0x10000u : 0u;
+            }
+            body(packed, key, val, at);
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Ordered split, part 1: per tile, how many elements lie above the threshold and
 // how many tie with it.  One workgroup per super-tile; writes each tile's exclusive
@@ -742,7 +842,6 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
                                                  const uint32_t* __restrict__ stage_cnt, StageArrays A,
                                                  uint2* __restrict__ tile_counts, uint2* __restrict__ stile_counts) {
     __shared__ uint32_t cg[GROUP], ce[GROUP];
-    __shared__ uint32_t sh[PICK_WORDS];
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = tid & (WAVE - 1), wave = wave_id();
     const uint32_t per = (stiles + gridDim.x - 1) / gridDim.x;
@@ -758,7 +857,7 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
             shift = state[j].shift;
             // third pick, redone by every workgroup of the layer: the exact k-th largest key
             uint32_t bin2, k_rem2;
-            block_pick<(int)HIST2>(layer_hist(hist, L, 2), state[j].k_rem1, sh, &bin2, &k_rem2);
+            wave_pick<(int)HIST2>(layer_hist(hist, L, 2), state[j].k_rem1, &bin2, &k_rem2);
             thr = (state[j].p22 << digit_bits(2)) | bin2;
             if (s == L.stile_begin && tid == 0) {
                 state[j].thr = thr;
@@ -825,29 +924,11 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
                     }
                 }
             } else {
-                // a RAW tile: several rounds of quads in flight, since neither k_refine_tiles nor look 2 has left its lines in
-                // this die's cache (one element per lane and round: 62 us for 25 tiles of eight distinct values, now 22)
-                constexpr uint32_t ROUND = WAVE * VEC, AHEAD = 2;          // elements of a round; rounds in flight together
-                const uint32_t first = (lt0 + tl) * TILE;
-#pragma unroll 1
-                for (uint32_t c = 0; c < TILE && first + c < L.n; c += AHEAD * ROUND) {
-                    float rv[AHEAD][4], wv[AHEAD][4];
-#pragma unroll
-                    for (uint32_t a = 0; a < AHEAD; ++a) {
-                        const uint32_t i = first + c + a * ROUND + lane * VEC;
-                        load_quad(rl, i, L.n, rv[a]);
-                        load_quad(wl, i, L.n, wv[a], 1.0f);
-                    }
-#pragma unroll
-                    for (uint32_t a = 0; a < AHEAD; ++a)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const uint32_t k2 = shifted(score_key(rv[a][q], wv[a][q], eps), shift);
-                            const bool inside = first + c + a * ROUND + lane * VEC + q < L.n;
-                            gt += inside && k2 > thr ? 1u : 0u;
-                            eq += inside && k2 == thr ? 1u : 0u;
-                        }
-                }
+                read_raw_tile(rl, wl, L.n, (lt0 + tl) * TILE, eps, shift, thr,
+                              [&](uint32_t packed, const uint32_t (&)[4], const float (&)[4], uint32_t) {
+                    gt += packed & 0xffffu;
+                    eq += packed >> 16;
+                });
             }
             gt = wave_sum(gt);
             eq = wave_sum(eq);
@@ -902,13 +983,34 @@ __global__ __launch_bounds__(BLOCK) void k_scan(const DevLayer* __restrict__ lay
     }
 }
 
-// The pairs of one tile, by one wavefront.  The slots being in index order saves the bitmaps in LDS that would rank
+// AHEAD times 64 consecutive entries of a tile's slot, in registers.
+template <uint32_t AHEAD>
+struct SlotPart {
+    uint32_t key[AHEAD], idx[AHEAD];
+    float val[AHEAD];
+};
+constexpr uint32_t SPLIT_AHEAD = 2, SPLIT_AHEAD_MORE = 4;    // requested before it is known what is kept of them; of fuller slots, at a time
+typedef SlotPart<SPLIT_AHEAD> SlotStart;
+// cnt: entries from `first` on.
+template <uint32_t AHEAD>
+__device__ __forceinline__ void request_slot(const StageArrays& A, uint64_t first, uint32_t cnt, SlotPart<AHEAD>& S) {
+    const uint32_t last = cnt < UNIFORM_TILE ? max(cnt, 1u) - 1u : 0u;       // lanes behind the last entry read it, or the first word
+#pragma unroll
+    for (uint32_t q = 0; q < AHEAD; ++q) {
+        const uint64_t e = first + min(q * WAVE + (threadIdx.x & (WAVE - 1)), last);
+        S.key[q] = A.key[e];
+        S.idx[q] = A.idx[e];
+        S.val[q] = A.val[e];
+    }
+}
+
+// The pairs of one tile, by one wavefront; S: its slot's first entries.  The slots being in index order saves the bitmaps in LDS that would rank
 // their entries: 8.7 -> 6.5 us a launch on a 25.6 M-element table, 59 -> 47 us on a layer of 400 M.  cnt: the tile's staged entries, UNIFORM_TILE or RAW_TILE; Gt, Et: elements
 // above the threshold / tying with it before the tile.
 template <bool FUSED>
 __device__ __forceinline__ void write_tile(const DevLayer& L, uint32_t lt, uint32_t cnt, uint32_t thr, uint32_t quota,
                                            uint32_t shift, uint32_t Gt, uint32_t Et, float* rl,
-                                           const float* __restrict__ wl, float eps, const StageArrays& A,
+                                           const float* __restrict__ wl, float eps, const StageArrays& A, SlotStart S,
                                            uint32_t* __restrict__ io, float* __restrict__ vo, float* __restrict__ go) {
     const uint32_t lane = threadIdx.x & (WAVE - 1);
     const uint32_t out_base = Gt + min(Et, quota);
@@ -935,84 +1037,60 @@ __device__ __forceinline__ void write_tile(const DevLayer& L, uint32_t lt, uint3
     }
     uint32_t G = Gt, E = Et;
     if (cnt != RAW_TILE) {
-        // a slot holds its tile's candidates in index order: 64 of them at a time (the first 128 requested before any is
-        // used), ranked by what stands before them
+        // a slot holds its tile's candidates in index order: 64 of them at a time, ranked by what stands before them
         const uint64_t sb = L.slot_begin + (uint64_t)lt * L.slot_cap;
         const uint64_t below = (1ull << lane) - 1ull;
-        constexpr uint32_t AHEAD = 2;
-        for (uint32_t e0 = 0; e0 < cnt; e0 += AHEAD * WAVE) {
-            uint32_t key[AHEAD], li[AHEAD];
-            float val[AHEAD];
+        auto write = [&](auto& part, auto ahead, uint32_t e0) {
 #pragma unroll
-            for (uint32_t q = 0; q < AHEAD; ++q) {
-                const uint32_t e = e0 + q * WAVE + lane;
-                const bool have = e < cnt;
-                key[q] = have ? A.key[sb + e] : 0u;
-                li[q] = have ? A.idx[sb + e] : 0xFFFFFFFFu;
-                val[q] = have ? A.val[sb + e] : 0.0f;
-            }
-#pragma unroll
-            for (uint32_t q = 0; q < AHEAD; ++q) {
+            for (uint32_t q = 0; q < ahead.value; ++q) {
                 const bool have = e0 + q * WAVE + lane < cnt;
-                const bool above = have && key[q] > thr, ties = have && key[q] == thr;
+                const bool above = have && part.key[q] > thr, ties = have && part.key[q] == thr;
                 const uint64_t ma = __ballot(above), mt = __ballot(ties);
                 const uint32_t gpre = G + __popcll(ma & below), epre = E + __popcll(mt & below);
                 uint32_t pos = 0xFFFFFFFFu;
                 if (above) pos = gpre + min(epre, quota);
                 else if (ties && epre < quota) pos = gpre + epre;
-                if (pos < L.k && li[q] < L.n) {
-                    io[pos] = (uint32_t)(L.offset + li[q]);
-                    vo[pos] = val[q];
-                    if (FUSED) { go[pos] = val[q]; rl[li[q]] = 0.0f; }
+                if (pos < L.k && part.idx[q] < L.n) {
+                    io[pos] = (uint32_t)(L.offset + part.idx[q]);
+                    vo[pos] = part.val[q];
+                    if (FUSED) { go[pos] = part.val[q]; rl[part.idx[q]] = 0.0f; }
                 }
                 G += __popcll(ma);
                 E += __popcll(mt);
             }
+        };
+        write(S, std::integral_constant<uint32_t, SPLIT_AHEAD>(), 0u);
+        for (uint32_t e0 = SPLIT_AHEAD * WAVE; e0 < cnt; e0 += SPLIT_AHEAD_MORE * WAVE) {
+            SlotPart<SPLIT_AHEAD_MORE> more;
+            request_slot(A, sb + e0, cnt - e0, more);
+            write(more, std::integral_constant<uint32_t, SPLIT_AHEAD_MORE>(), e0);
         }
         return;
     }
 
-    // RAW tile: every element is scored again, 256 at a time
-    for (uint32_t c = 0; c < TILE / (WAVE * VEC); ++c) {
-        const uint32_t cbase = tile_first + c * (WAVE * VEC);
-        if (cbase >= L.n) break;
-        const uint32_t i = cbase + lane * VEC;
-        float rv[4] = {0.f, 0.f, 0.f, 0.f}, wv[4] = {1.f, 1.f, 1.f, 1.f};
-        if (i < L.n) {
-            load_quad(rl, i, L.n, rv);
-            load_quad(wl, i, L.n, wv, 1.0f);
-        }
-        uint32_t key[4];
-        uint32_t packed = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            key[q] = shifted(score_key(rv[q], wv[q], eps), shift);
-            const bool valid = i + q < L.n;
-            packed += (valid && key[q] > thr) ? 1u : 0u;
-            packed += (valid && key[q] == thr) ? 0x10000u : 0u;
-        }
-        const uint32_t inc = wave_inclusive_scan(packed);
-        const uint32_t tot = wave_last(inc);
-        const uint32_t ex = inc - packed;
+    // RAW tile: every element is scored again
+    read_raw_tile(rl, wl, L.n, tile_first, eps, shift, thr,
+                  [&](uint32_t packed, const uint32_t (&key)[4], const float (&val)[4], uint32_t at) {
+        const uint32_t inc = wave_inclusive_scan(packed), tot = wave_last(inc), ex = inc - packed;
         uint32_t gpre = G + (ex & 0xffffu);
         uint32_t epre = E + (ex >> 16);
         if (packed) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (i + q >= L.n) break;
+            for (uint32_t q = 0; q < VEC; ++q) {
+                if (key[q] == NOT_AN_ELEMENT) continue;
                 uint32_t pos = 0xFFFFFFFFu;
                 if (key[q] > thr) { pos = gpre + min(epre, quota); ++gpre; }
                 else if (key[q] == thr) { if (epre < quota) pos = gpre + epre; ++epre; }
                 if (pos < L.k) {
-                    io[pos] = (uint32_t)(L.offset + i + q);
-                    vo[pos] = rv[q];
-                    if (FUSED) { go[pos] = rv[q]; rl[i + q] = 0.0f; }
+                    io[pos] = (uint32_t)(L.offset + at + q);
+                    vo[pos] = val[q];
+                    if (FUSED) { go[pos] = val[q]; rl[at + q] = 0.0f; }
                 }
             }
         }
         G += tot & 0xffffu;
         E += tot >> 16;
-    }
+    });
 }
 
 // Part 3: write the pairs.  An element above the threshold goes to position
@@ -1090,8 +1168,133 @@ __global__ __launch_bounds__(BLOCK) void k_write(ResidualPtrs R, const float* __
     float* go = FUSED ? gathered + (size_t)lead * K + L.out_offset : nullptr;
     if (lane == 0) tile_out[t] = Gt + min(Et, quota);
     const uint32_t cnt = staged_entries(stage_cnt[t]);
+    SlotStart S;
+    request_slot(A, L.slot_begin + (uint64_t)lt * L.slot_cap, cnt, S);
+    write_tile<FUSED>(L, lt, cnt, thr, quota, st.shift, Gt, Et, rl, w + L.offset, eps, A, S, io, vo, go);
+}
 
-    write_tile<FUSED>(L, lt, cnt, thr, quota, st.shift, Gt, Et, rl, w + L.offset, eps, A, io, vo, go);
+// ---------------------------------------------------------------------------
+// The ordered split where the units' records are there (see tie_record; plans whose slots hold few entries).  The threshold's last
+// digit is picked by every wavefront, so k_count has no launch.  One wavefront per tile, a super-tile per workgroup.  What
+// stands above the threshold or ties with it before the workgroup's tiles: SPLIT_TILES: added up from the records of the layer's earlier
+// tiles, SPLIT_STILES: of its earlier super-tiles, inside the workgroup's from the slots themselves.
+// Bound by its chain of dependent loads (row, counts and state, entries and histogram, records) and, where residuals are cleared,
+// by those scattered stores.  us a call, k_count and k_write / this: one layer of 1 M elements 30.1 / 26.7, six tensors of 235 k, four
+// workers 35.6 / 32.5, one worker's share of 25.6 M 146.6 / 144.9, 16 tensors of 61 M, eight workers 1142 / 1133; with kept
+// eighths instead of 64ths one layer of 1 M 59 / 54.  RECORD_MAX_CAP and RECORD_MAX_STILES (iwp_api.hip) are its lines.
+// ---------------------------------------------------------------------------
+constexpr int SPLIT_TILES = 0, SPLIT_STILES = 1;
+constexpr int SPLIT_BLOCK = GROUP * WAVE;
+
+// A unit's elements above the threshold (low half) and tying with it, from its word c.  low: the threshold's last digit.  No branch:
+// a unit without a record reads some word instead, so that a thread's loads do not wait for each other.
+typedef uint32_t u32_pair __attribute__((aligned(2)));
+__device__ __forceinline__ uint32_t unit_counts(uint32_t c, uint32_t unit, const uint32_t* hist, const uint32_t* records,
+                                                const DevLayer& L, uint32_t low) {
+    const uint32_t* record = tie_record(const_cast<uint32_t*>(hist), const_cast<uint32_t*>(records), L, unit);
+    // with the last digit of all, the upper half comes from the word behind the record (the workspace goes on there)
+    const uint32_t two = *reinterpret_cast<const u32_pair*>(reinterpret_cast<const uint16_t*>(c >> 16 ? record : hist) + low);
+    const uint32_t more = low + 1 < HIST2 ? two >> 16 : 0u;
+    return (c & 0xffffu) + (c >> 16 ? more + (((two & 0xffffu) - more) << 16) : 0u);
+}
+
+template <bool FUSED, int BEFORE>
+__global__ __launch_bounds__(SPLIT_BLOCK) void k_split(ResidualPtrs R, const float* __restrict__ w,
+                                                       const DevLayer* __restrict__ layers, uint32_t n_layers, uint32_t tiles,
+                                                       const uint32_t* __restrict__ leader, uint32_t W, float eps,
+                                                       const LayerState* __restrict__ state, const uint32_t* __restrict__ hist,
+                                                       const uint32_t* __restrict__ units, const uint32_t* __restrict__ records,
+                                                       const uint32_t* __restrict__ stage_cnt, StageArrays A,
+                                                       iwp_threshold* __restrict__ thr_out, uint32_t* __restrict__ tile_out,
+                                                       uint32_t* __restrict__ idx_out, float* __restrict__ val_out,
+                                                       float* __restrict__ gathered, uint64_t K) {
+    constexpr uint32_t WAVES = SPLIT_BLOCK / WAVE;
+    __shared__ uint2 red[WAVES], own[WAVES];
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = wave_id();
+    const uint32_t s = blockIdx.x;
+    const uint32_t j = layer_of_stile(layers, n_layers, tiles, s);
+    const DevLayer L = layers[j];
+    if (L.k == 0) return;
+    const uint32_t ntiles = (L.n + TILE - 1) / TILE;
+    const uint32_t lt0 = (s - L.stile_begin) * GROUP, lt = lt0 + wave;
+    const bool have = lt < ntiles;
+    const uint32_t t = L.tile_begin + lt;
+    const uint32_t cnt = have ? staged_entries(stage_cnt[t]) : 0u;
+    const uint32_t first = BEFORE == SPLIT_TILES ? L.tile_begin : L.stile_begin;
+    const uint32_t before = BEFORE == SPLIT_TILES ? lt0 : lt0 / GROUP;       // units
+    const uint32_t first_unit = tid < before ? units[first + tid] : 0u;
+    const uint64_t sb = L.slot_begin + (uint64_t)(have ? lt : lt0) * L.slot_cap;
+    SlotStart S;
+    request_slot(A, sb, cnt, S);
+    uint32_t low, quota;
+    wave_pick<(int)HIST2>(layer_hist(hist, L, 2), state[j].k_rem1, &low, &quota);
+    const uint32_t thr = (state[j].p22 << digit_bits(2)) | low, shift = state[j].shift;
+    if (lt0 == 0 && tid == 0 && thr_out) {
+        iwp_threshold th;
+        th.key = unshifted(thr, shift); th.n_gt = L.k - quota; th.n_eq_take = quota;
+        thr_out[j] = th;
+    }
+    const uint32_t lead = leader_of(leader, j, W);
+    float* rl = R.r[lead] + L.offset;
+    const float* wl = w + L.offset;
+    uint32_t g = 0, e = 0;
+    for (uint32_t u = tid; u < before; u += SPLIT_BLOCK) {
+        const uint32_t c = unit_counts(u == tid ? first_unit : units[first + u], u, hist, records, L, low);
+        g += c & 0xffffu;
+        e += c >> 16;
+    }
+    g = wave_sum(g);
+    e = wave_sum(e);
+    if (lane == 0) red[wave] = make_uint2(g, e);
+    uint32_t gt = 0, eq = 0;                                // of this tile; SPLIT_TILES: of the super-tile's earlier ones
+    if (BEFORE == SPLIT_TILES) {
+        const uint32_t c = lane < wave && lt0 + lane < ntiles
+                               ? unit_counts(units[L.tile_begin + lt0 + lane], lt0 + lane, hist, records, L, low) : 0u;
+        gt = c & 0xffffu;
+        eq = c >> 16;
+    } else if (cnt == UNIFORM_TILE) {
+        const uint32_t k0 = A.key[sb], n_tile = min(TILE, L.n - lt * TILE);
+        if (lane == 0) { gt = k0 > thr ? n_tile : 0u; eq = k0 == thr ? n_tile : 0u; }
+    } else if (cnt == RAW_TILE) {
+        read_raw_tile(rl, wl, L.n, lt * TILE, eps, shift, thr,
+                      [&](uint32_t packed, const uint32_t (&)[4], const float (&)[4], uint32_t) {
+            gt += packed & 0xffffu;
+            eq += packed >> 16;
+        });
+    } else {
+        for (uint32_t q = 0; q < SPLIT_AHEAD; ++q) {
+            const bool there = q * WAVE + lane < cnt;
+            gt += there && S.key[q] > thr ? 1u : 0u;
+            eq += there && S.key[q] == thr ? 1u : 0u;
+        }
+        for (uint32_t e0 = SPLIT_AHEAD * WAVE; e0 < cnt; e0 += 4 * WAVE) {
+            uint32_t k2[4];
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) k2[q] = e0 + q * WAVE + lane < cnt ? A.key[sb + e0 + q * WAVE + lane] : NOT_AN_ELEMENT;
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) {
+                gt += k2[q] != NOT_AN_ELEMENT && k2[q] > thr ? 1u : 0u;
+                eq += k2[q] == thr ? 1u : 0u;               // a key is never NOT_AN_ELEMENT (bit 31 is clear)
+            }
+        }
+    }
+    gt = wave_sum(gt);
+    eq = wave_sum(eq);
+    if (lane == 0) own[wave] = make_uint2(gt, eq);
+    __syncthreads();
+    uint32_t Gt = 0, Et = 0;                                // before this tile
+#pragma unroll
+    for (uint32_t v = 0; v < WAVES; ++v) { Gt += red[v].x; Et += red[v].y; }
+    if (BEFORE == SPLIT_TILES) {
+        Gt += gt; Et += eq;
+    } else {
+#pragma unroll
+        for (uint32_t v = 0; v < WAVES; ++v) { Gt += v < wave ? own[v].x : 0u; Et += v < wave ? own[v].y : 0u; }
+    }
+    if (!have) return;
+    if (lane == 0) tile_out[t] = Gt + min(Et, quota);
+    write_tile<FUSED>(L, lt, cnt, thr, quota, shift, Gt, Et, rl, wl, eps, A, S, idx_out + L.out_offset, val_out + L.out_offset,
+                      FUSED ? gathered + (size_t)lead * K + L.out_offset : nullptr);
 }
 
 // The importance keys themselves, for tests of the device arithmetic.
