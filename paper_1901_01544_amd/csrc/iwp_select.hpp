@@ -797,7 +797,8 @@ __global__ __launch_bounds__(BLOCK) void k_fold_counts(const DevLayer* __restric
 // has left its lines in this die's cache.  body(packed, key, val, i): the lane's four elements of a round, i the first one's position;
 // packed: of those above the threshold, in the high half of those tying with it; key[q] is NOT_AN_ELEMENT where position i + q is not
 // the lane's.  Every lane reads whole quads, at the layer's end the last one (a RAW tile has more than 64 elements), and leaves
-// out what comes before its own: loads in branches would wait for each other.
+// out what comes before its own: loads in branches waited for each other (a layer of 48 tiles, mostly zeros, kept at 0.2: k_count 22.2 -> 18.3 us,
+// k_write 25.1 -> 17.1).
 constexpr uint32_t RAW_ROUND = WAVE * VEC, RAW_AHEAD = 4;
 template <class Body>
 __device__ __forceinline__ void read_raw_tile(const float* rl, const float* wl, uint32_t n, uint32_t first, float eps, uint32_t shift,
@@ -989,7 +990,8 @@ struct SlotPart {
     uint32_t key[AHEAD], idx[AHEAD];
     float val[AHEAD];
 };
-constexpr uint32_t SPLIT_AHEAD = 2, SPLIT_AHEAD_MORE = 4;    // requested before it is known what is kept of them; of fuller slots, at a time
+// Requested before it is known what is kept of them; of fuller slots, at a time (2: full slots of 25 tiles 23.4 us, 4: 18.0).
+constexpr uint32_t SPLIT_AHEAD = 2, SPLIT_AHEAD_MORE = 4;
 typedef SlotPart<SPLIT_AHEAD> SlotStart;
 // cnt: entries from `first` on.
 template <uint32_t AHEAD>
