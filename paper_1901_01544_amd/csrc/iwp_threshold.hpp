@@ -13,6 +13,7 @@
 #pragma once
 
 #include "iwp_common.hpp"
+#include "iwp_exchange.hpp"
 #include "iwp_stream.hpp"
 
 namespace iwp {
@@ -539,7 +540,8 @@ __global__ __launch_bounds__(BLOCK) void k_reduce_update_counted(ResidualPtrs R,
         const uint32_t i = idx[jj];
         const bool ok = i < flat_end;
         float acc = 0.0f;
-        for (uint32_t p = 0; p < W; ++p) {
+        if (!static_mask) acc = ordered_sum(W, [&](uint32_t p) { return gathered[(size_t)p * max_pairs + jj]; });
+        for (uint32_t p = 0; static_mask && p < W; ++p) {
             float v;
             if ((direct >> p) & 1u) {
                 v = ok ? R.r[p][i] : 0.0f;
