@@ -394,21 +394,20 @@ int launch_small(const DevLayer* layers, const DevLayer* row, uint32_t n_layers,
     const bool emit = stop == FULL;
     float* gathered = fused ? ws.gathered : nullptr;
     const bool apart = max_n > TILE && n_layers > SMALL_ONE_LAUNCH && n_long < n_layers;
-#define IWP_SMALL(FUSED, THREADS, CHUNKS, FROM, TO)                                                                               \
-    IWP_LAUNCH_BLOCK("k_small", (k_small<FUSED, THREADS, CHUNKS>), n_layers, THREADS, s, P, w, layers, r, FROM, TO, leader, W, \
+#define IWP_SMALL_AS(FUSED, ONE, THREADS, CHUNKS, FROM, TO)                                                                      \
+    IWP_LAUNCH_BLOCK("k_small", (k_small<FUSED, ONE, THREADS, CHUNKS>), n_layers, THREADS, s, P, w, layers, r, FROM, TO, leader, W, \
                      eps, thr_out, emit, ws.tile_out, idx_out, val_out, gathered, pairs)
-    if (max_n <= TILE || apart) {
-        if (fused) IWP_SMALL(true, TINY_BLOCK, TINY_CHUNKS, 0u, TILE);
-        else IWP_SMALL(false, TINY_BLOCK, TINY_CHUNKS, 0u, TILE);
-    }
+#define IWP_SMALL(THREADS, CHUNKS, FROM, TO)                                                                                     \
+    do {                                                                                                                         \
+        if (fused) IWP_SMALL_AS(true, false, THREADS, CHUNKS, FROM, TO);                                                         \
+        else if (row) IWP_SMALL_AS(false, true, THREADS, CHUNKS, FROM, TO);                                                      \
+        else IWP_SMALL_AS(false, false, THREADS, CHUNKS, FROM, TO);                                                              \
+    } while (0)
+    if (max_n <= TILE || apart) IWP_SMALL(TINY_BLOCK, TINY_CHUNKS, 0u, TILE);
     const uint32_t from = apart ? TILE + 1 : 0u;
-    if (max_n > SMALL_MAX_N / 2) {
-        if (fused) IWP_SMALL(true, SMALL_BLOCK, SMALL_CHUNKS_MAX, from, SMALL_MAX_N);
-        else IWP_SMALL(false, SMALL_BLOCK, SMALL_CHUNKS_MAX, from, SMALL_MAX_N);
-    } else if (max_n > TILE) {
-        if (fused) IWP_SMALL(true, SMALL_BLOCK, SMALL_CHUNKS_MAX / 2, from, SMALL_MAX_N / 2);
-        else IWP_SMALL(false, SMALL_BLOCK, SMALL_CHUNKS_MAX / 2, from, SMALL_MAX_N / 2);
-    }
+    if (max_n > SMALL_MAX_N / 2) IWP_SMALL(SMALL_BLOCK, SMALL_CHUNKS_MAX, from, SMALL_MAX_N);
+    else if (max_n > TILE) IWP_SMALL(SMALL_BLOCK, SMALL_CHUNKS_MAX / 2, from, SMALL_MAX_N / 2);
+#undef IWP_SMALL_AS
 #undef IWP_SMALL
     return IWP_OK;
 }
