@@ -61,14 +61,16 @@ struct TimedLaunch {       // records an event pair around the launch made while
     }
 };
 
-// Launch `kernel<<<grid, BLOCK, 0, s>>>(args...)`, timed if asked for, and turn a
-// launch failure into IWP_EHIP.
-#define IWP_LAUNCH(name, kernel, grid, s, ...) IWP_LAUNCH_BLOCK(name, kernel, grid, BLOCK, s, __VA_ARGS__)
-#define IWP_LAUNCH_BLOCK(name, kernel, grid, block, s, ...)           \
+// Launch `kernel<<<grid, BLOCK, lds, s>>>(args...)`, timed if asked for, and turn a
+// launch failure into IWP_EHIP.  lds: bytes of LDS that no one uses, see few_at_a_time().
+#define IWP_LAUNCH(name, kernel, grid, s, ...) IWP_LAUNCH_AS(name, kernel, grid, BLOCK, 0u, s, __VA_ARGS__)
+#define IWP_LAUNCH_BLOCK(name, kernel, grid, block, s, ...) IWP_LAUNCH_AS(name, kernel, grid, block, 0u, s, __VA_ARGS__)
+#define IWP_LAUNCH_FEW(name, kernel, grid, lds, s, ...) IWP_LAUNCH_AS(name, kernel, grid, BLOCK, lds, s, __VA_ARGS__)
+#define IWP_LAUNCH_AS(name, kernel, grid, block, lds, s, ...)         \
     do {                                                              \
         {                                                             \
             TimedLaunch tl_(name, s);                                 \
-            kernel<<<(grid), (block), 0, (s)>>>(__VA_ARGS__);         \
+            kernel<<<(grid), (block), (lds), (s)>>>(__VA_ARGS__);     \
         }                                                             \
         hipError_t e_ = hipGetLastError();                            \
         if (e_ != hipSuccess) return hip_fail(e_, name);              \
@@ -231,6 +233,45 @@ constexpr uint32_t FOLD_SCAN_MAX_STILES = 4096;
 // Do the followers' passes take the tiles in runs (see in_runs)?
 uint32_t takes_runs(uint32_t tiles, uint32_t n_layers) { return tiles <= (uint64_t)RUN_TILES * n_layers ? 1u : 0u; }
 
+// LDS for a launch to ask for so that a compute unit holds no more than `resident` of its workgroups at a time.  The passes over
+// whole buffers are bound by what the memory delivers, and it delivers more to fewer streams, as long as these keep it busy.
+// own: what LDS the kernel itself has, or a little more; LDS is given out in pieces of 1280 bytes.
+constexpr uint32_t LDS_BYTES = 160u << 10, LDS_PIECE = 1280;
+constexpr uint32_t few_at_a_time(uint32_t resident, uint32_t own) {
+    return LDS_BYTES / resident / LDS_PIECE * LDS_PIECE - own;
+}
+
+// Which tables that pays on.  Tiles that end early keep less on their way: ten thousand layers of 3000 elements take 101 us in look 1
+// and 425 in the followers' pass, 111 and 484 four at a time; three thousand of 10000 elements 90 and 90, 430 and 413.
+bool fills_tiles(uint32_t tiles, uint32_t n_layers) { return tiles >= 2 * n_layers; }
+
+// Followers, n of them accumulating: 8 workers, a thousand tensors of 115.5 M elements, 1692 us with the eight workgroups a compute
+// unit that the registers allow, 1632 with four, 20 % more with two; eight tensors of 62.4 M, 857 and 818.  Three workers, 120 M in
+// one tensor, 468 and 457; two, 25 M in 16, 56.7 and 58.  Where many elements are sent, and written to the matrix as well, eight are better:
+// 20 M of 4 workers 309 and 310 us a step at 1 / 10, 373 and 391 at 1 / 5; 12.5 M of 12, all of them, 1118 and 1252.
+constexpr uint32_t FOLLOW_LDS = 2048;
+uint32_t few_followers(const Table& T, uint32_t n) {
+    return n >= 3 && fills_tiles(T.tiles, T.n_layers) && T.pairs * 16 <= (uint64_t)T.tiles * TILE ? few_at_a_time(4, FOLLOW_LDS) : 0u;
+}
+
+// Followers of a mask, n of them accumulating, in runs (others lose: 62.4 M in eight tensors 760 us, 775 five at a time): 8 workers, 25 M
+// elements in 160 tensors 345 us, 332 five at a time, 335 four; 40 M in a thousand 458 and 440.  The last round costs more than that
+// where there are few: 3 M in three tensors 44.8 and 46.3.
+constexpr uint32_t MANY_ROUNDS = 16 * 5 * 256;        // workgroups: sixteen times what is resident
+uint32_t few_mask_followers(uint32_t tiles, uint32_t n_layers, uint32_t n) {
+    return n >= 4 && (uint64_t)n * tiles >= MANY_ROUNDS && fills_tiles(tiles, n_layers) ? few_at_a_time(5, FOLLOW_LDS) : 0u;
+}
+
+// Look 1, where it accumulates (a selection's, which stores nothing but candidates, is the faster the more are there: 25.6 M elements
+// 46 us, 50 four at a time): 115.5 M in a thousand tensors 344.8 -> 333.3 us, 268 M in one 1105 -> 1087, 62.4 M in eight 169.5 -> 165.3;
+// 1000 x 8000 elements 31.1 -> 32.2, which is why tables that memory-side caches hold go without.  Statistics, 25.6 M: 73.2 -> 71.7.
+constexpr uint32_t LEAD_LDS = HIST0 * sizeof(uint32_t) + 512, FEW_READERS = few_at_a_time(4, 256);
+
+// The reduction of `pairs` values with their update, where these are far apart: 62.4 M / 64 of 8 workers 51.6 -> 48.8 us, 268 M / 64 of one
+// 185.6 -> 182.5; no difference at 1 / 20; all of 21 M elements of 7 workers are 20 % slower.  (The updates that follow a count on the
+// device, or a caller's list, gain as much, 33.8 -> 31.0 and 21.5 -> 19.7 us, but the host cannot see how dense theirs are.)
+uint32_t few_updates(uint32_t tiles, uint64_t pairs) { return pairs * 32 <= (uint64_t)tiles * TILE ? few_at_a_time(3, 0) : 0u; }
+
 int check_eps(float eps) { return (eps >= 0.0f && std::isfinite(eps)) ? IWP_OK : IWP_EINVAL; }
 
 // Sampling source of a call: the leaders' residuals and gradients (NULL entries allowed), or nothing (on: false, or no w).
@@ -278,8 +319,11 @@ int launch_leader_pass(const Table& T, const Workspace& ws, const WorkerPtrs& P,
         IWP_LAUNCH("k_leader_pass", (k_leader_pass<LGROUP, KEEP_W>), grid, s, P, w, T.layers, T.n_layers, leader, W, eps,
                    ws.hist, ws.state, ws.stage, ws.A);
     } else {
-        IWP_LAUNCH("k_leader_pass", (k_leader_pass<LGROUP, KEEP_NOTHING>), grid, s, P, w, T.layers, T.n_layers, leader, W,
-                   eps, ws.hist, ws.state, ws.stage, ws.A);
+        bool accumulates = false;
+        for (uint32_t p = 0; p < W; ++p) accumulates |= P.g[p] != nullptr;
+        const uint32_t few = accumulates && fills_tiles(T.tiles, T.n_layers) ? few_at_a_time(4, LEAD_LDS) : 0u;
+        IWP_LAUNCH_FEW("k_leader_pass", (k_leader_pass<LGROUP, KEEP_NOTHING>), grid, few, s, P, w, T.layers, T.n_layers, leader, W,
+                       eps, ws.hist, ws.state, ws.stage, ws.A);
     }
     return IWP_OK;
 }
@@ -934,12 +978,12 @@ int iwp_step_segmented(const iwp_plan* plan, float* w, const float* const* g, fl
         return IWP_OK;
     }
     if (acc.n && !leader_did_all)
-        IWP_LAUNCH("k_follow_gather", k_follow_gather, acc.n * T.tiles, s, P, acc, T.layers, T.n_layers, T.tiles,
+        IWP_LAUNCH_FEW("k_follow_gather", k_follow_gather, acc.n * T.tiles, few_followers(T, acc.n), s, P, acc, T.layers, T.n_layers, T.tiles,
                    takes_runs(T.tiles, T.n_layers), leader, W, idx_out, ws.tile_out, ws.gathered, T.pairs);
     if (T.any_k) {
         uint32_t static_mask = 0;
         for (uint32_t q = 0; q < stat.n; ++q) static_mask |= 1u << stat.id[q];
-        IWP_LAUNCH("k_reduce_update", k_reduce_update, (uint32_t)((T.pairs + BLOCK - 1) / BLOCK), s, R, static_mask, T.layers,
+        IWP_LAUNCH_FEW("k_reduce_update", k_reduce_update, (uint32_t)((T.pairs + BLOCK - 1) / BLOCK), few_updates(T.tiles, T.pairs), s, R, static_mask, T.layers,
                    T.n_layers, leader, ws.gathered, W, T.pairs, idx_out, w, scale, sum_out, plan->flat_end);
     }
     return IWP_OK;
@@ -1062,7 +1106,7 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
     if (rule) {
         // the chosen nodes accumulate while their statistics are taken; the mask pass then only re-reads
         if (z.tiles)
-            IWP_LAUNCH("k_leader_stats", k_leader_stats, n_lead * z.tiles, s, P, w, layers, z.n_layers, z.tiles, leaders,
+            IWP_LAUNCH_FEW("k_leader_stats", k_leader_stats, n_lead * z.tiles, fills_tiles(z.tiles, z.n_layers) ? FEW_READERS : 0u, s, P, w, layers, z.n_layers, z.tiles, leaders,
                        n_lead, W, eps, ws.tile_stats);
         IWP_LAUNCH("k_layer_thr", k_layer_thr, z.n_layers * n_lead, s, layers, z.tiles, leaders, n_lead, W, ws.tile_stats,
                    rule->alpha, rule->beta, rule->C, reinterpret_cast<double2*>(rule->stats_out), rule->thr_out);
@@ -1093,8 +1137,9 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
                    sum_out);
         return IWP_OK;
     }
-    IWP_LAUNCH("k_follow_mask", k_follow_mask, W * z.tiles, s, P, layers, z.n_layers, z.tiles, takes_runs(z.tiles, z.n_layers),
-               leaders, n_lead, W, mask32,
+    const uint32_t runs = takes_runs(z.tiles, z.n_layers);
+    const uint32_t few = runs ? few_mask_followers(z.tiles, z.n_layers, streaming) : 0u;
+    IWP_LAUNCH_FEW("k_follow_mask", k_follow_mask, W * z.tiles, few, s, P, layers, z.n_layers, z.tiles, runs, leaders, n_lead, W, mask32,
                ws.tile_counts, ws.tile_pos, count_out, max_pairs, ws.slots, idx_out, ws.gathered);
     const uint32_t pair_blocks = std::min<uint32_t>((max_pairs + BLOCK - 1) / BLOCK, 8192u);
     IWP_LAUNCH("k_reduce_update_counted", k_reduce_update_counted, pair_blocks, s, R, static_mask, z.n_layers, leaders, n_lead, W,
