@@ -165,7 +165,7 @@ __device__ __forceinline__ uint32_t score_key(float r, float w, float eps) {
 // order, loses nothing and ends inside 31 bits.
 constexpr uint32_t QUIET_NAN_KEY = 0x7fc00000u;
 __device__ __forceinline__ uint32_t shifted(uint32_t key, uint32_t shift) {
-    return key + (key < QUIET_NAN_KEY ? shift : 0u);
+    return max(key, min(key + shift, QUIET_NAN_KEY - 1u));   // key + shift below the NaN keys, key itself among them
 }
 __device__ __forceinline__ uint32_t unshifted(uint32_t key, uint32_t shift) {
     return key - (key < QUIET_NAN_KEY ? shift : 0u);
@@ -250,7 +250,6 @@ __device__ __forceinline__ void store_quad(float* __restrict__ base, uint32_t i,
 // made the compiler wait for one quad before it asked for the next.  Values past the end are not meant for use.
 // Against separate code for the two forms: look 1 364 -> 347 us, followers' pass 1898 -> 1877 us on a thousand packed
 // tensors of 115.5 M elements; with thresholds, tables of 0.3 to 1.2 M elements 39.5 -> 35.5 and 61.3 -> 58.6 us a step.
-// Look 1 holds 78 registers instead of 67 for it (6 wavefronts per SIMD instead of 7).
 struct Rest { float x[3]; };
 __device__ __forceinline__ bool holds_rest(uint32_t n, uint32_t base) {      // does this lane hold those elements?
     return base + TILE > n && (n & 3u) && (((n & ~3u) - base) & (CHUNK - 1u)) == threadIdx.x * VEC;
@@ -258,11 +257,13 @@ __device__ __forceinline__ bool holds_rest(uint32_t n, uint32_t base) {      // 
 template <bool NT, uint32_t CHUNKS>
 __device__ __forceinline__ void request_tile(const float* __restrict__ p, uint32_t n, uint32_t base,
                                              float (&v)[CHUNKS][4], Rest& rest) {
+    const float* pt = p + base;                              // uniform, with an offset of 32 bits per lane
+    const uint32_t left = n - base;
 #pragma unroll
     for (uint32_t u = 0; u < CHUNKS; ++u) {
-        const uint32_t i = base + u * CHUNK + threadIdx.x * VEC;
-        if (i + VEC <= n) {
-            const v4f t = load_v4<NT>(p + i);
+        const uint32_t i = u * CHUNK + threadIdx.x * VEC;
+        if (i + VEC <= left) {
+            const v4f t = load_v4<NT>(pt + i);
             v[u][0] = t.x; v[u][1] = t.y; v[u][2] = t.z; v[u][3] = t.w;
         }
     }
@@ -283,12 +284,21 @@ __device__ __forceinline__ void settle_tile(uint32_t n, uint32_t base, float (&v
         for (int c = 0; c < 3; ++c) v[u][c] = u == at ? rest.x[c] : v[u][c];
 }
 
+// The keys behind the layer's end, which were computed from no element.
+__device__ __forceinline__ void leave_out_rest(uint32_t n, uint32_t base, uint32_t (&key)[CHUNKS_PER_TILE][4]) {
+#pragma unroll
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q)
+            if (base + u * CHUNK + threadIdx.x * VEC + q >= n) key[u][q] = NOT_AN_ELEMENT;
+}
+
 // Stores the tile's elements that lie inside the layer.
 template <bool NT, uint32_t CHUNKS>
 __device__ __forceinline__ void store_tile(float* __restrict__ p, uint32_t n, uint32_t base,
                                            const float (&v)[CHUNKS][4]) {
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS; ++u) store_quad<NT>(p, base + u * CHUNK + threadIdx.x * VEC, n, v[u]);
+    for (uint32_t u = 0; u < CHUNKS; ++u) store_quad<NT>(p + base, u * CHUNK + threadIdx.x * VEC, n - base, v[u]);
 }
 
 // Sums and scans across the 64 lanes of a wavefront, by data-parallel-primitive moves (row shifts by 1, 2, 4 and 8 lanes of
@@ -483,27 +493,34 @@ __device__ __forceinline__ uint32_t tile_ranks(const uint32_t (&n)[CHUNKS], uint
 __device__ __forceinline__ uint32_t stage_tile(const uint32_t (&key)[CHUNKS_PER_TILE][4],
                                                const float (&val)[CHUNKS_PER_TILE][4], uint32_t base, uint32_t from,
                                                uint32_t cap, uint64_t sb, const StageArrays& A, uint32_t* slot) {
+    // as signed numbers NOT_AN_ELEMENT is less than any key (`from` beyond them all, from a caller's record: nothing of it is kept)
+    const int32_t least = (int32_t)min(from, 0x7fffffffu);
     uint32_t n[CHUNKS_PER_TILE], first[CHUNKS_PER_TILE], any = 0u;
 #pragma unroll
     for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
         n[u] = 0u;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) n[u] += (key[u][q] != NOT_AN_ELEMENT && key[u][q] >= from) ? 1u : 0u;
+        for (int q = 0; q < 4; ++q) n[u] += (int32_t)key[u][q] >= least ? 1u : 0u;
         any |= n[u];
     }
     const uint32_t tot = tile_ranks(n, first, slot);
     if (tot > cap) return RAW_TILE;
     if (any) {
+        // uniform pointers and a byte offset of 32 bits: one address register for the three stores
+        char* const key_to = reinterpret_cast<char*>(A.key + sb);
+        char* const idx_to = reinterpret_cast<char*>(A.idx + sb);
+        char* const val_to = reinterpret_cast<char*>(A.val + sb);
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-            uint32_t o = first[u];
+            uint32_t at = first[u] * (uint32_t)sizeof(uint32_t);
+            const uint32_t i = base + u * CHUNK + threadIdx.x * VEC;
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (key[u][q] != NOT_AN_ELEMENT && key[u][q] >= from) {
-                    A.key[sb + o] = key[u][q];
-                    A.idx[sb + o] = base + u * CHUNK + threadIdx.x * VEC + q;
-                    A.val[sb + o] = val[u][q];
-                    ++o;
+            for (uint32_t q = 0; q < 4; ++q)
+                if ((int32_t)key[u][q] >= least) {
+                    *reinterpret_cast<uint32_t*>(key_to + at) = key[u][q];
+                    *reinterpret_cast<uint32_t*>(idx_to + at) = i + q;
+                    *reinterpret_cast<float*>(val_to + at) = val[u][q];
+                    at += (uint32_t)sizeof(uint32_t);
                 }
         }
     }

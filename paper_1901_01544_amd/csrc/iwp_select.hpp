@@ -292,7 +292,6 @@ __device__ __forceinline__ void flush_hist(const uint32_t* lh, uint32_t* __restr
 __device__ __forceinline__ void scored_tile(const float* __restrict__ rl, const float* __restrict__ wl, uint32_t n,
                                             uint32_t base, float eps, uint32_t shift,
                                             uint32_t (&key)[CHUNKS_PER_TILE][4], float (&val)[CHUNKS_PER_TILE][4]) {
-    const uint32_t tid = threadIdx.x;
     float wgt[CHUNKS_PER_TILE][4];
     const bool full = base + TILE <= n;
     Rest val_rest, wgt_rest;
@@ -301,12 +300,10 @@ __device__ __forceinline__ void scored_tile(const float* __restrict__ rl, const 
     settle_tile(n, base, val, val_rest);
     settle_tile(n, base, wgt, wgt_rest);
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-        const uint32_t i = base + u * CHUNK + tid * VEC;
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            key[u][q] = (full || i + q < n) ? shifted(score_key(val[u][q], wgt[u][q], eps), shift) : NOT_AN_ELEMENT;
-    }
+        for (int q = 0; q < 4; ++q) key[u][q] = shifted(score_key(val[u][q], wgt[u][q], eps), shift);
+    if (!full) leave_out_rest(n, base, key);                // uniform
 }
 
 // ---------------------------------------------------------------------------
@@ -333,7 +330,7 @@ constexpr uint32_t STAGE_MAX_GRID = 32768;         // at most this many workgrou
 constexpr uint32_t STAGE_TILES_MAX = 64;           // tiles per workgroup, at most (their look-1 counts: one per lane)
 
 template <bool PICK>
-__global__ __launch_bounds__(BLOCK) void k_stage(ResidualPtrs R, const float* __restrict__ w,
+__global__ __launch_bounds__(BLOCK, PICK ? 4 : 5) void k_stage(ResidualPtrs R, const float* __restrict__ w,
                                                  const DevLayer* __restrict__ layers, uint32_t n_layers,
                                                  uint32_t tiles, const uint32_t* __restrict__ leader, uint32_t W,
                                                  float eps, LayerState* __restrict__ state,

@@ -144,6 +144,11 @@ __device__ __forceinline__ void follow_tile_from(uint32_t head, const float* g0,
 // cache is written back during whatever comes next.
 // clear: the histogram is cleared first, once the tile's loads are on their way; before them it kept every
 // workgroup from its loads (look 1 of one layer of 1 M elements 13.6 -> 12.8 us, thresholds of 25.6 M 51.4 -> 50.3).
+// What a wavefront issues counts: on small tables it is most of a workgroup's time, and where no gradient is streamed the
+// vector units are busy for two thirds of the pass, half of that with divides.  Hence no branch per element where a tile is whole and
+// none of a wavefront's scores is zero.  Look 1 of 25.6 M elements without / with a gradient 51.0 -> 48.5 / 75.0 -> 73.5 us;
+// whole calls, with look 2 and the records' pass likewise: one layer of 1 M 26.6 -> 25.1, six tensors of 235 k, four workers 32.6 -> 31.4,
+// thresholds and pairs of 25.6 M 116.7 -> 115.0, one worker's share of them 145.0 -> 142.8, a thousand tensors, eight workers 2334 -> 2323.
 constexpr int KEEP_NOTHING = 0, KEEP_W = 1, KEEP_W_AND_R = 2;
 template <bool ACC, int KEEP>
 __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* __restrict__ rl,
@@ -173,25 +178,33 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
     }
     const bool full = base + TILE <= n;
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
-        const uint32_t i = base + u * CHUNK + tid * VEC;
+    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            key[u][q] = (full || i + q < n) ? shifted(score_key(val[u][q], wv[u][q], eps), C.shift) : NOT_AN_ELEMENT;
-    }
+        for (int q = 0; q < 4; ++q) key[u][q] = shifted(score_key(val[u][q], wv[u][q], eps), C.shift);
+    if (!full) leave_out_rest(n, base, key);                // uniform
     // zero scores (zero residuals: a layer's untouched part) are counted in a register and added once per
     // wavefront: a tile of zeros would otherwise be 4096 atomics on one LDS word
-    uint32_t zeros = 0;
+    uint32_t least = key[0][0];
 #pragma unroll
     for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (key[u][q] == C.shift) ++zeros;
-            else if (key[u][q] != NOT_AN_ELEMENT) atomicAdd(&C.lh[key[u][q] >> digit_shift(0)], 1u);
-        }
-    if (__any(zeros != 0)) {
+        for (int q = 0; q < 4; ++q) least = min(least, key[u][q]);
+    if (full && !__any(least == C.shift)) {                 // a key is never less
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) atomicAdd(&C.lh[key[u][q] >> digit_shift(0)], 1u);
+    } else {
+        uint32_t zeros = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (key[u][q] == C.shift) ++zeros;
+                else if (key[u][q] != NOT_AN_ELEMENT) atomicAdd(&C.lh[key[u][q] >> digit_shift(0)], 1u);
+            }
         zeros = wave_sum(zeros);
-        if ((tid & (WAVE - 1)) == 0) atomicAdd(&C.lh[0], zeros);
+        if (zeros != 0 && (tid & (WAVE - 1)) == 0) atomicAdd(&C.lh[0], zeros);
     }
     if (C.stage_bin != NO_STAGE_BIN) {                      // uniform
         const uint32_t cnt = stage_tile(key, val, base, C.stage_bin << digit_shift(0), C.cap, C.slot_begin + (uint64_t)lt * C.cap, C.A,
@@ -216,6 +229,8 @@ __device__ __forceinline__ void leader_group(const float* gp, float* rp, const f
         else lead_tile<false, KEEP>(gl, rl, wl, L.n, t, eps, m, C, t == first_tile);
     }
     __syncthreads();
+    // neighbouring lanes, neighbouring bins: with four to a lane, read at once, the atomics meet fewer lines each and look 1 of
+    // 25.6 M elements takes 84 us instead of 49
     for (uint32_t b = threadIdx.x; b < HIST0; b += BLOCK) {
         const uint32_t v = C.lh[b];
         if (v) atomicAdd(&ghist[b], v);
@@ -263,7 +278,7 @@ __global__ __launch_bounds__(BLOCK) void k_accumulate_rest(WorkerPtrs P, const D
 // with LG == 1 one workgroup per tile of the table, otherwise GROUP / LG per super-tile (some of them past the end
 // of a short layer).
 template <uint32_t LG, int KEEP>
-__global__ __launch_bounds__(BLOCK) void k_leader_pass(WorkerPtrs P, const float* __restrict__ w,
+__global__ __launch_bounds__(BLOCK, 6) void k_leader_pass(WorkerPtrs P, const float* __restrict__ w,
                                                        const DevLayer* __restrict__ layers, uint32_t n_layers,
                                                        const uint32_t* __restrict__ leader, uint32_t W, float eps,
                                                        uint32_t* __restrict__ hist,

@@ -198,7 +198,7 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
 // once per node and left a mask for each, to be OR-ed and counted in a launch of its own (308 + 9 us), and the nodes' sent
 // values were read and cleared pair by pair behind everything else (the update 177 us, now 66).  Whole steps: that table
 // 1208 -> 1077 us, one node of 25.6 M elements with a line per layer 554 -> 522, three of 1.1 M 38 -> 29 (three launches less).
-// Up to three nodes are one group's (76, 107 and 144 registers); more are taken two to a group, by workgroups of two to four
+// Up to three nodes are one group's (59, 97 and 134 registers); more are taken two to a group, by workgroups of two to four
 // groups, which read the weights once each.  One group that takes them one after the other, storing each and fetching
 // its sent values again, had every node's loads wait for the one before: eight workers, four and eight nodes, us a step, against
 // that (and against a workgroup per node and tile): 30 k elements 35 / 24 (31) and 47 / 27 (35), 1.2 M 69 / 43 (60) and 88 / 49
