@@ -264,7 +264,8 @@ uint32_t few_mask_followers(uint32_t tiles, uint32_t n_layers, uint32_t n) {
 
 // Look 1, where it accumulates (a selection's, which stores nothing but candidates, is the faster the more are there: 25.6 M elements
 // 46 us, 50 four at a time): 115.5 M in a thousand tensors 344.8 -> 333.3 us, 268 M in one 1105 -> 1087, 62.4 M in eight 169.5 -> 165.3;
-// 1000 x 8000 elements 31.1 -> 32.2, which is why tables that memory-side caches hold go without.  Statistics, 25.6 M: 73.2 -> 71.7.
+// 1000 x 8000 elements 31.1 -> 32.2, 25.6 and 36 M alike, which is why smaller tables go without.  Statistics, 25.6 M: 73.2 -> 71.7.
+constexpr uint64_t FEW_LEADERS_MIN_BYTES = 160ull << 20;
 constexpr uint32_t LEAD_LDS = HIST0 * sizeof(uint32_t) + 512, FEW_READERS = few_at_a_time(4, 256);
 
 // The reduction of `pairs` values with their update, where these are far apart: 62.4 M / 64 of 8 workers 51.6 -> 48.8 us, 268 M / 64 of one
@@ -303,25 +304,28 @@ constexpr uint32_t leader_grid(uint32_t tiles, uint32_t stiles) {
 
 // Up to these table sizes (bytes of one flat buffer's share of the table) look 1 leaves the weights, or the weights
 // and the residual it writes, in the memory-side cache for the kernels that come back to them (see lead_tile).  Three
-// states in turn / one state alone, us a call, r and w kept, w kept, nothing kept: 8 M elements, one worker 65.1 / 65.3, 65.6 /
-// 65.6, 66.9 / 67.6; 15 M 104.6 / 93.3, 98.3 / 96.1, 98.6 / 98.7; 25.6 M 165 / 132, 153 / 137, 146 / 143; 40 M (r and w not
-// tried) 210 / 187 with w kept, 211 / 195 with nothing.
-constexpr uint64_t KEEP_W_AND_R_MAX_BYTES = 40ull << 20, KEEP_W_MAX_BYTES = 160ull << 20;
+// states in turn / one state alone, us a call of one worker, r and w kept, w kept, nothing kept: 8 M elements 56.7 / 58.5, 57.6 /
+// 59.4, 58.9 / 60.7; 15 M 97.0 / 83.9, 87.7 / 85.7, 88.1 / 87.8; 25.6 M 161 / 124.6, 142.7 / 124.4, 134.2 / 129.1; 36 M 208 / 166, 184 /
+// 155.6, 176 / 163; whole steps of eight workers, w kept, nothing: 25.6 M 484 / 461, 477 / 466, 36 M 655 / 629, 650 / 632.  What one
+// state alone gains beyond 64 MiB is what is left in the cache from call to call, which a training step in between replaces.
+// Without a gradient (a selection) nothing is written, and the pairs' pass reads again what was read: 25.6 M 114.9 with w kept, 116.6.
+constexpr uint64_t KEEP_W_AND_R_MAX_BYTES = 40ull << 20, KEEP_W_MAX_BYTES = 64ull << 20, KEEP_W_MAX_BYTES_READ_ONLY = 160ull << 20;
 
 int launch_leader_pass(const Table& T, const Workspace& ws, const WorkerPtrs& P, const float* w, const uint32_t* leader,
                        uint32_t W, float eps, hipStream_t s) {
     const uint32_t grid = leader_grid(T.tiles, T.stiles);
     const uint64_t bytes = (uint64_t)T.tiles * TILE * sizeof(float);
+    bool accumulates = false;
+    for (uint32_t p = 0; p < W; ++p) accumulates |= P.g[p] != nullptr;
     if (bytes <= KEEP_W_AND_R_MAX_BYTES) {
         IWP_LAUNCH("k_leader_pass", (k_leader_pass<LGROUP, KEEP_W_AND_R>), grid, s, P, w, T.layers, T.n_layers, leader, W,
                    eps, ws.hist, ws.state, ws.stage, ws.A);
-    } else if (bytes <= KEEP_W_MAX_BYTES) {
+    } else if (bytes <= (accumulates ? KEEP_W_MAX_BYTES : KEEP_W_MAX_BYTES_READ_ONLY)) {
         IWP_LAUNCH("k_leader_pass", (k_leader_pass<LGROUP, KEEP_W>), grid, s, P, w, T.layers, T.n_layers, leader, W, eps,
                    ws.hist, ws.state, ws.stage, ws.A);
     } else {
-        bool accumulates = false;
-        for (uint32_t p = 0; p < W; ++p) accumulates |= P.g[p] != nullptr;
-        const uint32_t few = accumulates && fills_tiles(T.tiles, T.n_layers) ? few_at_a_time(4, LEAD_LDS) : 0u;
+        const bool large = bytes > FEW_LEADERS_MIN_BYTES;
+        const uint32_t few = large && accumulates && fills_tiles(T.tiles, T.n_layers) ? few_at_a_time(4, LEAD_LDS) : 0u;
         IWP_LAUNCH_FEW("k_leader_pass", (k_leader_pass<LGROUP, KEEP_NOTHING>), grid, few, s, P, w, T.layers, T.n_layers, leader, W,
                        eps, ws.hist, ws.state, ws.stage, ws.A);
     }

@@ -140,7 +140,7 @@ __device__ __forceinline__ void follow_tile_from(uint32_t head, const float* g0,
 // residual (KEEP_W_AND_R) are accessed with ordinary loads and stores instead, so that
 // what touches them again within the step (the ordered write clears the sent positions
 // of the residual, the update adds to the weights at them) finds them there.  The host
-// picks by the table's size (KEEP_W_MAX_BYTES): a written residual that stays in the
+// picks by the table's size (launch_leader_pass): a written residual that stays in the
 // cache is written back during whatever comes next.
 // clear: the histogram is cleared first, once the tile's loads are on their way; before them it kept every
 // workgroup from its loads (look 1 of one layer of 1 M elements 13.6 -> 12.8 us, thresholds of 25.6 M 51.4 -> 50.3).
