@@ -311,24 +311,33 @@ constexpr uint32_t leader_grid(uint32_t tiles, uint32_t stiles) {
 // Without a gradient (a selection) nothing is written, and the pairs' pass reads again what was read: 25.6 M 114.9 with w kept, 116.6.
 constexpr uint64_t KEEP_W_AND_R_MAX_BYTES = 40ull << 20, KEEP_W_MAX_BYTES = 64ull << 20, KEEP_W_MAX_BYTES_READ_ONLY = 160ull << 20;
 
+// Threads of a workgroup, which has one tile: 512 instead of 256 halve what each wavefront issues, and that is what counts where the chip
+// holds all workgroups at once, or nearly, and where a gradient is streamed up to some rounds of them.  us a call, 256 / 512 in look
+// 1, in look 2 (k_stage<true>), in the records' pass: one layer of 0.1 M elements 22.1 / 21.3, 21.1, - ; of 1 M 25.4 / 25.4, 24.3, -,
+// in both 23.4 (1024: 24.5, 24.9); thresholds and pairs of 1 M 33.1 / 32.6, 32.3, 32.4.  Look 1: 8 M in one layer 55.6 / 54.3, one worker's
+// share of 25.6 M 135.3 / 133.3, a whole step of eight on it 479.3 / 476.9, 36 M 177.3 / 174.6; without a gradient 25.6 M 114.7 / 115.9, 50 M
+// 198 / 205; beyond 160 MiB a thousand tensors 2326 / 2345.  Look 2: 2.5 M 39.1 / 39.1, 4 M in 60 layers 40.3 / 40.8, 8 M in 40 62.8 /
+// 64.1.  The records' pass: 8 M in 40 layers 62.8 / 62.2, 15 M in 100 81.0 / 81.4.
+constexpr uint32_t WIDE_BLOCK = 512;
+constexpr uint32_t WIDE_STAGE_MAX_TILES = 512;
+constexpr uint64_t WIDE_LEADERS_MAX_BYTES = FEW_LEADERS_MIN_BYTES;
+
+inline uint64_t buffer_bytes(const Table& T) { return (uint64_t)T.tiles * TILE * sizeof(float); }
+
 int launch_leader_pass(const Table& T, const Workspace& ws, const WorkerPtrs& P, const float* w, const uint32_t* leader,
                        uint32_t W, float eps, hipStream_t s) {
     const uint32_t grid = leader_grid(T.tiles, T.stiles);
-    const uint64_t bytes = (uint64_t)T.tiles * TILE * sizeof(float);
+    const uint64_t bytes = buffer_bytes(T);
     bool accumulates = false;
     for (uint32_t p = 0; p < W; ++p) accumulates |= P.g[p] != nullptr;
-    if (bytes <= KEEP_W_AND_R_MAX_BYTES) {
-        IWP_LAUNCH("k_leader_pass", (k_leader_pass<LGROUP, KEEP_W_AND_R>), grid, s, P, w, T.layers, T.n_layers, leader, W,
-                   eps, ws.hist, ws.state, ws.stage, ws.A);
-    } else if (bytes <= (accumulates ? KEEP_W_MAX_BYTES : KEEP_W_MAX_BYTES_READ_ONLY)) {
-        IWP_LAUNCH("k_leader_pass", (k_leader_pass<LGROUP, KEEP_W>), grid, s, P, w, T.layers, T.n_layers, leader, W, eps,
-                   ws.hist, ws.state, ws.stage, ws.A);
-    } else {
-        const bool large = bytes > FEW_LEADERS_MIN_BYTES;
-        const uint32_t few = large && accumulates && fills_tiles(T.tiles, T.n_layers) ? few_at_a_time(4, LEAD_LDS) : 0u;
-        IWP_LAUNCH_FEW("k_leader_pass", (k_leader_pass<LGROUP, KEEP_NOTHING>), grid, few, s, P, w, T.layers, T.n_layers, leader, W,
-                       eps, ws.hist, ws.state, ws.stage, ws.A);
-    }
+#define IWP_LOOK1(KEEP, THREADS, LDS)                                                                                            \
+    IWP_LAUNCH_AS("k_leader_pass", (k_leader_pass<LGROUP, KEEP, THREADS>), grid, THREADS, LDS, s, P, w, T.layers, T.n_layers,    \
+                  leader, W, eps, ws.hist, ws.state, ws.stage, ws.A)
+    if (bytes <= KEEP_W_AND_R_MAX_BYTES) IWP_LOOK1(KEEP_W_AND_R, WIDE_BLOCK, 0u);
+    else if (bytes <= (accumulates ? KEEP_W_MAX_BYTES : KEEP_W_MAX_BYTES_READ_ONLY)) IWP_LOOK1(KEEP_W, BLOCK, 0u);
+    else if (accumulates && bytes <= WIDE_LEADERS_MAX_BYTES) IWP_LOOK1(KEEP_NOTHING, WIDE_BLOCK, 0u);
+    else IWP_LOOK1(KEEP_NOTHING, BLOCK, accumulates && fills_tiles(T.tiles, T.n_layers) ? few_at_a_time(4, LEAD_LDS) : 0u);
+#undef IWP_LOOK1
     return IWP_OK;
 }
 
@@ -393,12 +402,13 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
         : std::min<uint32_t>((T.tiles + STAGE_RESIDENT - 1) / STAGE_RESIDENT, STAGE_TILES_MAX);
     const uint32_t stage_grid = std::max<uint32_t>(std::min<uint32_t>((T.tiles + per_wg - 1) / per_wg, STAGE_MAX_GRID),
                                                    (T.tiles + WAVE - 1) / WAVE);
-    if (own_pick)
-        IWP_LAUNCH("k_stage", k_stage<true>, stage_grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
-                   ws.hist, ws.stage, ws.A);
-    else
-        IWP_LAUNCH("k_stage", k_stage<false>, stage_grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
-                   ws.hist, ws.stage, ws.A);
+#define IWP_LOOK2(PICK, THREADS)                                                                                                 \
+    IWP_LAUNCH_BLOCK("k_stage", (k_stage<PICK, THREADS>), stage_grid, THREADS, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, \
+                     eps, ws.state, ws.hist, ws.stage, ws.A)
+    if (!own_pick) IWP_LOOK2(false, BLOCK);
+    else if (T.tiles <= WIDE_STAGE_MAX_TILES) IWP_LOOK2(true, WIDE_BLOCK);
+    else IWP_LOOK2(true, BLOCK);
+#undef IWP_LOOK2
     const uint32_t stile_grid = std::min<uint32_t>(T.stiles, STILE_MAX_GRID);
     const bool record = T.by_records && stop == FULL;
     uint32_t* units = reinterpret_cast<uint32_t*>(ws.tile_counts);       // a word per tile or super-tile
@@ -464,8 +474,12 @@ int launch_small(const DevLayer* layers, const DevLayer* row, uint32_t n_layers,
 int run_compact_from(const Table& T, const Workspace& ws, const ResidualPtrs& R, const float* w, float eps,
                      const iwp_threshold* thr, uint32_t* idx_out, float* val_out, hipStream_t s) {
     if (!T.any_k || T.tiles == 0) return IWP_OK;
-    IWP_LAUNCH("k_stage_records", k_stage_records, T.tiles, s, R.r[0], w, T.layers, T.n_layers, thr, eps, ws.state, ws.stage,
-               ws.A, ws.tile_counts);
+#define IWP_RECORDS(THREADS)                                                                                                     \
+    IWP_LAUNCH_BLOCK("k_stage_records", k_stage_records<THREADS>, T.tiles, THREADS, s, R.r[0], w, T.layers, T.n_layers, thr, eps, \
+                     ws.state, ws.stage, ws.A, ws.tile_counts)
+    if (buffer_bytes(T) <= KEEP_W_AND_R_MAX_BYTES) IWP_RECORDS(WIDE_BLOCK);
+    else IWP_RECORDS(BLOCK);
+#undef IWP_RECORDS
     if (T.max_layer_stiles <= FOLD_MAX_TILES / GROUP) {
         IWP_LAUNCH("k_write", (k_write<false, FOLD_TILES>), T.stiles * (GROUP / (BLOCK / WAVE)), s, R, w, T.layers, T.n_layers, T.tiles,
                    nullptr, 1u, eps, ws.state, ws.stage, ws.A, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, nullptr,

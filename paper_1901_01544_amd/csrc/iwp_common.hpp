@@ -251,33 +251,34 @@ __device__ __forceinline__ void store_quad(float* __restrict__ base, uint32_t i,
 // Against separate code for the two forms: look 1 364 -> 347 us, followers' pass 1898 -> 1877 us on a thousand packed
 // tensors of 115.5 M elements; with thresholds, tables of 0.3 to 1.2 M elements 39.5 -> 35.5 and 61.3 -> 58.6 us a step.
 struct Rest { float x[3]; };
+template <uint32_t THREADS = BLOCK>
 __device__ __forceinline__ bool holds_rest(uint32_t n, uint32_t base) {      // does this lane hold those elements?
-    return base + TILE > n && (n & 3u) && (((n & ~3u) - base) & (CHUNK - 1u)) == threadIdx.x * VEC;
+    return base + TILE > n && (n & 3u) && (((n & ~3u) - base) & (THREADS * VEC - 1u)) == threadIdx.x * VEC;
 }
-template <bool NT, uint32_t CHUNKS>
+template <bool NT, uint32_t THREADS = BLOCK, uint32_t CHUNKS>
 __device__ __forceinline__ void request_tile(const float* __restrict__ p, uint32_t n, uint32_t base,
                                              float (&v)[CHUNKS][4], Rest& rest) {
     const float* pt = p + base;                              // uniform, with an offset of 32 bits per lane
     const uint32_t left = n - base;
 #pragma unroll
     for (uint32_t u = 0; u < CHUNKS; ++u) {
-        const uint32_t i = u * CHUNK + threadIdx.x * VEC;
+        const uint32_t i = (u * THREADS + threadIdx.x) * VEC;
         if (i + VEC <= left) {
             const v4f t = load_v4<NT>(pt + i);
             v[u][0] = t.x; v[u][1] = t.y; v[u][2] = t.z; v[u][3] = t.w;
         }
     }
-    if (holds_rest(n, base)) {
+    if (holds_rest<THREADS>(n, base)) {
         const uint32_t whole = n & ~3u;
 #pragma unroll
         for (uint32_t c = 0; c < 3; ++c) rest.x[c] = p[min(whole + c, n - 1u)];
     }
 }
 
-template <uint32_t CHUNKS>
+template <uint32_t THREADS = BLOCK, uint32_t CHUNKS>
 __device__ __forceinline__ void settle_tile(uint32_t n, uint32_t base, float (&v)[CHUNKS][4], const Rest& rest) {
-    if (!holds_rest(n, base)) return;
-    const uint32_t at = ((n & ~3u) - base) / CHUNK;          // which of the lane's quads
+    if (!holds_rest<THREADS>(n, base)) return;
+    const uint32_t at = ((n & ~3u) - base) / (THREADS * VEC);          // which of the lane's quads
 #pragma unroll
     for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
@@ -285,20 +286,21 @@ __device__ __forceinline__ void settle_tile(uint32_t n, uint32_t base, float (&v
 }
 
 // The keys behind the layer's end, which were computed from no element.
-__device__ __forceinline__ void leave_out_rest(uint32_t n, uint32_t base, uint32_t (&key)[CHUNKS_PER_TILE][4]) {
+template <uint32_t THREADS = BLOCK, uint32_t CHUNKS>
+__device__ __forceinline__ void leave_out_rest(uint32_t n, uint32_t base, uint32_t (&key)[CHUNKS][4]) {
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+    for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
         for (uint32_t q = 0; q < 4; ++q)
-            if (base + u * CHUNK + threadIdx.x * VEC + q >= n) key[u][q] = NOT_AN_ELEMENT;
+            if (base + (u * THREADS + threadIdx.x) * VEC + q >= n) key[u][q] = NOT_AN_ELEMENT;
 }
 
 // Stores the tile's elements that lie inside the layer.
-template <bool NT, uint32_t CHUNKS>
+template <bool NT, uint32_t THREADS = BLOCK, uint32_t CHUNKS>
 __device__ __forceinline__ void store_tile(float* __restrict__ p, uint32_t n, uint32_t base,
                                            const float (&v)[CHUNKS][4]) {
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS; ++u) store_quad<NT>(p + base, u * CHUNK + threadIdx.x * VEC, n - base, v[u]);
+    for (uint32_t u = 0; u < CHUNKS; ++u) store_quad<NT>(p + base, (u * THREADS + threadIdx.x) * VEC, n - base, v[u]);
 }
 
 // Sums and scans across the 64 lanes of a wavefront, by data-parallel-primitive moves (row shifts by 1, 2, 4 and 8 lanes of
@@ -447,13 +449,14 @@ __device__ __forceinline__ uint32_t bitmap_rank(const uint32_t* map, const uint3
 
 // Of a tile's marked elements, how many stand before each lane's quads.  n[u]: marked elements (0 to 4) in the lane's quad of
 // chunk u (the lane's elements are consecutive, chunks follow each other); first[u]: marked ones of the tile before that
-// quad.  Returns the tile's total.  All 256 threads call it; `slot`: STAGE_WORDS words of LDS, not to be used again before
+// quad.  Returns the tile's total.  All threads call it; `slot`: STAGE_WORDS words of LDS, not to be used again before
 // the next __syncthreads().
-constexpr uint32_t STAGE_WORDS = 2 * BLOCK / WAVE;
-template <uint32_t CHUNKS>
+constexpr uint32_t STAGE_WORDS = 16;                        // a word per wavefront and pair of chunks
+template <uint32_t THREADS = BLOCK, uint32_t CHUNKS>
 __device__ __forceinline__ uint32_t tile_ranks(const uint32_t (&n)[CHUNKS], uint32_t (&first)[CHUNKS], uint32_t* slot) {
-    static_assert(CHUNKS <= 4 && CHUNK < 65536, "two chunks' counts in one word");
+    static_assert(CHUNKS <= 4 && TILE < 65536, "two chunks' counts in one word");
     constexpr uint32_t PAIRS = (CHUNKS + 1) / 2;
+    static_assert(PAIRS * (THREADS / WAVE) <= STAGE_WORDS, "a word per wavefront and pair of chunks");
     const uint32_t lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x >> 6;
     uint32_t c[PAIRS] = {}, inc[PAIRS], before[PAIRS], tot[PAIRS];
 #pragma unroll
@@ -469,7 +472,7 @@ __device__ __forceinline__ uint32_t tile_ranks(const uint32_t (&n)[CHUNKS], uint
         before[h] = inc[h] - c[h];
         tot[h] = 0;
 #pragma unroll
-        for (uint32_t v = 0; v < BLOCK / WAVE; ++v) {
+        for (uint32_t v = 0; v < THREADS / WAVE; ++v) {
             const uint32_t x = slot[PAIRS * v + h];
             before[h] += v < wave ? x : 0u;
             tot[h] += x;
@@ -488,22 +491,23 @@ __device__ __forceinline__ uint32_t tile_ranks(const uint32_t (&n)[CHUNKS], uint
 // in index order, so that the ordered split can rank a slot's entries by their place in it.  key[u][q] / val[u][q]: the
 // lane's element q of chunk u (the lane's elements are consecutive, chunks follow each other), NOT_AN_ELEMENT past
 // the layer's end.  Returns the number of copies, or RAW_TILE if they exceed the
-// slot (then nothing is written).  All 256 threads call it; `slot`: STAGE_WORDS words of LDS, not to be used again
+// slot (then nothing is written).  All threads call it; `slot`: STAGE_WORDS words of LDS, not to be used again
 // before the next __syncthreads().
-__device__ __forceinline__ uint32_t stage_tile(const uint32_t (&key)[CHUNKS_PER_TILE][4],
-                                               const float (&val)[CHUNKS_PER_TILE][4], uint32_t base, uint32_t from,
+template <uint32_t THREADS = BLOCK, uint32_t CHUNKS>
+__device__ __forceinline__ uint32_t stage_tile(const uint32_t (&key)[CHUNKS][4],
+                                               const float (&val)[CHUNKS][4], uint32_t base, uint32_t from,
                                                uint32_t cap, uint64_t sb, const StageArrays& A, uint32_t* slot) {
     // as signed numbers NOT_AN_ELEMENT is less than any key (`from` beyond them all, from a caller's record: nothing of it is kept)
     const int32_t least = (int32_t)min(from, 0x7fffffffu);
-    uint32_t n[CHUNKS_PER_TILE], first[CHUNKS_PER_TILE], any = 0u;
+    uint32_t n[CHUNKS], first[CHUNKS], any = 0u;
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+    for (uint32_t u = 0; u < CHUNKS; ++u) {
         n[u] = 0u;
 #pragma unroll
         for (int q = 0; q < 4; ++q) n[u] += (int32_t)key[u][q] >= least ? 1u : 0u;
         any |= n[u];
     }
-    const uint32_t tot = tile_ranks(n, first, slot);
+    const uint32_t tot = tile_ranks<THREADS>(n, first, slot);
     if (tot > cap) return RAW_TILE;
     if (any) {
         // uniform pointers and a byte offset of 32 bits: one address register for the three stores
@@ -511,9 +515,9 @@ __device__ __forceinline__ uint32_t stage_tile(const uint32_t (&key)[CHUNKS_PER_
         char* const idx_to = reinterpret_cast<char*>(A.idx + sb);
         char* const val_to = reinterpret_cast<char*>(A.val + sb);
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u) {
+        for (uint32_t u = 0; u < CHUNKS; ++u) {
             uint32_t at = first[u] * (uint32_t)sizeof(uint32_t);
-            const uint32_t i = base + u * CHUNK + threadIdx.x * VEC;
+            const uint32_t i = base + (u * THREADS + threadIdx.x) * VEC;
 #pragma unroll
             for (uint32_t q = 0; q < 4; ++q)
                 if ((int32_t)key[u][q] >= least) {

@@ -280,30 +280,31 @@ __global__ __launch_bounds__(WAVE) void k_final_pick(const DevLayer* __restrict_
 }
 
 // LDS histogram -> global, non-empty bins only.
-template <int NB>
+template <int NB, uint32_t THREADS = BLOCK>
 __device__ __forceinline__ void flush_hist(const uint32_t* lh, uint32_t* __restrict__ gh) {
-    for (uint32_t b = threadIdx.x; b < NB; b += BLOCK) {
+    for (uint32_t b = threadIdx.x; b < NB; b += THREADS) {
         const uint32_t v = lh[b];
         if (v) atomicAdd(&gh[b], v);
     }
 }
 
 // One tile's residuals and keys in registers, every load issued before the first use; NOT_AN_ELEMENT past the layer's end.
+template <uint32_t THREADS = BLOCK, uint32_t CHUNKS>
 __device__ __forceinline__ void scored_tile(const float* __restrict__ rl, const float* __restrict__ wl, uint32_t n,
                                             uint32_t base, float eps, uint32_t shift,
-                                            uint32_t (&key)[CHUNKS_PER_TILE][4], float (&val)[CHUNKS_PER_TILE][4]) {
-    float wgt[CHUNKS_PER_TILE][4];
+                                            uint32_t (&key)[CHUNKS][4], float (&val)[CHUNKS][4]) {
+    float wgt[CHUNKS][4];
     const bool full = base + TILE <= n;
     Rest val_rest, wgt_rest;
-    request_tile<true>(rl, n, base, val, val_rest);
-    request_tile<true>(wl, n, base, wgt, wgt_rest);
-    settle_tile(n, base, val, val_rest);
-    settle_tile(n, base, wgt, wgt_rest);
+    request_tile<true, THREADS>(rl, n, base, val, val_rest);
+    request_tile<true, THREADS>(wl, n, base, wgt, wgt_rest);
+    settle_tile<THREADS>(n, base, val, val_rest);
+    settle_tile<THREADS>(n, base, wgt, wgt_rest);
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+    for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
         for (int q = 0; q < 4; ++q) key[u][q] = shifted(score_key(val[u][q], wgt[u][q], eps), shift);
-    if (!full) leave_out_rest(n, base, key);                // uniform
+    if (!full) leave_out_rest<THREADS>(n, base, key);                // uniform
 }
 
 // ---------------------------------------------------------------------------
@@ -329,8 +330,8 @@ constexpr uint32_t STAGE_RESIDENT = 1280;          // ... five workgroups per co
 constexpr uint32_t STAGE_MAX_GRID = 32768;         // at most this many workgroups, unless that takes more than 64 tiles each
 constexpr uint32_t STAGE_TILES_MAX = 64;           // tiles per workgroup, at most (their look-1 counts: one per lane)
 
-template <bool PICK>
-__global__ __launch_bounds__(BLOCK, PICK ? 4 : 5) void k_stage(ResidualPtrs R, const float* __restrict__ w,
+template <bool PICK, uint32_t THREADS>
+__global__ __launch_bounds__(THREADS, PICK ? 4 : 5) void k_stage(ResidualPtrs R, const float* __restrict__ w,
                                                  const DevLayer* __restrict__ layers, uint32_t n_layers,
                                                  uint32_t tiles, const uint32_t* __restrict__ leader, uint32_t W,
                                                  float eps, LayerState* __restrict__ state,
@@ -339,6 +340,7 @@ __global__ __launch_bounds__(BLOCK, PICK ? 4 : 5) void k_stage(ResidualPtrs R, c
     __shared__ uint32_t lh[HIST1];
     __shared__ uint32_t slot[STAGE_WORDS];
     __shared__ uint32_t sh[PICK_WORDS];
+    constexpr uint32_t CHUNKS = TILE / (THREADS * VEC);
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
     // the workgroup's tiles are consecutive (at most 64: the host sizes the grid accordingly); their counts
     // from look 1 are fetched in one go, and a layer's row and state only when the layer changes, so that a
@@ -356,7 +358,7 @@ __global__ __launch_bounds__(BLOCK, PICK ? 4 : 5) void k_stage(ResidualPtrs R, c
         if (j != cur_j) {
             if (filled) {
                 __syncthreads();
-                flush_hist<HIST1>(lh, layer_hist(hist, L, 1));
+                flush_hist<HIST1, THREADS>(lh, layer_hist(hist, L, 1));
                 filled = false;
             }
             L = layers[j];
@@ -365,7 +367,7 @@ __global__ __launch_bounds__(BLOCK, PICK ? 4 : 5) void k_stage(ResidualPtrs R, c
             shift = state[j].shift;
             if (PICK) {
                 uint32_t k_rem0;
-                first_pick<BLOCK>(L, hist, state[j].stage_bin, sh, &b1, &k_rem0, &prestaged);
+                first_pick<THREADS>(L, hist, state[j].stage_bin, sh, &b1, &k_rem0, &prestaged);
                 if (t == L.tile_begin && tid == 0) {       // for the launches that follow
                     state[j].b1 = b1;
                     state[j].k_rem0 = k_rem0;
@@ -382,7 +384,7 @@ __global__ __launch_bounds__(BLOCK, PICK ? 4 : 5) void k_stage(ResidualPtrs R, c
         if (prestaged && !do_slots && !raw) continue;      // uniform
         if (!filled) {
             __syncthreads();                               // a flush above has read lh
-            for (uint32_t b = tid; b < HIST1; b += BLOCK) lh[b] = 0u;
+            for (uint32_t b = tid; b < HIST1; b += THREADS) lh[b] = 0u;
             __syncthreads();
             filled = true;
         }
@@ -392,19 +394,19 @@ __global__ __launch_bounds__(BLOCK, PICK ? 4 : 5) void k_stage(ResidualPtrs R, c
             // its tiles are requested before any of them is used
             const uint32_t ntiles = (L.n + TILE - 1) / TILE;
             const uint32_t last = min(lt + STAGE_GROUP, ntiles);
-            constexpr uint32_t MINE = STAGE_GROUP / (BLOCK / WAVE);
+            constexpr uint32_t MINE = STAGE_GROUP / (THREADS / WAVE);
             uint32_t cnt[MINE];
             uint32_t key[MINE][4];
 #pragma unroll
             for (uint32_t m = 0; m < MINE; ++m) {
-                const uint32_t tt = lt + wave + m * (BLOCK / WAVE);
+                const uint32_t tt = lt + wave + m * (THREADS / WAVE);
                 cnt[m] = tt < last ? stage_cnt[L.tile_begin + tt] : 0u;
                 if (cnt[m] & RESTAGED) cnt[m] = 0u;        // overflowed in look 1 (RAW, or already filled again by
                                                            // the tile's own unit, which also histograms it)
             }
 #pragma unroll
             for (uint32_t m = 0; m < MINE; ++m) {
-                const uint64_t sbb = L.slot_begin + (uint64_t)(lt + wave + m * (BLOCK / WAVE)) * L.slot_cap;
+                const uint64_t sbb = L.slot_begin + (uint64_t)(lt + wave + m * (THREADS / WAVE)) * L.slot_cap;
 #pragma unroll
                 for (uint32_t q = 0; q < 4; ++q) {
                     const uint32_t e = q * WAVE + lane;
@@ -417,7 +419,7 @@ __global__ __launch_bounds__(BLOCK, PICK ? 4 : 5) void k_stage(ResidualPtrs R, c
                 for (uint32_t q = 0; q < 4; ++q)
                     if (key[m][q] != NOT_AN_ELEMENT && (key[m][q] >> digit_shift(0)) == b1)
                         atomicAdd(&lh[(key[m][q] >> digit_shift(1)) & (HIST1 - 1)], 1u);
-                const uint64_t sbb = L.slot_begin + (uint64_t)(lt + wave + m * (BLOCK / WAVE)) * L.slot_cap;
+                const uint64_t sbb = L.slot_begin + (uint64_t)(lt + wave + m * (THREADS / WAVE)) * L.slot_cap;
                 for (uint32_t e = 4 * WAVE + lane; e < cnt[m]; e += WAVE) {    // fuller slots: the rest
                     const uint32_t k2 = A.key[sbb + e];
                     if ((k2 >> digit_shift(0)) == b1) atomicAdd(&lh[(k2 >> digit_shift(1)) & (HIST1 - 1)], 1u);
@@ -429,15 +431,15 @@ __global__ __launch_bounds__(BLOCK, PICK ? 4 : 5) void k_stage(ResidualPtrs R, c
             const float* rl = R.r[leader_of(leader, j, W)] + L.offset;
             const float* wl = w + L.offset;
             const uint32_t base = lt * TILE;
-            uint32_t key[CHUNKS_PER_TILE][4];
-            float val[CHUNKS_PER_TILE][4];
-            scored_tile(rl, wl, L.n, base, eps, shift, key, val);
+            uint32_t key[CHUNKS][4];
+            float val[CHUNKS][4];
+            scored_tile<THREADS>(rl, wl, L.n, base, eps, shift, key, val);
             // a tile whose keys are all the same (typically a tile of zero residuals in a layer whose threshold is
             // zero, where everything ties) is recorded as such: one entry instead of an overflowing slot
             const uint32_t k0 = shifted(score_key(rl[base], wl[base], eps), shift);   // the tile's first element
             bool same = true;
 #pragma unroll
-            for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+            for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) same = same && (key[u][q] == k0 || key[u][q] == NOT_AN_ELEMENT);
             const bool uniform_tile = __syncthreads_and(same ? 1 : 0) != 0;
@@ -451,19 +453,19 @@ __global__ __launch_bounds__(BLOCK, PICK ? 4 : 5) void k_stage(ResidualPtrs R, c
                 }
             } else {
 #pragma unroll
-                for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+                for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
                         if (key[u][q] != NOT_AN_ELEMENT && (key[u][q] >> digit_shift(0)) == b1)
                             atomicAdd(&lh[(key[u][q] >> digit_shift(1)) & (HIST1 - 1)], 1u);
-                const uint32_t cnt = stage_tile(key, val, base, b1 << digit_shift(0), L.slot_cap, sb, A, slot);
+                const uint32_t cnt = stage_tile<THREADS>(key, val, base, b1 << digit_shift(0), L.slot_cap, sb, A, slot);
                 if (tid == 0) stage_cnt[t] = (prestaged && cnt != RAW_TILE) ? (cnt | RESTAGED) : cnt;
             }
         }
     }
     if (filled) {
         __syncthreads();
-        flush_hist<HIST1>(lh, layer_hist(hist, L, 1));
+        flush_hist<HIST1, THREADS>(lh, layer_hist(hist, L, 1));
     }
 }
 
@@ -722,14 +724,16 @@ __global__ __launch_bounds__(BLOCK) void k_refine_tiles(ResidualPtrs R, const fl
 // reading back move 24 bytes per pair against 8 per element read again.  One layer of 25 M elements, copies / read again:
 // keep 0.4 125 / 112 us, 0.5 149 / 118, 0.999 254 / 163; of 1 M elements 24 / 39, 27 / 37, 40 / 38.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_stage_records(const float* __restrict__ r, const float* __restrict__ w,
+template <uint32_t THREADS>
+__global__ __launch_bounds__(THREADS) void k_stage_records(const float* __restrict__ r, const float* __restrict__ w,
                                                          const DevLayer* __restrict__ layers, uint32_t n_layers,
                                                          const iwp_threshold* __restrict__ thr, float eps,
                                                          LayerState* __restrict__ state,
                                                          uint32_t* __restrict__ stage_cnt, StageArrays A,
                                                          uint2* __restrict__ tile_counts) {
+    constexpr uint32_t CHUNKS = TILE / (THREADS * VEC);
     __shared__ uint32_t slot[STAGE_WORDS];
-    __shared__ uint32_t part[BLOCK / WAVE];
+    __shared__ uint32_t part[THREADS / WAVE];
     const uint32_t t = blockIdx.x;
     const uint32_t j = layer_of_tile(layers, n_layers, t);
     const DevLayer L = layers[j];
@@ -743,12 +747,12 @@ __global__ __launch_bounds__(BLOCK) void k_stage_records(const float* __restrict
         st.stage_bin = NO_STAGE_BIN; st.shift = 0; st.prestaged = 0;
         state[j] = st;
     }
-    uint32_t key[CHUNKS_PER_TILE][4];
-    float val[CHUNKS_PER_TILE][4];
-    scored_tile(r + L.offset, w + L.offset, L.n, lt * TILE, eps, 0u, key, val);
+    uint32_t key[CHUNKS][4];
+    float val[CHUNKS][4];
+    scored_tile<THREADS>(r + L.offset, w + L.offset, L.n, lt * TILE, eps, 0u, key, val);
     uint32_t c = 0;                                        // above the threshold; high half: tying with it
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+    for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             c += key[u][q] == NOT_AN_ELEMENT ? 0u : key[u][q] > from ? 1u : key[u][q] == from ? 0x10000u : 0u;
@@ -756,11 +760,13 @@ __global__ __launch_bounds__(BLOCK) void k_stage_records(const float* __restrict
     if ((threadIdx.x & (WAVE - 1)) == 0) part[threadIdx.x >> 6] = c;
     uint32_t cnt = RAW_TILE;
     if (from != 0u && L.k < L.n - L.k)                     // uniform; either way a barrier before the sum below
-        cnt = stage_tile(key, val, lt * TILE, from, L.slot_cap, L.slot_begin + (uint64_t)lt * L.slot_cap, A, slot);
+        cnt = stage_tile<THREADS>(key, val, lt * TILE, from, L.slot_cap, L.slot_begin + (uint64_t)lt * L.slot_cap, A, slot);
     else
         __syncthreads();
     if (threadIdx.x == 0) {
-        const uint32_t sum = part[0] + part[1] + part[2] + part[3];
+        uint32_t sum = 0;
+#pragma unroll
+        for (uint32_t v = 0; v < THREADS / WAVE; ++v) sum += part[v];
         stage_cnt[t] = cnt;
         tile_counts[t] = make_uint2(sum & 0xffffu, sum >> 16);
     }

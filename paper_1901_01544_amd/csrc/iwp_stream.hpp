@@ -6,7 +6,7 @@
 //    the residual at those indices and the clearing of the sent positions
 //    (Alg. 1 split lines), so the exchange needs no scattered second pass.
 //
-// Work unit: one TILE (4096 elements = 4 quads per lane) per workgroup, all loads
+// Work unit: one TILE (4096 elements = 4 quads per lane of 256, 2 of 512) per workgroup, all loads
 // of a tile issued before the first use, non-temporal accesses for data that is
 // not read again soon.  This shape measured fastest for a 2-read-1-write stream
 // on MI355X (about 6.2 TB/s against 5.3 TB/s for 16K-element tiles and 4.6 TB/s
@@ -150,54 +150,55 @@ __device__ __forceinline__ void follow_tile_from(uint32_t head, const float* g0,
 // whole calls, with look 2 and the records' pass likewise: one layer of 1 M 26.6 -> 25.1, six tensors of 235 k, four workers 32.6 -> 31.4,
 // thresholds and pairs of 25.6 M 116.7 -> 115.0, one worker's share of them 145.0 -> 142.8, a thousand tensors, eight workers 2334 -> 2323.
 constexpr int KEEP_NOTHING = 0, KEEP_W = 1, KEEP_W_AND_R = 2;
-template <bool ACC, int KEEP>
+template <bool ACC, int KEEP, uint32_t THREADS>
 __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* __restrict__ rl,
                                           const float* __restrict__ wl, uint32_t n, uint32_t lt,
                                           float eps, float m, const LeadCtx& C, bool clear) {
+    constexpr uint32_t CHUNKS = TILE / (THREADS * VEC);
     const uint32_t tid = threadIdx.x;
     const uint32_t base = lt * TILE;
-    uint32_t key[CHUNKS_PER_TILE][4];
-    float val[CHUNKS_PER_TILE][4], gv[CHUNKS_PER_TILE][4], wv[CHUNKS_PER_TILE][4];
+    uint32_t key[CHUNKS][4];
+    float val[CHUNKS][4], gv[CHUNKS][4], wv[CHUNKS][4];
     Rest val_rest, gv_rest, wv_rest;
-    request_tile<true>(rl, n, base, val, val_rest);
-    if (ACC) request_tile<true>(gl, n, base, gv, gv_rest);
-    request_tile<(KEEP < KEEP_W)>(wl, n, base, wv, wv_rest);
+    request_tile<true, THREADS>(rl, n, base, val, val_rest);
+    if (ACC) request_tile<true, THREADS>(gl, n, base, gv, gv_rest);
+    request_tile<(KEEP < KEEP_W), THREADS>(wl, n, base, wv, wv_rest);
     if (clear) {                                            // uniform; the loads are on their way
-        for (uint32_t b = tid; b < HIST0 / 4; b += BLOCK) reinterpret_cast<uint4*>(C.lh)[b] = make_uint4(0u, 0u, 0u, 0u);
+        for (uint32_t b = tid; b < HIST0 / 4; b += THREADS) reinterpret_cast<uint4*>(C.lh)[b] = make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
     }
-    settle_tile(n, base, val, val_rest);
-    if (ACC) settle_tile(n, base, gv, gv_rest);
-    settle_tile(n, base, wv, wv_rest);
+    settle_tile<THREADS>(n, base, val, val_rest);
+    if (ACC) settle_tile<THREADS>(n, base, gv, gv_rest);
+    settle_tile<THREADS>(n, base, wv, wv_rest);
     if (ACC) {
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+        for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
             for (int q = 0; q < 4; ++q) val[u][q] = accum(val[u][q], gv[u][q], m);
-        store_tile<(KEEP < KEEP_W_AND_R)>(rl, n, base, val);
+        store_tile<(KEEP < KEEP_W_AND_R), THREADS>(rl, n, base, val);
     }
     const bool full = base + TILE <= n;
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+    for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
         for (int q = 0; q < 4; ++q) key[u][q] = shifted(score_key(val[u][q], wv[u][q], eps), C.shift);
-    if (!full) leave_out_rest(n, base, key);                // uniform
+    if (!full) leave_out_rest<THREADS>(n, base, key);                // uniform
     // zero scores (zero residuals: a layer's untouched part) are counted in a register and added once per
     // wavefront: a tile of zeros would otherwise be 4096 atomics on one LDS word
     uint32_t least = key[0][0];
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+    for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
         for (int q = 0; q < 4; ++q) least = min(least, key[u][q]);
     if (full && !__any(least == C.shift)) {                 // a key is never less
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+        for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
             for (int q = 0; q < 4; ++q) atomicAdd(&C.lh[key[u][q] >> digit_shift(0)], 1u);
     } else {
         uint32_t zeros = 0;
 #pragma unroll
-        for (uint32_t u = 0; u < CHUNKS_PER_TILE; ++u)
+        for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 if (key[u][q] == C.shift) ++zeros;
@@ -207,7 +208,7 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
         if (zeros != 0 && (tid & (WAVE - 1)) == 0) atomicAdd(&C.lh[0], zeros);
     }
     if (C.stage_bin != NO_STAGE_BIN) {                      // uniform
-        const uint32_t cnt = stage_tile(key, val, base, C.stage_bin << digit_shift(0), C.cap, C.slot_begin + (uint64_t)lt * C.cap, C.A,
+        const uint32_t cnt = stage_tile<THREADS>(key, val, base, C.stage_bin << digit_shift(0), C.cap, C.slot_begin + (uint64_t)lt * C.cap, C.A,
                                         C.slot + (lt & 1u) * STAGE_WORDS);
         if (tid == 0) C.stage_cnt[lt] = cnt;
     }
@@ -215,7 +216,7 @@ __device__ __forceinline__ void lead_tile(const float* __restrict__ gl, float* _
 
 // The leader's share of one group (up to LGROUP tiles of the same layer):
 // one LDS histogram of the top digit for the whole group, flushed once.
-template <int KEEP>
+template <int KEEP, uint32_t THREADS>
 __device__ __forceinline__ void leader_group(const float* gp, float* rp, const float* __restrict__ w, const DevLayer& L,
                                              uint32_t first_tile /*in layer*/, uint32_t group_tiles, float eps, float m,
                                              LeadCtx& C, uint32_t* __restrict__ ghist) {
@@ -225,13 +226,13 @@ __device__ __forceinline__ void leader_group(const float* gp, float* rp, const f
     const uint32_t ntiles = (L.n + TILE - 1) / TILE;
     const uint32_t last = min(first_tile + group_tiles, ntiles);
     for (uint32_t t = first_tile; t < last; ++t) {
-        if (gp) lead_tile<true, KEEP>(gl, rl, wl, L.n, t, eps, m, C, t == first_tile);
-        else lead_tile<false, KEEP>(gl, rl, wl, L.n, t, eps, m, C, t == first_tile);
+        if (gp) lead_tile<true, KEEP, THREADS>(gl, rl, wl, L.n, t, eps, m, C, t == first_tile);
+        else lead_tile<false, KEEP, THREADS>(gl, rl, wl, L.n, t, eps, m, C, t == first_tile);
     }
     __syncthreads();
     // neighbouring lanes, neighbouring bins: with four to a lane, read at once, the atomics meet fewer lines each and look 1 of
     // 25.6 M elements takes 84 us instead of 49
-    for (uint32_t b = threadIdx.x; b < HIST0; b += BLOCK) {
+    for (uint32_t b = threadIdx.x; b < HIST0; b += THREADS) {
         const uint32_t v = C.lh[b];
         if (v) atomicAdd(&ghist[b], v);
     }
@@ -277,8 +278,8 @@ __global__ __launch_bounds__(BLOCK) void k_accumulate_rest(WorkerPtrs P, const D
 // Leaders only: one workgroup per group of LG tiles of every layer with k > 0.  The grid:
 // with LG == 1 one workgroup per tile of the table, otherwise GROUP / LG per super-tile (some of them past the end
 // of a short layer).
-template <uint32_t LG, int KEEP>
-__global__ __launch_bounds__(BLOCK, 6) void k_leader_pass(WorkerPtrs P, const float* __restrict__ w,
+template <uint32_t LG, int KEEP, uint32_t THREADS>
+__global__ __launch_bounds__(THREADS, 6) void k_leader_pass(WorkerPtrs P, const float* __restrict__ w,
                                                        const DevLayer* __restrict__ layers, uint32_t n_layers,
                                                        const uint32_t* __restrict__ leader, uint32_t W, float eps,
                                                        uint32_t* __restrict__ hist,
@@ -305,7 +306,7 @@ __global__ __launch_bounds__(BLOCK, 6) void k_leader_pass(WorkerPtrs P, const fl
     LeadCtx C = lead_ctx(lh, slot, L, state, j, stage_cnt, A);
     // consecutive workgroups of a layer flush into different copies of its first-digit histogram
     uint32_t* h0 = layer_hist(hist, L, 0) + (size_t)((first / LG) & (L.h0_copies - 1u)) * HIST0;
-    leader_group<KEEP>(P.g[p], P.r[p], w, L, first, LG, eps, P.momentum, C, h0);
+    leader_group<KEEP, THREADS>(P.g[p], P.r[p], w, L, first, LG, eps, P.momentum, C, h0);
 }
 
 // The other workers, after the leader's pairs are known: accumulate, and where the
