@@ -108,66 +108,86 @@ constexpr uint32_t TRUST_DENSE = 1, TRUST_ALWAYS = 2;
 constexpr int INIT_BLOCK = 1024;                   // threads of a k_init workgroup
 constexpr uint32_t SAMPLE_LOW_BITS = 7;            // the key's low bits that the sample does not resolve
 
-// The key from which look 1 should copy out (its low SAMPLE_LOW_BITS bits zero).
+// The key from which look 1 should copy out (its low SAMPLE_LOW_BITS bits zero).  A run is a wavefront's, so whether it is there and
+// whole is the same in all lanes: no branch per element, and the loads of two runs are on their way together.
 __device__ __forceinline__ uint32_t sample_stage_key(const DevLayer& L, const float* gp, const float* rp,
                                                      const float* __restrict__ w, float eps, float m, uint32_t* lh,
                                                      uint32_t* sh) {
     constexpr uint32_t WAVES = INIT_BLOCK / WAVE;
     constexpr uint32_t ROUND = 2, ROUNDS = SAMPLE_RUNS / (WAVES * ROUND);   // runs a wavefront has in flight; rounds
-    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = wave_id();
     const float* rl = rp + L.offset;
     const float* gl = gp ? gp + L.offset : nullptr;
     const float* wl = w + L.offset;
     const uint32_t runs_total = (L.n - 1) / SAMPLE_RUN + 1;
     const uint32_t runs = L.sample >> 16, rank = (L.sample & 0xffffu) + 1u;
-    for (uint32_t b = tid; b < HIST0; b += INIT_BLOCK) lh[b] = 0u;
+    static_assert(HIST0 == 4 * INIT_BLOCK, "four bins a thread");
+    reinterpret_cast<uint4*>(lh)[tid] = make_uint4(0u, 0u, 0u, 0u);
     uint32_t key[ROUNDS][ROUND][4];
+    bool there[ROUNDS][ROUND];                               // uniform
 #pragma unroll
     for (uint32_t d = 0; d < ROUNDS; ++d) {
         float rv[ROUND][4], gv[ROUND][4], wv[ROUND][4];
-        uint32_t e[ROUND];
-        const bool any = d * ROUND * WAVES < runs;       // uniform
+        uint32_t from[ROUND];
 #pragma unroll
         for (uint32_t c = 0; c < ROUND; ++c) {
             const uint32_t i = (d * ROUND + c) * WAVES + wave;
-            const uint64_t pos = (uint64_t)(i * runs_total / runs) * SAMPLE_RUN + lane * VEC;   // i * runs_total < 2^30
-            e[c] = (i < runs && pos < L.n) ? (uint32_t)pos : 0xFFFFFFFFu;
-            if (any && e[c] != 0xFFFFFFFFu) {
-                load_quad(rl, e[c], L.n, rv[c]);
-                if (gp) load_quad(gl, e[c], L.n, gv[c]);
-                load_quad(wl, e[c], L.n, wv[c], 1.0f);
+            there[d][c] = i < runs;
+            from[c] = i * runs_total / runs * SAMPLE_RUN;     // i * runs_total < 2^30; a run starts inside the layer
+            if (!there[d][c]) continue;
+            const uint32_t left = L.n - from[c], e = lane * VEC;
+            if (left >= SAMPLE_RUN) {
+                auto whole = [&](const float* p, float (&v)[4]) {
+                    const v4f t = load_v4<false>(p + from[c] + e);
+                    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+                };
+                whole(rl, rv[c]);
+                if (gp) whole(gl, gv[c]);
+                whole(wl, wv[c]);
+            } else {                                         // the layer's last run
+                load_quad(rl + from[c], e, left, rv[c]);
+                if (gp) load_quad(gl + from[c], e, left, gv[c]);
+                load_quad(wl + from[c], e, left, wv[c], 1.0f);
             }
         }
 #pragma unroll
-        for (uint32_t c = 0; c < ROUND; ++c)
+        for (uint32_t c = 0; c < ROUND; ++c) {
+            if (!there[d][c]) continue;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                key[d][c][q] = NOT_AN_ELEMENT;
-                if (any && e[c] != 0xFFFFFFFFu && (uint64_t)e[c] + q < L.n)
-                    key[d][c][q] = score_key(gp ? accum(rv[c][q], gv[c][q], m) : rv[c][q], wv[c][q], eps);
+            for (uint32_t q = 0; q < 4; ++q)
+                key[d][c][q] = score_key(gp ? accum(rv[c][q], gv[c][q], m) : rv[c][q], wv[c][q], eps);
+            if (L.n - from[c] < SAMPLE_RUN) {
+#pragma unroll
+                for (uint32_t q = 0; q < 4; ++q)
+                    if (lane * VEC + q >= L.n - from[c]) key[d][c][q] = NOT_AN_ELEMENT;
             }
+        }
     }
     __syncthreads();
 #pragma unroll
     for (uint32_t d = 0; d < ROUNDS; ++d)
 #pragma unroll
-        for (uint32_t c = 0; c < ROUND; ++c)
+        for (uint32_t c = 0; c < ROUND; ++c) {
+            if (!there[d][c]) continue;
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (key[d][c][q] != NOT_AN_ELEMENT) atomicAdd(&lh[key[d][c][q] >> digit_shift(0)], 1u);
+            for (uint32_t q = 0; q < 4; ++q)                 // NOT_AN_ELEMENT: the word behind the bins
+                atomicAdd(&lh[min(key[d][c][q] >> digit_shift(0), HIST0)], 1u);
+        }
     __syncthreads();
     uint32_t top, k_rem, mid, k_rem2;
     block_pick<(int)HIST0, INIT_BLOCK>(lh, rank, sh, &top, &k_rem);
-    for (uint32_t b = tid; b < HIST0; b += INIT_BLOCK) lh[b] = 0u;
+    reinterpret_cast<uint4*>(lh)[tid] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
 #pragma unroll
     for (uint32_t d = 0; d < ROUNDS; ++d)
 #pragma unroll
-        for (uint32_t c = 0; c < ROUND; ++c)
+        for (uint32_t c = 0; c < ROUND; ++c) {
+            if (!there[d][c]) continue;
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (key[d][c][q] != NOT_AN_ELEMENT && (key[d][c][q] >> digit_shift(0)) == top)
+            for (uint32_t q = 0; q < 4; ++q)                 // NOT_AN_ELEMENT shares no element's digit
+                if ((key[d][c][q] >> digit_shift(0)) == top)
                     atomicAdd(&lh[(key[d][c][q] >> SAMPLE_LOW_BITS) & (HIST0 - 1)], 1u);
+        }
     __syncthreads();
     block_pick<(int)HIST0, INIT_BLOCK>(lh, k_rem, sh, &mid, &k_rem2);
     return (top << digit_shift(0)) | (mid << SAMPLE_LOW_BITS);
@@ -179,7 +199,7 @@ __global__ __launch_bounds__(INIT_BLOCK, 8) void k_init(uint32_t* __restrict__ w
                                                      const DevLayer* __restrict__ layers,
                                                      DevLayer* __restrict__ single_table, DevLayer row, DevLayer sentinel,
                                                      SampleSource S) {
-    __shared__ uint32_t lh[HIST0];
+    __shared__ alignas(16) uint32_t lh[HIST0 + 1];
     __shared__ uint32_t sh[PICK_WORDS];
     const uint32_t n_layers = gridDim.x - zero_blocks;
     if (blockIdx.x >= n_layers) {                            // the workspace's parts are whole 256-byte blocks
