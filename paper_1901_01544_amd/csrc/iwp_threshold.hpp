@@ -74,6 +74,44 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
     out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
+// The lane's elements whose score is above a threshold -> bits of nib.  The score is |r| / d, d = |w| + eps, rounded.  No divide where the
+// answer does not hang on the rounding: f = t * d - |r|, rounded once, has the sign of the exact value.  f > 0: |r| / d < t, and rounded it
+// is at most t.  f + |r| / 2^21 < 0: |r| / d exceeds t by more than a unit in t's last place, and rounded it does, too; this takes a t
+// well above the subnormal numbers (SHORT_MIN) and finite.  Where a lane has neither (a NaN, an infinity, a score within 2^-21 of t),
+// its wavefront divides.  Two fused multiply-adds and two compares for a divide's dozen instructions, which count where a table is small:
+// steps with thresholds, one chosen node 20 k elements 15.5 -> 15.0 us, 400 k 18.7 -> 18.1, two nodes 20 k 19.0 -> 17.9, 1 M 28.5 -> 27.2,
+// three nodes 400 k 21.4 -> 20.0, 10 M 110.0 -> 108.4; one node of 10 M or more is bound by memory either way.  With random selection
+// the score itself is needed.
+constexpr float SHORT_MIN = 0x1p-100f, SHORT_MAX = 0x1p127f;
+template <uint32_t CHUNKS>
+__device__ __forceinline__ void add_above(const float (&rv)[CHUNKS][4], const float (&wv)[CHUNKS][4], float eps, float t,
+                                          uint32_t (&nib)[CHUNKS]) {
+    uint32_t mine[CHUNKS] = {};
+    bool open = !(t >= SHORT_MIN && t <= SHORT_MAX);
+    if (!open) {                                             // uniform
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS; ++u)
+#pragma unroll
+            for (uint32_t c = 0; c < VEC; ++c) {
+                const float a = fabsf(rv[u][c]), d = fabsf(wv[u][c]) + eps;
+                const float f = __builtin_fmaf(t, d, -a);
+                const bool above = __builtin_fmaf(a, 0x1p-21f, f) < 0.0f;
+                mine[u] |= above ? 1u << c : 0u;
+                open = open || !(above || f > 0.0f);
+            }
+    }
+    if (__any(open)) {
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS; ++u) {
+            mine[u] = 0u;
+#pragma unroll
+            for (uint32_t c = 0; c < VEC; ++c) mine[u] |= fabsf(rv[u][c]) / (fabsf(wv[u][c]) + eps) > t ? 1u << c : 0u;
+        }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < CHUNKS; ++u) nib[u] |= mine[u];
+}
+
 // The tile that starts at element `base` of its layer, CHUNKS chunks of it, for all chosen nodes of the layer: accumulate,
 // score, compare, encode, and hand over what is sent.  Layers that end within a tile's first chunk take one chunk only, which
 // spares them three quarters of the divides (and draws).  The nodes' values stay in registers until the common mask is known:
@@ -123,25 +161,46 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
     settle_tile(n, base, wv, wv_rest);
 #pragma unroll
     for (int s = 0; s < NL; ++s) settle(s);
+    const bool ragged = base + CHUNKS * CHUNK > n;           // uniform
+    if (ragged) {                                            // behind the layer's end: a score that is far from a threshold
 #pragma unroll
-    for (uint32_t u = 0; u < CHUNKS; ++u) {                  // the elements that one of the nodes in registers sends
-        const uint32_t i = base + u * CHUNK + tid * VEC;
-        uint32_t word4[4] = {0u, 0u, 0u, 0u};
-        if (rs.on) philox4x32_10(i >> 2, j, rs.step0, rs.step1, rs.key0, rs.key1, word4);   // i is a multiple of 4
+        for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
-        for (int s = 0; s < NL; ++s) {
-            if (!on[s]) continue;
+            for (uint32_t c = 0; c < VEC; ++c) {
+                const bool behind = base + u * CHUNK + tid * VEC + c >= n;
+                wv[u][c] = behind ? 1.0f : wv[u][c];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const float score = fabsf(rv[s][u][c]) / (fabsf(wv[u][c]) + eps);
-                bool send = score > th[s];
-                if (rs.on) {
+                for (int s = 0; s < NL; ++s) rv[s][u][c] = behind ? 0.0f : rv[s][u][c];
+            }
+    }
+    if (rs.on) {
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS; ++u) {
+            const uint32_t i = base + u * CHUNK + tid * VEC;
+            uint32_t word4[4];
+            philox4x32_10(i >> 2, j, rs.step0, rs.step1, rs.key0, rs.key1, word4);   // i is a multiple of 4
+#pragma unroll
+            for (int s = 0; s < NL; ++s) {
+                if (!on[s]) continue;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float score = fabsf(rv[s][u][c]) / (fabsf(wv[u][c]) + eps);
                     const float draw = (float)(word4[c] >> 8) * 0x1p-24f;
                     const float prob = score / th[s];
-                    send = send || draw < prob;
+                    if (score > th[s] || draw < prob) nib[u] |= 1u << c;
                 }
-                if (i + c < n && send) nib[u] |= 1u << c;
             }
+        }
+    } else {                                                 // the elements that one of the nodes in registers sends
+#pragma unroll
+        for (int s = 0; s < NL; ++s)
+            if (on[s]) add_above<CHUNKS>(rv[s], wv, eps, th[s], nib);
+    }
+    if (ragged) {
+#pragma unroll
+        for (uint32_t u = 0; u < CHUNKS; ++u) {
+            const uint32_t i = base + u * CHUNK + tid * VEC;
+            nib[u] &= i < n ? 0xFu >> (VEC - min(n - i, (uint32_t)VEC)) : 0u;
         }
     }
     if (GROUPS > 1) {
