@@ -1142,19 +1142,18 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
         else IWP_MASK(2, 4);
     }
 #undef IWP_MASK
-    IWP_LAUNCH_BLOCK("k_tile_offsets", k_tile_offsets, 1u, OFFSETS_BLOCK, s, layers, z.n_layers, z.tiles, ws.tile_counts, max_pairs,
-                     ws.tile_pos, ws.lay_out, count_out);
-    if (z.tiles == 0) return IWP_OK;
     uint32_t static_mask = 0, streaming = 0;
     for (uint32_t p = 0; p < W; ++p) {
         if (g[p]) ++streaming; else static_mask |= 1u << p;
     }
-    if (follows_together(*plan, streaming)) {
+    if (z.tiles && follows_together(*plan, streaming)) {
         IWP_LAUNCH("k_follow_mask_sum", k_follow_mask_sum, CHUNKS_A_TILE * z.tiles, s, P, first_streaming(g, W), layers, z.n_layers,
-                   leaders, n_lead, W, mask32, ws.tile_counts, ws.tile_pos, count_out, max_pairs, ws.slots, idx_out, w, scale,
-                   sum_out);
+                   z.tiles, leaders, n_lead, W, mask32, ws.tile_counts, count_out, max_pairs, ws.slots, idx_out, w, scale, sum_out);
         return IWP_OK;
     }
+    IWP_LAUNCH_BLOCK("k_tile_offsets", k_tile_offsets, 1u, OFFSETS_BLOCK, s, layers, z.n_layers, z.tiles, ws.tile_counts, max_pairs,
+                     ws.tile_pos, ws.lay_out, count_out);
+    if (z.tiles == 0) return IWP_OK;
     const uint32_t runs = takes_runs(z.tiles, z.n_layers);
     const uint32_t few = runs ? few_mask_followers(z.tiles, z.n_layers, streaming) : 0u;
     IWP_LAUNCH_FEW("k_follow_mask", k_follow_mask, W * z.tiles, few, s, P, layers, z.n_layers, z.tiles, runs, leaders, n_lead, W, mask32,
