@@ -224,11 +224,19 @@ struct Table {                // what the launches need to know about a layer ta
     uint32_t max_copies;         // copies of its first-digit histogram
     bool look_twice;             // roomy slots, no sampled mark (LOOK_TWICE_TILES)
     bool by_records;             // the split goes by the units' records
+    bool long_sparse;            // a layer of more than FOLD_SCAN_MAX_STILES super-tiles, and no slot of more than SPARSE_MAX_CAP entries
 };
 
 // Up to this many super-tiles per layer (128 Mi elements) k_write adds up the earlier super-tiles'
 // counts itself (16 loads per thread at most); beyond, a scan launch is cheaper.
 constexpr uint32_t FOLD_SCAN_MAX_STILES = 4096;
+// Up to this many entries a slot (one of 170 elements kept), such tables' third digit, counts and pairs are found by wavefronts that take
+// a super-tile or two at once (k_count_stiles).  Fuller slots have them go
+// through most tiles one after the other: 300 M elements kept at 1/120 alike, at 1/64 1458 -> 1519 us a step.
+constexpr uint32_t SPARSE_MAX_CAP = 64 + 3 * 24;
+inline bool is_long_sparse(uint32_t max_cap, uint32_t max_stiles) {
+    return max_stiles > FOLD_SCAN_MAX_STILES && max_cap <= SPARSE_MAX_CAP;
+}
 
 // Do the followers' passes take the tiles in runs (see in_runs)?
 uint32_t takes_runs(uint32_t tiles, uint32_t n_layers) { return tiles <= (uint64_t)RUN_TILES * n_layers ? 1u : 0u; }
@@ -351,10 +359,14 @@ int launch_write(const Table& T, const Workspace& ws, const ResidualPtrs& R, con
                    ws.stage, ws.A, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, gathered,
                    T.pairs);
     } else {
-        IWP_LAUNCH("k_scan", k_scan, T.n_layers, s, T.layers, ws.stile_counts);
-        IWP_LAUNCH("k_write", (k_write<FUSED, FOLDED>), grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
-                   ws.stage, ws.A, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, gathered,
-                   T.pairs);
+        IWP_LAUNCH_BLOCK("k_scan", k_scan, T.n_layers, SCAN_BLOCK, s, T.layers, ws.stile_counts);
+        if (T.long_sparse)
+            IWP_LAUNCH("k_write_stiles", k_write_stiles<FUSED>, (T.stiles + BLOCK / WAVE - 1) / (BLOCK / WAVE), s, R, w, T.layers,
+                       T.n_layers, T.tiles, T.stiles, leader, W, eps, ws.state, ws.stage, ws.A, ws.tile_counts, ws.stile_counts,
+                       ws.tile_out, idx_out, val_out, gathered, T.pairs);
+        else
+            IWP_LAUNCH("k_write", (k_write<FUSED, FOLDED>), grid, s, R, w, T.layers, T.n_layers, T.tiles, leader, W, eps, ws.state,
+                       ws.stage, ws.A, ws.tile_counts, ws.stile_counts, ws.tile_out, idx_out, val_out, gathered, T.pairs);
     }
     return IWP_OK;
 }
@@ -409,7 +421,7 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
     else if (T.tiles <= WIDE_STAGE_MAX_TILES) IWP_LOOK2(true, WIDE_BLOCK);
     else IWP_LOOK2(true, BLOCK);
 #undef IWP_LOOK2
-    const uint32_t stile_grid = std::min<uint32_t>(T.stiles, STILE_MAX_GRID);
+    const uint32_t stile_grid = T.long_sparse ? (T.stiles + STILES_TOGETHER - 1) / STILES_TOGETHER : std::min<uint32_t>(T.stiles, STILE_MAX_GRID);
     const bool record = T.by_records && stop == FULL;
     uint32_t* units = reinterpret_cast<uint32_t*>(ws.tile_counts);       // a word per tile or super-tile
 #define IWP_REFINE(RECORD)                                                                                                       \
@@ -430,7 +442,11 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
         IWP_LAUNCH_BLOCK("k_final_pick", k_final_pick, T.n_layers, WAVE, s, T.layers, ws.hist, ws.state, thr_out);
         return IWP_OK;
     }
-    IWP_LAUNCH("k_count", k_count, stile_grid, s, R, w, T.layers, T.n_layers, T.tiles, T.stiles, leader, W, eps, ws.state,
+    if (T.long_sparse)
+        IWP_LAUNCH("k_count_stiles", k_count_stiles, (T.stiles + BLOCK / WAVE - 1) / (BLOCK / WAVE), s, R, w, T.layers, T.n_layers,
+                   T.tiles, T.stiles, leader, W, eps, ws.state, ws.hist, thr_out, ws.stage, ws.A, ws.tile_counts, ws.stile_counts);
+    else
+        IWP_LAUNCH("k_count", k_count, stile_grid, s, R, w, T.layers, T.n_layers, T.tiles, T.stiles, leader, W, eps, ws.state,
                ws.hist, thr_out, ws.stage, ws.A, ws.tile_counts, ws.stile_counts);
     if (fused) return launch_write<true>(T, ws, R, w, leader, W, eps, idx_out, val_out, s);
     return launch_write<false>(T, ws, R, w, leader, W, eps, idx_out, val_out, s);
@@ -507,6 +523,7 @@ struct iwp_plan {
     bool all_dense = true;        // each of those keeps at least one element in HINT_KEEP
     bool look_twice = false;      // roomy slots; marks by samples only where samples() says so (LOOK_TWICE_TILES)
     bool by_records = false;      // the split goes by the units' records
+    bool long_sparse = false;     // see is_long_sparse()
     uint32_t max_copies = 1;      // most copies of a layer's first-digit histogram
     float momentum = 1.0f;        // r <- momentum * r + g in every call that accumulates through this plan
 };
@@ -541,7 +558,7 @@ bool samples(const iwp_plan& plan, bool hinted) {
 
 static Table table_of(const iwp_plan& p) {
     return Table{p.dev, p.z.n_layers, p.z.tiles, p.z.stiles, p.z.pairs, p.any_k, p.max_layer_stiles, p.max_copies, p.look_twice,
-                 p.by_records};
+                 p.by_records, p.long_sparse};
 }
 
 extern "C" {
@@ -617,7 +634,7 @@ static int single_common(SingleOp op, const float* w, const float* g, float* r, 
     int rc = launch_init(ws, 1, z.tiles, nullptr, nullptr, &row, &sentinel, S, s);
     if (rc) return rc;
     const Table T{ws.single_table, 1, z.tiles, z.stiles, k, k > 0, z.stiles, row.h0_copies, looks_twice(z.tiles, 1),
-                  goes_by_records(slot_cap_of(n, k), z.stiles)};
+                  goes_by_records(slot_cap_of(n, k), z.stiles), is_long_sparse(slot_cap_of(n, k), z.stiles)};
     if (op == OP_COMPACT) return run_compact_from(T, ws, R, w, eps, from_thr, idx_out, val_out, s);
     if (k > 0) {
         rc = launch_leader_pass(T, ws, P, w, nullptr, 1u, eps, s);
@@ -770,6 +787,7 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     plan->max_n = max_n;
     plan->n_long = n_long;
     plan->all_dense = all_dense;
+    plan->long_sparse = is_long_sparse(max_cap, max_stiles);
     // roomy slots, or what larger tables hold in reserve for them, unless the library's static scratch would no longer do
     Sizes roomier = plan->z;
     roomier.slots += any_k ? roomy_reserve(tiles) : 0u;

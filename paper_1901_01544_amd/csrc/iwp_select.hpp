@@ -327,6 +327,22 @@ __device__ __forceinline__ void scored_tile(const float* __restrict__ rl, const 
     if (!full) leave_out_rest<THREADS>(n, base, key);                // uniform
 }
 
+// The staged keys of n <= 64 consecutive tiles from tile lt of a layer on, none of which has more than 64 (lane i's c: entries of tile
+// lt + i): a wavefront takes every fourth tile (THREADS / 64th), and all its tiles' entries are requested before any of them is used.
+template <uint32_t THREADS, class Body>
+__device__ __forceinline__ void each_key_of_64_tiles(const StageArrays& A, const DevLayer& L, uint32_t lt, uint32_t n, uint32_t c, Body body) {
+    constexpr uint32_t WAVES = THREADS / WAVE, MINE = WAVE / WAVES;
+    const uint32_t lane = threadIdx.x & (WAVE - 1), wave = wave_id();
+    uint32_t key[MINE];
+#pragma unroll
+    for (uint32_t m = 0; m < MINE; ++m) {
+        const uint32_t i = wave + m * WAVES;
+        key[m] = i < n && lane < from_lane(c, i) ? A.key[L.slot_begin + (uint64_t)(lt + i) * L.slot_cap + lane] : NOT_AN_ELEMENT;
+    }
+#pragma unroll
+    for (uint32_t m = 0; m < MINE; ++m) body(key[m]);
+}
+
 // ---------------------------------------------------------------------------
 // Look 2: the second digit's histogram of the elements inside b1, and staged candidates
 // for the passes that follow.  The unit of work is a tile; a workgroup takes consecutive
@@ -361,7 +377,7 @@ __global__ __launch_bounds__(THREADS, PICK ? 4 : 5) void k_stage(ResidualPtrs R,
     __shared__ uint32_t slot[STAGE_WORDS];
     __shared__ uint32_t sh[PICK_WORDS];
     constexpr uint32_t CHUNKS = TILE / (THREADS * VEC);
-    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid >> 6;
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = wave_id();
     // the workgroup's tiles are consecutive (at most 64: the host sizes the grid accordingly); their counts
     // from look 1 are fetched in one go, and a layer's row and state only when the layer changes, so that a
     // tile with nothing to do costs no memory access at all
@@ -399,7 +415,9 @@ __global__ __launch_bounds__(THREADS, PICK ? 4 : 5) void k_stage(ResidualPtrs R,
         }
         if (L.k == 0) continue;
         const uint32_t lt = t - L.tile_begin;
-        const bool do_slots = prestaged && lt % STAGE_GROUP == 0;
+        // slots: of every STAGE_GROUP tiles by the first one's workgroup, or, where a workgroup has more tiles than that, its own ones
+        const bool own = per >= STAGE_GROUP;
+        const bool do_slots = prestaged && (own ? t == max(t0, L.tile_begin) : lt % STAGE_GROUP == 0);
         const bool raw = prestaged && from_lane(my_cnt, t - t0) == RAW_TILE;
         if (prestaged && !do_slots && !raw) continue;      // uniform
         if (!filled) {
@@ -409,24 +427,32 @@ __global__ __launch_bounds__(THREADS, PICK ? 4 : 5) void k_stage(ResidualPtrs R,
             filled = true;
         }
 
-        if (do_slots) {
+        const uint32_t ntiles = (L.n + TILE - 1) / TILE;
+        const uint32_t n_slots = min(own ? t1 - t : STAGE_GROUP, ntiles - lt);
+        // lane i: look 1's count of tile t + i.  A tile that overflowed there has its own unit, which also histograms it
+        uint32_t own_cnt = own ? (uint32_t)__shfl((int)my_cnt, (int)((lane + t - t0) & (WAVE - 1))) : 0u;
+        if (lane >= n_slots || (own_cnt & RESTAGED)) own_cnt = 0u;
+        if (do_slots && own && !__any(own_cnt > WAVE)) {     // uniform
+            each_key_of_64_tiles<THREADS>(A, L, lt, n_slots, own_cnt, [&](uint32_t key) {    // b1 is no NOT_AN_ELEMENT's digit
+                if ((key >> digit_shift(0)) == b1) atomicAdd(&lh[(key >> digit_shift(1)) & (HIST1 - 1)], 1u);
+            });
+        } else if (do_slots) for (uint32_t g0 = 0; g0 < n_slots; g0 += STAGE_GROUP) {
             // a wavefront takes every fourth tile of the group; the counts and the first 256 entries of all
             // its tiles are requested before any of them is used
-            const uint32_t ntiles = (L.n + TILE - 1) / TILE;
-            const uint32_t last = min(lt + STAGE_GROUP, ntiles);
+            const uint32_t from = lt + g0, last = min(from + STAGE_GROUP, lt + n_slots);
             constexpr uint32_t MINE = STAGE_GROUP / (THREADS / WAVE);
             uint32_t cnt[MINE];
             uint32_t key[MINE][4];
 #pragma unroll
             for (uint32_t m = 0; m < MINE; ++m) {
-                const uint32_t tt = lt + wave + m * (THREADS / WAVE);
-                cnt[m] = tt < last ? stage_cnt[L.tile_begin + tt] : 0u;
+                const uint32_t tt = from + wave + m * (THREADS / WAVE);
+                cnt[m] = tt < last ? (own ? from_lane(own_cnt, tt - lt) : stage_cnt[L.tile_begin + tt]) : 0u;
                 if (cnt[m] & RESTAGED) cnt[m] = 0u;        // overflowed in look 1 (RAW, or already filled again by
                                                            // the tile's own unit, which also histograms it)
             }
 #pragma unroll
             for (uint32_t m = 0; m < MINE; ++m) {
-                const uint64_t sbb = L.slot_begin + (uint64_t)(lt + wave + m * (THREADS / WAVE)) * L.slot_cap;
+                const uint64_t sbb = L.slot_begin + (uint64_t)(from + wave + m * (THREADS / WAVE)) * L.slot_cap;
 #pragma unroll
                 for (uint32_t q = 0; q < 4; ++q) {
                     const uint32_t e = q * WAVE + lane;
@@ -439,7 +465,7 @@ __global__ __launch_bounds__(THREADS, PICK ? 4 : 5) void k_stage(ResidualPtrs R,
                 for (uint32_t q = 0; q < 4; ++q)
                     if (key[m][q] != NOT_AN_ELEMENT && (key[m][q] >> digit_shift(0)) == b1)
                         atomicAdd(&lh[(key[m][q] >> digit_shift(1)) & (HIST1 - 1)], 1u);
-                const uint64_t sbb = L.slot_begin + (uint64_t)(lt + wave + m * (THREADS / WAVE)) * L.slot_cap;
+                const uint64_t sbb = L.slot_begin + (uint64_t)(from + wave + m * (THREADS / WAVE)) * L.slot_cap;
                 for (uint32_t e = 4 * WAVE + lane; e < cnt[m]; e += WAVE) {    // fuller slots: the rest
                     const uint32_t k2 = A.key[sbb + e];
                     if ((k2 >> digit_shift(0)) == b1) atomicAdd(&lh[(k2 >> digit_shift(1)) & (HIST1 - 1)], 1u);
@@ -494,6 +520,7 @@ __global__ __launch_bounds__(THREADS, PICK ? 4 : 5) void k_stage(ResidualPtrs R,
 // (the prologue's pick appended to b1), taken from the tile slots (or from r, w for RAW
 // tiles).  One workgroup per super-tile.
 // ---------------------------------------------------------------------------
+constexpr uint32_t STILES_TOGETHER = WAVE / GROUP; // tables of long layers: k_refine2 takes that many at once where slots hold few entries
 constexpr uint32_t STILE_MAX_GRID = 8192;          // k_refine2 / k_count: beyond this many super-tiles a workgroup takes
                                                    // several consecutive ones (one pick for all of them)
 
@@ -561,6 +588,17 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
         if (L.k == 0) continue;
         const uint32_t ntiles = (L.n + TILE - 1) / TILE;
         const uint32_t lt0 = (s - L.stile_begin) * GROUP;
+        if (!RECORD && per > 1) {                              // the workgroup's super-tiles of the layer at once, up to eight
+            const uint32_t n = min(min(s1 - s, STILES_TOGETHER) * GROUP, ntiles - lt0);
+            const uint32_t c = lane < n ? staged_entries(stage_cnt[L.tile_begin + lt0 + lane]) : 0u;
+            if (!__any(c > WAVE)) {                           // uniform; no RAW or UNIFORM tile among them
+                each_key_of_64_tiles<BLOCK>(A, L, lt0, n, c, [&](uint32_t key) {
+                    if ((key >> digit_shift(1)) == prefix) atomicAdd(&lh[key & (HIST2 - 1)], 1u);
+                });
+                s += (n - 1) / GROUP;
+                continue;
+            }
+        }
         const uint32_t nt = min(GROUP, ntiles - lt0);
         // the super-tile's eight counts, one per lane; a wavefront takes tiles wave and wave + 4, the counts
         // and the first 256 entries of both requested before any of them is used
@@ -973,37 +1011,45 @@ __global__ __launch_bounds__(BLOCK) void k_count(ResidualPtrs R, const float* __
 }
 
 // Part 2: exclusive prefix of the super-tile totals inside each layer, in order.
-// One workgroup per layer, eight consecutive super-tiles per lane and round.
-__global__ __launch_bounds__(BLOCK) void k_scan(const DevLayer* __restrict__ layers, uint2* __restrict__ stile_counts) {
-    constexpr uint32_t PER = 8;
-    __shared__ uint32_t slot_g[4], slot_e[4];
+// One workgroup per layer, eight parts of 1024 consecutive super-tiles a round: a chain of a load, two scans and a store per 8192 of
+// them.  A layer of 400 M elements, 12 k of them: 256 threads with eight consecutive ones each 12.4 us, 1024 threads 12.1 (each access
+// a line per lane), now 7.3.
+constexpr int SCAN_BLOCK = 1024;
+__global__ __launch_bounds__(SCAN_BLOCK) void k_scan(const DevLayer* __restrict__ layers, uint2* __restrict__ stile_counts) {
+    constexpr uint32_t PER = 8, WAVES = SCAN_BLOCK / WAVE;
+    __shared__ uint2 sums[2][PER][WAVES];
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = wave_id();
     const uint32_t j = blockIdx.x;
     if (layers[j].k == 0) return;
     const uint32_t sb = layers[j].stile_begin;
     const uint32_t se = sb + (layers[j].n + STILE - 1) / STILE;
-    uint32_t G = 0, E = 0;
-    for (uint32_t b = sb; b < se; b += BLOCK * PER) {
-        const uint32_t s0 = b + threadIdx.x * PER;
-        uint2 v[PER];
-        uint32_t lg = 0, le = 0;
+    uint32_t G = 0, E = 0;                                  // before the part
+    for (uint32_t b = sb, round = 0; b < se; b += SCAN_BLOCK * PER, ++round) {
+        uint2 v[PER], upto[PER];
+        auto& ws = sums[round & 1u];                         // the round before may still be reading the other
 #pragma unroll
         for (uint32_t q = 0; q < PER; ++q) {
-            v[q] = (s0 + q < se) ? stile_counts[s0 + q] : make_uint2(0u, 0u);
-            lg += v[q].x;
-            le += v[q].y;
+            const uint32_t s = b + q * SCAN_BLOCK + tid;
+            v[q] = s < se ? stile_counts[s] : make_uint2(0u, 0u);
         }
-        uint32_t tot_g, tot_e;
-        uint32_t pg = G + block_exclusive_scan(lg, slot_g, &tot_g);
-        uint32_t pe = E + block_exclusive_scan(le, slot_e, &tot_e);
 #pragma unroll
         for (uint32_t q = 0; q < PER; ++q) {
-            if (s0 + q < se) stile_counts[s0 + q] = make_uint2(pg, pe);
-            pg += v[q].x;
-            pe += v[q].y;
+            upto[q] = make_uint2(wave_inclusive_scan(v[q].x), wave_inclusive_scan(v[q].y));
+            if (lane == WAVE - 1) ws[q][wave] = upto[q];
         }
-        G += tot_g;
-        E += tot_e;
         __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < PER; ++q) {
+            if (b + q * SCAN_BLOCK >= se) break;             // uniform
+            const uint2 c = lane < WAVES ? ws[q][lane] : make_uint2(0u, 0u);     // the wavefronts' totals
+            const uint32_t cg = wave_inclusive_scan(c.x), ce = wave_inclusive_scan(c.y);
+            const uint32_t g = G + upto[q].x - v[q].x + from_lane(cg - c.x, wave);
+            const uint32_t e = E + upto[q].y - v[q].y + from_lane(ce - c.y, wave);
+            G += wave_last(cg);
+            E += wave_last(ce);
+            const uint32_t s = b + q * SCAN_BLOCK + tid;
+            if (s < se) stile_counts[s] = make_uint2(g, e);
+        }
     }
 }
 
@@ -1029,13 +1075,35 @@ __device__ __forceinline__ void request_slot(const StageArrays& A, uint64_t firs
     }
 }
 
+// 64 entries of a slot, one per lane (have: there is one): those that are kept go to their places behind G elements above the threshold
+// and E that tie with it, which are counted on.
+template <bool FUSED>
+__device__ __forceinline__ void write_entries(const DevLayer& L, uint32_t key, uint32_t idx, float val, bool have, uint32_t thr,
+                                              uint32_t quota, uint32_t& G, uint32_t& E, float* rl, uint32_t* __restrict__ io,
+                                              float* __restrict__ vo, float* __restrict__ go) {
+    const uint64_t below = (1ull << (threadIdx.x & (WAVE - 1))) - 1ull;
+    const bool above = have && key > thr, ties = have && key == thr;
+    const uint64_t ma = __ballot(above), mt = __ballot(ties);
+    const uint32_t gpre = G + __popcll(ma & below), epre = E + __popcll(mt & below);
+    uint32_t pos = 0xFFFFFFFFu;
+    if (above) pos = gpre + min(epre, quota);
+    else if (ties && epre < quota) pos = gpre + epre;
+    if (pos < L.k && idx < L.n) {
+        io[pos] = (uint32_t)(L.offset + idx);
+        vo[pos] = val;
+        if (FUSED) { go[pos] = val; rl[idx] = 0.0f; }
+    }
+    G += __popcll(ma);
+    E += __popcll(mt);
+}
+
 // The pairs of one tile, by one wavefront; S: its slot's first entries.  The slots being in index order saves the bitmaps in LDS that would rank
 // their entries: 8.7 -> 6.5 us a launch on a 25.6 M-element table, 59 -> 47 us on a layer of 400 M.  cnt: the tile's staged entries, UNIFORM_TILE or RAW_TILE; Gt, Et: elements
 // above the threshold / tying with it before the tile.
-template <bool FUSED>
+template <bool FUSED, uint32_t AHEAD>
 __device__ __forceinline__ void write_tile(const DevLayer& L, uint32_t lt, uint32_t cnt, uint32_t thr, uint32_t quota,
                                            uint32_t shift, uint32_t Gt, uint32_t Et, float* rl,
-                                           const float* __restrict__ wl, float eps, const StageArrays& A, SlotStart S,
+                                           const float* __restrict__ wl, float eps, const StageArrays& A, const SlotPart<AHEAD>& S,
                                            uint32_t* __restrict__ io, float* __restrict__ vo, float* __restrict__ go) {
     const uint32_t lane = threadIdx.x & (WAVE - 1);
     const uint32_t out_base = Gt + min(Et, quota);
@@ -1064,28 +1132,13 @@ __device__ __forceinline__ void write_tile(const DevLayer& L, uint32_t lt, uint3
     if (cnt != RAW_TILE) {
         // a slot holds its tile's candidates in index order: 64 of them at a time, ranked by what stands before them
         const uint64_t sb = L.slot_begin + (uint64_t)lt * L.slot_cap;
-        const uint64_t below = (1ull << lane) - 1ull;
         auto write = [&](auto& part, auto ahead, uint32_t e0) {
 #pragma unroll
-            for (uint32_t q = 0; q < ahead.value; ++q) {
-                const bool have = e0 + q * WAVE + lane < cnt;
-                const bool above = have && part.key[q] > thr, ties = have && part.key[q] == thr;
-                const uint64_t ma = __ballot(above), mt = __ballot(ties);
-                const uint32_t gpre = G + __popcll(ma & below), epre = E + __popcll(mt & below);
-                uint32_t pos = 0xFFFFFFFFu;
-                if (above) pos = gpre + min(epre, quota);
-                else if (ties && epre < quota) pos = gpre + epre;
-                if (pos < L.k && part.idx[q] < L.n) {
-                    io[pos] = (uint32_t)(L.offset + part.idx[q]);
-                    vo[pos] = part.val[q];
-                    if (FUSED) { go[pos] = part.val[q]; rl[part.idx[q]] = 0.0f; }
-                }
-                G += __popcll(ma);
-                E += __popcll(mt);
-            }
+            for (uint32_t q = 0; q < ahead.value; ++q)
+                write_entries<FUSED>(L, part.key[q], part.idx[q], part.val[q], e0 + q * WAVE + lane < cnt, thr, quota, G, E, rl, io, vo, go);
         };
-        write(S, std::integral_constant<uint32_t, SPLIT_AHEAD>(), 0u);
-        for (uint32_t e0 = SPLIT_AHEAD * WAVE; e0 < cnt; e0 += SPLIT_AHEAD_MORE * WAVE) {
+        write(S, std::integral_constant<uint32_t, AHEAD>(), 0u);
+        for (uint32_t e0 = AHEAD * WAVE; e0 < cnt; e0 += SPLIT_AHEAD_MORE * WAVE) {
             SlotPart<SPLIT_AHEAD_MORE> more;
             request_slot(A, sb + e0, cnt - e0, more);
             write(more, std::integral_constant<uint32_t, SPLIT_AHEAD_MORE>(), e0);
@@ -1128,8 +1181,8 @@ __device__ __forceinline__ void write_tile(const DevLayer& L, uint32_t lt, uint3
 // One wavefront per tile, four tiles (half a super-tile) per workgroup.  What stands before a tile in its layer:
 // FOLD_STILES: the super-tile totals are as k_count left them and the workgroup adds up the layer's earlier ones itself;
 // FOLD_TILES: the tiles' own counts are (k_stage_records), and it adds up those, which saves k_fold_counts, 5 us, on layers of
-// up to FOLD_MAX_TILES tiles (thresholds and pairs of 25.6 M elements 119.1 -> 116.3 us, one layer of 1 M, pairs alone, 15 -> 9); FOLDED: k_scan has turned the
-// super-tile totals into prefixes.
+// up to FOLD_MAX_TILES tiles (thresholds and pairs of 25.6 M elements 119.1 -> 116.3 us, one layer of 1 M, pairs alone, 15 -> 9);
+// FOLDED: k_scan has turned the super-tile totals into prefixes.
 constexpr int FOLDED = 0, FOLD_STILES = 1, FOLD_TILES = 2;
 constexpr uint32_t FOLD_MAX_TILES = 4096;          // 16 loads per thread at most
 template <bool FUSED, int FOLD>
@@ -1196,6 +1249,145 @@ __global__ __launch_bounds__(BLOCK) void k_write(ResidualPtrs R, const float* __
     SlotStart S;
     request_slot(A, L.slot_begin + (uint64_t)lt * L.slot_cap, cnt, S);
     write_tile<FUSED>(L, lt, cnt, thr, quota, st.shift, Gt, Et, rl, w + L.offset, eps, A, S, io, vo, go);
+}
+
+// ---------------------------------------------------------------------------
+// Counts and pairs of tables with a layer of more than FOLD_SCAN_MAX_STILES super-tiles whose slots hold few entries (SPARSE_MAX_CAP,
+// iwp_api.hip), with k_scan between them: one wavefront per super-tile, the counts and the first 64 entries of all its tiles requested together.  Nothing is shared between wavefronts.
+// Bound by the chain row -> state and counts -> entries, of which the chip has some ten thousand at once, not by what is read: of a
+// layer of 400 M elements kept at 1/1000 a tile's slot holds six entries, and with a workgroup per super-tile or half of one the counts
+// took 25 us and the pairs 45, now 8 and 27 (20 of which the clears of scattered residuals take); the whole step 1440 -> 1392 with look 2's and
+// k_refine2's part (each_key_of_64_tiles), 300 M kept at 1/300 1079 -> 1050, at 1/180 1173 -> 1162.
+// ---------------------------------------------------------------------------
+template <class Body>
+__device__ __forceinline__ void each_bit(uint32_t bits, Body body) {
+#pragma unroll 1
+    for (; bits; bits &= bits - 1u) body((uint32_t)__ffs((int)bits) - 1u);
+}
+
+__global__ __launch_bounds__(BLOCK) void k_count_stiles(ResidualPtrs R, const float* __restrict__ w,
+                                                        const DevLayer* __restrict__ layers, uint32_t n_layers,
+                                                        uint32_t tiles, uint32_t stiles, const uint32_t* __restrict__ leader,
+                                                        uint32_t W, float eps, LayerState* __restrict__ state,
+                                                        const uint32_t* __restrict__ hist, iwp_threshold* __restrict__ thr_out,
+                                                        const uint32_t* __restrict__ stage_cnt, StageArrays A,
+                                                        uint2* __restrict__ tile_counts, uint2* __restrict__ stile_counts) {
+    const uint32_t lane = threadIdx.x & (WAVE - 1), s = blockIdx.x * (BLOCK / WAVE) + wave_id();
+    if (s >= stiles) return;
+    const uint32_t j = layer_of_stile(layers, n_layers, tiles, s);
+    const DevLayer L = layers[j];
+    if (L.k == 0) return;
+    const uint32_t lt0 = (s - L.stile_begin) * GROUP, nt = min(GROUP, (L.n + TILE - 1) / TILE - lt0);
+    const uint64_t sb0 = L.slot_begin + (uint64_t)lt0 * L.slot_cap;
+    const uint32_t my_cnt = lane < nt ? staged_entries(stage_cnt[L.tile_begin + lt0 + lane]) : 0u;
+    uint32_t key[GROUP];
+#pragma unroll
+    for (uint32_t q = 0; q < GROUP; ++q) {
+        const uint32_t cnt = from_lane(my_cnt, q);
+        key[q] = lane < cnt ? A.key[sb0 + (uint64_t)q * L.slot_cap + lane] : NOT_AN_ELEMENT;   // RAW, UNIFORM: not used
+    }
+    uint32_t bin2, quota;
+    wave_pick<(int)HIST2>(layer_hist(hist, L, 2), state[j].k_rem1, &bin2, &quota);
+    const uint32_t thr = (state[j].p22 << digit_bits(2)) | bin2, shift = state[j].shift;
+    if (s == L.stile_begin && lane == 0) {
+        state[j].thr = thr;
+        state[j].n_eq_take = quota;
+        if (thr_out) {
+            iwp_threshold th;
+            th.key = unshifted(thr, shift); th.n_gt = L.k - quota; th.n_eq_take = quota;
+            thr_out[j] = th;
+        }
+    }
+    uint32_t gt = 0, eq = 0;                                 // lane q: of tile q
+#pragma unroll
+    for (uint32_t q = 0; q < GROUP; ++q) {
+        const uint32_t g = (uint32_t)__popcll(__ballot((int32_t)key[q] > (int32_t)thr));         // NOT_AN_ELEMENT: negative
+        const uint32_t e = (uint32_t)__popcll(__ballot(key[q] == thr));
+        gt = lane == q ? g : gt;
+        eq = lane == q ? e : eq;
+    }
+    each_bit((uint32_t)__ballot(my_cnt > WAVE), [&](uint32_t q) {
+        const uint32_t cnt = from_lane(my_cnt, q), first = (lt0 + q) * TILE;
+        const uint64_t sb = sb0 + (uint64_t)q * L.slot_cap;
+        uint32_t g = 0, e = 0;
+        if (cnt == UNIFORM_TILE) {                           // all keys of the tile are the slot's one entry
+            const uint32_t k0 = A.key[sb], n_tile = min(TILE, L.n - first);
+            if (lane == 0) { g = k0 > thr ? n_tile : 0u; e = k0 == thr ? n_tile : 0u; }
+        } else if (cnt == RAW_TILE) {
+            read_raw_tile(R.r[leader_of(leader, j, W)] + L.offset, w + L.offset, L.n, first, eps, shift, thr,
+                          [&](uint32_t packed, const uint32_t (&)[4], const float (&)[4], uint32_t) {
+                g += packed & 0xffffu;
+                e += packed >> 16;
+            });
+        } else {
+            for (uint32_t e0 = 0; e0 < cnt; e0 += 4 * WAVE) {
+                uint32_t k2[4];
+#pragma unroll
+                for (uint32_t c = 0; c < 4; ++c) k2[c] = e0 + c * WAVE + lane < cnt ? A.key[sb + e0 + c * WAVE + lane] : NOT_AN_ELEMENT;
+#pragma unroll
+                for (uint32_t c = 0; c < 4; ++c) {
+                    g += (int32_t)k2[c] > (int32_t)thr ? 1u : 0u;
+                    e += k2[c] == thr ? 1u : 0u;
+                }
+            }
+        }
+        g = wave_sum(g);
+        e = wave_sum(e);
+        gt = lane == q ? g : gt;
+        eq = lane == q ? e : eq;
+    });
+    const uint32_t g = wave_inclusive_scan(gt), e = wave_inclusive_scan(eq);
+    if (lane < nt) tile_counts[L.tile_begin + lt0 + lane] = make_uint2(g - gt, e - eq);
+    if (lane == WAVE - 1) stile_counts[s] = make_uint2(g, e);
+}
+
+template <bool FUSED>
+__global__ __launch_bounds__(BLOCK) void k_write_stiles(ResidualPtrs R, const float* __restrict__ w,
+                                                        const DevLayer* __restrict__ layers, uint32_t n_layers,
+                                                        uint32_t tiles, uint32_t stiles, const uint32_t* __restrict__ leader,
+                                                        uint32_t W, float eps, const LayerState* __restrict__ state,
+                                                        const uint32_t* __restrict__ stage_cnt, StageArrays A,
+                                                        const uint2* __restrict__ tile_counts,
+                                                        const uint2* __restrict__ stile_counts,
+                                                        uint32_t* __restrict__ tile_out,
+                                                        uint32_t* __restrict__ idx_out, float* __restrict__ val_out,
+                                                        float* __restrict__ gathered, uint64_t K) {
+    const uint32_t lane = threadIdx.x & (WAVE - 1), s = blockIdx.x * (BLOCK / WAVE) + wave_id();
+    if (s >= stiles) return;
+    const uint32_t j = layer_of_stile(layers, n_layers, tiles, s);
+    const DevLayer L = layers[j];
+    if (L.k == 0) return;
+    const uint32_t lt0 = (s - L.stile_begin) * GROUP, nt = min(GROUP, (L.n + TILE - 1) / TILE - lt0), t0 = L.tile_begin + lt0;
+    const uint64_t sb0 = L.slot_begin + (uint64_t)lt0 * L.slot_cap;
+    const uint32_t my_cnt = lane < nt ? staged_entries(stage_cnt[t0 + lane]) : 0u;
+    uint2 before = lane < nt ? tile_counts[t0 + lane] : make_uint2(0u, 0u);
+    const uint2 sc = stile_counts[s];                        // before the super-tile (k_scan)
+    before.x += sc.x;
+    before.y += sc.y;
+    SlotPart<1> S[GROUP];
+#pragma unroll
+    for (uint32_t q = 0; q < GROUP; ++q) request_slot(A, sb0 + (uint64_t)(q < nt ? q : 0u) * L.slot_cap, from_lane(my_cnt, q), S[q]);
+    const uint32_t thr = state[j].thr, quota = state[j].n_eq_take, shift = state[j].shift;
+    if (lane < nt) tile_out[t0 + lane] = before.x + min(before.y, quota);
+    const uint32_t lead = leader_of(leader, j, W);
+    float* rl = R.r[lead] + L.offset;
+    uint32_t* io = idx_out + L.out_offset;
+    float* vo = val_out + L.out_offset;
+    float* go = FUSED ? gathered + (size_t)lead * K + L.out_offset : nullptr;
+#pragma unroll
+    for (uint32_t q = 0; q < GROUP; ++q) {
+        const uint32_t cnt = from_lane(my_cnt, q);
+        if (cnt > WAVE) continue;                            // uniform
+        uint32_t G = from_lane(before.x, q), E = from_lane(before.y, q);
+        write_entries<FUSED>(L, S[q].key[0], S[q].idx[0], S[q].val[0], lane < cnt, thr, quota, G, E, rl, io, vo, go);
+    }
+    each_bit((uint32_t)__ballot(my_cnt > WAVE), [&](uint32_t q) {
+        const uint32_t cnt = from_lane(my_cnt, q);
+        SlotStart more;
+        request_slot(A, sb0 + (uint64_t)q * L.slot_cap, cnt, more);
+        write_tile<FUSED>(L, lt0 + q, cnt, thr, quota, shift, from_lane(before.x, q), from_lane(before.y, q), rl, w + L.offset, eps, A,
+                          more, io, vo, go);
+    });
 }
 
 // ---------------------------------------------------------------------------
