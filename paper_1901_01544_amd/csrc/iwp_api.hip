@@ -1139,18 +1139,28 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     uint32_t* mask32 = reinterpret_cast<uint32_t*>(mask_out);
     const DevLayer* layers = plan->dev;
+    TileStats stats;                                         // only where the masks' launch merges them
+    memset(&stats, 0, sizeof stats);
     if (rule) {
         // the chosen nodes accumulate while their statistics are taken; the mask pass then only re-reads
         if (z.tiles)
             IWP_LAUNCH_FEW("k_leader_stats", k_leader_stats, n_lead * z.tiles, fills_tiles(z.tiles, z.n_layers) ? FEW_READERS : 0u, s, P, w, layers, z.n_layers, z.tiles, leaders,
                        n_lead, W, eps, ws.tile_stats);
-        IWP_LAUNCH("k_layer_thr", k_layer_thr, z.n_layers * n_lead, s, layers, z.tiles, leaders, n_lead, W, ws.tile_stats,
-                   rule->alpha, rule->beta, rule->C, reinterpret_cast<double2*>(rule->stats_out), rule->thr_out);
+        const LayerRule lr{rule->alpha, rule->beta, rule->C, reinterpret_cast<double2*>(rule->stats_out), rule->thr_out};
+        if (z.tiles && (uint64_t)n_lead * z.tiles <= RULE_MAX_TABLE && plan->max_layer_stiles <= RULE_MAX_TILES / GROUP)
+            stats = TileStats{ws.tile_stats, z.tiles, lr};
+        else
+            IWP_LAUNCH("k_layer_thr", k_layer_thr, z.n_layers * n_lead, s, layers, z.tiles, leaders, n_lead, W, ws.tile_stats, lr);
         thr = rule->thr_out;
     }
-#define IWP_MASK(NL, GROUPS)                                                                                                 \
-    IWP_LAUNCH_BLOCK("k_leader_mask", (k_leader_mask<NL, GROUPS>), z.tiles, dim3(BLOCK, GROUPS), s, P, w, layers, z.n_layers, leaders, \
-                     n_lead, W, thr, rule != nullptr, rule == nullptr, rs, eps, mask32, ws.tile_counts, ws.slots)
+#define IWP_MASK_AS(NL, GROUPS, RULE)                                                                                        \
+    IWP_LAUNCH_BLOCK("k_leader_mask", (k_leader_mask<NL, GROUPS, RULE>), z.tiles, dim3(BLOCK, GROUPS), s, P, w, layers, z.n_layers, \
+                     leaders, n_lead, W, thr, rule != nullptr, rule == nullptr, stats, rs, eps, mask32, ws.tile_counts, ws.slots)
+#define IWP_MASK(NL, GROUPS)                       \
+    do {                                           \
+        if (stats.of) IWP_MASK_AS(NL, GROUPS, true); \
+        else IWP_MASK_AS(NL, GROUPS, false);       \
+    } while (0)
     if (z.tiles) {
         if (n_lead == 1) IWP_MASK(1, 1);
         else if (n_lead == 2) IWP_MASK(2, 1);
@@ -1160,6 +1170,7 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
         else IWP_MASK(2, 4);
     }
 #undef IWP_MASK
+#undef IWP_MASK_AS
     uint32_t static_mask = 0, streaming = 0;
     for (uint32_t p = 0; p < W; ++p) {
         if (g[p]) ++streaming; else static_mask |= 1u << p;

@@ -74,6 +74,45 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
     out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
+// The layer-wise rule (Section 3.4, Eq. 4) from a layer's mean and population variance.
+struct LayerRule {
+    double alpha, beta, C;
+    double2* stats_out;                                      // per layer and slot: (mean, variance)
+    float* thr_out;                                          // ... and the threshold, rounded to binary32
+    __device__ __forceinline__ float threshold(double mean, double var) const {
+        const double ratio = var / mean;
+        return (float)(ratio > C ? alpha + beta * ratio : alpha - beta * ratio);
+    }
+    __device__ __forceinline__ void write(size_t slot, double mean, double var) const {
+        stats_out[slot] = make_double2(mean, var);
+        thr_out[slot] = threshold(mean, var);
+    }
+};
+
+// What the masks' launch needs to merge the tiles' statistics by itself (RULE: layers of up to RULE_MAX_TILES tiles, tables of up to
+// RULE_MAX_TABLE over all slots): every wavefront does, one tile per lane, in k_layer_thr's order of additions, while its tile's loads are on their way.  That saves a launch of a few
+// workgroups: one chosen node, 20 k elements 19.0 -> 16.8 us a step, 400 k 23.6 -> 21.0, 3 M in 300 layers 60.5 -> 58.5; two, 400 k
+// 26.2 -> 24.3; four, 100 k 25.5 -> 24.0.  Three nodes of 3 M (880 tiles) lose, 74.8 -> 76.1: the registers that it takes.
+constexpr uint32_t RULE_MAX_TILES = WAVE, RULE_MAX_TABLE = 1024;
+struct TileStats {
+    const double2* of;                                       // slot by slot, the table's tiles
+    uint32_t tiles;
+    LayerRule rule;
+};
+__device__ __forceinline__ double wave_sum_f64(double v) {   // in all lanes
+#pragma unroll
+    for (int d = WAVE / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, WAVE);
+    return v;
+}
+__device__ __forceinline__ double2 merged_by_wave(const DevLayer& L, const double2* ts) {
+    const uint32_t lane = threadIdx.x & (WAVE - 1), ntiles = (L.n + TILE - 1) / TILE;
+    const bool have = lane < ntiles;
+    const double2 v = have ? ts[lane] : make_double2(0.0, 0.0);
+    const double n = (double)L.n, mean = wave_sum_f64(v.x) / n;
+    const double nt = (double)(have ? min(TILE, L.n - lane * TILE) : 1u), d = v.x / nt - mean;
+    return make_double2(mean, wave_sum_f64(have ? v.y + nt * (d * d) : 0.0) / n);
+}
+
 // The lane's elements whose score is above a threshold -> bits of nib.  The score is |r| / d, d = |w| + eps, rounded.  No divide where the
 // answer does not hang on the rounding: f = t * d - |r|, rounded once, has the sign of the exact value.  f > 0: |r| / d < t, and rounded it
 // is at most t.  f + |r| / 2^21 < 0: |r| / d exceeds t by more than a unit in t's last place, and rounded it does, too; this takes a t
@@ -116,11 +155,11 @@ __device__ __forceinline__ void add_above(const float (&rv)[CHUNKS][4], const fl
 // score, compare, encode, and hand over what is sent.  Layers that end within a tile's first chunk take one chunk only, which
 // spares them three quarters of the divides (and draws).  The nodes' values stay in registers until the common mask is known:
 // NL nodes per group of 256 threads (threadIdx.y), the groups' masks meet in LDS (meet, BLOCK words each; one group has none).
-template <uint32_t CHUNKS, int NL, int GROUPS>
+template <uint32_t CHUNKS, int NL, int GROUPS, bool RULE>
 __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __restrict__ wl, const DevLayer& L, uint32_t j,
                                           uint32_t t, uint32_t base, const uint32_t* __restrict__ leaders, uint32_t n_lead,
                                           uint32_t W, const float* __restrict__ thr, bool thr_per_slot, bool accumulate,
-                                          const RandomSel& rs, float eps, uint32_t* __restrict__ mw,
+                                          const TileStats& stats, const RandomSel& rs, float eps, uint32_t* __restrict__ mw,
                                           uint32_t* __restrict__ tile_counts, const ChosenSlots& S, uint32_t* part,
                                           uint32_t (*meet)[BLOCK]) {
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1);
@@ -131,14 +170,14 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
     Rest wv_rest, rv_rest[NL], gv_rest[NL];
     float* rl[NL];
     const float* gl[NL];
-    float th[NL];
+    float th[NL] = {};
     bool on[NL];
     uint32_t nib[CHUNKS] = {};
     request_tile<true>(wl, n, base, wv, wv_rest);
     auto request = [&](int s, uint32_t q, bool there) {      // node in slot q of the layer -> registers s
         const uint32_t p = chosen_at(leaders, n_lead, j, q, W);
         on[s] = there && !chosen_before(leaders, n_lead, j, q, W, p);
-        th[s] = thr_per_slot ? thr[(size_t)j * n_lead + q] : thr[j];
+        if (!RULE) th[s] = thr_per_slot ? thr[(size_t)j * n_lead + q] : thr[j];
         rl[s] = P.r[p] + L.offset;
         gl[s] = accumulate && P.g[p] ? P.g[p] + L.offset : nullptr;
         if (!on[s]) return;
@@ -158,6 +197,19 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
     // one group: exactly NL nodes, their slots constants
 #pragma unroll
     for (int s = 0; s < NL; ++s) request(s, GROUPS > 1 ? min(q0 + s, n_lead - 1u) : (uint32_t)s, GROUPS == 1 || q0 + s < n_lead);
+    if (RULE) {                                              // the loads are on their way
+#pragma unroll 1
+        for (uint32_t s = 0; s < NL && q0 + s < n_lead; ++s) {
+            const uint32_t p = chosen_at(leaders, n_lead, j, q0 + s, W);
+            uint32_t first = 0;                              // a slot that repeats an earlier node takes that node's tiles
+            while (chosen_at(leaders, n_lead, j, first, W) != p) ++first;
+            const double2 v = merged_by_wave(L, stats.of + (size_t)first * stats.tiles + L.tile_begin);
+            const float t0 = stats.rule.threshold(v.x, v.y);
+#pragma unroll
+            for (uint32_t x = 0; x < NL; ++x) th[x] = x == s ? t0 : th[x];
+            if (base == 0 && tid == 0) stats.rule.write((size_t)j * n_lead + q0 + s, v.x, v.y);
+        }
+    }
     settle_tile(n, base, wv, wv_rest);
 #pragma unroll
     for (int s = 0; s < NL; ++s) settle(s);
@@ -173,7 +225,7 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
                 for (int s = 0; s < NL; ++s) rv[s][u][c] = behind ? 0.0f : rv[s][u][c];
             }
     }
-    if (rs.on) {
+    if (!RULE && rs.on) {
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS; ++u) {
             const uint32_t i = base + u * CHUNK + tid * VEC;
@@ -263,12 +315,12 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
 // that (and against a workgroup per node and tile): 30 k elements 35 / 24 (31) and 47 / 27 (35), 1.2 M 69 / 43 (60) and 88 / 49
 // (70), 61 M 1374 / 1064 (1327) and 1618 / 1268 (1571).
 // ---------------------------------------------------------------------------
-template <int NL, int GROUPS>
+template <int NL, int GROUPS, bool RULE>
 __global__ __launch_bounds__(BLOCK * GROUPS) void k_leader_mask(WorkerPtrs P, const float* __restrict__ w,
                                                        const DevLayer* __restrict__ layers, uint32_t n_layers,
                                                        const uint32_t* __restrict__ leaders, uint32_t n_lead, uint32_t W,
                                                        const float* __restrict__ thr, bool thr_per_slot, bool accumulate,
-                                                       RandomSel rs, float eps, uint32_t* __restrict__ mask_out,
+                                                       TileStats stats, RandomSel rs, float eps, uint32_t* __restrict__ mask_out,
                                                        uint32_t* __restrict__ tile_counts, ChosenSlots S) {
     __shared__ uint32_t part[GROUPS * STAGE_WORDS];
     __shared__ uint32_t meet[GROUPS > 1 ? GROUPS : 1][BLOCK];
@@ -279,11 +331,15 @@ __global__ __launch_bounds__(BLOCK * GROUPS) void k_leader_mask(WorkerPtrs P, co
     const float* wl = w + L.offset;
     uint32_t* mw = mask_out + L.mask_begin;
     if (L.n - base <= CHUNK)
-        mask_tile<1, NL, GROUPS>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, rs, eps, mw, tile_counts,
-                                 S, part, meet);
+        mask_tile<1, NL, GROUPS, RULE>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, stats, rs, eps, mw,
+                                 tile_counts, S, part, meet);
     else
-        mask_tile<CHUNKS_PER_TILE, NL, GROUPS>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, rs, eps, mw,
-                                               tile_counts, S, part, meet);
+        mask_tile<CHUNKS_PER_TILE, NL, GROUPS, RULE>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, stats, rs, eps,
+                                               mw, tile_counts, S, part, meet);
+    if (RULE && threadIdx.y == 0)                            // layers without elements have no tile
+        for (uint32_t l = t * BLOCK + threadIdx.x; l < n_layers; l += gridDim.x * BLOCK)
+            if (layers[l].n == 0)
+                for (uint32_t q = 0; q < n_lead; ++q) stats.rule.write((size_t)l * n_lead + q, 0.0, 0.0);
 }
 
 // One tile of a chosen node in registers: residual (after adding the gradient and storing
@@ -378,9 +434,7 @@ __global__ __launch_bounds__(BLOCK) void k_leader_stats(WorkerPtrs P, const floa
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(BLOCK) void k_layer_thr(const DevLayer* __restrict__ layers, uint32_t tiles,
                                                      const uint32_t* __restrict__ leaders, uint32_t n_lead, uint32_t W,
-                                                     const double2* __restrict__ tile_stats, double alpha, double beta,
-                                                     double C, double2* __restrict__ stats_out,
-                                                     float* __restrict__ thr_out) {
+                                                     const double2* __restrict__ tile_stats, LayerRule rule) {
     __shared__ double slot[BLOCK / WAVE];
     const uint32_t j = blockIdx.x / n_lead;
     const uint32_t q = blockIdx.x - j * n_lead;
@@ -401,12 +455,7 @@ __global__ __launch_bounds__(BLOCK) void k_layer_thr(const DevLayer* __restrict_
         part += ts[t].y + nt * (d * d);
     }
     const double var = L.n ? block_sum_f64(part, slot) / n : 0.0;
-    if (threadIdx.x == 0) {
-        const double ratio = var / mean;
-        const double thr = ratio > C ? alpha + beta * ratio : alpha - beta * ratio;
-        stats_out[blockIdx.x] = make_double2(mean, var);
-        thr_out[blockIdx.x] = (float)thr;
-    }
+    if (threadIdx.x == 0) rule.write(blockIdx.x, mean, var);
 }
 
 // ---------------------------------------------------------------------------
