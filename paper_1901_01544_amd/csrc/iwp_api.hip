@@ -1180,13 +1180,20 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
                    z.tiles, leaders, n_lead, W, mask32, ws.tile_counts, count_out, max_pairs, ws.slots, idx_out, w, scale, sum_out);
         return IWP_OK;
     }
-    IWP_LAUNCH_BLOCK("k_tile_offsets", k_tile_offsets, 1u, OFFSETS_BLOCK, s, layers, z.n_layers, z.tiles, ws.tile_counts, max_pairs,
-                     ws.tile_pos, ws.lay_out, count_out);
+    const bool add_up = z.tiles && z.tiles <= ADD_UP_TILES;
+    if (!add_up)
+        IWP_LAUNCH_BLOCK("k_tile_offsets", k_tile_offsets, 1u, OFFSETS_BLOCK, s, layers, z.n_layers, z.tiles, ws.tile_counts, max_pairs,
+                         ws.tile_pos, ws.lay_out, count_out);
     if (z.tiles == 0) return IWP_OK;
     const uint32_t runs = takes_runs(z.tiles, z.n_layers);
-    const uint32_t few = runs ? few_mask_followers(z.tiles, z.n_layers, streaming) : 0u;
-    IWP_LAUNCH_FEW("k_follow_mask", k_follow_mask, W * z.tiles, few, s, P, layers, z.n_layers, z.tiles, runs, leaders, n_lead, W, mask32,
-               ws.tile_counts, ws.tile_pos, count_out, max_pairs, ws.slots, idx_out, ws.gathered);
+    uint32_t few = runs ? few_mask_followers(z.tiles, z.n_layers, streaming) : 0u;
+    if (few && add_up) few -= ADD_UP_TILES * (uint32_t)sizeof(uint32_t);         // what the kernel has more
+#define IWP_FOLLOW_MASK(ADD_UP)                                                                                              \
+    IWP_LAUNCH_FEW("k_follow_mask", k_follow_mask<ADD_UP>, W * z.tiles, few, s, P, layers, z.n_layers, z.tiles, runs, leaders, n_lead, \
+                   W, mask32, ws.tile_counts, ws.tile_pos, ws.lay_out, count_out, max_pairs, ws.slots, idx_out, ws.gathered)
+    if (add_up) IWP_FOLLOW_MASK(true);
+    else IWP_FOLLOW_MASK(false);
+#undef IWP_FOLLOW_MASK
     const uint32_t pair_blocks = std::min<uint32_t>((max_pairs + BLOCK - 1) / BLOCK, 8192u);
     IWP_LAUNCH("k_reduce_update_counted", k_reduce_update_counted, pair_blocks, s, R, static_mask, z.n_layers, leaders, n_lead, W,
                ws.lay_out, count_out, max_pairs, ws.gathered, idx_out, w, scale, sum_out, plan->flat_end);

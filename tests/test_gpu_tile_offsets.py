@@ -1,5 +1,5 @@
-"""Where the tiles' pairs start, found by every workgroup of the one launch (up to 256 tiles) or by a launch of its own (257): the counts
-that the caller sees with empty layers among the others and more layers than threads, and a total that just fits the caller's
+"""Where the tiles' pairs start, found by every workgroup of the one launch (up to 256 tiles) or of the workers' pass (up to 1024), or by a
+launch of its own: the counts that the caller sees with empty layers among the others and more layers than threads, and a total that just fits the caller's
 room, or exceeds it by one."""
 import numpy as np
 import pytest
@@ -13,7 +13,7 @@ W, TILE = 2, 4096
 
 
 @pytest.mark.parametrize("room", ["all", "fits", "one too few"])
-@pytest.mark.parametrize("tiles,empty", [(1, 0), (9, 700), (255, 3), (256, 0), (257, 3)])
+@pytest.mark.parametrize("tiles,empty", [(1, 0), (9, 700), (255, 3), (256, 0), (257, 700), (1024, 3), (1025, 0)])
 def test_counts(gpu_lib, tiles, empty, room):
     rng = np.random.default_rng(tiles)
     sizes = [1, 5 * TILE - 1, TILE] if tiles >= 9 else [TILE - 3]
