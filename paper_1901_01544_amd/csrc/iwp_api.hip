@@ -325,9 +325,10 @@ constexpr uint64_t KEEP_W_AND_R_MAX_BYTES = 40ull << 20, KEEP_W_MAX_BYTES = 64ul
 // in both 23.4 (1024: 24.5, 24.9); thresholds and pairs of 1 M 33.1 / 32.6, 32.3, 32.4.  Look 1: 8 M in one layer 55.6 / 54.3, one worker's
 // share of 25.6 M 135.3 / 133.3, a whole step of eight on it 479.3 / 476.9, 36 M 177.3 / 174.6; without a gradient 25.6 M 114.7 / 115.9, 50 M
 // 198 / 205; beyond 160 MiB a thousand tensors 2326 / 2345.  Look 2: 2.5 M 39.1 / 39.1, 4 M in 60 layers 40.3 / 40.8, 8 M in 40 62.8 /
-// 64.1.  The records' pass: 8 M in 40 layers 62.8 / 62.2, 15 M in 100 81.0 / 81.4.
+// 64.1.  The records' pass: 8 M in 40 layers 62.8 / 62.2, 15 M in 100 81.0 / 81.4.  Masks of up to three nodes: 20 k elements 11.8 / 11.0,
+// two nodes 14.7 / 13.5, 1 M, two nodes 24.7 / 23.6, with random selection 30.1 / 27.9, 10 M 109.3 / 108.0, three nodes 108.3 / 107.5.
 constexpr uint32_t WIDE_BLOCK = 512;
-constexpr uint32_t WIDE_STAGE_MAX_TILES = 512;
+constexpr uint32_t WIDE_STAGE_MAX_TILES = 512, WIDE_MASK_MAX_TILES = 2560;
 constexpr uint64_t WIDE_LEADERS_MAX_BYTES = FEW_LEADERS_MIN_BYTES;
 
 inline uint64_t buffer_bytes(const Table& T) { return (uint64_t)T.tiles * TILE * sizeof(float); }
@@ -401,8 +402,8 @@ int run_select(const Table& T, const Workspace& ws, const ResidualPtrs& R, const
     // Consecutive tiles per look-2 workgroup.  Where look 1's copies are complete only every STAGE_GROUP-th tile has work, and
     // few workgroups mean few flushes into a layer's one second-digit histogram; where they are not (a threshold among
     // zeros, a sample that misleads), tiles are read again, and few workgroups leave the chip idle.  Up to 32767 tiles at
-    // least about a thousand workgroups, of three tiles at most; beyond, as many as the chip holds at once (1280: five per
-    // compute unit at 91 registers), of 64 tiles at most.  Threshold among zeros, selection alone, against 64 tiles from
+    // least about a thousand workgroups, of three tiles at most; beyond, about as many as the chip holds at once (1280: five per
+    // compute unit), of 64 tiles at most.  Threshold among zeros, selection alone, against 64 tiles from
     // 4096 tiles on and 4 below: one layer of 3 M elements 181 -> 92 us, 10 M 371 -> 158, 30 M 641 -> 319, 60 M 794 -> 580,
     // 150 M 1588 -> 1330; complete copies within 3 % from 1 M to 300 M (keep 0.2 of 10 M elements 192 -> 150).  Five tiles
     // instead of three: 326, 586; candidates crowded into blocks of nine tiles in 160 layers of 25 M 241 instead of 230;
@@ -1153,21 +1154,26 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
             IWP_LAUNCH("k_layer_thr", k_layer_thr, z.n_layers * n_lead, s, layers, z.tiles, leaders, n_lead, W, ws.tile_stats, lr);
         thr = rule->thr_out;
     }
-#define IWP_MASK_AS(NL, GROUPS, RULE)                                                                                        \
-    IWP_LAUNCH_BLOCK("k_leader_mask", (k_leader_mask<NL, GROUPS, RULE>), z.tiles, dim3(BLOCK, GROUPS), s, P, w, layers, z.n_layers, \
-                     leaders, n_lead, W, thr, rule != nullptr, rule == nullptr, stats, rs, eps, mask32, ws.tile_counts, ws.slots)
-#define IWP_MASK(NL, GROUPS)                       \
-    do {                                           \
-        if (stats.of) IWP_MASK_AS(NL, GROUPS, true); \
-        else IWP_MASK_AS(NL, GROUPS, false);       \
+#define IWP_MASK_AS(NL, GROUPS, RULE, THREADS)                                                                               \
+    IWP_LAUNCH_BLOCK("k_leader_mask", (k_leader_mask<NL, GROUPS, RULE, THREADS>), z.tiles, dim3(THREADS, GROUPS), s, P, w, layers, \
+                     z.n_layers, leaders, n_lead, W, thr, rule != nullptr, rule == nullptr, stats, rs, eps, mask32, ws.tile_counts, \
+                     ws.slots)
+#define IWP_MASK(NL, GROUPS, THREADS)                       \
+    do {                                                    \
+        if (stats.of) IWP_MASK_AS(NL, GROUPS, true, THREADS); \
+        else IWP_MASK_AS(NL, GROUPS, false, THREADS);       \
     } while (0)
     if (z.tiles) {
-        if (n_lead == 1) IWP_MASK(1, 1);
-        else if (n_lead == 2) IWP_MASK(2, 1);
-        else if (n_lead == 3) IWP_MASK(3, 1);
-        else if (n_lead == 4) IWP_MASK(2, 2);
-        else if (n_lead <= 6) IWP_MASK(2, 3);
-        else IWP_MASK(2, 4);
+        const bool wide = z.tiles <= WIDE_MASK_MAX_TILES;
+        if (n_lead == 1 && wide) IWP_MASK(1, 1, WIDE_BLOCK);
+        else if (n_lead == 1) IWP_MASK(1, 1, BLOCK);
+        else if (n_lead == 2 && wide) IWP_MASK(2, 1, WIDE_BLOCK);
+        else if (n_lead == 2) IWP_MASK(2, 1, BLOCK);
+        else if (n_lead == 3 && wide) IWP_MASK(3, 1, WIDE_BLOCK);
+        else if (n_lead == 3) IWP_MASK(3, 1, BLOCK);
+        else if (n_lead == 4) IWP_MASK(2, 2, BLOCK);
+        else if (n_lead <= 6) IWP_MASK(2, 3, BLOCK);
+        else IWP_MASK(2, 4, BLOCK);
     }
 #undef IWP_MASK
 #undef IWP_MASK_AS

@@ -154,14 +154,16 @@ __device__ __forceinline__ void add_above(const float (&rv)[CHUNKS][4], const fl
 // The tile that starts at element `base` of its layer, CHUNKS chunks of it, for all chosen nodes of the layer: accumulate,
 // score, compare, encode, and hand over what is sent.  Layers that end within a tile's first chunk take one chunk only, which
 // spares them three quarters of the divides (and draws).  The nodes' values stay in registers until the common mask is known:
-// NL nodes per group of 256 threads (threadIdx.y), the groups' masks meet in LDS (meet, BLOCK words each; one group has none).
-template <uint32_t CHUNKS, int NL, int GROUPS, bool RULE>
+// NL nodes per group of THREADS threads (threadIdx.y), the groups' masks meet in LDS (meet, BLOCK words each; one group has none).
+template <uint32_t CHUNKS, int NL, int GROUPS, bool RULE, uint32_t THREADS>
 __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __restrict__ wl, const DevLayer& L, uint32_t j,
                                           uint32_t t, uint32_t base, const uint32_t* __restrict__ leaders, uint32_t n_lead,
                                           uint32_t W, const float* __restrict__ thr, bool thr_per_slot, bool accumulate,
                                           const TileStats& stats, const RandomSel& rs, float eps, uint32_t* __restrict__ mw,
                                           uint32_t* __restrict__ tile_counts, const ChosenSlots& S, uint32_t* part,
                                           uint32_t (*meet)[BLOCK]) {
+    constexpr uint32_t SPAN = THREADS * VEC;                 // elements of a chunk
+    static_assert(GROUPS == 1 || THREADS == BLOCK, "groups are of BLOCK threads");
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1);
     const uint32_t group = GROUPS > 1 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.y) : 0u;   // the same in a wavefront
     const uint32_t q0 = group * NL;
@@ -173,7 +175,7 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
     float th[NL] = {};
     bool on[NL];
     uint32_t nib[CHUNKS] = {};
-    request_tile<true>(wl, n, base, wv, wv_rest);
+    request_tile<true, THREADS>(wl, n, base, wv, wv_rest);
     auto request = [&](int s, uint32_t q, bool there) {      // node in slot q of the layer -> registers s
         const uint32_t p = chosen_at(leaders, n_lead, j, q, W);
         on[s] = there && !chosen_before(leaders, n_lead, j, q, W, p);
@@ -181,14 +183,14 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
         rl[s] = P.r[p] + L.offset;
         gl[s] = accumulate && P.g[p] ? P.g[p] + L.offset : nullptr;
         if (!on[s]) return;
-        request_tile<true>(rl[s], n, base, rv[s], rv_rest[s]);
-        if (gl[s]) request_tile<true>(gl[s], n, base, gv[s], gv_rest[s]);
+        request_tile<true, THREADS>(rl[s], n, base, rv[s], rv_rest[s]);
+        if (gl[s]) request_tile<true, THREADS>(gl[s], n, base, gv[s], gv_rest[s]);
     };
     auto settle = [&](int s) {
         if (!on[s]) return;
-        settle_tile(n, base, rv[s], rv_rest[s]);
+        settle_tile<THREADS>(n, base, rv[s], rv_rest[s]);
         if (!gl[s]) return;
-        settle_tile(n, base, gv[s], gv_rest[s]);
+        settle_tile<THREADS>(n, base, gv[s], gv_rest[s]);
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
@@ -210,16 +212,16 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
             if (base == 0 && tid == 0) stats.rule.write((size_t)j * n_lead + q0 + s, v.x, v.y);
         }
     }
-    settle_tile(n, base, wv, wv_rest);
+    settle_tile<THREADS>(n, base, wv, wv_rest);
 #pragma unroll
     for (int s = 0; s < NL; ++s) settle(s);
-    const bool ragged = base + CHUNKS * CHUNK > n;           // uniform
+    const bool ragged = base + CHUNKS * SPAN > n;           // uniform
     if (ragged) {                                            // behind the layer's end: a score that is far from a threshold
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS; ++u)
 #pragma unroll
             for (uint32_t c = 0; c < VEC; ++c) {
-                const bool behind = base + u * CHUNK + tid * VEC + c >= n;
+                const bool behind = base + u * SPAN + tid * VEC + c >= n;
                 wv[u][c] = behind ? 1.0f : wv[u][c];
 #pragma unroll
                 for (int s = 0; s < NL; ++s) rv[s][u][c] = behind ? 0.0f : rv[s][u][c];
@@ -228,7 +230,7 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
     if (!RULE && rs.on) {
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
+            const uint32_t i = base + u * SPAN + tid * VEC;
             uint32_t word4[4];
             philox4x32_10(i >> 2, j, rs.step0, rs.step1, rs.key0, rs.key1, word4);   // i is a multiple of 4
 #pragma unroll
@@ -251,7 +253,7 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
     if (ragged) {
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS; ++u) {
-            const uint32_t i = base + u * CHUNK + tid * VEC;
+            const uint32_t i = base + u * SPAN + tid * VEC;
             nib[u] &= i < n ? 0xFu >> (VEC - min(n - i, (uint32_t)VEC)) : 0u;
         }
     }
@@ -272,11 +274,11 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
     for (uint32_t u = 0; u < CHUNKS; ++u) {
         // eight lanes (32 consecutive elements) make one word of the encoded mask
         word[u] = or_of_8_lanes(nib[u] << (4u * (lane & 7u)));
-        const uint32_t widx = base / 32 + u * (CHUNK / 32) + (tid >> 3);
+        const uint32_t widx = base / 32 + u * (SPAN / 32) + (tid >> 3);
         if (group == 0 && (lane & 7u) == 0u && widx < nwords) mw[widx] = word[u];
         count[u] = __popc(nib[u]);
     }
-    const uint32_t total = tile_ranks(count, first, part + group * STAGE_WORDS);
+    const uint32_t total = tile_ranks<THREADS>(count, first, part + group * STAGE_WORDS);
     if (group == 0 && tid == 0) tile_counts[t] = total;
     const bool hand_over = total <= S.cap;                   // otherwise the next pass fetches and clears them
 #pragma unroll
@@ -295,7 +297,7 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
         // (single elements, partial lines, take 63 us instead of 49 where one of 59 of 25.6 M elements is sent)
 #pragma unroll
         for (uint32_t u = 0; u < CHUNKS; ++u)
-            if (gl[s] || (hand_over && word[u])) store_quad<true>(rl[s], base + u * CHUNK + tid * VEC, n, rv[s][u]);
+            if (gl[s] || (hand_over && word[u])) store_quad<true>(rl[s], base + u * SPAN + tid * VEC, n, rv[s][u]);
     }
 }
 
@@ -309,14 +311,15 @@ __device__ __forceinline__ void mask_tile(const WorkerPtrs& P, const float* __re
 // once per node and left a mask for each, to be OR-ed and counted in a launch of its own (308 + 9 us), and the nodes' sent
 // values were read and cleared pair by pair behind everything else (the update 177 us, now 66).  Whole steps: that table
 // 1208 -> 1077 us, one node of 25.6 M elements with a line per layer 554 -> 522, three of 1.1 M 38 -> 29 (three launches less).
-// Up to three nodes are one group's (59, 97 and 134 registers); more are taken two to a group, by workgroups of two to four
+// Up to three nodes are one group's (59, 96 and 133 registers of 256 threads; 36, 56 and 78 of 512 on small tables, see WIDE_BLOCK in
+// iwp_api.hip); more are taken two to a group, by workgroups of two to four
 // groups, which read the weights once each.  One group that takes them one after the other, storing each and fetching
 // its sent values again, had every node's loads wait for the one before: eight workers, four and eight nodes, us a step, against
 // that (and against a workgroup per node and tile): 30 k elements 35 / 24 (31) and 47 / 27 (35), 1.2 M 69 / 43 (60) and 88 / 49
 // (70), 61 M 1374 / 1064 (1327) and 1618 / 1268 (1571).
 // ---------------------------------------------------------------------------
-template <int NL, int GROUPS, bool RULE>
-__global__ __launch_bounds__(BLOCK * GROUPS) void k_leader_mask(WorkerPtrs P, const float* __restrict__ w,
+template <int NL, int GROUPS, bool RULE, uint32_t THREADS>
+__global__ __launch_bounds__(THREADS * GROUPS) void k_leader_mask(WorkerPtrs P, const float* __restrict__ w,
                                                        const DevLayer* __restrict__ layers, uint32_t n_layers,
                                                        const uint32_t* __restrict__ leaders, uint32_t n_lead, uint32_t W,
                                                        const float* __restrict__ thr, bool thr_per_slot, bool accumulate,
@@ -330,14 +333,14 @@ __global__ __launch_bounds__(BLOCK * GROUPS) void k_leader_mask(WorkerPtrs P, co
     const uint32_t base = (t - L.tile_begin) * TILE;
     const float* wl = w + L.offset;
     uint32_t* mw = mask_out + L.mask_begin;
-    if (L.n - base <= CHUNK)
-        mask_tile<1, NL, GROUPS, RULE>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, stats, rs, eps, mw,
+    if (L.n - base <= THREADS * VEC)
+        mask_tile<1, NL, GROUPS, RULE, THREADS>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, stats, rs, eps, mw,
                                  tile_counts, S, part, meet);
     else
-        mask_tile<CHUNKS_PER_TILE, NL, GROUPS, RULE>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, stats, rs, eps,
+        mask_tile<TILE / (THREADS * VEC), NL, GROUPS, RULE, THREADS>(P, wl, L, j, t, base, leaders, n_lead, W, thr, thr_per_slot, accumulate, stats, rs, eps,
                                                mw, tile_counts, S, part, meet);
     if (RULE && threadIdx.y == 0)                            // layers without elements have no tile
-        for (uint32_t l = t * BLOCK + threadIdx.x; l < n_layers; l += gridDim.x * BLOCK)
+        for (uint32_t l = t * THREADS + threadIdx.x; l < n_layers; l += gridDim.x * THREADS)
             if (layers[l].n == 0)
                 for (uint32_t q = 0; q < n_lead; ++q) stats.rule.write((size_t)l * n_lead + q, 0.0, 0.0);
 }
@@ -461,7 +464,7 @@ __global__ __launch_bounds__(BLOCK) void k_layer_thr(const DevLayer* __restrict_
 // ---------------------------------------------------------------------------
 // The tiles' counts -> where each tile's pairs start in the packed outputs (layers in table order), where each layer's do
 // (lay_out[j], lay_out[n_layers] = total), the counts the caller sees, and the capacity check.  One workgroup, four quads of
-// tiles per lane and round: a chain of one load, a scan and a store per 16384 tiles (5.3 us; sixteen dwords per lane, not
+// tiles per lane and round (tables of more than ADD_UP_TILES tiles; on others the workgroups of the next launch add up): a chain of one load, a scan and a store per 16384 tiles (5.3 us; sixteen dwords per lane, not
 // coalesced, 15.5).  Both arrays hold whole 256-byte blocks.
 // ---------------------------------------------------------------------------
 constexpr int OFFSETS_BLOCK = 1024;
