@@ -857,31 +857,41 @@ __global__ __launch_bounds__(BLOCK) void k_fold_counts(const DevLayer* __restric
 // A RAW tile read again by one wavefront, RAW_AHEAD rounds of 256 elements in flight together, since neither k_refine_tiles nor look 2
 // has left its lines in this die's cache.  body(packed, key, val, i): the lane's four elements of a round, i the first one's position;
 // packed: of those above the threshold, in the high half of those tying with it; key[q] is NOT_AN_ELEMENT where position i + q is not
-// the lane's.  Every lane reads whole quads, at the layer's end the last one (a RAW tile has more than 64 elements), and leaves
+// the lane's.  Every lane reads whole quads, at the layer's end the last one, and leaves
 // out what comes before its own: loads in branches waited for each other (a layer of 48 tiles, mostly zeros, kept at 0.2: k_count 22.2 -> 18.3 us,
-// k_write 25.1 -> 17.1).
+// k_write 25.1 -> 17.1).  Layers of fewer elements than a quad, which k_stage_records can leave RAW, are read element by element.
 constexpr uint32_t RAW_ROUND = WAVE * VEC, RAW_AHEAD = 4;
 template <class Body>
 __device__ __forceinline__ void read_raw_tile(const float* rl, const float* wl, uint32_t n, uint32_t first, float eps, uint32_t shift,
                                               uint32_t thr, Body body) {
     const uint32_t lane = threadIdx.x & (WAVE - 1);
+    const uint32_t last = n >= VEC ? n - VEC : 0u;           // the layer's last quad
 #pragma unroll 1
     for (uint32_t c = 0; c < TILE && first + c < n; c += RAW_AHEAD * RAW_ROUND) {
         v4f rv[RAW_AHEAD], wv[RAW_AHEAD];
+        if (n >= VEC) {                                      // uniform
 #pragma unroll
-        for (uint32_t a = 0; a < RAW_AHEAD; ++a) {
-            const uint32_t at = min(first + c + a * RAW_ROUND + lane * VEC, n - VEC);
-            rv[a] = load_v4<false>(rl + at);
-            wv[a] = load_v4<false>(wl + at);
+            for (uint32_t a = 0; a < RAW_AHEAD; ++a) {
+                const uint32_t at = min(first + c + a * RAW_ROUND + lane * VEC, last);
+                rv[a] = load_v4<false>(rl + at);
+                wv[a] = load_v4<false>(wl + at);
+            }
+        } else {
+            const uint32_t e1 = min(1u, n - 1u), e2 = n - 1u;
+#pragma unroll
+            for (uint32_t a = 0; a < RAW_AHEAD; ++a) {
+                rv[a] = v4f{rl[0], rl[e1], rl[e2], 0.0f};
+                wv[a] = v4f{wl[0], wl[e1], wl[e2], 1.0f};
+            }
         }
 #pragma unroll
         for (uint32_t a = 0; a < RAW_AHEAD; ++a) {
-            const uint32_t i = first + c + a * RAW_ROUND + lane * VEC, at = min(i, n - VEC);
+            const uint32_t i = first + c + a * RAW_ROUND + lane * VEC, at = min(i, last);
             const float val[4] = {rv[a].x, rv[a].y, rv[a].z, rv[a].w}, wgt[4] = {wv[a].x, wv[a].y, wv[a].z, wv[a].w};
             uint32_t key[4], packed = 0;
 #pragma unroll
             for (uint32_t q = 0; q < VEC; ++q) {
-                key[q] = at + q >= i ? shifted(score_key(val[q], wgt[q], eps), shift) : NOT_AN_ELEMENT;
+                key[q] = at + q >= i && at + q < n ? shifted(score_key(val[q], wgt[q], eps), shift) : NOT_AN_ELEMENT;
                 packed += key[q] == NOT_AN_ELEMENT ? 0u : key[q] > thr ? 1u : key[q] == thr ? 0x10000u : 0u;
             }
             body(packed, key, val, at);
