@@ -152,11 +152,6 @@ inline uint32_t h0_copies_of(uint32_t n, uint32_t k, uint32_t flushes = FLUSHES_
     return c;
 }
 
-// Units (see tie_record) of a layer, and how many of their records do not fit into its first-digit histograms.
-inline uint32_t records_apart(uint32_t n, uint32_t k, uint32_t copies, bool per_tile) {
-    const uint32_t units = k == 0 ? 0u : per_tile ? tiles_of(n) : stiles_of(n), inside = records_inside(copies);
-    return units > inside ? units - inside : 0u;
-}
 // Plans whose slots hold at most RECORD_MAX_CAP entries (an eighth of the elements kept) and whose layers at most RECORD_MAX_STILES
 // super-tiles go by records.  Fuller slots are read twice by k_split: 25 M elements kept at 0.1 gain 0 to 1 %, small tables still 8.  Longer
 // layers have every workgroup add up thousands of records; with a launch that does so once, 400 M elements kept at 1/1000
@@ -164,6 +159,14 @@ inline uint32_t records_apart(uint32_t n, uint32_t k, uint32_t copies, bool per_
 constexpr uint32_t RECORD_MAX_CAP = 64 + 3 * TILE / 8, RECORD_MAX_STILES = 4096;
 inline bool goes_by_records(uint32_t max_cap, uint32_t max_stiles) {
     return max_cap <= RECORD_MAX_CAP && max_stiles <= RECORD_MAX_STILES;
+}
+// Units (see tie_record) of a layer, and how many of their records do not fit into its first-digit histograms.  Longer layers and
+// fuller slots, which do not go by records, count as the longest layer that does, 4 MB at most, so that a workspace that fits
+// them fits shorter and sparser ones.
+inline uint32_t records_apart(uint32_t n, uint32_t k, uint32_t copies, bool per_tile) {
+    const uint32_t units = k == 0 ? 0u : per_tile ? tiles_of(n) : std::min(stiles_of(n), RECORD_MAX_STILES);
+    const uint32_t inside = records_inside(copies);
+    return units > inside ? units - inside : 0u;
 }
 
 struct Sizes {                // everything the workspace layout depends on
