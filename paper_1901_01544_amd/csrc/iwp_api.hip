@@ -792,10 +792,11 @@ int iwp_plan_create(const iwp_layer* layers, uint32_t n_layers, iwp_plan** plan_
     plan->n_long = n_long;
     plan->all_dense = all_dense;
     plan->long_sparse = is_long_sparse(max_cap, max_stiles);
-    // roomy slots, or what larger tables hold in reserve for them, unless the library's static scratch would no longer do
+    // roomy slots and records, or what larger tables hold in reserve for them, unless the library's static scratch would no longer do
     Sizes roomier = plan->z;
     roomier.slots += any_k ? roomy_reserve(tiles) : 0u;
     roomier.records = any_k ? std::max<uint64_t>(lay_out_records(false), record_reserve(tiles)) : 0u;
+    if (!goes_by_records(max_cap, max_stiles) && carve(nullptr, roomier).bytes > IWP_STATIC_SCRATCH_BYTES) roomier.records = 0;
     if (carve(nullptr, roomier).bytes <= IWP_STATIC_SCRATCH_BYTES) {
         plan->z = roomier;
         plan->look_twice = looks_twice(tiles, n_layers);

@@ -1,5 +1,5 @@
-"""Bytes of the workspace: what fits a layer fits shorter and sparser ones, and layers too long for records hold room for no more of them
-than the longest layer that has them."""
+"""Bytes of the workspace: what fits a layer fits shorter and sparser ones, layers too long for records hold room for no more of them
+than the longest layer that has them, and tables that do not go by records do not lose the second look to their room."""
 import pytest
 
 TILE, STILE = 4096, 8 * 4096
@@ -26,3 +26,41 @@ def test_no_records_beyond_the_longest_layer_that_has_them(share):
     n = n0 + more * STILE
     grown = iwp.workspace_bytes(n, n // share) - iwp.workspace_bytes(n0, n0 // share)
     assert grown <= more * stile + 16 * 256                     # each array is whole 256-byte blocks
+
+
+@pytest.mark.gpu
+def test_second_look_up_to_the_static_scratch(gpu_lib):
+    """Everything kept (no records), 1024 tiles, as many layers as the slots and their reserve leave room for in the static scratch: the
+    tiles' own third digit is launched, two layers later it is not."""
+    import torch
+    iwp = gpu_lib
+    tiles = 1024
+    n = tiles * TILE
+    r, w = torch.rand(n, device="cuda"), torch.ones(n, device="cuda")
+    idx, val = torch.empty(n, dtype=torch.int32, device="cuda"), torch.empty(n, device="cuda")
+
+    def plan_of(layers):
+        sizes = [(tiles - layers + 1) * TILE] + [TILE] * (layers - 1)
+        rows, at = [], 0
+        for m in sizes:
+            rows.append((at, m, m, at))
+            at += m
+        return iwp.Plan(rows)
+
+    def looks_twice(layers):
+        plan = plan_of(layers)
+        ws = torch.empty(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+        idx.fill_(-1)
+        iwp.timing_enable("k_refine_tiles")
+        iwp.compress_segmented(plan, w, [None], [r], None, 1e-8, idx, val, None, ws)
+        torch.cuda.synchronize()
+        launches = iwp.timing_collect()[1]
+        assert torch.equal(idx, torch.arange(n, dtype=torch.int32, device="cuda")) and torch.equal(val, r)
+        return launches > 0
+
+    bytes_of = {layers: plan_of(layers).workspace_bytes for layers in (590, 600)}       # without the reserve
+    each = (bytes_of[600] - bytes_of[590]) / 10
+    room = iwp.IWP_STATIC_SCRATCH_BYTES - 1024 * 320 * 12 - 1024                         # 1024: blocks of 256 bytes
+    last = 590 - int(-(-(bytes_of[590] - room) // each))
+    assert 540 < last < 588
+    assert looks_twice(last) and not looks_twice(last + 2)
