@@ -1168,13 +1168,14 @@ static int run_threshold_step(const iwp_plan* plan, float* w, const float* const
         else IWP_MASK_AS(NL, GROUPS, false, THREADS);       \
     } while (0)
     if (z.tiles) {
+        static_assert(RULE_MAX_TABLE <= WIDE_MASK_MAX_TILES, "the rule is merged by workgroups of WIDE_BLOCK, or by groups");
         const bool wide = z.tiles <= WIDE_MASK_MAX_TILES;
         if (n_lead == 1 && wide) IWP_MASK(1, 1, WIDE_BLOCK);
-        else if (n_lead == 1) IWP_MASK(1, 1, BLOCK);
+        else if (n_lead == 1) IWP_MASK_AS(1, 1, false, BLOCK);
         else if (n_lead == 2 && wide) IWP_MASK(2, 1, WIDE_BLOCK);
-        else if (n_lead == 2) IWP_MASK(2, 1, BLOCK);
+        else if (n_lead == 2) IWP_MASK_AS(2, 1, false, BLOCK);
         else if (n_lead == 3 && wide) IWP_MASK(3, 1, WIDE_BLOCK);
-        else if (n_lead == 3) IWP_MASK(3, 1, BLOCK);
+        else if (n_lead == 3) IWP_MASK_AS(3, 1, false, BLOCK);
         else if (n_lead == 4) IWP_MASK(2, 2, BLOCK);
         else if (n_lead <= 6) IWP_MASK(2, 3, BLOCK);
         else IWP_MASK(2, 4, BLOCK);
