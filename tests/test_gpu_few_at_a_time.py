@@ -28,6 +28,27 @@ def test_steps(gpu_lib, W, sizes, share):
         assert_step_equal(gs.download(), w, r_ref, *ref, ps.layers, tag="W=%d step %d" % (W, t))
 
 
+@pytest.mark.parametrize("W,sizes,share", [(3, [300 * TILE + 5, 9 * TILE], 40), (2, [300 * TILE + 5, 9 * TILE], 40),
+                                           (3, [300 * TILE, 9 * TILE], 16), (3, [300 * TILE, 9 * TILE], 15),
+                                           (3, [300 * TILE, 9 * TILE], 32), (3, [300 * TILE, 9 * TILE], 31),
+                                           (5, [2 * TILE] * 130 + [9 * TILE], 33), (5, [TILE - 1] * 300 + [9 * TILE], 33)])
+def test_steps_of_more_tiles_than_one_launch_takes(gpu_lib, W, sizes, share):
+    """From 257 tiles on the followers and the update have launches of their own, which the rules are about."""
+    ps = wl.custom_set([(n, n // share) for n in sizes], W=W, seed=share, align=1, start=3)
+    w = wl.gen_weights(ps)
+    sets = [wl.gen_gradient(ps, s) for s in range(W)]
+    gs = GpuSet(gpu_lib, ps, w, sets, fused=True, hint="none")
+    r_ref = [np.zeros(ps.flat, np.float32) for _ in range(W)]
+    for t, kernel in enumerate(("k_follow_gather", "k_reduce_update")):
+        lead = wl.leaders(ps, t)
+        ids = [(p + t) % W for p in range(W)]
+        ref = oracle.step(w, [sets[i] for i in ids], r_ref, ps.rows(), lead, float(ps.eps), float(ps.scale))
+        gpu_lib.timing_enable(kernel)
+        gs.step(ids, lead)
+        assert gpu_lib.timing_collect()[1] == 1
+        assert_step_equal(gs.download(), w, r_ref, *ref, ps.layers, tag="W=%d step %d" % (W, t))
+
+
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("tiles", [1275, 1280, 1281])             # 16 workers: 20480 workgroups at the line
 def test_threshold_step(gpu_lib, tiles):

@@ -1,6 +1,7 @@
-"""Layers on both sides of 4096 super-tiles, beyond which counts and pairs are found by a wavefront per super-tile and the counts are
-scanned by a launch of their own: slots of few and of many entries, tiles of equal scores at, above and below the threshold, tiles
-that overflow their slots, a short layer behind the long one.  Weights of one and no eps: the score is |r| itself."""
+"""Layers on both sides of 4096 super-tiles, beyond which the super-tiles' counts are scanned by a launch of their own: slots of few and of
+many entries, tiles of equal scores at, above and below the threshold, tiles that overflow their slots, behind the long one a short layer
+that keeps too many for the kernels that take a super-tile by a wavefront (test_gpu_long_layers_led.py has those).  Weights of one and no eps: the
+score is |r| itself."""
 import numpy as np
 import pytest
 
