@@ -318,7 +318,9 @@ constexpr uint32_t leader_grid(uint32_t tiles, uint32_t stiles) {
 // states in turn / one state alone, us a call of one worker, r and w kept, w kept, nothing kept: 8 M elements 56.7 / 58.5, 57.6 /
 // 59.4, 58.9 / 60.7; 15 M 97.0 / 83.9, 87.7 / 85.7, 88.1 / 87.8; 25.6 M 161 / 124.6, 142.7 / 124.4, 134.2 / 129.1; 36 M 208 / 166, 184 /
 // 155.6, 176 / 163; whole steps of eight workers, w kept, nothing: 25.6 M 484 / 461, 477 / 466, 36 M 655 / 629, 650 / 632.  What one
-// state alone gains beyond 64 MiB is what is left in the cache from call to call, which a training step in between replaces.
+// state alone gains beyond 64 MiB is what is left in the cache from call to call.  With 300 MB (1.2 GB) of other copies between the calls, as
+// a training step has them, on one state, w kept, nothing: 17 M 104.9, 103.3 (106.9, 103.7), 25.6 M 144.2, 139.9 (143.5, 139.3), 36 M
+// 181.2, 176.5 (179.6, 175.2), steps of eight workers 17 M 337, 334, 25.6 M 484.5, 478.5, 36 M 661, 651.
 // Without a gradient (a selection) nothing is written, and the pairs' pass reads again what was read: 25.6 M 114.9 with w kept, 116.6.
 constexpr uint64_t KEEP_W_AND_R_MAX_BYTES = 40ull << 20, KEEP_W_MAX_BYTES = 64ull << 20, KEEP_W_MAX_BYTES_READ_ONLY = 160ull << 20;
 

@@ -437,7 +437,7 @@ __global__ __launch_bounds__(THREADS, PICK ? 4 : 5) void k_stage(ResidualPtrs R,
                 if ((key >> digit_shift(0)) == b1) atomicAdd(&lh[(key >> digit_shift(1)) & (HIST1 - 1)], 1u);
             });
         } else if (do_slots) for (uint32_t g0 = 0; g0 < n_slots; g0 += STAGE_GROUP) {
-            // a wavefront takes every fourth tile of the group; the counts and the first 256 entries of all
+            // a wavefront takes every fourth tile of the group (THREADS / 64th); the counts and the first 256 entries of all
             // its tiles are requested before any of them is used
             const uint32_t from = lt + g0, last = min(from + STAGE_GROUP, lt + n_slots);
             constexpr uint32_t MINE = STAGE_GROUP / (THREADS / WAVE);
@@ -678,7 +678,7 @@ __global__ __launch_bounds__(BLOCK) void k_refine2(ResidualPtrs R, const float* 
 // The third digit on tables without a sampled mark (LOOK_TWICE_TILES), one workgroup per tile.  There look 2 copies whole bins of
 // the first digit, and where scores crowd into one bin every tile overflows its slot.  Such a tile is read a third time, from the
 // caches, but by this launch alone: the 22-bit prefix is known here and leaves little more than is kept, so what is at or above it
-// goes into the slot after all, and k_count and k_write find copies (a tile that still overflows, by ties, stays RAW).
+// goes into the slot after all, and k_split (or k_count and k_write) finds copies (a tile that still overflows, by ties, stays RAW).
 // Bound by latency, and for such tiles by the divides: a workgroup per tile puts them on all compute units, where k_refine2's
 // workgroup of a super-tile has eight tiles in turn.  One layer of 1 M elements kept at 1/64, us a call, k_refine2 / this: scores
 // inside one bin 104 / 40 (45.5 when such layers were sampled), normally distributed 31.0 / 30.0 (38.4); kept at 0.001, an

@@ -1,14 +1,16 @@
 // Tables of small layers: the leader's whole part of a step -- accumulate, score, select, split -- in one launch, one
 // workgroup per layer with the layer in registers.
 //
-// Latency bound: a small layer's seven launches (k_init ... k_write) take about 4 us each, whatever the layer holds, and
-// every one reads back what the one before has written.  Here the layer is read once and the three digits of the k-th
-// largest key are found by three histograms in LDS.  One layer of 1000 elements: 30.6 -> 10.8 us a call, now 7.7.
+// Latency bound: a small layer's five launches (k_init ... k_split; seven up to k_write when this was first measured) take about 4 us
+// each, whatever the layer holds, and every one reads back what the one before has written.  Here the layer is read once and the three
+// digits of the k-th largest key are found by three histograms in LDS.  One layer of 1000 elements: 30.6 -> 10.8 us a call, now 7.7; the
+// times here are of events around every call, which add 2 to 3 us: of calls in a row 5.6 (the launch alone 5.3).
 // A lone workgroup is bound by the instructions its wavefronts issue, one in four cycles, and by barriers: 2000 instructions in a row
 // take 3.4 us.  So: everything that is the same for all lanes in scalar registers, chunks behind the layer's end skipped by a
 // scalar branch, elements counted without branches, only the kept ones of a quad walked through, two barriers a digit (small_pick)
 // where there were five.  us a call, before / now: 1000 elements 10.2 / 7.7, 4096 12.6 / 10.8, 16384 15.8 / 14.3, 20000 24.1 / 17.2,
-// 32768 29.5 / 22.1 (all kept 38.0 / 33.9); whole steps, four workers, 300 layers of 300 18.5 / 14.6, 1000 of 16000 186 / 157.
+// 32768 29.5 / 22.1 (all kept 38.0 / 33.9), of calls in a row 8.0 / 5.6, 10.4 / 8.7, 13.7 / 12.1, 21.3 / 14.5,
+// 25.8 / 19.0 (34.5 / 30.5); whole steps, four workers, 300 layers of 300 18.5 / 14.6, 1000 of 16000 186 / 157.
 // Layers of one tile take a workgroup of 4 wavefronts, eight of which a compute unit holds, longer ones 16 wavefronts,
 // two or (beyond 16384 elements) one a unit; a large table of both takes a launch for each kind.  3000 layers of 300
 // elements 119 us by 16 wavefronts, 30 by 4, 94 to 123 by the long route; 6000 ragged ones of 1 M elements, the longest

@@ -144,9 +144,12 @@ __device__ __forceinline__ void follow_tile_from(uint32_t head, const float* g0,
 // cache is written back during whatever comes next.
 // clear: the histogram is cleared first, once the tile's loads are on their way; before them it kept every
 // workgroup from its loads (look 1 of one layer of 1 M elements 13.6 -> 12.8 us, thresholds of 25.6 M 51.4 -> 50.3).
-// What a wavefront issues counts: on small tables it is most of a workgroup's time, and where no gradient is streamed the
-// vector units are busy for two thirds of the pass, half of that with divides.  Hence no branch per element where a tile is whole and
-// none of a wavefront's scores is zero.  Look 1 of 25.6 M elements without / with a gradient 51.0 -> 48.5 / 75.0 -> 73.5 us;
+// With a gradient it is bound by the stream itself: 25.6 M elements 71 us, 69.5 without histogram and copies, 400 M in one layer 1069 and 1067,
+// a thousand tensors of 115.5 M 316 and 320.  Without one, 25.6 M (weights kept, 3 us of it): 50 us, the stream 35, copies (1.6 per element that
+// is kept, partial lines) 7 with the histogram and 11 without, histogram 3 to 5, most of it the flush; the divide is 1 of them: it hides
+// behind the rest (an approximate one 48.5).  What a wavefront issues counts on small tables, where it is most of a workgroup's time, and
+// without a gradient.  Hence no branch per element where a tile is whole and none of a wavefront's scores is zero.
+// Look 1 of 25.6 M elements without / with a gradient 51.0 -> 48.5 / 75.0 -> 73.5 us;
 // whole calls, with look 2 and the records' pass likewise: one layer of 1 M 26.6 -> 25.1, six tensors of 235 k, four workers 32.6 -> 31.4,
 // thresholds and pairs of 25.6 M 116.7 -> 115.0, one worker's share of them 145.0 -> 142.8, a thousand tensors, eight workers 2334 -> 2323.
 constexpr int KEEP_NOTHING = 0, KEEP_W = 1, KEEP_W_AND_R = 2;
